@@ -1092,19 +1092,44 @@ __global__ void __launch_bounds__(256) k_wgrad3(const WgradArgs a)
             }
 }
 
-// Sum the partials in chunk order into the canonical gradient (rows x taps x
-// cin, dropping padded input channels).
+// Sum the partials into the canonical gradient (rows x taps x cin, dropping
+// padded input channels).  A block takes 64 consecutive partial columns (16
+// threads of four each) and splits the chunks over 16 slices: slice s adds
+// chunks s, s + 16, ... in order, then the slices are added in order, so the
+// result is the same on every run.  Bound by reading the partials; one thread
+// per column adding up to 1,024 chunks in turn left the 32-channel layers with
+// 36 blocks of one long chain (9,216 columns x 1,024 chunks): a 4 x 256x256
+// training step took 3.31 ms that way, 2.23 ms this way, 9 x 960x544 22.0 and
+// 20.6 ms.
+constexpr int WR_COLS = 64, WR_SLICES = 16;
 __global__ void __launch_bounds__(256) k_wgrad_reduce(const float *__restrict__ part, int chunks, int M, int taps,
                                                       int K, int cin, float *__restrict__ gw)
 {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n = M * taps * cin;
-    if (e >= n) return;
-    const int ci = e % cin, mt = e / cin, t = mt % taps, m = mt / taps;
-    const int64_t cols = (int64_t)taps * K;
+    __shared__ __attribute__((aligned(16))) float red[WR_SLICES][WR_COLS];
+    const int c4 = threadIdx.x & 15, sl = threadIdx.x >> 4;
+    const int64_t n = (int64_t)M * taps * K;   // K is a multiple of 32
+    const int64_t col = (int64_t)blockIdx.x * WR_COLS + 4 * c4;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (col < n)
+#pragma unroll 4
+        for (int c = sl; c < chunks; c += WR_SLICES) {
+            const float4 v = *(const float4 *)(part + (int64_t)c * n + col);
+            a.x += v.x;
+            a.y += v.y;
+            a.z += v.z;
+            a.w += v.w;
+        }
+    *(float4 *)&red[sl][4 * c4] = a;
+    __syncthreads();
+    if (threadIdx.x >= WR_COLS) return;
+    const int64_t q = (int64_t)blockIdx.x * WR_COLS + threadIdx.x;
+    if (q >= n) return;
     float s = 0.f;
-    for (int c = 0; c < chunks; ++c) s += part[(int64_t)c * M * cols + (int64_t)m * cols + t * K + ci];
-    gw[e] = s;
+#pragma unroll
+    for (int k = 0; k < WR_SLICES; ++k) s += red[k][threadIdx.x];
+    const int64_t mt = q / K;
+    const int ci = (int)(q - mt * K);
+    if (ci < cin) gw[mt * cin + ci] = s;
 }
 
 // ---------------------------------------------------------------- elementwise layers
@@ -1923,9 +1948,9 @@ hipError_t wgrad(unet_state *n, unet_act *a, int li, const uint16_t *X, int x_cs
         hipLaunchKernelGGL(k_wgrad<TAP>, grid, dim3(256), 0, s, w);
     }
     NCHK(hipGetLastError());
-    const int nel = l.cout * taps * l.cin;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((nel + 255) / 256), dim3(256), 0, s, (const float *)a->part, chunks,
-                       l.cout, taps, l.cin_pad, l.cin, n->g + l.w_off);
+    const int nel = l.cout * taps * l.cin_pad;
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((nel + WR_COLS - 1) / WR_COLS), dim3(256), 0, s, (const float *)a->part,
+                       chunks, l.cout, taps, l.cin_pad, l.cin, n->g + l.w_off);
     return hipGetLastError();
 }
 
