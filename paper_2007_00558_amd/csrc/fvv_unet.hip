@@ -1024,72 +1024,159 @@ __global__ void __launch_bounds__(256) k_wgrad(const WgradArgs a)
         }
 }
 
-// Weight gradient of a 3x3 convolution with all nine taps in one workgroup:
-// the 32-pixel gradient tile is staged once per step and reused by the
-// nine shifted input tiles (9 x 2 MFMAs per wave per step).  grid: x = input
-// channel block of 32, y = 64-row block, z = pixel chunk.
-__global__ void __launch_bounds__(256) k_wgrad3(const WgradArgs a)
+// Eight pixels of one channel for v_mfma_f32_32x32x16_bf16 from LDS rows of 32
+// channels per pixel (64 bytes, no padding): two transpose reads
+// (ds_read_b64_tr_b16: the 16 lanes of a group read a 4-pixel x 16-channel
+// block, 8 bytes each, and lane i receives channel i of the four pixels).  p
+// is the fragment's first pixel plus tr_lane(): lane l then holds channel
+// l mod 32 of pixels 8 floor(l/32) .. + 7.  Four consecutive pixels are 256
+// bytes, so a group's reads fall in distinct banks at any first pixel.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+__device__ __forceinline__ int tr_lane()
 {
-    __shared__ __attribute__((aligned(16))) uint16_t Gt[64 * WG_LD];
-    __shared__ __attribute__((aligned(16))) uint16_t Xt[9 * 32 * WG_LD];
-    const int cb = blockIdx.x;
-    const int mb = blockIdx.y * 64;
-    const int HW = a.H * a.W, P = a.NB * HW;
-    const int p_begin = blockIdx.z * a.chunk, p_end = min(P, p_begin + a.chunk);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lr = lane & 15, lg = lane >> 4;
-    f32x4 acc[9][2];
+    const int lane = threadIdx.x & 63;
+    return (8 * (lane >> 5) + ((lane & 15) >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+}
+__device__ __forceinline__ bf16x8 tr_frag(const uint16_t *p)
+{
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * 32));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Weight gradient of a 3x3 convolution: dW[m][tap][ci] = sum over pixels of
+// G[p][m] X[p + tap][ci], on v_mfma_f32_32x32x16_bf16 contracting over 16
+// pixels of an image row.  A workgroup's four waves are WM row tiles of 32 x
+// WK input-channel tiles of 32 x WP shares of the staged rows; each wave
+// holds its 32 x 32 tile of all nine taps (144 accumulators).  A stage is
+// ROWS x 16 pixels of the gradient and the (ROWS + 2) x 18 input patch around
+// them, copied to LDS in the tensors' own channel order (coalesced 16-byte
+// loads and stores, the next stage in registers while this one's MFMAs run);
+// the transpose the contraction needs happens in the LDS reads.  An input
+// fragment (one row, one column shift) meets the gradient rows above, at and
+// below it, so three fragments and one gradient row feed nine MFMAs.
+// Staging every tap's shifted tile transposed with 2-byte LDS stores, as
+// before, was bound by those stores: the 14 launches of a 9 x 960x544 step took
+// 7.54 ms, now 1.52 ms (the 64-channel and wider layers, 0.91 TFLOP, 0.85 ms;
+// the full-resolution ones are bound by reading their tensors).
+// grid: x = input-channel blocks, y = row blocks, z = chunks of stages.
+template <int WM, int WK, int WP, int ROWS>
+constexpr int wg3_lds_bytes() { return (WM * ROWS * 16 + WK * (ROWS + 2) * 18) * 64; }
+
+template <int WM, int WK, int WP, int ROWS>
+__global__ void __launch_bounds__(256, 2) k_wgrad3(const WgradArgs a)
+{
+    static_assert(WM * WK * WP == 4 && ROWS % WP == 0, "four waves");
+    constexpr int RW = ROWS / WP;                       // rows per wave
+    constexpr int GPL = ROWS * 16 * 32, XPL = (ROWS + 2) * 18 * 32;   // elements of a 32-channel plane
+    constexpr int NGU = ROWS * 16 * WM * 4, NXU = (ROWS + 2) * 18 * WK * 4;   // 16-byte units of a stage
+    constexpr int NG = (NGU + 255) / 256, NX = (NXU + 255) / 256;
+    extern __shared__ __attribute__((aligned(16))) uint8_t wg3_smem[];
+    uint16_t *const Gs = (uint16_t *)wg3_smem, *const Xs = Gs + WM * GPL;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lc = lane & 31, lh = lane >> 5;
+    const int wm = wave % WM, wk = (wave / WM) % WK, wp = wave / (WM * WK);
+    const int kb = blockIdx.x * 32 * WK, mb = blockIdx.y * 32 * WM;
+    const int tx = (a.W + 15) / 16, ty = (a.H + ROWS - 1) / ROWS;
+    const int stages = a.NB * ty * tx, chunks = gridDim.z;
+    const int s_begin = (int)((int64_t)stages * blockIdx.z / chunks);
+    const int s_end = (int)((int64_t)stages * (blockIdx.z + 1) / chunks);
+    const int x_src = a.x_src ? a.x_src : a.K;
+    uint4 fg[NG], fx[NX];
+    auto fetch = [&](int st) {
+        const int txi = st % tx, r = st / tx, tyi = r % ty, b = r / ty;
+        const int y0 = tyi * ROWS, x0 = txi * 16;
 #pragma unroll
-    for (int t = 0; t < 9; ++t) acc[t][0] = acc[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int p0 = p_begin; p0 < p_end; p0 += 32) {
-        {   // gradient tile: 32 pixels x 64 rows
-            const int pl = tid >> 3, rg = tid & 7;
-            const int p = p0 + pl, m = mb + rg * 8;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (p < p_end && m < a.M) v = *(const uint4 *)(a.G + (int64_t)p * a.g_cs + a.g_off + m);
-            const uint16_t *h = (const uint16_t *)&v;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) Gt[(rg * 8 + j) * WG_LD + pl] = h[j];
+        for (int k = 0; k < NG; ++k) {
+            const int u = tid + k * 256, c = u % (WM * 4), px = u / (WM * 4);
+            const int y = y0 + (px >> 4), x = x0 + (px & 15);
+            fg[k] = make_uint4(0, 0, 0, 0);
+            if (u < NGU && y < a.H && x < a.W)
+                fg[k] = *(const uint4 *)(a.G + (uint32_t)(((b * a.H + y) * a.W + x) * a.g_cs + a.g_off + mb + c * 8));
         }
-        // nine input tiles: 32 pixels x 32 channels each, shifted by the tap
-        for (int e = tid; e < 9 * 128; e += 256) {
-            const int t = e >> 7, rem = e & 127, pl = rem >> 2, cg = rem & 3;
-            const int p = p0 + pl;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (p < p_end) {
-                const int b = p / HW, r = p - b * HW, y = r / a.W, x = r - y * a.W;
-                const int sy = y + t / 3 - 1, sx = x + t % 3 - 1;
-                if (sy >= 0 && sx >= 0 && sy < a.H && sx < a.W && cb * 32 + cg * 8 < (a.x_src ? a.x_src : a.K))
-                    v = *(const uint4 *)(a.X + (((int64_t)b * a.H + sy) * a.W + sx) * a.x_cs + a.x_off + cb * 32 +
-                                         cg * 8);
-            }
-            const uint16_t *h = (const uint16_t *)&v;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) Xt[(t * 32 + cg * 8 + j) * WG_LD + pl] = h[j];
+        for (int k = 0; k < NX; ++k) {
+            const int u = tid + k * 256, c = u % (WK * 4), px = u / (WK * 4), pr = px / 18;
+            const int y = y0 - 1 + pr, x = x0 - 1 + px - pr * 18;
+            fx[k] = make_uint4(0, 0, 0, 0);
+            if (u < NXU && y >= 0 && y < a.H && x >= 0 && x < a.W && kb + c * 8 < x_src)
+                fx[k] = *(const uint4 *)(a.X + (uint32_t)(((b * a.H + y) * a.W + x) * a.x_cs + a.x_off + kb + c * 8));
         }
-        __syncthreads();
-        const bf16x8 af = __builtin_bit_cast(bf16x8, *(const uint4 *)&Gt[(wave * 16 + lr) * WG_LD + 8 * lg]);
+    };
+    auto stash = [&]() {
 #pragma unroll
-        for (int t = 0; t < 9; ++t)
+        for (int k = 0; k < NG; ++k) {
+            const int u = tid + k * 256, c = u % (WM * 4), px = u / (WM * 4);
+            if (u < NGU) *(uint4 *)(Gs + (c >> 2) * GPL + px * 32 + (c & 3) * 8) = fg[k];
+        }
 #pragma unroll
-            for (int n = 0; n < 2; ++n) {
-                const bf16x8 bf =
-                    __builtin_bit_cast(bf16x8, *(const uint4 *)&Xt[(t * 32 + n * 16 + lr) * WG_LD + 8 * lg]);
-                acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, acc[t][n], 0, 0, 0);
-            }
-        __syncthreads();
-    }
-    const int cols = 9 * a.K;
-    float *out = a.part + (int64_t)blockIdx.z * a.M * cols;
+        for (int k = 0; k < NX; ++k) {
+            const int u = tid + k * 256, c = u % (WK * 4), px = u / (WK * 4);
+            if (u < NXU) *(uint4 *)(Xs + (c >> 2) * XPL + px * 32 + (c & 3) * 8) = fx[k];
+        }
+    };
+    f32x16 acc[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int n = 0; n < 2; ++n)
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    const uint16_t *const gl = Gs + wm * GPL + wp * RW * 16 * 32 + tr_lane();
+    const uint16_t *const xl = Xs + wk * XPL + wp * RW * 18 * 32 + tr_lane();
+    if (s_begin < s_end) fetch(s_begin);
+    for (int st = s_begin; st < s_end; ++st) {
+        __syncthreads();   // every wave is done with the previous stage
+        stash();
+        __syncthreads();
+        if (st + 1 < s_end) fetch(st + 1);
+        bf16x8 ga[3], xb[3];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = mb + wave * 16 + 4 * lg + r;
-                if (m < a.M) out[(int64_t)m * cols + t * a.K + cb * 32 + n * 16 + lr] = acc[t][n][r];
+        for (int ir = 0; ir < RW + 2; ++ir) {   // patch rows of this wave
+            if (ir < RW) ga[ir % 3] = tr_frag(gl + ir * 16 * 32);
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) xb[dx] = tr_frag(xl + (ir * 18 + dx) * 32);
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                const int r = ir - dy;
+                if (r < 0 || r >= RW) continue;
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+                    acc[dy * 3 + dx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga[r % 3], xb[dx], acc[dy * 3 + dx], 0, 0, 0);
             }
+        }
+    }
+    if (WP > 1) {
+        // the row shares added in order in LDS, three taps at a time
+        float *const red = (float *)wg3_smem;   // [(WP - 1) * WM * WK][48][64]
+        static_assert(WP == 1 || (WP - 1) * WM * WK * 48 * 64 * 4 <= wg3_lds_bytes<WM, WK, WP, ROWS>(),
+                      "the shares of three taps fit the staging buffers");
+#pragma unroll
+        for (int t0 = 0; t0 < 9; t0 += 3) {
+            __syncthreads();
+            if (wp > 0)
+#pragma unroll
+                for (int e = 0; e < 48; ++e)
+                    red[(((wp - 1) * WM * WK + wk * WM + wm) * 48 + e) * 64 + lane] = acc[t0 + e / 16][e % 16];
+            __syncthreads();
+            if (wp == 0)
+#pragma unroll
+                for (int w = 0; w < WP - 1; ++w)
+#pragma unroll
+                    for (int e = 0; e < 48; ++e)
+                        acc[t0 + e / 16][e % 16] += red[((w * WM * WK + wk * WM + wm) * 48 + e) * 64 + lane];
+        }
+        if (wp > 0) return;
+    }
+    const int cols = 9 * a.K;
+    float *out = a.part + (int64_t)blockIdx.z * a.M * cols + kb + wk * 32 + lc;
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int m = mb + wm * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
+            out[(int64_t)m * cols + t * a.K] = acc[t][r];
+        }
 }
 
 // Sum the partials into the canonical gradient (rows x taps x cin, dropping
@@ -1459,9 +1546,8 @@ const Layers &layers()
     return t;
 }
 
-// chunking of a weight-gradient contraction over P pixels
-// Pixel chunking of a weight-gradient contraction over P pixels for a
-// layer whose grid has `wgs` workgroups per chunk: about 1024 workgroups in
+// Pixel chunking of a transposed convolution's weight-gradient contraction
+// over P pixels for a layer whose grid has `wgs` workgroups per chunk: about 1024 workgroups in
 // all, chunks of at least 256 pixels (multiples of 32).
 int wgrad_chunks(size_t P, int wgs)
 {
@@ -1475,8 +1561,32 @@ int wgrad_chunk(size_t P, int wgs)
 }
 int wgrad_wgs(const unet_layer &l)
 {
-    const int mblk = (l.cout + 63) / 64, kblk = l.cin_pad / 32;
-    return l.kind == 0 ? mblk * kblk : mblk * kblk * l.taps;
+    return (l.cout + 63) / 64 * (l.cin_pad / 32) * l.taps;
+}
+
+// Tiles of a 3x3 layer's weight gradient (k_wgrad3): 64 x 64 blocks of rows x
+// input channels, or what a 32-channel side leaves, and the rows of a stage.
+struct Wg3Shape {
+    int wm, wk, rows;
+};
+Wg3Shape wg3_shape(const unet_layer &l)
+{
+    if (l.cout == 32) return {1, l.cin_pad == 32 ? 1 : 2, l.cin_pad == 32 ? 16 : 8};
+    return {2, l.cin_pad == 32 ? 1 : 2, 8};
+}
+// Chunks of `stages` for a layer of `tiles` workgroup tiles: as many as the
+// device holds at once (two workgroups on each of 256 CUs), fewer where the
+// partials (tiles x 147 KB written and read per chunk, about 0.07 us each)
+// would cost more than the stages (about 2 us each) they divide.
+int wg3_chunks(int64_t stages, int tiles)
+{
+    const double bal = std::sqrt(27.0 * (double)stages / tiles);
+    return (int)std::max<int64_t>(1, std::min<int64_t>({512 / tiles, (int64_t)bal, stages}));
+}
+int wg3_tiles(const unet_layer &l)
+{
+    const Wg3Shape h = wg3_shape(l);
+    return (l.cout / (32 * h.wm)) * (l.cin_pad / (32 * h.wk));
 }
 
 size_t partial_floats(size_t P0)
@@ -1486,10 +1596,13 @@ size_t partial_floats(size_t P0)
     for (int i = 0; i < kNL; ++i) {
         const unet_layer &l = T.L[i];
         if (l.kind == 2) continue;
-        // a contraction over P <= Pk pixels has ceil(P / chunk) <= wgrad_chunks(P)
-        // <= wgrad_chunks(Pk) chunks (chunk >= P / wgrad_chunks(P), monotone in P)
         const size_t Pk = P0 >> (2 * kSumLevel[i]);
-        const size_t chunks = (size_t)wgrad_chunks(Pk, wgrad_wgs(l));
+        // transposed convolutions: a contraction over P <= Pk pixels has
+        // ceil(P / chunk) <= wgrad_chunks(P) <= wgrad_chunks(Pk) chunks (chunk
+        // >= P / wgrad_chunks(P), monotone in P); 3x3: no more stages than
+        // pixels, chunks monotone in the stages
+        const size_t chunks = l.kind == 0 ? (size_t)wg3_chunks((int64_t)std::max<size_t>(1, Pk), wg3_tiles(l))
+                                          : (size_t)wgrad_chunks(Pk, wgrad_wgs(l));
         m = std::max(m, chunks * l.cout * l.taps * l.cin_pad);
     }
     return m;
@@ -1917,6 +2030,15 @@ hipError_t mask_round(unet_state *n, unet_act *a, const float *g, int g_cs, int 
     return hipGetLastError();
 }
 
+template <int WM, int WK, int WP, int ROWS>
+void wgrad3_launch(const WgradArgs &w, int chunks, hipStream_t s)
+{
+    constexpr int lds = wg3_lds_bytes<WM, WK, WP, ROWS>();
+    static_assert(lds <= 65536, "a stage must fit 64 KB");
+    const dim3 grid(w.K / (32 * WK), w.M / (32 * WM), chunks);
+    hipLaunchKernelGGL((k_wgrad3<WM, WK, WP, ROWS>), grid, dim3(256), lds, s, w);
+}
+
 // weight gradient of layer li from a->G (its masked output gradient) and
 // its input X; (NB, H, W) is the contraction grid (the coarse grid for convT)
 template <int TAP>
@@ -1924,8 +2046,6 @@ hipError_t wgrad(unet_state *n, unet_act *a, int li, const uint16_t *X, int x_cs
 {
     const unet_layer &l = layers().L[li];
     const int P = NB * H * W;
-    const int chunk = wgrad_chunk((size_t)P, wgrad_wgs(l));
-    const int chunks = (P + chunk - 1) / chunk;
     WgradArgs w{};
     w.G = a->G;
     w.g_cs = l.cout;
@@ -1938,12 +2058,23 @@ hipError_t wgrad(unet_state *n, unet_act *a, int li, const uint16_t *X, int x_cs
     w.M = l.cout;
     w.K = l.cin_pad;
     w.x_src = l.cin;
-    w.chunk = chunk;
     constexpr int taps = TAP == TAP_CONV3 ? 9 : (TAP == TAP_FINE4 ? 4 : 1);
+    int chunks;
     if (TAP == TAP_CONV3) {
-        dim3 grid(l.cin_pad / 32, (l.cout + 63) / 64, chunks);
-        hipLaunchKernelGGL(k_wgrad3, grid, dim3(256), 0, s, w);
+        const Wg3Shape h = wg3_shape(l);
+        const int64_t stages = (int64_t)NB * ((H + h.rows - 1) / h.rows) * ((W + 15) / 16);
+        chunks = wg3_chunks(stages, wg3_tiles(l));
+        if (h.wm == 1 && h.wk == 1)
+            wgrad3_launch<1, 1, 4, 16>(w, chunks, s);
+        else if (h.wm == 1)
+            wgrad3_launch<1, 2, 2, 8>(w, chunks, s);
+        else if (h.wk == 1)
+            wgrad3_launch<2, 1, 2, 8>(w, chunks, s);
+        else
+            wgrad3_launch<2, 2, 1, 8>(w, chunks, s);
     } else {
+        w.chunk = wgrad_chunk((size_t)P, wgrad_wgs(l));
+        chunks = (P + w.chunk - 1) / w.chunk;
         dim3 grid(taps * (l.cin_pad / 32), (l.cout + 63) / 64, chunks);
         hipLaunchKernelGGL(k_wgrad<TAP>, grid, dim3(256), 0, s, w);
     }

@@ -1,0 +1,48 @@
+"""Gradients of one training step at sizes where the training kernels' tiles
+end unevenly: rows and columns that no stage divides (8-row and 16-column
+stages at every level of the network, down to one row and one column at the
+coarsest), several images, a partial last row, and enough pixels that the
+weights-resident and persistent kernels run.  Reference: the oracle in
+float64 over the images of the batch; tolerance per layer: twice the spread
+of the oracle evaluated in float32 (+1 %), the bar of the other gradient
+tests (a ReLU input or a max-pool pair within rounding distance of a tie
+routes a whole gradient entry elsewhere in any two evaluations)."""
+import numpy as np
+import pytest
+
+from test_gpu_learned import ctx, flat, fvv, rand_params, say, scene_stack, to_device_stack, unflat  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,H,W,valid", [(1, 8, 8, 8), (2, 8, 24, 7), (3, 24, 40, 21), (1, 72, 136, 72),
+                                         (2, 136, 8, 130), (1, 264, 520, 260)])
+def test_gradients_ragged(fvv, ctx, oracle_lib, N, H, W, valid):  # noqa: F811
+    import torch
+    from oracle import unet
+    say(f"[gpu] gradients {N}x{H}x{W} valid={valid}")
+    P = rand_params(400 + H + W)
+    ctx.net_load(flat(P))
+    st = np.stack([scene_stack(oracle_lib, 410 + q, W, H) for q in range(N)])
+    target = np.random.default_rng(420).uniform(0, 1, (N, H, W, 3)).astype(np.float32)
+    loss = ctx.net_train_step(to_device_stack(st), torch.from_numpy(target).cuda(), N, H, W, valid, lr=0.0,
+                              apply=False)
+    g = unflat(ctx.net_read(fvv.NET_GRADS))
+    tot, ref, ref32 = 0.0, {}, {}
+    for q in range(N):
+        lq, rg = unet.loss_and_grads(P, st[q], target[q], valid)
+        _, rg32 = unet.loss_and_grads(P, st[q], target[q], valid, acc=np.float32)
+        tot += lq / N
+        for name, *_ in unet.LAYERS:
+            for k in (0, 1):
+                ref[name, k] = ref.get((name, k), 0.0) + np.asarray(rg[name][k], np.float64).ravel() / N
+                ref32[name, k] = ref32.get((name, k), 0.0) + np.asarray(rg32[name][k], np.float64).ravel() / N
+    assert abs(loss - tot) <= 1e-3 * tot
+    bad = []
+    for (name, k), r in ref.items():
+        nrm = max(np.linalg.norm(r), 1e-30)
+        rel = np.linalg.norm(g[name][k].astype(np.float64).ravel() - r) / nrm
+        floor = np.linalg.norm(ref32[name, k] - r) / nrm
+        if rel > 2 * floor + 0.01:
+            bad.append((name, "Wb"[k], rel, floor))
+    assert not bad, bad
