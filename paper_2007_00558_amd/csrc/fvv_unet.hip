@@ -941,88 +941,7 @@ struct WgradArgs {
     int NB, H, W;            // pixel grid of the contraction (the coarse grid for convT)
     int M, K;                // rows; input channels per tap (multiple of 32)
     int x_src;               // channels X holds at x_off (0 = K); staged channels beyond are zero
-    int chunk;               // pixels per workgroup (multiple of 32)
 };
-
-constexpr int WG_LD = 40;    // LDS row length in bf16 (32 pixels + pad, 16-byte aligned rows)
-
-// grid: x = tap * (K/32) + column block of 32 channels, y = 64-row block,
-// z = pixel chunk.  LDS holds the chunk's 32-pixel steps transposed to
-// [channel][pixel] so each lane reads 8 consecutive pixels of one channel.
-template <int TAP>
-__global__ void __launch_bounds__(256) k_wgrad(const WgradArgs a)
-{
-    __shared__ __attribute__((aligned(16))) uint16_t Gt[64 * WG_LD];
-    __shared__ __attribute__((aligned(16))) uint16_t Xt[32 * WG_LD];
-    const int taps = TAP == TAP_CONV3 ? 9 : (TAP == TAP_FINE4 ? 4 : 1);
-    const int ncb = a.K / 32;
-    const int t = blockIdx.x / ncb, cb = blockIdx.x - t * ncb;
-    const int mb = blockIdx.y * 64;
-    const int HW = a.H * a.W, P = a.NB * HW;
-    const int p_begin = blockIdx.z * a.chunk, p_end = min(P, p_begin + a.chunk);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lr = lane & 15, lg = lane >> 4;
-    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-    for (int p0 = p_begin; p0 < p_end; p0 += 32) {
-        // gradient tile: 32 pixels x 64 rows (8 rows per thread)
-        {
-            const int pl = tid >> 3, rg = tid & 7;
-            const int p = p0 + pl;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            const int m = mb + rg * 8;
-            if (p < p_end && m < a.M) {
-                const int b = p / HW, r = p - b * HW, y = r / a.W, x = r - y * a.W;
-                int64_t gp;
-                if (TAP == TAP_FINE4)
-                    gp = ((int64_t)b * 2 * a.H + 2 * y + (t >> 1)) * (2 * a.W) + 2 * x + (t & 1);
-                else
-                    gp = p;
-                v = *(const uint4 *)(a.G + gp * a.g_cs + a.g_off + m);
-            }
-            const uint16_t *h = (const uint16_t *)&v;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) Gt[(rg * 8 + j) * WG_LD + pl] = h[j];
-        }
-        // input tile: 32 pixels x 32 channels (threads 0..127)
-        if (tid < 128) {
-            const int pl = tid >> 2, cg = tid & 3;
-            const int p = p0 + pl;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (p < p_end) {
-                const int b = p / HW, r = p - b * HW, y = r / a.W, x = r - y * a.W;
-                int64_t xp = -1;
-                if (TAP == TAP_CONV3) {
-                    const int sy = y + t / 3 - 1, sx = x + t % 3 - 1;
-                    if (sy >= 0 && sx >= 0 && sy < a.H && sx < a.W) xp = ((int64_t)b * a.H + sy) * a.W + sx;
-                } else {
-                    xp = p;
-                }
-                if (xp >= 0 && cb * 32 + cg * 8 < (a.x_src ? a.x_src : a.K))
-                    v = *(const uint4 *)(a.X + xp * a.x_cs + a.x_off + cb * 32 + cg * 8);
-            }
-            const uint16_t *h = (const uint16_t *)&v;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) Xt[(cg * 8 + j) * WG_LD + pl] = h[j];
-        }
-        __syncthreads();
-        const bf16x8 af = __builtin_bit_cast(bf16x8, *(const uint4 *)&Gt[(wave * 16 + lr) * WG_LD + 8 * lg]);
-#pragma unroll
-        for (int n = 0; n < 2; ++n) {
-            const bf16x8 bf = __builtin_bit_cast(bf16x8, *(const uint4 *)&Xt[(n * 16 + lr) * WG_LD + 8 * lg]);
-            acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, acc[n], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    const int cols = taps * a.K;
-    float *out = a.part + (int64_t)blockIdx.z * a.M * cols;
-#pragma unroll
-    for (int n = 0; n < 2; ++n)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int m = mb + wave * 16 + 4 * lg + r;
-            if (m < a.M) out[(int64_t)m * cols + t * a.K + cb * 32 + n * 16 + lr] = acc[n][r];
-        }
-}
 
 // Eight pixels of one channel for v_mfma_f32_32x32x16_bf16 from LDS rows of 32
 // channels per pixel (64 bytes, no padding): two transpose reads
@@ -1177,6 +1096,130 @@ __global__ void __launch_bounds__(256, 2) k_wgrad3(const WgradArgs a)
             const int m = mb + wm * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
             out[(int64_t)m * cols + t * a.K] = acc[t][r];
         }
+}
+
+// Weight gradient of a 2x2 transposed convolution: dW[m][tap][ci] = sum over
+// coarse pixels of G[fine pixel of tap][m] X[p][ci].  As k_wgrad3, with a wave
+// holding 32 rows x 64 input channels of the four taps (128 accumulators: four
+// gradient and two input fragments feed eight MFMAs) and stages of ROWS x 16
+// coarse pixels; the fine gradient pixels of a tap are staged as a plane of
+// their own, so its fragments are runs of pixels too.  One tap and 32 channels
+// per workgroup, staged through 2-byte transposed LDS stores, read both
+// tensors once per tap and channel block: the three launches of a
+// 9 x 960x544 step took 1.05 ms, now 0.21 ms.
+template <int WM, int WK, int ROWS>
+constexpr int wgT_lds_bytes() { return (WM * 4 + WK * 2) * ROWS * 16 * 64; }
+
+template <int WM, int WK, int WP, int ROWS>
+__global__ void __launch_bounds__(256, 2) k_wgradT(const WgradArgs a)
+{
+    static_assert(WM * WK * WP == 4 && ROWS % WP == 0, "four waves");
+    constexpr int RW = ROWS / WP, PX = ROWS * 16, PL = PX * 32;   // rows per wave; pixels and elements of a plane
+    constexpr int NGU = 4 * PX * WM * 4, NXU = PX * WK * 8;
+    constexpr int NG = NGU / 256, NX = NXU / 256;
+    static_assert(NGU % 256 == 0 && NXU % 256 == 0, "whole rounds of 16-byte units");
+    extern __shared__ __attribute__((aligned(16))) uint8_t wgT_smem[];
+    uint16_t *const Gs = (uint16_t *)wgT_smem, *const Xs = Gs + WM * 4 * PL;   // [WM][tap], [WK * 2] planes
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lc = lane & 31, lh = lane >> 5;
+    const int wm = wave % WM, wk = (wave / WM) % WK, wp = wave / (WM * WK);
+    const int kb = blockIdx.x * 64 * WK, mb = blockIdx.y * 32 * WM;
+    const int tx = (a.W + 15) / 16, ty = (a.H + ROWS - 1) / ROWS;
+    const int stages = a.NB * ty * tx, chunks = gridDim.z;
+    const int s_begin = (int)((int64_t)stages * blockIdx.z / chunks);
+    const int s_end = (int)((int64_t)stages * (blockIdx.z + 1) / chunks);
+    uint4 fg[NG], fx[NX];
+    auto fetch = [&](int st) {
+        const int txi = st % tx, r = st / tx, tyi = r % ty, b = r / ty;
+        const int y0 = tyi * ROWS, x0 = txi * 16;
+#pragma unroll
+        for (int k = 0; k < NG; ++k) {
+            const int u = tid + k * 256, c = u % (WM * 4), px = u / (WM * 4), fr = px >> 5, fc = px & 31;
+            fg[k] = make_uint4(0, 0, 0, 0);
+            if (y0 + (fr >> 1) < a.H && x0 + (fc >> 1) < a.W)
+                fg[k] = *(const uint4 *)(a.G + (uint32_t)(((b * 2 * a.H + 2 * y0 + fr) * 2 * a.W + 2 * x0 + fc) * a.g_cs +
+                                                          a.g_off + mb + c * 8));
+        }
+#pragma unroll
+        for (int k = 0; k < NX; ++k) {
+            const int u = tid + k * 256, c = u % (WK * 8), px = u / (WK * 8);
+            const int y = y0 + (px >> 4), x = x0 + (px & 15);
+            fx[k] = make_uint4(0, 0, 0, 0);
+            if (y < a.H && x < a.W)
+                fx[k] = *(const uint4 *)(a.X + (uint32_t)(((b * a.H + y) * a.W + x) * a.x_cs + a.x_off + kb + c * 8));
+        }
+    };
+    auto stash = [&]() {
+#pragma unroll
+        for (int k = 0; k < NG; ++k) {
+            const int u = tid + k * 256, c = u % (WM * 4), px = u / (WM * 4), fr = px >> 5, fc = px & 31;
+            const int plane = (c >> 2) * 4 + (fr & 1) * 2 + (fc & 1);
+            *(uint4 *)(Gs + plane * PL + ((fr >> 1) * 16 + (fc >> 1)) * 32 + (c & 3) * 8) = fg[k];
+        }
+#pragma unroll
+        for (int k = 0; k < NX; ++k) {
+            const int u = tid + k * 256, c = u % (WK * 8), px = u / (WK * 8);
+            *(uint4 *)(Xs + (c >> 2) * PL + px * 32 + (c & 3) * 8) = fx[k];
+        }
+    };
+    f32x16 acc[4][2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][n][r] = 0.f;
+    const uint16_t *const gl = Gs + wm * 4 * PL + wp * RW * 16 * 32 + tr_lane();
+    const uint16_t *const xl = Xs + wk * 2 * PL + wp * RW * 16 * 32 + tr_lane();
+    if (s_begin < s_end) fetch(s_begin);
+    for (int st = s_begin; st < s_end; ++st) {
+        __syncthreads();   // every wave is done with the previous stage
+        stash();
+        __syncthreads();
+        if (st + 1 < s_end) fetch(st + 1);
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const bf16x8 x0 = tr_frag(xl + r * 512), x1 = tr_frag(xl + PL + r * 512);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const bf16x8 g = tr_frag(gl + t * PL + r * 512);
+                acc[t][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g, x0, acc[t][0], 0, 0, 0);
+                acc[t][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g, x1, acc[t][1], 0, 0, 0);
+            }
+        }
+    }
+    if (WP > 1) {
+        // the row shares added in order in LDS, one tap at a time
+        float *const red = (float *)wgT_smem;   // [(WP - 1) * WM * WK][32][64]
+        static_assert((WP - 1) * WM * WK * 32 * 64 * 4 <= wgT_lds_bytes<WM, WK, ROWS>(), "a tap's shares fit");
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            __syncthreads();
+            if (wp > 0)
+#pragma unroll
+                for (int e = 0; e < 32; ++e)
+                    red[(((wp - 1) * WM * WK + wk * WM + wm) * 32 + e) * 64 + lane] = acc[t][e / 16][e % 16];
+            __syncthreads();
+            if (wp == 0)
+#pragma unroll
+                for (int w = 0; w < WP - 1; ++w)
+#pragma unroll
+                    for (int e = 0; e < 32; ++e)
+                        acc[t][e / 16][e % 16] += red[((w * WM * WK + wk * WM + wm) * 32 + e) * 64 + lane];
+        }
+        if (wp > 0) return;
+    }
+    const int cols = 4 * a.K;
+    float *out = a.part + (int64_t)blockIdx.z * a.M * cols + kb + wk * 64 + lc;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int m = mb + wm * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
+                out[(int64_t)m * cols + t * a.K + n * 32] = acc[t][n][r];
+            }
 }
 
 // Sum the partials into the canonical gradient (rows x taps x cin, dropping
@@ -1546,47 +1589,32 @@ const Layers &layers()
     return t;
 }
 
-// Pixel chunking of a transposed convolution's weight-gradient contraction
-// over P pixels for a layer whose grid has `wgs` workgroups per chunk: about 1024 workgroups in
-// all, chunks of at least 256 pixels (multiples of 32).
-int wgrad_chunks(size_t P, int wgs)
-{
-    const size_t want = std::max<size_t>(1, 1024 / (size_t)std::max(1, wgs));
-    return (int)std::max<size_t>(1, std::min<size_t>((P + 255) / 256, want));
-}
-int wgrad_chunk(size_t P, int wgs)
-{
-    const size_t c = (P + wgrad_chunks(P, wgs) - 1) / wgrad_chunks(P, wgs);
-    return (int)((c + 31) / 32 * 32);
-}
-int wgrad_wgs(const unet_layer &l)
-{
-    return (l.cout + 63) / 64 * (l.cin_pad / 32) * l.taps;
-}
-
-// Tiles of a 3x3 layer's weight gradient (k_wgrad3): 64 x 64 blocks of rows x
-// input channels, or what a 32-channel side leaves, and the rows of a stage.
-struct Wg3Shape {
-    int wm, wk, rows;
+// Weight gradients: waves of a workgroup over rows (wm, 32 each) and input
+// channels (wk: 32 each in k_wgrad3, 64 in k_wgradT), the rest sharing the rows
+// of a stage.  Two by two where the layer has the channels.
+struct WgShape {
+    int wm, wk, rows, kw;
 };
-Wg3Shape wg3_shape(const unet_layer &l)
+WgShape wg_shape(const unet_layer &l)
 {
-    if (l.cout == 32) return {1, l.cin_pad == 32 ? 1 : 2, l.cin_pad == 32 ? 16 : 8};
-    return {2, l.cin_pad == 32 ? 1 : 2, 8};
+    if (l.kind == 1) return l.cout == 32 ? WgShape{1, 1, 8, 64} : WgShape{2, 2, 4, 64};
+    const bool k32 = l.cin_pad == 32;
+    if (l.cout == 32) return {1, k32 ? 1 : 2, k32 ? 16 : 8, 32};
+    return {2, k32 ? 1 : 2, 8, 32};
+}
+int wg_tiles(const unet_layer &l)
+{
+    const WgShape h = wg_shape(l);
+    return (l.cout / (32 * h.wm)) * (l.cin_pad / (h.kw * h.wk));
 }
 // Chunks of `stages` for a layer of `tiles` workgroup tiles: as many as the
 // device holds at once (two workgroups on each of 256 CUs), fewer where the
-// partials (tiles x 147 KB written and read per chunk, about 0.07 us each)
+// partials (up to 147 KB per tile and chunk, written and read: about 0.07 us)
 // would cost more than the stages (about 2 us each) they divide.
-int wg3_chunks(int64_t stages, int tiles)
+int wg_chunks(int64_t stages, int tiles)
 {
     const double bal = std::sqrt(27.0 * (double)stages / tiles);
     return (int)std::max<int64_t>(1, std::min<int64_t>({512 / tiles, (int64_t)bal, stages}));
-}
-int wg3_tiles(const unet_layer &l)
-{
-    const Wg3Shape h = wg3_shape(l);
-    return (l.cout / (32 * h.wm)) * (l.cin_pad / (32 * h.wk));
 }
 
 size_t partial_floats(size_t P0)
@@ -1596,14 +1624,9 @@ size_t partial_floats(size_t P0)
     for (int i = 0; i < kNL; ++i) {
         const unet_layer &l = T.L[i];
         if (l.kind == 2) continue;
-        const size_t Pk = P0 >> (2 * kSumLevel[i]);
-        // transposed convolutions: a contraction over P <= Pk pixels has
-        // ceil(P / chunk) <= wgrad_chunks(P) <= wgrad_chunks(Pk) chunks (chunk
-        // >= P / wgrad_chunks(P), monotone in P); 3x3: no more stages than
-        // pixels, chunks monotone in the stages
-        const size_t chunks = l.kind == 0 ? (size_t)wg3_chunks((int64_t)std::max<size_t>(1, Pk), wg3_tiles(l))
-                                          : (size_t)wgrad_chunks(Pk, wgrad_wgs(l));
-        m = std::max(m, chunks * l.cout * l.taps * l.cin_pad);
+        // no more stages than pixels; the chunks grow with the stages
+        const size_t Pk = std::max<size_t>(1, P0 >> (2 * kSumLevel[i]));
+        m = std::max(m, (size_t)wg_chunks((int64_t)Pk, wg_tiles(l)) * l.cout * l.taps * l.cin_pad);
     }
     return m;
 }
@@ -2039,13 +2062,20 @@ void wgrad3_launch(const WgradArgs &w, int chunks, hipStream_t s)
     hipLaunchKernelGGL((k_wgrad3<WM, WK, WP, ROWS>), grid, dim3(256), lds, s, w);
 }
 
+template <int WM, int WK, int WP, int ROWS>
+void wgradT_launch(const WgradArgs &w, int chunks, hipStream_t s)
+{
+    constexpr int lds = wgT_lds_bytes<WM, WK, ROWS>();
+    static_assert(lds <= 65536, "a stage must fit 64 KB");
+    const dim3 grid(w.K / (64 * WK), w.M / (32 * WM), chunks);
+    hipLaunchKernelGGL((k_wgradT<WM, WK, WP, ROWS>), grid, dim3(256), lds, s, w);
+}
+
 // weight gradient of layer li from a->G (its masked output gradient) and
 // its input X; (NB, H, W) is the contraction grid (the coarse grid for convT)
-template <int TAP>
 hipError_t wgrad(unet_state *n, unet_act *a, int li, const uint16_t *X, int x_cs, int NB, int H, int W, hipStream_t s)
 {
     const unet_layer &l = layers().L[li];
-    const int P = NB * H * W;
     WgradArgs w{};
     w.G = a->G;
     w.g_cs = l.cout;
@@ -2058,30 +2088,26 @@ hipError_t wgrad(unet_state *n, unet_act *a, int li, const uint16_t *X, int x_cs
     w.M = l.cout;
     w.K = l.cin_pad;
     w.x_src = l.cin;
-    constexpr int taps = TAP == TAP_CONV3 ? 9 : (TAP == TAP_FINE4 ? 4 : 1);
-    int chunks;
-    if (TAP == TAP_CONV3) {
-        const Wg3Shape h = wg3_shape(l);
-        const int64_t stages = (int64_t)NB * ((H + h.rows - 1) / h.rows) * ((W + 15) / 16);
-        chunks = wg3_chunks(stages, wg3_tiles(l));
-        if (h.wm == 1 && h.wk == 1)
-            wgrad3_launch<1, 1, 4, 16>(w, chunks, s);
-        else if (h.wm == 1)
-            wgrad3_launch<1, 2, 2, 8>(w, chunks, s);
-        else if (h.wk == 1)
-            wgrad3_launch<2, 1, 2, 8>(w, chunks, s);
+    const WgShape h = wg_shape(l);
+    const int chunks = wg_chunks((int64_t)NB * ((H + h.rows - 1) / h.rows) * ((W + 15) / 16), wg_tiles(l));
+    if (l.kind == 1) {
+        if (h.wm == 1)
+            wgradT_launch<1, 1, 4, 8>(w, chunks, s);
         else
-            wgrad3_launch<2, 2, 1, 8>(w, chunks, s);
+            wgradT_launch<2, 2, 1, 4>(w, chunks, s);
+    } else if (h.wm == 1 && h.wk == 1) {
+        wgrad3_launch<1, 1, 4, 16>(w, chunks, s);
+    } else if (h.wm == 1) {
+        wgrad3_launch<1, 2, 2, 8>(w, chunks, s);
+    } else if (h.wk == 1) {
+        wgrad3_launch<2, 1, 2, 8>(w, chunks, s);
     } else {
-        w.chunk = wgrad_chunk((size_t)P, wgrad_wgs(l));
-        chunks = (P + w.chunk - 1) / w.chunk;
-        dim3 grid(taps * (l.cin_pad / 32), (l.cout + 63) / 64, chunks);
-        hipLaunchKernelGGL(k_wgrad<TAP>, grid, dim3(256), 0, s, w);
+        wgrad3_launch<2, 2, 1, 8>(w, chunks, s);
     }
     NCHK(hipGetLastError());
-    const int nel = l.cout * taps * l.cin_pad;
+    const int nel = l.cout * l.taps * l.cin_pad;
     hipLaunchKernelGGL(k_wgrad_reduce, dim3((nel + WR_COLS - 1) / WR_COLS), dim3(256), 0, s, (const float *)a->part,
-                       chunks, l.cout, taps, l.cin_pad, l.cin, n->g + l.w_off);
+                       chunks, l.cout, l.taps, l.cin_pad, l.cin, n->g + l.w_off);
     return hipGetLastError();
 }
 
@@ -2320,64 +2346,64 @@ hipError_t unet_train(unet_state *n, unet_act *a, const uint16_t *stack, const f
     NCHK(hipMemcpyAsync(a->loss_dev, a->part + 99, 4, hipMemcpyDeviceToDevice, s));
     // decoder, level 0
     NCHK(mask_round(n, a, a->g0, 32, 0, a->d0b, 32, 0, true, 32, P0, L_D0B, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_D0B, a->d0a, 32, NB, H, W, s));
+    NCHK(wgrad(n, a, L_D0B, a->d0a, 32, NB, H, W, s));
     NCHK(conv_dgrad(n, a, L_D0B, a->g1, NB, H, W, s));
     NCHK(mask_round(n, a, a->g1, 32, 0, a->d0a, 32, 0, true, 32, P0, L_D0A, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_D0A, a->cat0, 64, NB, H, W, s));
+    NCHK(wgrad(n, a, L_D0A, a->cat0, 64, NB, H, W, s));
     NCHK(conv_dgrad(n, a, L_D0A, a->gs0, NB, H, W, s));              // [g_up0 | g_skip0]
     NCHK(mask_round(n, a, a->gs0, 64, 0, nullptr, 0, 0, false, 32, P0, L_UP0, s));
-    NCHK(wgrad<TAP_FINE4>(n, a, L_UP0, a->d1b, 64, NB, H1, W1, s));
+    NCHK(wgrad(n, a, L_UP0, a->d1b, 64, NB, H1, W1, s));
     NCHK(convT_dgrad(n, a, L_UP0, a->g0, NB, H1, W1, s));            // g(d1b) [P1][64]
     // level 1
     NCHK(mask_round(n, a, a->g0, 64, 0, a->d1b, 64, 0, true, 64, P1, L_D1B, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_D1B, a->d1a, 64, NB, H1, W1, s));
+    NCHK(wgrad(n, a, L_D1B, a->d1a, 64, NB, H1, W1, s));
     NCHK(conv_dgrad(n, a, L_D1B, a->g1, NB, H1, W1, s));
     NCHK(mask_round(n, a, a->g1, 64, 0, a->d1a, 64, 0, true, 64, P1, L_D1A, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_D1A, a->cat1, 128, NB, H1, W1, s));
+    NCHK(wgrad(n, a, L_D1A, a->cat1, 128, NB, H1, W1, s));
     NCHK(conv_dgrad(n, a, L_D1A, a->gs1, NB, H1, W1, s));            // [g_up1 | g_skip1]
     NCHK(mask_round(n, a, a->gs1, 128, 0, nullptr, 0, 0, false, 64, P1, L_UP1, s));
-    NCHK(wgrad<TAP_FINE4>(n, a, L_UP1, a->d2b, 128, NB, H2, W2, s));
+    NCHK(wgrad(n, a, L_UP1, a->d2b, 128, NB, H2, W2, s));
     NCHK(convT_dgrad(n, a, L_UP1, a->g0, NB, H2, W2, s));            // g(d2b) [P2][128]
     // level 2
     NCHK(mask_round(n, a, a->g0, 128, 0, a->d2b, 128, 0, true, 128, P2, L_D2B, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_D2B, a->d2a, 128, NB, H2, W2, s));
+    NCHK(wgrad(n, a, L_D2B, a->d2a, 128, NB, H2, W2, s));
     NCHK(conv_dgrad(n, a, L_D2B, a->g1, NB, H2, W2, s));
     NCHK(mask_round(n, a, a->g1, 128, 0, a->d2a, 128, 0, true, 128, P2, L_D2A, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_D2A, a->cat2, 256, NB, H2, W2, s));
+    NCHK(wgrad(n, a, L_D2A, a->cat2, 256, NB, H2, W2, s));
     NCHK(conv_dgrad(n, a, L_D2A, a->gs2, NB, H2, W2, s));            // [g_up2 | g_skip2]
     NCHK(mask_round(n, a, a->gs2, 256, 0, nullptr, 0, 0, false, 128, P2, L_UP2, s));
-    NCHK(wgrad<TAP_FINE4>(n, a, L_UP2, a->mb, 256, NB, H3, W3, s));
+    NCHK(wgrad(n, a, L_UP2, a->mb, 256, NB, H3, W3, s));
     NCHK(convT_dgrad(n, a, L_UP2, a->g0, NB, H3, W3, s));            // g(mb) [P3][256]
     // bottleneck
     NCHK(mask_round(n, a, a->g0, 256, 0, a->mb, 256, 0, true, 256, P3, L_MB, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_MB, a->ma, 256, NB, H3, W3, s));
+    NCHK(wgrad(n, a, L_MB, a->ma, 256, NB, H3, W3, s));
     NCHK(conv_dgrad(n, a, L_MB, a->g1, NB, H3, W3, s));
     NCHK(mask_round(n, a, a->g1, 256, 0, a->ma, 256, 0, true, 256, P3, L_MA, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_MA, a->p3, 128, NB, H3, W3, s));
+    NCHK(wgrad(n, a, L_MA, a->p3, 128, NB, H3, W3, s));
     NCHK(conv_dgrad(n, a, L_MA, a->g0, NB, H3, W3, s));              // g(p3) [P3][128]
     // encoder, level 2: g(enc2b) = pool routing of g(p3) + skip
     NCHK(pool_back(a->cat2, 256, 128, a->g0, a->gs2, 256, 128, a->g1, NB, H2, W2, 128, s));
     NCHK(mask_round(n, a, a->g1, 128, 0, a->cat2, 256, 128, true, 128, P2, L_E2B, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_E2B, a->e2a, 128, NB, H2, W2, s));
+    NCHK(wgrad(n, a, L_E2B, a->e2a, 128, NB, H2, W2, s));
     NCHK(conv_dgrad(n, a, L_E2B, a->g0, NB, H2, W2, s));
     NCHK(mask_round(n, a, a->g0, 128, 0, a->e2a, 128, 0, true, 128, P2, L_E2A, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_E2A, a->p2, 64, NB, H2, W2, s));
+    NCHK(wgrad(n, a, L_E2A, a->p2, 64, NB, H2, W2, s));
     NCHK(conv_dgrad(n, a, L_E2A, a->g1, NB, H2, W2, s));             // g(p2) [P2][64]
     // level 1
     NCHK(pool_back(a->cat1, 128, 64, a->g1, a->gs1, 128, 64, a->g0, NB, H1, W1, 64, s));
     NCHK(mask_round(n, a, a->g0, 64, 0, a->cat1, 128, 64, true, 64, P1, L_E1B, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_E1B, a->e1a, 64, NB, H1, W1, s));
+    NCHK(wgrad(n, a, L_E1B, a->e1a, 64, NB, H1, W1, s));
     NCHK(conv_dgrad(n, a, L_E1B, a->g1, NB, H1, W1, s));
     NCHK(mask_round(n, a, a->g1, 64, 0, a->e1a, 64, 0, true, 64, P1, L_E1A, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_E1A, a->p1, 32, NB, H1, W1, s));
+    NCHK(wgrad(n, a, L_E1A, a->p1, 32, NB, H1, W1, s));
     NCHK(conv_dgrad(n, a, L_E1A, a->g0, NB, H1, W1, s));             // g(p1) [P1][32]
     // level 0
     NCHK(pool_back(a->cat0, 64, 32, a->g0, a->gs0, 64, 32, a->g1, NB, H, W, 32, s));
     NCHK(mask_round(n, a, a->g1, 32, 0, a->cat0, 64, 32, true, 32, P0, L_E0B, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_E0B, a->e0a, 32, NB, H, W, s));
+    NCHK(wgrad(n, a, L_E0B, a->e0a, 32, NB, H, W, s));
     NCHK(conv_dgrad(n, a, L_E0B, a->g0, NB, H, W, s));
     NCHK(mask_round(n, a, a->g0, 32, 0, a->e0a, 32, 0, true, 32, P0, L_E0A, s));
-    NCHK(wgrad<TAP_CONV3>(n, a, L_E0A, stack, UNET_IN, NB, H, W, s));
+    NCHK(wgrad(n, a, L_E0A, stack, UNET_IN, NB, H, W, s));
     if (apply) {
         n->step += 1;
         NCHK(prep_weights(n, lr, 1, s));
