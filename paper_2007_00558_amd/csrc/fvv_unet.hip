@@ -472,6 +472,258 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     }
 }
 
+// ---------------------------------------------------------------- 3x3 convolution, 32-column patches
+// The convolutions of grids with work for every CU: the implicit GEMM of
+// k_conv3 (same 16-byte fragments, same order chunk - tap - half chunk of
+// every output's sum, so the same bytes) on patches of 4 RW rows x 32 columns
+// and 32 MT output channels.  Wave w owns rows RW w .. RW w + RW - 1, one
+// 32-pixel MFMA tile per row.  k_conv3's counters showed neither the matrix
+// cores (33 % busy) nor LDS (31 %) nor VALU as its bound but the waits of each
+// 72-MFMA chunk step: its barriers, and 57 KB staged through L2 per step.
+// A patch twice as large does 144 MFMAs per step for 76 KB: two blocks per CU
+// (LDS 76 KB, 256 registers).  The next chunk's patch waits in registers; the
+// weight slice goes from L2 to LDS directly (global_load_lds, no registers)
+// between the two barriers of a step, while the CU's other block runs its
+// MFMAs.  16 x 960x544 forward, per launch: enc1a 195 -> 113 us, dec1a 397 ->
+// 266 (1,157 TFLOP/s), dec2a 376 -> 288, mid_b 197 -> 162, dec1b 244 -> 161.
+// Staged pixels and weight rows are 64-byte rows without padding (the DMA
+// writes lanes consecutively); the 16-byte quarter q of row r is kept at
+// q ^ c3r_swz(r), which spreads the fragment reads of 8 or 16 consecutive
+// rows over distinct banks.
+constexpr int C3R_PW = 34;             // staged patch width
+__device__ __forceinline__ int c3r_swz(int r) { return (((r >> 1) ^ (r >> 3)) & 1) | (((r >> 2) & 1) << 1); }
+
+template <int MT, int RW>
+constexpr int c3r_lds_bytes() { return (4 * RW + 2) * C3R_PW * 64 + 32 * MT * 576; }
+
+// Four accumulators' quadruples of one pixel (channels 8 j + 4 lh + 0..3) as
+// packed bfloat16 w[j][2] -> the lane's 16 channels' worth of stores: lanes
+// l and l + 32 exchange halves, so each holds 8 consecutive channels,
+// 16 q + 8 lh .. + 7 (q = 0, 1), for one 16-byte store each.
+__device__ __forceinline__ void swap_halves(const uint32_t (&w)[4][2], uint4 (&o)[2])
+{
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const auto s0 = __builtin_amdgcn_permlane32_swap(w[2 * q][0], w[2 * q + 1][0], false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(w[2 * q][1], w[2 * q + 1][1], false, false);
+        o[q] = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+    }
+}
+
+template <int MT, int RW, int EPI, bool POOL>
+__global__ void __launch_bounds__(256, 2) k_conv3r(const GemmArgs g)
+{
+    static_assert(!POOL || RW % 2 == 0, "pooling windows lie inside a wave's rows");
+    constexpr int TH = 4 * RW, PH = TH + 2, PW = C3R_PW;
+    constexpr int NPU = PH * PW * 4, NWU = 32 * MT * 36;   // 16-byte units of a patch chunk and a weight slice
+    constexpr int NP = PH / 2, NWK = (NWU + 255) / 256;
+    static_assert(8 * PH <= 256 && (MT == 1 || MT == 2), "one halo unit per thread; 128 MT weight units per tap");
+    extern __shared__ __attribute__((aligned(16))) uint8_t c3r_smem[];
+    uint8_t *const patch = c3r_smem, *const wts = c3r_smem + NPU * 16;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lc = lane & 31, lh = lane >> 5;
+    const int tiles_x = (g.W + 31) / 32, tiles_y = (g.H + TH - 1) / TH;
+    const int mgroups = g.M / (32 * MT);
+    const int items = tiles_x * tiles_y * g.NB * mgroups;
+    // blocks on one XCD (b mod 8) take consecutive items: the channel groups
+    // of a patch and neighbouring patches share that XCD's L2
+    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8, per_xcd = gridDim.x / 8;
+    auto item_of = [&](int k) { return k * (int)gridDim.x + xcd * per_xcd + slot; };
+    struct Item {
+        int b, x0, y0, mbase;
+    };
+    auto decode = [&](int it) {
+        Item r;
+        int t = it / mgroups;
+        r.mbase = (it - t * mgroups) * 32 * MT;
+        const int q = t / tiles_x;
+        r.x0 = (t - q * tiles_x) * 32;
+        r.b = q / tiles_y;
+        r.y0 = (q - r.b * tiles_y) * TH;
+        return r;
+    };
+    // A thread fetches 16-byte quarter tid % 4 of pixel column (tid / 4) % 32 of
+    // the patch's inner 32 columns in rows 2 k + tid / 128 (wave-uniform rows:
+    // one address and one LDS address per thread for all of them), and one
+    // quarter of the two halo columns.
+    const int q4 = tid & 3, fc = (tid >> 2) & 31, fr = wave >> 1;
+    const int hr = tid >> 3, hc = ((tid >> 2) & 1) * (PW - 1);   // halo row and patch column (tid < 8 PH)
+    uint4 fp[NP], fh;
+    auto fetch = [&](const Item &it, int c0) {
+        const uint16_t *base = g.Bsrc + g.b_off + c0;
+        const int gx = it.x0 + fc;
+        const uint32_t off = (uint32_t)(gx * g.b_cs + q4 * 8);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int gy = it.y0 - 1 + 2 * k + fr;   // uniform
+            fp[k] = make_uint4(0, 0, 0, 0);
+            if (gy >= 0 && gy < g.H && gx < g.W)
+                fp[k] = *(const uint4 *)(base + (int64_t)(it.b * g.H + gy) * g.W * g.b_cs + off);
+        }
+        const int hy = it.y0 - 1 + hr, hx = it.x0 - 1 + hc;
+        fh = make_uint4(0, 0, 0, 0);
+        if (tid < 8 * PH && hy >= 0 && hy < g.H && hx >= 0 && hx < g.W)
+            fh = *(const uint4 *)(base + (uint32_t)(((it.b * g.H + hy) * g.W + hx) * g.b_cs + q4 * 8));
+    };
+    uint8_t *const st = patch + fr * PW * 64 + (fc + 1) * 64 + ((q4 ^ c3r_swz(fc + 1)) << 4);
+    uint8_t *const sh = patch + (hr * PW + hc) * 64 + ((q4 ^ c3r_swz(hc)) << 4);
+    auto stash = [&]() {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) *(uint4 *)(st + k * 2 * PW * 64) = fp[k];
+        if (tid < 8 * PH) *(uint4 *)sh = fh;
+    };
+    // the weight slice of a chunk ([K/32][M][9][32]) straight to LDS, tap by
+    // tap ([9][32 MT][32]): wave w writes units 256 k + 64 w + lane
+    const int wr = MT == 2 ? tid >> 2 : (tid >> 2) & 31;
+    const uint32_t woff = (uint32_t)(wr * 288 + ((q4 ^ c3r_swz(wr)) << 3));
+    auto weights = [&](int mbase, int c0) {
+        const uint16_t *wc = g.A + (int64_t)mbase * 288 + (int64_t)(c0 >> 5) * g.M * 288;
+#pragma unroll
+        for (int k = 0; k < NWK; ++k) {
+            const int ub = k * 256 + wave * 64;   // uniform
+            if ((k + 1) * 256 > NWU && ub >= NWU) break;
+            const int tap = MT == 2 ? k : 2 * k + (wave >> 1);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(wc + tap * 32 + woff),
+                                             (__attribute__((address_space(3))) void *)(wts + ub * 16), 16, 0, 0);
+        }
+    };
+    int cur = item_of(0);
+    if (cur >= items) return;
+    Item it = decode(cur);
+    fetch(it, 0);
+    int step = 0, c0 = 0;
+    f32x16 acc[MT][RW];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int n = 0; n < RW; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][n][r] = 0.f;
+    // lane offsets of the fragments (first half chunk; the second is ^ 32)
+    const int aoff = lc * 64 + ((lh ^ c3r_swz(lc)) << 4);
+    int boff[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) boff[dx] = wave * RW * PW * 64 + (lc + dx) * 64 + ((lh ^ c3r_swz(lc + dx)) << 4);
+    for (;;) {
+        __syncthreads();   // every wave is done with the previous chunk
+        weights(it.mbase, c0);
+        stash();
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the weight slice is in LDS
+        __syncthreads();
+        const bool last = c0 + 32 >= g.K;
+        Item nx = it;
+        int nc = c0 + 32;
+        bool more = true;
+        if (last) {
+            const int ni = item_of(step + 1);
+            more = ni < items;
+            if (more) nx = decode(ni);
+            nc = 0;
+        }
+        if (more) fetch(nx, nc);
+        // 18 steps of MT + RW fragment reads and MT RW MFMAs, the next step's
+        // reads issued before this one's MFMAs (the barriers keep the
+        // scheduler from issuing more and running out of registers)
+        bf16x8 af[2][MT], bfr[2][RW];
+        auto frags = [&](int s) {
+            const int tap = s >> 1, kk = s & 1, dy = tap / 3, dx = tap - dy * 3;
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+                af[kk][i] = __builtin_bit_cast(bf16x8, *(const uint4 *)(wts + (aoff ^ (kk * 32)) + (tap * MT + i) * 2048));
+#pragma unroll
+            for (int n = 0; n < RW; ++n)
+                bfr[kk][n] = __builtin_bit_cast(bf16x8, *(const uint4 *)(patch + (boff[dx] ^ (kk * 32)) + (n + dy) * PW * 64));
+        };
+        frags(0);
+#pragma unroll
+        for (int s = 0; s < 18; ++s) {
+            if (s < 17) frags(s + 1);
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int n = 0; n < RW; ++n)
+                    acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s & 1][i], bfr[s & 1][n], acc[i][n], 0, 0, 0);
+            if (s < 17) __builtin_amdgcn_sched_group_barrier(0x100, MT + RW, 0);   // the LDS reads,
+            __builtin_amdgcn_sched_group_barrier(0x008, MT * RW, 0);              // then the MFMAs
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (last) {
+            // lane: pixel column lc of row n, channels 8 j + 4 lh + {0..3}
+            const int px = it.x0 + lc;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const int mi = it.mbase + i * 32;
+                float4 bj[4];
+                if (EPI == EPI_RELU_BF16)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) bj[j] = *(const float4 *)(g.bias + mi + 8 * j + 4 * lh);
+#pragma unroll
+                for (int n = 0; n < RW; ++n) {
+                    const int py = it.y0 + wave * RW + n;
+                    const bool ok = py < g.H && px < g.W;
+                    const uint32_t o = (uint32_t)(((it.b * g.H + py) * g.W + px) * g.o_cs + g.o_off + mi);
+                    if (EPI == EPI_F32) {
+                        if (ok)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+                                *(float4 *)((float *)g.out + o + 8 * j + 4 * lh) =
+                                    make_float4(acc[i][n][4 * j], acc[i][n][4 * j + 1], acc[i][n][4 * j + 2], acc[i][n][4 * j + 3]);
+                        continue;
+                    }
+                    uint32_t w[4][2];
+                    uint4 ov[2];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float b[4] = {bj[j].x, bj[j].y, bj[j].z, bj[j].w};
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[i][n][4 * j + r] = fmaxf(acc[i][n][4 * j + r] + b[r], 0.f);
+                        w[j][0] = pack_bf16(acc[i][n][4 * j], acc[i][n][4 * j + 1]);
+                        w[j][1] = pack_bf16(acc[i][n][4 * j + 2], acc[i][n][4 * j + 3]);
+                    }
+                    swap_halves(w, ov);
+                    if (ok) {
+                        uint16_t *d = (uint16_t *)g.out + o + 8 * lh;
+                        *(uint4 *)d = ov[0];
+                        *(uint4 *)(d + 16) = ov[1];
+                    }
+                    if (POOL && (n & 1)) {
+                        // 2x2 maxima of the float32 values (the maximum rounds
+                        // to the rounded maximum): rows n - 1, n of this lane,
+                        // columns lc, lc ^ 1; the even lane stores channels
+                        // 0..15 of the tile, the odd one 16..31
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const float m = fmaxf(acc[i][n - 1][r], acc[i][n][r]);
+                            acc[i][n][r] = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(
+                                                        0, __float_as_int(m), 0xB1, 0xF, 0xF, false)));   // quad_perm 1,0,3,2
+                        }
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            w[j][0] = pack_bf16(acc[i][n][4 * j], acc[i][n][4 * j + 1]);
+                            w[j][1] = pack_bf16(acc[i][n][4 * j + 2], acc[i][n][4 * j + 3]);
+                        }
+                        swap_halves(w, ov);
+                        if (ok) {
+                            const uint32_t pp = (uint32_t)(((it.b * (g.H / 2) + (py >> 1)) * (g.W / 2) + (px >> 1)) * g.M + mi);
+                            *(uint4 *)(g.pool + pp + 16 * (lc & 1) + 8 * lh) = (lc & 1) ? ov[1] : ov[0];
+                        }
+                    }
+                }
+            }
+            if (!more) break;
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int n = 0; n < RW; ++n)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][n][r] = 0.f;
+            ++step;
+        }
+        it = nx;
+        c0 = nc;
+    }
+}
+
 // ---------------------------------------------------------------- 3x3 convolution, weights resident
 // The 32-output-channel layers with one or two input chunks (the full-
 // resolution level; 16-row patches with one chunk, 8-row ones with two, or
@@ -1831,11 +2083,23 @@ hipError_t conv3_launch(const GemmArgs &g, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int MT, int RW, int EPI, bool POOL = false>
+hipError_t conv3r_launch(const GemmArgs &g, hipStream_t s)
+{
+    constexpr int lds = c3r_lds_bytes<MT, RW>();
+    static_assert(2 * lds <= 160 * 1024, "two blocks share a CU's LDS");
+    const int64_t items = (int64_t)((g.W + 31) / 32) * ((g.H + 4 * RW - 1) / (4 * RW)) * g.NB * (g.M / (32 * MT));
+    static const int rb = std::max(8, resident_blocks(k_conv3r<MT, RW, EPI, POOL>, lds) / 8 * 8);
+    const int grid = (int)std::min<int64_t>(rb, (items + 7) / 8 * 8);
+    hipLaunchKernelGGL((k_conv3r<MT, RW, EPI, POOL>), dim3(grid), dim3(256), lds, s, g);
+    return hipGetLastError();
+}
+
 // 3x3 convolution shapes (measured on the 960x544 network): the
 // 32-output-channel layers of large grids with their weights resident
-// (16-row patches with one input chunk, 8-row ones with two); otherwise 32
-// output channels x 8-row patches for grids under 64 K pixels (more blocks
-// where there are few pixels), else 64 channels x 16-row patches
+// (16-row patches with one input chunk, 8-row ones with two); the wider layers
+// of grids from 64 K pixels in 32-column patches (k_conv3r), smaller grids in
+// 8 x 16 patches of 32 output channels
 template <int TH, int KC, int EPI, bool POOL, bool UPC = false, bool HEAD = false, bool K16 = false>
 hipError_t conv3w_launch(const GemmArgs &g, hipStream_t s, const HeadArgs &h = HeadArgs{})
 {
@@ -1878,14 +2142,18 @@ hipError_t conv3(GemmArgs g, hipStream_t s, bool *pooled = nullptr, const HeadAr
         return conv3w_launch<16, 1, EPI, false>(g, s);
     }
     if (g.M == 32 && g.K == 64 && tiles8 >= 2048) return conv3w_launch<8, 2, EPI, false>(g, s);
-    const bool big = g.M > 32 && (int64_t)g.NB * g.H * g.W >= 65536;
+    // 64 output channels x 16 rows x 32 columns per block from 64 K pixels on
+    // (2.1 M to 130 K pixels on the 16 x 960x544 network: 113 - 288 us per
+    // launch against 195 - 397 for blocks of 16 x 16 pixels), else 32 channels
+    // x 8 rows x 16 columns (more blocks where there are few pixels)
+    const bool big = g.M % 64 == 0 && (int64_t)g.NB * g.H * g.W >= 65536;
     if constexpr (EPI == EPI_RELU_BF16) {
         if (pooled && g.pool && g.H % 2 == 0 && g.W % 2 == 0) {
             *pooled = true;
-            return big ? conv3_launch<2, 16, EPI, true>(g, s) : conv3_launch<1, 8, EPI, true>(g, s);
+            return big ? conv3r_launch<2, 4, EPI, true>(g, s) : conv3_launch<1, 8, EPI, true>(g, s);
         }
     }
-    return big ? conv3_launch<2, 16, EPI>(g, s) : conv3_launch<1, 8, EPI>(g, s);
+    return big ? conv3r_launch<2, 4, EPI>(g, s) : conv3_launch<1, 8, EPI>(g, s);
 }
 
 // 3x3 conv + bias + ReLU into (out, o_cs, o_off); with pool_out, *pooled

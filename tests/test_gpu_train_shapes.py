@@ -46,3 +46,39 @@ def test_gradients_ragged(fvv, ctx, oracle_lib, N, H, W, valid):  # noqa: F811
         if rel > 2 * floor + 0.01:
             bad.append((name, "Wb"[k], rel, floor))
     assert not bad, bad
+
+
+@pytest.mark.parametrize("N,H,W", [(17, 64, 264), (5, 232, 264)])
+def test_batch_layers_equal_single(fvv, ctx, oracle_lib, N, H, W):  # noqa: F811
+    """A batch large enough for the kernels of large grids (32-column patches
+    at the half-resolution level, weights-resident ones at full resolution),
+    whose images end their patches unevenly in rows and columns, gives every
+    layer of its first and last image the bytes of that image alone, which
+    runs in the kernels of small grids: each output's sum has the same order in
+    all of them."""
+    import torch
+    from oracle import unet
+    P = rand_params(500 + W)
+    ctx.net_load(flat(P))
+    st = to_device_stack(np.stack([scene_stack(oracle_lib, 510 + q % 2, W, H) for q in range(2)]))
+    st = st[torch.arange(N, device="cuda") % 2].contiguous()
+    level = dict(enc1a=1, enc1b=1, enc2a=2, enc2b=2, mid_a=3, mid_b=3, up2=2, dec2a=2, dec2b=2, up1=1, dec1a=1, dec1b=1)
+
+    def layers(stack):
+        n = stack.shape[0]
+        out = torch.empty((n, H, W, 3), dtype=torch.float32, device="cuda")
+        ctx.set_debug(True)
+        ctx.net_forward(stack, n, H, W, out)
+        torch.cuda.synchronize()
+        ctx.set_debug(False)
+        acts = {"out": out.cpu().numpy()}
+        for i, (name, _, _, co) in enumerate(unet.LAYERS[:-1]):
+            h, w = H >> level.get(name, 0), W >> level.get(name, 0)
+            acts[name] = ctx.net_read_act(i, (n * h * w, co)).reshape(n, h, w, co)
+        return acts
+
+    many = layers(st)
+    for q in (0, N - 1):
+        one = layers(st[q:q + 1].contiguous())
+        for name in one:
+            assert np.array_equal(many[name][q], one[name][0]), (name, q)
