@@ -55,6 +55,8 @@ struct GemmArgs {
     const uint16_t *A;       // [M][taps][K] bf16
     const uint16_t *Bsrc;    // NHWC bf16 activations
     int b_cs, b_off;         // channel stride / offset of Bsrc
+    int b_split;             // channels from b_split on lie b_skip elements further on (a concatenation's
+    uint32_t b_skip;         // second plane); b_skip 0 = one plane
     const float *bias;       // per output channel (EPI_RELU_BF16, EPI_CONVT_BF16)
     void *out;
     int o_cs, o_off;
@@ -325,10 +327,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     // an item's rows is one contiguous run, element e of it at 8 e
     auto fetch = [&](const int32_t *po, int mbase, int c0) {
         const bool qin = c0 + (tid & 3) * 8 < k_src;
+        const uint32_t skip = c0 >= g.b_split ? g.b_skip : 0u;
 #pragma unroll
         for (int k = 0; k < NPF; ++k) {
             fp[k] = make_uint4(0, 0, 0, 0);
-            if (po[k] >= 0 && qin) fp[k] = *(const uint4 *)(g.Bsrc + (uint32_t)(po[k] + c0));
+            if (po[k] >= 0 && qin) fp[k] = *(const uint4 *)(g.Bsrc + ((uint32_t)(po[k] + c0) + skip));
         }
         const uint16_t *wc = g.A + (int64_t)mbase * 288 + (int64_t)(c0 >> 5) * g.M * 288;
 #pragma unroll
@@ -550,7 +553,7 @@ __global__ void __launch_bounds__(256, 2) k_conv3r(const GemmArgs g)
     const int hr = tid >> 3, hc = ((tid >> 2) & 1) * (PW - 1);   // halo row and patch column (tid < 8 PH)
     uint4 fp[NP], fh;
     auto fetch = [&](const Item &it, int c0) {
-        const uint16_t *base = g.Bsrc + g.b_off + c0;
+        const uint16_t *base = g.Bsrc + g.b_off + c0 + (c0 >= g.b_split ? g.b_skip : 0u);
         const int gx = it.x0 + fc;
         const uint32_t off = (uint32_t)(gx * g.b_cs + q4 * 8);
 #pragma unroll
@@ -862,7 +865,7 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g, const HeadArgs
 #pragma unroll
             for (int c = UPC ? 1 : 0; c < KC; ++c) {
                 fp[c][k] = make_uint4(0, 0, 0, 0);
-                if (in && c * 32 + (tid & 3) * 8 < k_src) fp[c][k] = *(const uint4 *)(g.Bsrc + (uint32_t)(off + c * 32));
+                if (in && c * 32 + (tid & 3) * 8 < k_src) fp[c][k] = *(const uint4 *)(g.Bsrc + ((uint32_t)(off + c * 32) + (c * 32 >= g.b_split ? g.b_skip : 0u)));
             }
         }
         if constexpr (UPC) fetch_up(tl);
@@ -1189,6 +1192,8 @@ struct WgradArgs {
     int g_cs, g_off;
     const uint16_t *X;       // bf16 layer input (columns)
     int x_cs, x_off;
+    int x_split;             // channels from x_split on lie x_skip elements further on (0 = one plane)
+    uint32_t x_skip;
     float *part;             // [chunks][M][taps*K] fp32 partial sums
     int NB, H, W;            // pixel grid of the contraction (the coarse grid for convT)
     int M, K;                // rows; input channels per tap (multiple of 32)
@@ -1273,7 +1278,8 @@ __global__ void __launch_bounds__(256, 2) k_wgrad3(const WgradArgs a)
             const int y = y0 - 1 + pr, x = x0 - 1 + px - pr * 18;
             fx[k] = make_uint4(0, 0, 0, 0);
             if (u < NXU && y >= 0 && y < a.H && x >= 0 && x < a.W && kb + c * 8 < x_src)
-                fx[k] = *(const uint4 *)(a.X + (uint32_t)(((b * a.H + y) * a.W + x) * a.x_cs + a.x_off + kb + c * 8));
+                fx[k] = *(const uint4 *)(a.X + ((uint32_t)(((b * a.H + y) * a.W + x) * a.x_cs + a.x_off + kb + c * 8) +
+                                                (kb + c * 8 >= a.x_split ? a.x_skip : 0u)));
         }
     };
     auto stash = [&]() {
@@ -1898,7 +1904,8 @@ struct unet_state {
     bool loaded = false;
 };
 
-// Forward activations (bf16; concat buffers hold [up | skip]) and, for
+// Forward activations (bf16; concat buffers hold a plane of the up half,
+// then one of the skip half, each NHWC) and, for
 // training, the fp32 gradient ping-pong, the concat gradients, the bf16
 // matrix-core operand and the partial sums.
 struct unet_act {
@@ -2159,10 +2166,11 @@ hipError_t conv3(GemmArgs g, hipStream_t s, bool *pooled = nullptr, const HeadAr
 // 3x3 conv + bias + ReLU into (out, o_cs, o_off); with pool_out, *pooled
 // tells whether the 2x2 max-pool of the output was written there as well,
 // with head, *headed whether the head ran on the output as well (and
-// head_only then leaves out unwritten)
+// head_only then leaves out unwritten).  split: the input is a concatenation
+// of two planes of that many channels each (i_cs = split)
 hipError_t conv_fwd(unet_state *n, int li, const uint16_t *in, int i_cs, int i_off, uint16_t *out, int o_cs, int o_off,
                     int NB, int H, int W, hipStream_t s, uint16_t *pool_out = nullptr, bool *pooled = nullptr,
-                    const HeadArgs *head = nullptr, bool *headed = nullptr, bool head_only = false)
+                    const HeadArgs *head = nullptr, bool *headed = nullptr, bool head_only = false, int split = 0)
 {
     const unet_layer &l = layers().L[li];
     GemmArgs g{};
@@ -2178,7 +2186,9 @@ hipError_t conv_fwd(unet_state *n, int li, const uint16_t *in, int i_cs, int i_o
     g.H = H;
     g.W = W;
     g.K = l.cin_pad;
-    g.k_src = std::min(i_cs - i_off, l.cin_pad);
+    g.k_src = split ? g.K : std::min(i_cs - i_off, l.cin_pad);
+    g.b_split = split;
+    g.b_skip = split ? (uint32_t)((size_t)NB * H * W - 1) * (uint32_t)split : 0u;
     g.M = l.cout;
     g.pool = pool_out;
     return conv3<EPI_RELU_BF16>(g, s, pooled, head, headed, head_only);
@@ -2232,6 +2242,15 @@ hipError_t pool(const uint16_t *in, int i_cs, int i_off, uint16_t *out, int NB, 
     return hipGetLastError();
 }
 
+// A concatenation at resolution level lv (32 << lv channels per half) holds
+// the up half's plane, then the skip half's, each NHWC: a half is written and
+// read in whole cache lines (interleaved per pixel, the 32-channel halves were
+// 64 bytes of every 128-byte line).
+uint16_t *skip_plane(uint16_t *cat, int lv, int NB, int H, int W)
+{
+    return cat + (((size_t)NB * H * W) >> (2 * lv)) * (size_t)(32 << lv);
+}
+
 // Whether the finest transposed convolution can run inside the next
 // convolution (weights-resident kernel with two input chunks).
 bool up0_fusable(int NB, int H, int W)
@@ -2240,14 +2259,16 @@ bool up0_fusable(int NB, int H, int W)
 }
 
 // dec0a with its input chunk 0 (the finest transposed convolution of d1b)
-// computed per patch: cat0's first 32 channels are neither written nor read
+// computed per patch: cat0's first plane is neither written nor read
 hipError_t dec0a_fused(unet_state *n, unet_act *a, int NB, int H, int W, hipStream_t s)
 {
     const unet_layer &l = layers().L[L_D0A], &u = layers().L[L_UP0];
     GemmArgs g{};
     g.A = n->wf + l.wf_off;
     g.Bsrc = a->cat0;
-    g.b_cs = 64;
+    g.b_cs = 32;
+    g.b_split = 32;
+    g.b_skip = (uint32_t)((size_t)NB * H * W - 1) * 32u;
     g.bias = n->w + l.b_off;
     g.out = a->d0a;
     g.o_cs = 32;
@@ -2274,28 +2295,31 @@ hipError_t forward_all(unet_state *n, unet_act *a, const uint16_t *stack, int NB
     a->H = H;
     a->W = W;
     const int H1 = H / 2, W1 = W / 2, H2 = H / 4, W2 = W / 4, H3 = H / 8, W3 = W / 8;
+    // the skip planes of the concatenations
+    uint16_t *const sk0 = skip_plane(a->cat0, 0, NB, H, W), *const sk1 = skip_plane(a->cat1, 1, NB, H, W),
+                   *const sk2 = skip_plane(a->cat2, 2, NB, H, W);
     NCHK(conv_fwd(n, L_E0A, stack, UNET_IN, 0, a->e0a, 32, 0, NB, H, W, s));
     bool pooled = false;
-    NCHK(conv_fwd(n, L_E0B, a->e0a, 32, 0, a->cat0, 64, 32, NB, H, W, s, a->p1, &pooled));
-    if (!pooled) NCHK(pool(a->cat0, 64, 32, a->p1, NB, H, W, 32, s));
+    NCHK(conv_fwd(n, L_E0B, a->e0a, 32, 0, sk0, 32, 0, NB, H, W, s, a->p1, &pooled));
+    if (!pooled) NCHK(pool(sk0, 32, 0, a->p1, NB, H, W, 32, s));
     NCHK(conv_fwd(n, L_E1A, a->p1, 32, 0, a->e1a, 64, 0, NB, H1, W1, s));
-    NCHK(conv_fwd(n, L_E1B, a->e1a, 64, 0, a->cat1, 128, 64, NB, H1, W1, s, a->p2, &pooled));
-    if (!pooled) NCHK(pool(a->cat1, 128, 64, a->p2, NB, H1, W1, 64, s));
+    NCHK(conv_fwd(n, L_E1B, a->e1a, 64, 0, sk1, 64, 0, NB, H1, W1, s, a->p2, &pooled));
+    if (!pooled) NCHK(pool(sk1, 64, 0, a->p2, NB, H1, W1, 64, s));
     NCHK(conv_fwd(n, L_E2A, a->p2, 64, 0, a->e2a, 128, 0, NB, H2, W2, s));
-    NCHK(conv_fwd(n, L_E2B, a->e2a, 128, 0, a->cat2, 256, 128, NB, H2, W2, s, a->p3, &pooled));
-    if (!pooled) NCHK(pool(a->cat2, 256, 128, a->p3, NB, H2, W2, 128, s));
+    NCHK(conv_fwd(n, L_E2B, a->e2a, 128, 0, sk2, 128, 0, NB, H2, W2, s, a->p3, &pooled));
+    if (!pooled) NCHK(pool(sk2, 128, 0, a->p3, NB, H2, W2, 128, s));
     NCHK(conv_fwd(n, L_MA, a->p3, 128, 0, a->ma, 256, 0, NB, H3, W3, s));
     NCHK(conv_fwd(n, L_MB, a->ma, 256, 0, a->mb, 256, 0, NB, H3, W3, s));
-    NCHK(convT_fwd(n, L_UP2, a->mb, 256, NB, H3, W3, a->cat2, 256, s));
-    NCHK(conv_fwd(n, L_D2A, a->cat2, 256, 0, a->d2a, 128, 0, NB, H2, W2, s));
+    NCHK(convT_fwd(n, L_UP2, a->mb, 256, NB, H3, W3, a->cat2, 128, s));
+    NCHK(conv_fwd(n, L_D2A, a->cat2, 128, 0, a->d2a, 128, 0, NB, H2, W2, s, nullptr, nullptr, nullptr, nullptr, false, 128));
     NCHK(conv_fwd(n, L_D2B, a->d2a, 128, 0, a->d2b, 128, 0, NB, H2, W2, s));
-    NCHK(convT_fwd(n, L_UP1, a->d2b, 128, NB, H2, W2, a->cat1, 128, s));
-    NCHK(conv_fwd(n, L_D1A, a->cat1, 128, 0, a->d1a, 64, 0, NB, H1, W1, s));
+    NCHK(convT_fwd(n, L_UP1, a->d2b, 128, NB, H2, W2, a->cat1, 64, s));
+    NCHK(conv_fwd(n, L_D1A, a->cat1, 64, 0, a->d1a, 64, 0, NB, H1, W1, s, nullptr, nullptr, nullptr, nullptr, false, 64));
     NCHK(conv_fwd(n, L_D1B, a->d1a, 64, 0, a->d1b, 64, 0, NB, H1, W1, s));
     a->up0_stored = !(lean && up0_fusable(NB, H, W));
     if (a->up0_stored) {
-        NCHK(convT_fwd(n, L_UP0, a->d1b, 64, NB, H1, W1, a->cat0, 64, s));
-        NCHK(conv_fwd(n, L_D0A, a->cat0, 64, 0, a->d0a, 32, 0, NB, H, W, s));
+        NCHK(convT_fwd(n, L_UP0, a->d1b, 64, NB, H1, W1, a->cat0, 32, s));
+        NCHK(conv_fwd(n, L_D0A, a->cat0, 32, 0, a->d0a, 32, 0, NB, H, W, s, nullptr, nullptr, nullptr, nullptr, false, 32));
     } else {
         NCHK(dec0a_fused(n, a, NB, H, W, s));
     }
@@ -2340,8 +2364,10 @@ void wgradT_launch(const WgradArgs &w, int chunks, hipStream_t s)
 }
 
 // weight gradient of layer li from a->G (its masked output gradient) and
-// its input X; (NB, H, W) is the contraction grid (the coarse grid for convT)
-hipError_t wgrad(unet_state *n, unet_act *a, int li, const uint16_t *X, int x_cs, int NB, int H, int W, hipStream_t s)
+// its input X; (NB, H, W) is the contraction grid (the coarse grid for convT);
+// split as in conv_fwd
+hipError_t wgrad(unet_state *n, unet_act *a, int li, const uint16_t *X, int x_cs, int NB, int H, int W, hipStream_t s,
+                 int split = 0)
 {
     const unet_layer &l = layers().L[li];
     WgradArgs w{};
@@ -2349,6 +2375,8 @@ hipError_t wgrad(unet_state *n, unet_act *a, int li, const uint16_t *X, int x_cs
     w.g_cs = l.cout;
     w.X = X;
     w.x_cs = x_cs;
+    w.x_split = split;
+    w.x_skip = split ? (uint32_t)((size_t)NB * H * W - 1) * (uint32_t)split : 0u;
     w.part = a->part;
     w.NB = NB;
     w.H = H;
@@ -2590,6 +2618,8 @@ hipError_t unet_train(unet_state *n, unet_act *a, const uint16_t *stack, const f
     const int P0 = NB * H * W, P1 = P0 / 4, P2 = P1 / 4, P3 = P2 / 4;
     const int H1 = H / 2, W1 = W / 2, H2 = H / 4, W2 = W / 4, H3 = H / 8, W3 = W / 8;
     const Layers &T = layers();
+    const uint16_t *const sk0 = skip_plane(a->cat0, 0, NB, H, W), *const sk1 = skip_plane(a->cat1, 1, NB, H, W),
+                         *const sk2 = skip_plane(a->cat2, 2, NB, H, W);
     // head: loss, gradient at dec0b, head weight/bias gradients
     HeadArgs h{};
     h.a = a->d0b;
@@ -2617,7 +2647,7 @@ hipError_t unet_train(unet_state *n, unet_act *a, const uint16_t *stack, const f
     NCHK(wgrad(n, a, L_D0B, a->d0a, 32, NB, H, W, s));
     NCHK(conv_dgrad(n, a, L_D0B, a->g1, NB, H, W, s));
     NCHK(mask_round(n, a, a->g1, 32, 0, a->d0a, 32, 0, true, 32, P0, L_D0A, s));
-    NCHK(wgrad(n, a, L_D0A, a->cat0, 64, NB, H, W, s));
+    NCHK(wgrad(n, a, L_D0A, a->cat0, 32, NB, H, W, s, 32));
     NCHK(conv_dgrad(n, a, L_D0A, a->gs0, NB, H, W, s));              // [g_up0 | g_skip0]
     NCHK(mask_round(n, a, a->gs0, 64, 0, nullptr, 0, 0, false, 32, P0, L_UP0, s));
     NCHK(wgrad(n, a, L_UP0, a->d1b, 64, NB, H1, W1, s));
@@ -2627,7 +2657,7 @@ hipError_t unet_train(unet_state *n, unet_act *a, const uint16_t *stack, const f
     NCHK(wgrad(n, a, L_D1B, a->d1a, 64, NB, H1, W1, s));
     NCHK(conv_dgrad(n, a, L_D1B, a->g1, NB, H1, W1, s));
     NCHK(mask_round(n, a, a->g1, 64, 0, a->d1a, 64, 0, true, 64, P1, L_D1A, s));
-    NCHK(wgrad(n, a, L_D1A, a->cat1, 128, NB, H1, W1, s));
+    NCHK(wgrad(n, a, L_D1A, a->cat1, 64, NB, H1, W1, s, 64));
     NCHK(conv_dgrad(n, a, L_D1A, a->gs1, NB, H1, W1, s));            // [g_up1 | g_skip1]
     NCHK(mask_round(n, a, a->gs1, 128, 0, nullptr, 0, 0, false, 64, P1, L_UP1, s));
     NCHK(wgrad(n, a, L_UP1, a->d2b, 128, NB, H2, W2, s));
@@ -2637,7 +2667,7 @@ hipError_t unet_train(unet_state *n, unet_act *a, const uint16_t *stack, const f
     NCHK(wgrad(n, a, L_D2B, a->d2a, 128, NB, H2, W2, s));
     NCHK(conv_dgrad(n, a, L_D2B, a->g1, NB, H2, W2, s));
     NCHK(mask_round(n, a, a->g1, 128, 0, a->d2a, 128, 0, true, 128, P2, L_D2A, s));
-    NCHK(wgrad(n, a, L_D2A, a->cat2, 256, NB, H2, W2, s));
+    NCHK(wgrad(n, a, L_D2A, a->cat2, 128, NB, H2, W2, s, 128));
     NCHK(conv_dgrad(n, a, L_D2A, a->gs2, NB, H2, W2, s));            // [g_up2 | g_skip2]
     NCHK(mask_round(n, a, a->gs2, 256, 0, nullptr, 0, 0, false, 128, P2, L_UP2, s));
     NCHK(wgrad(n, a, L_UP2, a->mb, 256, NB, H3, W3, s));
@@ -2650,24 +2680,24 @@ hipError_t unet_train(unet_state *n, unet_act *a, const uint16_t *stack, const f
     NCHK(wgrad(n, a, L_MA, a->p3, 128, NB, H3, W3, s));
     NCHK(conv_dgrad(n, a, L_MA, a->g0, NB, H3, W3, s));              // g(p3) [P3][128]
     // encoder, level 2: g(enc2b) = pool routing of g(p3) + skip
-    NCHK(pool_back(a->cat2, 256, 128, a->g0, a->gs2, 256, 128, a->g1, NB, H2, W2, 128, s));
-    NCHK(mask_round(n, a, a->g1, 128, 0, a->cat2, 256, 128, true, 128, P2, L_E2B, s));
+    NCHK(pool_back(sk2, 128, 0, a->g0, a->gs2, 256, 128, a->g1, NB, H2, W2, 128, s));
+    NCHK(mask_round(n, a, a->g1, 128, 0, sk2, 128, 0, true, 128, P2, L_E2B, s));
     NCHK(wgrad(n, a, L_E2B, a->e2a, 128, NB, H2, W2, s));
     NCHK(conv_dgrad(n, a, L_E2B, a->g0, NB, H2, W2, s));
     NCHK(mask_round(n, a, a->g0, 128, 0, a->e2a, 128, 0, true, 128, P2, L_E2A, s));
     NCHK(wgrad(n, a, L_E2A, a->p2, 64, NB, H2, W2, s));
     NCHK(conv_dgrad(n, a, L_E2A, a->g1, NB, H2, W2, s));             // g(p2) [P2][64]
     // level 1
-    NCHK(pool_back(a->cat1, 128, 64, a->g1, a->gs1, 128, 64, a->g0, NB, H1, W1, 64, s));
-    NCHK(mask_round(n, a, a->g0, 64, 0, a->cat1, 128, 64, true, 64, P1, L_E1B, s));
+    NCHK(pool_back(sk1, 64, 0, a->g1, a->gs1, 128, 64, a->g0, NB, H1, W1, 64, s));
+    NCHK(mask_round(n, a, a->g0, 64, 0, sk1, 64, 0, true, 64, P1, L_E1B, s));
     NCHK(wgrad(n, a, L_E1B, a->e1a, 64, NB, H1, W1, s));
     NCHK(conv_dgrad(n, a, L_E1B, a->g1, NB, H1, W1, s));
     NCHK(mask_round(n, a, a->g1, 64, 0, a->e1a, 64, 0, true, 64, P1, L_E1A, s));
     NCHK(wgrad(n, a, L_E1A, a->p1, 32, NB, H1, W1, s));
     NCHK(conv_dgrad(n, a, L_E1A, a->g0, NB, H1, W1, s));             // g(p1) [P1][32]
     // level 0
-    NCHK(pool_back(a->cat0, 64, 32, a->g0, a->gs0, 64, 32, a->g1, NB, H, W, 32, s));
-    NCHK(mask_round(n, a, a->g1, 32, 0, a->cat0, 64, 32, true, 32, P0, L_E0B, s));
+    NCHK(pool_back(sk0, 32, 0, a->g0, a->gs0, 64, 32, a->g1, NB, H, W, 32, s));
+    NCHK(mask_round(n, a, a->g1, 32, 0, sk0, 32, 0, true, 32, P0, L_E0B, s));
     NCHK(wgrad(n, a, L_E0B, a->e0a, 32, NB, H, W, s));
     NCHK(conv_dgrad(n, a, L_E0B, a->g0, NB, H, W, s));
     NCHK(mask_round(n, a, a->g0, 32, 0, a->e0a, 32, 0, true, 32, P0, L_E0A, s));
@@ -2691,23 +2721,23 @@ hipError_t unet_read_act(unet_act *a, int layer, void *host, size_t bytes, hipSt
     int cs = 0, off = 0, C = 0;
     switch (layer) {
     case L_E0A: src = a->e0a; cs = 32; C = 32; break;
-    case L_E0B: src = a->cat0; cs = 64; off = 32; C = 32; break;
+    case L_E0B: src = skip_plane(a->cat0, 0, a->NB, a->H, a->W); cs = C = 32; break;
     case L_E1A: src = a->e1a; cs = 64; C = 64; break;
-    case L_E1B: src = a->cat1; cs = 128; off = 64; C = 64; break;
+    case L_E1B: src = skip_plane(a->cat1, 1, a->NB, a->H, a->W); cs = C = 64; break;
     case L_E2A: src = a->e2a; cs = 128; C = 128; break;
-    case L_E2B: src = a->cat2; cs = 256; off = 128; C = 128; break;
+    case L_E2B: src = skip_plane(a->cat2, 2, a->NB, a->H, a->W); cs = C = 128; break;
     case L_MA: src = a->ma; cs = 256; C = 256; break;
     case L_MB: src = a->mb; cs = 256; C = 256; break;
-    case L_UP2: src = a->cat2; cs = 256; C = 128; break;
+    case L_UP2: src = a->cat2; cs = 128; C = 128; break;
     case L_D2A: src = a->d2a; cs = 128; C = 128; break;
     case L_D2B: src = a->d2b; cs = 128; C = 128; break;
-    case L_UP1: src = a->cat1; cs = 128; C = 64; break;
+    case L_UP1: src = a->cat1; cs = 64; C = 64; break;
     case L_D1A: src = a->d1a; cs = 64; C = 64; break;
     case L_D1B: src = a->d1b; cs = 64; C = 64; break;
     case L_UP0:
         if (!a->up0_stored) return hipErrorInvalidValue;
         src = a->cat0;
-        cs = 64;
+        cs = 32;
         C = 32;
         break;
     case L_D0A: src = a->d0a; cs = 32; C = 32; break;
