@@ -708,7 +708,10 @@ __global__ void __launch_bounds__(256, 2) k_conv3r(const GemmArgs g)
                         swap_halves(w, ov);
                         if (ok) {
                             const uint32_t pp = (uint32_t)(((it.b * (g.H / 2) + (py >> 1)) * (g.W / 2) + (px >> 1)) * g.M + mi);
-                            *(uint4 *)(g.pool + pp + 16 * (lc & 1) + 8 * lh) = (lc & 1) ? ov[1] : ov[0];
+                            const bool odd = lc & 1;   // by component: no address of the pair is taken
+                            *(uint4 *)(g.pool + pp + 16 * (lc & 1) + 8 * lh) =
+                                make_uint4(odd ? ov[1].x : ov[0].x, odd ? ov[1].y : ov[0].y, odd ? ov[1].z : ov[0].z,
+                                           odd ? ov[1].w : ov[0].w);
                         }
                     }
                 }
