@@ -23,7 +23,7 @@
 #define FVV_SPL_RECOMPUTE 0xFFFFFFFFu   // splat record whose footprint does not pack (x0 = 8191 with x1 > x0)
 #define FVV_TILE 32                 // output tile edge (pixels) of the fused kernel
 #define FVV_SBLK 8                  // source block edge (pixels) of the binning
-#define FVV_BIN_BPW 4               // source blocks per wave of the binning
+#define FVV_BIN_G 4                 // edge (source blocks) of a binning workgroup's square of blocks
 #define FVV_TILE_CAP_MIN 128        // minimum bin-list entries per output tile
 #define FVV_MAX_RIG 32              // cameras in a rig
 #define FVV_XCDS 8                  // XCDs of an MI355X: workgroup i runs on XCD i mod 8
@@ -40,6 +40,8 @@ struct fvv_src_desc {
     int32_t nbx;            // source blocks per row: ceil(W / FVV_SBLK)
     int32_t nblk;           // source blocks: nbx * ceil(H / FVV_SBLK)
     uint64_t nbx_magic;     // ceil(2^40 / nbx): blk / nbx = (blk nbx_magic) >> 40 (blk < 2^24)
+    int32_t ngx, ngrp;      // binning workgroups per row of blocks, and in all
+    uint64_t ngx_magic;     // ceil(2^40 / ngx)
     float wgt;              // view weight, 1 / centre distance
     float A[9], a[3], B[9], b[3];
     float sx, sy;           // focal ratios virtual / source (footprint scale)
@@ -141,7 +143,7 @@ inline void fvv_prof_end(fvv_prof *p, hipStream_t s, int stage, hipEvent_t e0)
 struct fvv_batch_dims {
     int n_views;
     int max_k;            // largest source-slot count of the batch
-    int max_blocks;       // largest source-block count of a selected camera
+    int max_groups;       // largest binning workgroup count of a selected camera
     int max_tiles_x;      // largest ntx
     int max_tiles_y;      // largest nty
     int total_tiles;      // tiles of all views

@@ -82,6 +82,7 @@ struct Workspace {
 struct ViewLayout {
     int ntx, nty, n_tiles, blk_stride, tile_cap, K;
     int nsrc;             // source slots: K, or 2K when layered
+    int max_groups;       // largest binning workgroup count of its cameras (plan_view)
     int32_t idx[FVV_MAX_K];
     double w[FVV_MAX_K];
 };
@@ -387,6 +388,13 @@ void pair_dir(const fvv_camera &s, const fvv_camera &d, float M[9], float m[3])
 int nblocks(const fvv_camera &c)
 {
     return ((c.width + FVV_SBLK - 1) / FVV_SBLK) * ((c.height + FVV_SBLK - 1) / FVV_SBLK);
+}
+
+// binning workgroups of a source camera: squares of FVV_BIN_G^2 blocks
+int bin_groups(const fvv_camera &c)
+{
+    constexpr int e = FVV_SBLK * FVV_BIN_G;
+    return ((c.width + e - 1) / e) * ((c.height + e - 1) / e);
 }
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -740,7 +748,11 @@ int32_t plan_view(fvv_ctx *c, const fvv_camera &vc, const fvv_synth_params &P, i
     const int K = select_k(c->rig.data(), pres, n, vc, P.k_nearest, L.idx, L.w);
     if (K < 1) return fail(c, FVV_E_STATE, "no camera present in the frame set");
     int nb[FVV_MAX_K];
-    for (int k = 0; k < K; ++k) nb[k] = nblocks(c->rig[L.idx[k]]);
+    L.max_groups = 0;
+    for (int k = 0; k < K; ++k) {
+        nb[k] = nblocks(c->rig[L.idx[k]]);
+        L.max_groups = std::max(L.max_groups, bin_groups(c->rig[L.idx[k]]));
+    }
     layout_sizes(L, vc.width, vc.height, nb, K, layered);
     return FVV_OK;
 }
@@ -792,6 +804,9 @@ void fill_desc(fvv_ctx *c, fvv_view_desc &d, const fvv_camera &vc, const ViewLay
         sd.nbx = (sc.width + FVV_SBLK - 1) / FVV_SBLK;
         sd.nbx_magic = ((1ULL << 40) + (uint64_t)sd.nbx - 1) / (uint64_t)sd.nbx;
         sd.nblk = nblocks(sc);
+        sd.ngx = (sd.nbx + FVV_BIN_G - 1) / FVV_BIN_G;
+        sd.ngrp = bin_groups(sc);
+        sd.ngx_magic = ((1ULL << 40) + (uint64_t)sd.ngx - 1) / (uint64_t)sd.ngx;
         sd.wgt = (float)L.w[k];
         pair_dir(sc, vc, sd.A, sd.a);
         pair_dir(vc, sc, sd.B, sd.b);
@@ -865,7 +880,7 @@ int32_t launch_views(fvv_ctx *c, Workspace &Wk, const fvv_camera *virts, const f
         dims.total_tiles += L.n_tiles;
         dims.max_k = std::max(dims.max_k, L.nsrc);
         dims.any_layered = dims.any_layered || layered;
-        dims.max_blocks = std::max(dims.max_blocks, L.blk_stride);
+        dims.max_groups = std::max(dims.max_groups, L.max_groups);
         dims.max_tiles_x = std::max(dims.max_tiles_x, L.ntx);
         dims.max_tiles_y = std::max(dims.max_tiles_y, L.nty);
         dims.fill_bg = dims.fill_bg || Ps[v].fill_mode == FVV_FILL_BG;
@@ -1746,7 +1761,7 @@ int32_t fvv_synthesize_noalloc(fvv_ctx *c, const fvv_camera *virt, const fvv_syn
     d.open_list = (int2 *)(base + off_open);
     d.out = (uint8_t *)out_dev;
     d.out_pitch = out_pitch;
-    const fvv_batch_dims dims{1, L.nsrc, L.blk_stride, L.ntx, L.nty, L.n_tiles, P.fill_mode == FVV_FILL_BG, false,
+    const fvv_batch_dims dims{1, L.nsrc, L.max_groups, L.ntx, L.nty, L.n_tiles, P.fill_mode == FVV_FILL_BG, false,
                               P.path == FVV_PATH_LAYERED};
     const hipStream_t s = (hipStream_t)stream;
     if (c->slots[si].ready_stream != s) HIPCHECK(c, hipStreamWaitEvent(s, c->slots[si].ready, 0));
