@@ -60,7 +60,7 @@ struct fvv_view_desc {
                             // src[K..2K) background layers of the same cameras
     // binning
     int32_t *counts;        // ntx*nty tile counters (zero between calls; cleared by the tile kernel)
-    int32_t *list;          // ntx*nty*tile_cap entries: source slot << 24 | source block
+    int32_t *list;          // ntx*nty*tile_cap entries (fvv_list_entry)
     int4 *bbox;             // nsrc*blk_stride tile ranges (x0, x1, y0, y1; x0 > x1 = empty)
     // per-pixel splat records written by the binning, nsrc*blk_stride*64
     // (slot, block, lane): x = depth bits of the projected point
@@ -89,6 +89,16 @@ struct fvv_view_desc {
     float *dbg_depth;
     fvv_src_desc src[FVV_KMAX];
 };
+
+// A bin-list entry: source slot (< 8), block row and column (< 8192 each: a
+// source edge is at most 65,535 pixels).
+__host__ __device__ inline int32_t fvv_list_entry(int slot, int row, int col)
+{
+    return (int32_t)((uint32_t)slot << 26 | (uint32_t)row << 13 | (uint32_t)col);
+}
+__host__ __device__ inline uint32_t fvv_entry_slot(int32_t e) { return (uint32_t)e >> 26; }
+__host__ __device__ inline uint32_t fvv_entry_row(int32_t e) { return ((uint32_t)e >> 13) & 0x1FFFu; }
+__host__ __device__ inline uint32_t fvv_entry_col(int32_t e) { return (uint32_t)e & 0x1FFFu; }
 
 // source slots of a view: one per selected camera, two when layered
 __host__ __device__ inline int fvv_nsrc(const fvv_view_desc &d) { return d.layered ? 2 * d.K : d.K; }

@@ -88,18 +88,16 @@ __device__ __forceinline__ float div_by(float a, float b, float y)
 // RN(1/b) for a normal b with a normal reciprocal (every projected depth,
 // 0.01 < b < 2^126): the hardware reciprocal (within one ulp of 1/b) refined
 // by one Newton step in fused multiply-adds, y0 + y0 (1 - b y0), is the
-// correctly rounded reciprocal for every significand of b except all ones.
-// There the step can stay on the even neighbour one ulp below RN(1/b), whose
-// significand is odd (1/b lies just above the midpoint of the two), so that
-// significand gets its low bit set.  Three instructions fewer than the
-// correctly rounded division; fvv_check_reciprocal compares the two over
+// correctly rounded reciprocal for every significand of b and every such y0 but
+// one: b all ones and y0 the even neighbour below 1/b, where the step ends in a
+// tie.  The hardware's y0 for that significand is the odd neighbour above (its
+// result depends on the significand alone), so the step is exact for all;
+// fvv_check_reciprocal compares it with the correctly rounded division over
 // every significand of a range of binades on the device.
 __device__ __forceinline__ float rcp_rn(float b)
 {
     const float y0 = __builtin_amdgcn_rcpf(b);
-    const float y1 = __fmaf_rn(__fmaf_rn(-b, y0, 1.0f), y0, y0);
-    const uint32_t ones = ((f2u(b) & 0x7FFFFFu) + 1u) >> 23;   // 1 iff the significand is all ones
-    return u2f(f2u(y1) | ones);
+    return __fmaf_rn(__fmaf_rn(-b, y0, 1.0f), y0, y0);
 }
 
 // Row of source block blk (< 2^24; nbx <= 8192): with m = ceil(2^40 / nbx),
@@ -378,10 +376,10 @@ __global__ void __launch_bounds__(256) k_bin(const fvv_view_desc *__restrict__ v
         s_t[wave * BIN_G + q] = tr;
         if (q < nq) vd.bbox[(int64_t)k * vd.blk_stride + blk0 + q] = tr;
     }
-    auto put = [&](int tile, int pos, int blk) {
+    auto put = [&](int tile, int pos, int row, int col) {
         if (pos < vd.tile_cap)
             ((__attribute__((address_space(1))) int32_t *)vd.list)[(uint64_t)(uint32_t)tile * (uint32_t)vd.tile_cap +
-                                                                   (uint32_t)pos] = (k << 24) | blk;
+                                                                   (uint32_t)pos] = fvv_list_entry(k, row, col);
     };
     auto reserve = [&](int tile, int n) {
         return __hip_atomic_fetch_add((__attribute__((address_space(1))) int32_t *)(vd.counts + tile), n, __ATOMIC_RELAXED,
@@ -424,8 +422,7 @@ __global__ void __launch_bounds__(256) k_bin(const fvv_view_desc *__restrict__ v
         if (n)
             s_base[threadIdx.x] = reserve((u.z + (int)(threadIdx.x / BIN_UNION)) * vd.ntx + u.x + (int)(threadIdx.x % BIN_UNION), n);
         __syncthreads();
-        if (on) put((r.z + ey) * vd.ntx + r.x + ex, s_base[cell] + rank,
-                    (gy * BIN_G + g / BIN_G) * s.nbx + bx0 + g % BIN_G);
+        if (on) put((r.z + ey) * vd.ntx + r.x + ex, s_base[cell] + rank, gy * BIN_G + g / BIN_G, bx0 + g % BIN_G);
     } else {
         for (int q = 0; q < BIN_G; ++q) {
             const int4 r = s_t[wave * BIN_G + q];
@@ -433,7 +430,7 @@ __global__ void __launch_bounds__(256) k_bin(const fvv_view_desc *__restrict__ v
             const int nx = r.y - r.x + 1, n = nx * (r.w - r.z + 1);
             for (int e = lane; e < n; e += 64) {
                 const int tile = (r.z + e / nx) * vd.ntx + r.x + e % nx;
-                put(tile, reserve(tile, 1), blk0 + q);
+                put(tile, reserve(tile, 1), by, bx0 + q);
             }
         }
     }
@@ -506,11 +503,147 @@ __device__ __forceinline__ unsigned long long filter_key(unsigned long long c, u
 }
 
 // ---------------------------------------------------------------- blend
-// Backward warp of output pixel (x, y) at depth zf into the K source slots
-// from k0 (one layer's selected cameras); taps whose source depth agrees with
-// the warped depth within tau are mixed bilinearly, cameras by their
-// distance weights.  Returns true and the RGBA8 colour if any camera
-// contributes.
+// What a sample needs of a source camera, in scalar registers: read once per
+// camera (left to the compiler, the reads sink into the branches that use them,
+// and every sample waits for the scalar cache again).
+struct Cam {
+    float B[9], b[3], wgt, tau;
+    int W, H;
+    const uint2 *texel;
+    const fvv_src_desc *d;   // the rest (samples at the image edge)
+};
+// (PIN: callers in uniform control flow only.)
+template <bool PIN>
+__device__ __forceinline__ Cam load_cam(const fvv_src_desc &s, float tau)
+{
+    Cam c;
+    c.tau = tau;
+    c.d = &s;
+#pragma unroll
+    for (int e = 0; e < 9; ++e) c.B[e] = s.B[e];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) c.b[e] = s.b[e];
+    c.wgt = s.wgt;
+    c.W = s.W;
+    c.H = s.H;
+    c.texel = s.texel;
+    if constexpr (PIN) {
+#pragma unroll
+        for (int e = 0; e < 9; ++e) asm volatile("" : "+s"(c.B[e]));
+#pragma unroll
+        for (int e = 0; e < 3; ++e) asm volatile("" : "+s"(c.b[e]));
+        asm volatile("" : "+s"(c.wgt), "+s"(c.tau), "+s"(c.W), "+s"(c.H), "+s"(c.texel));
+    }
+    return c;
+}
+
+// Colour sum c and weight sum of four taps tx with bilinear weights wt: those
+// whose source depth agrees with the warped depth q2 within lim.  A texel
+// without depth holds FVV_NO_DEPTH, a NaN as float32, so the consistency test
+// alone rejects it (NaN <= lim is false).
+__device__ __forceinline__ float mix_taps(const uint2 (&tx)[4], const float (&wt)[4], float q2, float lim, float (&c)[3])
+{
+    float csum = 0.f;
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        const float w = fabsf(__fsub_rn(u2f(tx[n].y), q2)) <= lim ? wt[n] : 0.0f;
+        c[0] = n ? fmaf(w, (float)(tx[n].x & 0xFF), c[0]) : w * (float)(tx[n].x & 0xFF);
+        c[1] = n ? fmaf(w, (float)((tx[n].x >> 8) & 0xFF), c[1]) : w * (float)((tx[n].x >> 8) & 0xFF);
+        c[2] = n ? fmaf(w, (float)((tx[n].x >> 16) & 0xFF), c[2]) : w * (float)((tx[n].x >> 16) & 0xFF);
+        csum = n ? csum + w : w;
+    }
+    return csum;
+}
+
+// A sample with a tap off the image (or no tap on it: returns 0): the four taps
+// are read from clamped coordinates; a tap off the image gets weight 0 (adding
+// 0 * colour and 0 to the sums leaves them unchanged, as skipping it would).
+__device__ __forceinline__ float sample_edge(const Cam &s, float u, float v, float q2, float lim, float (&c)[3])
+{
+    c[0] = c[1] = c[2] = 0.f;
+    if (!(u >= -0.5f && u <= s.d->umax) || !(v >= -0.5f && v <= s.d->vmax)) return 0.f;
+    const float fi0 = floorf(u), fj0 = floorf(v);
+    const float fu = __fsub_rn(u, fi0), fv = __fsub_rn(v, fj0);
+    const int i0 = (int)fi0, j0 = (int)fj0;   // -1 .. W - 1, -1 .. H - 1: only the outer taps can fall off
+    const float gu = 1.0f - fu, gv = 1.0f - fv;
+    const float wx0 = i0 >= 0 ? gu : 0.0f, wx1 = i0 + 1 < s.W ? fu : 0.0f;
+    const float wy0 = j0 >= 0 ? gv : 0.0f, wy1 = j0 + 1 < s.H ? fv : 0.0f;
+    const float wt[4] = {wx0 * wy0, wx1 * wy0, wx0 * wy1, wx1 * wy1};
+    const int ic[2] = {max(i0, 0), min(i0 + 1, s.W - 1)};
+    const uint32_t jr[2] = {(uint32_t)__umul24((uint32_t)max(j0, 0), (uint32_t)s.W),
+                            (uint32_t)__umul24((uint32_t)min(j0 + 1, s.H - 1), (uint32_t)s.W)};
+    const gmem<unsigned long long> *tex = gptr((const unsigned long long *)s.texel);
+    uint2 tx[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        const unsigned long long t = tex[jr[n >> 1] + (uint32_t)ic[n & 1]];
+        tx[n] = make_uint2((uint32_t)t, (uint32_t)(t >> 32));
+    }
+    return mix_taps(tx, wt, q2, lim, c);
+}
+
+// One camera's sample of an output pixel: backward warp of pixel (fx, y) at
+// depth zf (a NaN where the pixel has none) into source s, and the bilinear
+// colour sum c of the four taps whose source depth agrees with the warped depth
+// within tau; returns their weight sum (0 or a NaN: the camera gives nothing).
+// by = B[1] y, B[4] y, B[7] y, shared by the pixels of an output row; qinv is
+// the correctly rounded reciprocal of the warped depth.
+// Decisions (sample in range, tap valid and depth-consistent, camera survives)
+// in float32 op by op; the colour mix is value arithmetic and uses fused
+// multiply-adds and hardware reciprocals.
+// A sample whose four taps lie inside the image -- all but those at its very
+// edge -- needs no range tests, clamped coordinates or edge weights: it takes
+// two 16-byte loads (the taps of a row are neighbours in memory) and two integer
+// compares: 87 vector instructions per pixel and camera against 114.
+__device__ __forceinline__ float sample(const Cam &s, const float (&by)[3], float fx, float zf, float (&c)[3],
+                                        float &qinv)
+{
+    const float q0 = __fadd_rn(__fmul_rn(__fadd_rn(__fadd_rn(__fmul_rn(s.B[0], fx), by[0]), s.B[2]), zf), s.b[0]);
+    const float q1 = __fadd_rn(__fmul_rn(__fadd_rn(__fadd_rn(__fmul_rn(s.B[3], fx), by[1]), s.B[5]), zf), s.b[1]);
+    const float q2 = __fadd_rn(__fmul_rn(__fadd_rn(__fadd_rn(__fmul_rn(s.B[6], fx), by[2]), s.B[8]), zf), s.b[2]);
+    const float r = rcp_rn(q2);
+    qinv = r;
+    const float u = div_by(q0, q2, r), v = div_by(q1, q2, r);
+    const float lim = __fmul_rn(s.tau, q2);
+    // floor; a NaN coordinate (overflowed products only) converts to 0 and its
+    // weights are NaN, so it ends without a positive weight sum
+    int i0, j0;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i0) : "v"(u));
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(j0) : "v"(v));
+    const bool front = q2 > FVV_ZCLIP;
+    const bool inside = front & ((uint32_t)i0 < (uint32_t)(s.W - 1)) & ((uint32_t)j0 < (uint32_t)(s.H - 1));
+    float csum = 0.f;
+    if (inside) {
+        const float fu = __builtin_amdgcn_fractf(u), fv = __builtin_amdgcn_fractf(v);   // u - floor(u), exact for u >= 0
+        const float gu = 1.0f - fu, gv = 1.0f - fv;
+        const float wt[4] = {gu * gv, fu * gv, gu * fv, fu * fv};
+        // 32-bit byte offsets (a source has < 2^27 pixels of 8 bytes)
+        const uint32_t o = (__umul24((uint32_t)j0, (uint32_t)s.W) + (uint32_t)i0) * 8u;
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(8)));
+        const auto *base = (const __attribute__((address_space(1))) uint8_t *)s.texel;
+        const u32x4 a = *(const __attribute__((address_space(1))) u32x4 *)(base + o);
+        const u32x4 b = *(const __attribute__((address_space(1))) u32x4 *)(base + (o + (uint32_t)s.W * 8u));
+        const uint2 tx[4] = {make_uint2(a.x, a.y), make_uint2(a.z, a.w), make_uint2(b.x, b.y), make_uint2(b.z, b.w)};
+        csum = mix_taps(tx, wt, q2, lim, c);
+    }
+    if (__builtin_expect((__builtin_amdgcn_ballot_w64(front) & ~__builtin_amdgcn_ballot_w64(inside)) != 0, 0))   // uniform
+        if (front & !inside) csum = sample_edge(s, u, v, q2, lim, c);
+    return csum;
+}
+
+// the mixed colour as RGBA8
+__device__ __forceinline__ uint32_t mixed(const float (&acc)[3], float wsum)
+{
+    const float iw = __builtin_amdgcn_rcpf(wsum);
+    const float r = fminf(floorf(fmaf(acc[0], iw, 0.5f)), 255.f);
+    const float g = fminf(floorf(fmaf(acc[1], iw, 0.5f)), 255.f);
+    const float b = fminf(floorf(fmaf(acc[2], iw, 0.5f)), 255.f);
+    return (uint32_t)r | ((uint32_t)g << 8) | ((uint32_t)b << 16) | 0xFF000000u;
+}
+
+// The samples of output pixel (x, y) at depth zf in the K source slots from k0
+// (one layer's selected cameras), cameras mixed by their distance weights.
+// Returns true and the RGBA8 colour if any camera contributes.
 //
 // ST (learned path): also the pixel's stack channels ch[0..14] from the
 // same per-camera samples: for each of the first three slots that
@@ -521,71 +654,26 @@ template <bool ST>
 __device__ __forceinline__ bool blend_pixel(const fvv_view_desc &vd, int k0, int x, int y, float zf, uint32_t &rgba,
                                             float *ch = nullptr)
 {
-    // Decisions (sample in range, tap valid and depth-consistent, camera
-    // survives) in float32 op by op; the colour mix is value arithmetic and
-    // uses fused multiply-adds and hardware reciprocals.
-    float acc0 = 0.f, acc1 = 0.f, acc2 = 0.f, wsum = 0.f;
+    float acc[3] = {0.f, 0.f, 0.f}, wsum = 0.f;
+    const float fx = (float)x, fy = (float)y;
     auto camera = [&](int k, float *chk) {
-        const fvv_src_desc &s = vd.src[k];
-        float q0, q1, q2;
-        project(s.B, s.b, (float)x, (float)y, zf, q0, q1, q2);
-        if (!(q2 > FVV_ZCLIP)) return;
-        const float r = rcp_rn(q2);
-        const float u = div_by(q0, q2, r), v = div_by(q1, q2, r);
-        if (!(u >= -0.5f && u <= s.umax)) return;
-        if (!(v >= -0.5f && v <= s.vmax)) return;
-        const float fi0 = floorf(u), fj0 = floorf(v);
-        const float fu = __fsub_rn(u, fi0), fv = __fsub_rn(v, fj0);
-        const int i0 = (int)fi0, j0 = (int)fj0;
-        const float lim = __fmul_rn(vd.tau, q2);
-        // i0 >= -1 and i0 <= W - 1 (likewise j0): only the outer taps can fall
-        // off.  The four taps are read together from clamped coordinates; a
-        // tap off the image or not depth-consistent gets weight 0 (adding
-        // 0 * colour and 0 to the sums leaves them unchanged, as skipping it
-        // would).
-        const float gu = 1.0f - fu, gv = 1.0f - fv;
-        const float wx0 = i0 >= 0 ? gu : 0.0f, wx1 = i0 + 1 < s.W ? fu : 0.0f;
-        const float wy0 = j0 >= 0 ? gv : 0.0f, wy1 = j0 + 1 < s.H ? fv : 0.0f;
-        const float wt[4] = {wx0 * wy0, wx1 * wy0, wx0 * wy1, wx1 * wy1};
-        const int ic[2] = {max(i0, 0), min(i0 + 1, s.W - 1)};
-        // 32-bit texel indices (a source has < 2^27 pixels): a uniform base
-        // plus a 32-bit offset needs no 64-bit address arithmetic
-        const uint32_t jr[2] = {(uint32_t)__umul24((uint32_t)max(j0, 0), (uint32_t)s.W),
-                                (uint32_t)__umul24((uint32_t)min(j0 + 1, s.H - 1), (uint32_t)s.W)};
-        const gmem<unsigned long long> *tex = gptr((const unsigned long long *)s.texel);
-        uint2 tx[4];
+        const Cam s = load_cam<false>(vd.src[k], vd.tau);
+        const float by[3] = {__fmul_rn(s.B[1], fy), __fmul_rn(s.B[4], fy), __fmul_rn(s.B[7], fy)};
+        float c[3], r;
+        const float csum = sample(s, by, fx, zf, c, r);
+        if (!(csum > 0.f)) return;
+        const float rc = __builtin_amdgcn_rcpf(csum), inv = s.wgt * rc;
 #pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            const unsigned long long t = tex[jr[n >> 1] + (uint32_t)ic[n & 1]];
-            tx[n] = make_uint2((uint32_t)t, (uint32_t)(t >> 32));
-        }
-        float c0 = 0.f, c1 = 0.f, c2 = 0.f, csum = 0.f;
-#pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            // a texel without depth holds FVV_NO_DEPTH, a NaN as float32,
-            // so the consistency test alone rejects it (NaN <= lim is false)
-            const float w = fabsf(__fsub_rn(u2f(tx[n].y), q2)) <= lim ? wt[n] : 0.0f;
-            c0 = fmaf(w, (float)(tx[n].x & 0xFF), c0);
-            c1 = fmaf(w, (float)((tx[n].x >> 8) & 0xFF), c1);
-            c2 = fmaf(w, (float)((tx[n].x >> 16) & 0xFF), c2);
-            csum += w;
-        }
-        // a camera without a consistent tap adds nothing (no branch, so the
-        // colour words are read with the depths)
-        const bool any = csum > 0.f;
-        const float inv = any ? s.wgt * __builtin_amdgcn_rcpf(csum) : 0.0f;
-        acc0 = fmaf(c0, inv, acc0);
-        acc1 = fmaf(c1, inv, acc1);
-        acc2 = fmaf(c2, inv, acc2);
-        wsum += any ? s.wgt : 0.0f;
-        if (ST && chk && any) {
+        for (int e = 0; e < 3; ++e) acc[e] = fmaf(c[e], inv, acc[e]);
+        wsum += s.wgt;
+        if (ST && chk) {
             // colour / csum / 255: value arithmetic (within a bfloat16 step
             // of the exact quotient); the inverse depth 0.5 / q2 is exact:
             // half of the correctly rounded reciprocal
-            const float icol = __builtin_amdgcn_rcpf(csum) * (1.0f / 255.0f);
-            chk[0] = c0 * icol;
-            chk[1] = c1 * icol;
-            chk[2] = c2 * icol;
+            const float icol = rc * (1.0f / 255.0f);
+            chk[0] = c[0] * icol;
+            chk[1] = c[1] * icol;
+            chk[2] = c[2] * icol;
             chk[3] = fminf(0.5f * r, 1.0f);
             chk[4] = 1.0f;
         }
@@ -600,12 +688,41 @@ __device__ __forceinline__ bool blend_pixel(const fvv_view_desc &vd, int k0, int
         for (int k = 0; k < vd.K; ++k) camera(k0 + k, nullptr);
     }
     if (!(wsum > 0.f)) return false;
-    const float iw = __builtin_amdgcn_rcpf(wsum);
-    const float r = fminf(floorf(fmaf(acc0, iw, 0.5f)), 255.f);
-    const float g = fminf(floorf(fmaf(acc1, iw, 0.5f)), 255.f);
-    const float b = fminf(floorf(fmaf(acc2, iw, 0.5f)), 255.f);
-    rgba = (uint32_t)r | ((uint32_t)g << 8) | ((uint32_t)b << 16) | 0xFF000000u;
+    rgba = mixed(acc, wsum);
     return true;
+}
+
+// Four pixels (x .. x + 3, y) at depths zf (NaN = none) in the first K slots,
+// camera by camera: a camera's matrices and row terms are read and computed
+// once for the four.  slot / rgba of a pixel with a mixed colour.
+__device__ __forceinline__ void blend_four(const fvv_view_desc &vd, int x, int y, const float (&zf)[4],
+                                           uint32_t (&slot)[4], uint32_t (&rgba)[4])
+{
+    float acc[4][3], wsum[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q][0] = acc[q][1] = acc[q][2] = wsum[q] = 0.f;
+    const float fx = (float)x, fy = (float)y;
+    for (int k = 0; k < vd.K; ++k) {
+        const Cam s = load_cam<true>(vd.src[k], vd.tau);
+        const float by[3] = {__fmul_rn(s.B[1], fy), __fmul_rn(s.B[4], fy), __fmul_rn(s.B[7], fy)};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float c[3], r;
+            const float csum = sample(s, by, fx + (float)q, zf[q], c, r);
+            if (csum > 0.f) {
+                const float inv = s.wgt * __builtin_amdgcn_rcpf(csum);
+#pragma unroll
+                for (int e = 0; e < 3; ++e) acc[q][e] = fmaf(c[e], inv, acc[q][e]);
+                wsum[q] += s.wgt;
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (wsum[q] > 0.f) {
+            slot[q] = f2u(zf[q]);
+            rgba[q] = mixed(acc[q], wsum[q]);
+        }
 }
 
 // Learned-path input of output pixel (x, y): channels ch[0..14] from
@@ -707,84 +824,98 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
     // and its block arithmetic runs on the scalar unit
     const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int si = lane & (FVV_SBLK - 1), sj = lane / FVV_SBLK;
-    // this lane's splat record of block `ent`, written by the binning
-    // (the same projection and footprint as splat_point, computed once per
-    // block instead of once per tile that lists it)
-    auto block_rec = [&](int ent) -> unsigned long long {
-        ent = __builtin_amdgcn_readfirstlane(ent);   // uniform (see above)
-        return gptr(vd.spl)[((uint32_t)((ent >> 24) * vd.blk_stride + (ent & 0xFFFFFF)) << 6) + (uint32_t)lane];
+    // A list entry (source slot, block row, block column), taken up: this
+    // lane's splat record, written by the binning (the same projection and
+    // footprint as splat_point, computed once per block instead of once per
+    // tile that lists it), and in scalar registers the low key word of the
+    // block's first pixel, the source's width and the entry itself.
+    struct Taken {
+        unsigned long long rec;
+        uint32_t lo;
+        int W, ent;
     };
-    auto splat_entry = [&](int ent, unsigned long long rec) {
-        ent = __builtin_amdgcn_readfirstlane(ent);   // uniform; the pipeline's copies lose that
-        const uint32_t rz = (uint32_t)rec, rf = (uint32_t)(rec >> 32);
-        // a point without depth (its record's footprint is 0) is dropped
-        // with the empty footprints below: one lane branch per entry, not two
-        const bool live = rz != FVV_NO_DEPTH;
-        const fvv_src_desc &s = vd.src[(uint32_t)ent >> 24];
-        const int blk = ent & 0xFFFFFF;
-        const int by = block_row(blk, s), bx = blk - by * s.nbx;
-        const int i = bx * FVV_SBLK + si, j = by * FVV_SBLK + sj;
-        Footprint f;
-        if (rf != FVV_SPL_RECOMPUTE) {
-            f.x0 = (int)(rf & 0x1FFFu);
-            f.y0 = (int)((rf >> 13) & 0x1FFFu);
-            f.x1 = f.x0 + (int)((rf >> 26) & 7u);
-            f.y1 = f.y0 + (int)(rf >> 29);
-            f.key = ((unsigned long long)rz << 32) | ((unsigned long long)(uint32_t)s.cam << 27) |
-                    (unsigned long long)(uint32_t)(j * s.W + i);
-        } else if (!splat_point(s, W, H, vd.max_fp, i, j, gptr(s.depth)[(uint32_t)(j * s.W + i)], f)) {
-            return;
+    auto take = [&](int ent) {
+        ent = __builtin_amdgcn_readfirstlane(ent);   // uniform (see above)
+        const uint32_t k = fvv_entry_slot(ent), by = fvv_entry_row(ent), bx = fvv_entry_col(ent);
+        const fvv_src_desc &s = vd.src[k];
+        Taken t;
+        t.ent = ent;
+        t.W = s.W;
+        t.lo = ((uint32_t)s.cam << 27) + (by * (uint32_t)s.W + bx) * FVV_SBLK;
+        const uint32_t blk = k * (uint32_t)vd.blk_stride + by * (uint32_t)s.nbx + bx;
+        t.rec = (gptr(vd.spl) + ((uint64_t)blk << 6))[(uint32_t)lane];
+        return t;
+    };
+    auto splat = [&](const Taken &e) {
+        const uint32_t rz = (uint32_t)e.rec, rf = (uint32_t)(e.rec >> 32);
+        const uint32_t W1 = (uint32_t)__builtin_amdgcn_readfirstlane(e.W);   // uniform; the pipeline's copies lose that
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)e.lo);
+        // window coordinates of the footprint, clipped to the window; a point
+        // without depth (its record's footprint is 0) is dropped with the empty
+        // ones: one lane branch per entry
+        int x0 = (int)(rf & 0x1FFFu) - WX0, y0 = (int)((rf >> 13) & 0x1FFFu) - WY0;
+        int x1 = x0 + (int)((rf >> 26) & 7u), y1 = y0 + (int)(rf >> 29);
+        unsigned long long key = ((unsigned long long)rz << 32) | (lo + __umul24((uint32_t)sj, W1) + (uint32_t)si);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(rf == FVV_SPL_RECOMPUTE) != 0, 0)) {
+            const int ent = __builtin_amdgcn_readfirstlane(e.ent);
+            const fvv_src_desc &s = vd.src[fvv_entry_slot(ent)];
+            const int i = (int)fvv_entry_col(ent) * FVV_SBLK + si, j = (int)fvv_entry_row(ent) * FVV_SBLK + sj;
+            if (rf == FVV_SPL_RECOMPUTE) {
+                Footprint f;
+                const bool on = splat_point(s, W, H, vd.max_fp, i, j, gptr(s.depth)[(uint32_t)(j * s.W + i)], f);
+                x0 = on ? f.x0 - WX0 : 1;
+                x1 = on ? f.x1 - WX0 : 0;
+                y0 = on ? f.y0 - WY0 : 0;
+                y1 = on ? f.y1 - WY0 : 0;
+            }
         }
-        const int xa = max(f.x0, WX0), xb = live ? min(f.x1, WX0 + WN - 1) : xa - 1;
-        const int ya = max(f.y0, WY0), yb = min(f.y1, WY0 + WN - 1);
-        unsigned long long *zl = (LAYERED && (ent >> 24) >= vd.K) ? zk + WN * WN : zk;
-        if (xa > xb || ya > yb) return;
+        const int xa = max(x0, 0), xb = min(x1, WN - 1), ya = max(y0, 0), yb = min(y1, WN - 1);
+        unsigned long long *zl = (LAYERED && (int)fvv_entry_slot(__builtin_amdgcn_readfirstlane(e.ent)) >= vd.K) ? zk + WN * WN : zk;
+        if ((xa > xb) | (ya > yb) | (rz == FVV_NO_DEPTH)) return;
         // the first 2 x 2 pixels of the footprint (all of it at the usual
         // magnifications) as predicated atomics, the rest in a loop
-        unsigned long long *z0 = zl + (ya - WY0) * WN + (xa - WX0);
+        unsigned long long *z0 = zl + (__umul24((uint32_t)ya, WN) + (uint32_t)xa);
         const bool wx = xa < xb, wy = ya < yb;
-        atomicMin(z0, f.key);
-        if (wx) atomicMin(z0 + 1, f.key);
-        if (wy) atomicMin(z0 + WN, f.key);
-        if (wx && wy) atomicMin(z0 + WN + 1, f.key);
-        if (xb - xa > 1 || yb - ya > 1) {
+        atomicMin(z0, key);
+        if (wx) atomicMin(z0 + 1, key);
+        if (wy) atomicMin(z0 + WN, key);
+        if (wx & wy) atomicMin(z0 + WN + 1, key);
+        if ((xb - xa > 1) | (yb - ya > 1)) {
             for (int y = ya; y <= yb; ++y)
                 for (int x = xa; x <= xb; ++x)
-                    if (x - xa > 1 || y - ya > 1) atomicMin(&zl[(y - WY0) * WN + (x - WX0)], f.key);
+                    if (x - xa > 1 || y - ya > 1) atomicMin(&zl[y * WN + x], key);
         }
     };
     if (!scan_all) {
         // The wave's entries are e = wave + TNW q; the splat records of the
         // next two entries are in flight while the current one is splatted,
-        // so the dependent loads of consecutive entries overlap instead of
-        // queueing.
-        // the list was written by the binning and is only read here: wave-
+        // and the list entries of the two after those, so the dependent loads
+        // of consecutive entries overlap instead of queueing.
+        // The list was written by the binning and is only read here: wave-
         // uniform entries come through the scalar cache (constant address
-        // space), straight into scalar registers
+        // space), straight into scalar registers.
         const __attribute__((address_space(4))) int32_t *lst =
             (const __attribute__((address_space(4))) int32_t *)(vd.list + (int64_t)tile * vd.tile_cap + wave);
         const int nq = __builtin_amdgcn_readfirstlane(n_entries > wave ? (n_entries - wave + TNW - 1) / TNW : 0);
-        auto entry = [&](int q) -> int { return lst[(uint32_t)(TNW * q)]; };
-        // Two records in flight, in two registers that alternate (the loop
-        // takes two entries per trip): a register is reloaded only after its
-        // record has been taken, so taking one waits for that load alone.
-        // Past the last entry the last record is loaded again (unused), so
-        // the loads need no branches.
+        // past the last entry the last one is taken again (unused), so the
+        // loads need no branches
+        auto entry = [&](int q) -> int { return lst[(uint32_t)(TNW * min(q, nq - 1))]; };
+        // two records in two registers that alternate (the loop takes two
+        // entries per trip): a register is reloaded only after its record has
+        // been taken, so taking one waits for that load alone
         if (nq > 0) {
-            int e0 = entry(0), e1 = entry(min(1, nq - 1));
-            unsigned long long z0 = block_rec(e0), z1 = block_rec(e1);
+            Taken t0 = take(entry(0)), t1 = take(entry(1));
+            int n0 = entry(2), n1 = entry(3);
             for (int q = 0; q < nq; q += 2) {
-                const int ec0 = e0;
-                const unsigned long long zc0 = z0;
-                e0 = entry(min(q + 2, nq - 1));
-                z0 = block_rec(e0);
-                splat_entry(ec0, zc0);
+                const Taken c0 = t0;
+                t0 = take(n0);
+                n0 = entry(q + 4);
+                splat(c0);
                 if (q + 1 >= nq) break;
-                const int ec1 = e1;
-                const unsigned long long zc1 = z1;
-                e1 = entry(min(q + 3, nq - 1));
-                z1 = block_rec(e1);
-                splat_entry(ec1, zc1);
+                const Taken c1 = t1;
+                t1 = take(n1);
+                n1 = entry(q + 5);
+                splat(c1);
             }
         }
     } else {
@@ -794,8 +925,8 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
             if (blk >= vd.src[k].nblk) continue;
             const int4 r = vd.bbox[e];
             if (!(r.x <= tx && tx <= r.y && r.z <= ty && ty <= r.w)) continue;
-            const int ent = (k << 24) | blk;
-            splat_entry(ent, block_rec(ent));
+            const int by = block_row(blk, vd.src[k]);
+            splat(take(fvv_list_entry(k, by, blk - by * vd.src[k].nbx)));
         }
     }
     __syncthreads();
@@ -808,64 +939,98 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
     // thread of the tile.
     const int ly = t / TPR, lx0 = (t % TPR) * 4;
     const int y = Y0 + ly;
+    // the depths of the filtered points (an empty key's depth word is a NaN;
+    // pixels off the image have none)
+    float zf[4];
+    if (LAYERED) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int x = X0 + lx0 + q;
-        unsigned long long kf = FVV_KEY_EMPTY;
-        bool need = false;
-        if (x < W && y < H) {
-            const unsigned long long *w3 = zk + ly * WN + lx0 + q;
-            const unsigned long long c = w3[WN + 1];
-            unsigned long long nb[8] = {w3[0], w3[1], w3[2], w3[WN], w3[WN + 2], w3[2 * WN], w3[2 * WN + 1],
-                                        w3[2 * WN + 2]};
-            if (LAYERED) {
-                kf = filter_key(c, nb, vd.tau);
-            } else {
-                kf = c;
-                need = filter_needs_median(c, nb, vd.tau);
+        for (int q = 0; q < 4; ++q) {
+            const int x = X0 + lx0 + q;
+            unsigned long long kf = FVV_KEY_EMPTY;
+            if (x < W && y < H) {
+                const unsigned long long *w3 = zk + ly * WN + lx0 + q;
+                unsigned long long nb[8] = {w3[0], w3[1], w3[2], w3[WN], w3[WN + 2], w3[2 * WN], w3[2 * WN + 1],
+                                            w3[2 * WN + 2]};
+                kf = filter_key(w3[WN + 1], nb, vd.tau);
+                if (vd.dbg_zf) vd.dbg_zf[(int64_t)y * W + x] = kf;
+            }
+            zf[q] = u2f((uint32_t)(kf >> 32));
+        }
+    } else {
+        // The decision (filter_needs_median) needs the keys' depth words only,
+        // and the four pixels' 3 x 3 windows share theirs: 18 words, whose
+        // column sums of empty marks (sign bits: an empty key's word is all
+        // ones, a valid depth's sign is clear) serve three pixels each.
+        uint32_t h[3][6];
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int c = 0; c < 6; ++c) h[r][c] = (uint32_t)(zk[(ly + r) * WN + lx0 + c] >> 32);
+        uint32_t col[6];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) col[c] = (h[0][c] >> 31) + (h[1][c] >> 31) + (h[2][c] >> 31);
+        bool need[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t cz = h[1][q + 1];
+            const uint32_t empty = col[q] + col[q + 1] + col[q + 2] - (cz >> 31);
+            const float z0 = u2f(cz);
+            // the smallest |z_k - z0| (an empty neighbour's NaN is passed over;
+            // all NaN compares false)
+            float d = fabsf(__fsub_rn(u2f(h[0][q]), z0));
+#pragma unroll
+            for (int e = 1; e < 9; ++e)
+                if (e != 4) d = fminf(d, fabsf(__fsub_rn(u2f(h[e / 3][q + e % 3]), z0)));
+            // empty (z0 a NaN, so the comparison fails), or no neighbour near
+            need[q] = (empty <= 3) & !(d <= __fmul_rn(vd.tau, z0)) & (X0 + lx0 + q < W) & (y < H);
+            zf[q] = (X0 + lx0 + q < W) & (y < H) ? z0 : u2f(FVV_NO_DEPTH);
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(need[q]);
+            if (m) {
+                int base = 0;
+                if (lane == 0) base = atomicAdd(&s_nmed, __popcll(m));
+                base = __builtin_amdgcn_readfirstlane(base);   // every lane is active here: lane 0's value
+                const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+                if (need[q]) s_med[base + rank] = (uint16_t)(ly * T + lx0 + q);
             }
         }
-        s_kf[ly * T + lx0 + q] = kf;
-        const unsigned long long m = __ballot(need);
-        if (m) {
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&s_nmed, __popcll(m));
-            base = __builtin_amdgcn_readfirstlane(base);   // every lane is active here: lane 0's value
-            const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-            if (need) s_med[base + rank] = (uint16_t)(ly * T + lx0 + q);
+        __syncthreads();
+        for (int e = t; e < s_nmed; e += TNT) {
+            const int pix = s_med[e];
+            const unsigned long long *w3 = zk + (pix / T) * WN + (pix % T);
+            unsigned long long nb[8] = {w3[0], w3[1], w3[2], w3[WN], w3[WN + 2], w3[2 * WN], w3[2 * WN + 1],
+                                        w3[2 * WN + 2]};
+            s_kf[pix] = lower_median8(nb, valid_count(nb));
         }
-    }
-    __syncthreads();
-    for (int e = t; e < s_nmed; e += TNT) {
-        const int pix = s_med[e];
-        const unsigned long long *w3 = zk + (pix / T) * WN + (pix % T);
-        unsigned long long nb[8] = {w3[0], w3[1], w3[2], w3[WN], w3[WN + 2], w3[2 * WN], w3[2 * WN + 1],
-                                    w3[2 * WN + 2]};
-        s_kf[pix] = lower_median8(nb, valid_count(nb));
-    }
-    __syncthreads();
-    unsigned long long kfs[4];
+        __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 4; ++q) kfs[q] = s_kf[ly * T + lx0 + q];
-    __syncthreads();   // the key buffer becomes the slot and colour buffers
+        for (int q = 0; q < 4; ++q) {
+            const int pix = ly * T + lx0 + q;
+            if (need[q]) zf[q] = u2f((uint32_t)(s_kf[pix] >> 32));
+            if (vd.dbg_zf && X0 + lx0 + q < W && y < H)
+                vd.dbg_zf[(int64_t)y * W + X0 + lx0 + q] = need[q] ? s_kf[pix] : zk[(ly + 1) * WN + lx0 + q + 1];
+        }
+        __syncthreads();   // the key buffer becomes the slot and colour buffers
+    }
 
     // ---- S3: backward fetch and blend
     uint32_t pslot[4], prgb[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int x = X0 + lx0 + q;
         pslot[q] = FVV_HOLE;
         prgb[q] = 0;
-        const unsigned long long kf = kfs[q];
+    }
+    if (!STACK) blend_four(vd, X0 + lx0, y, zf, pslot, prgb);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int x = X0 + lx0 + q;
         float ch[STACK ? 16 : 1];   // the learned-path stack channels of the pixel
 #pragma unroll
         for (int c = 0; c < (STACK ? 16 : 1); ++c) ch[c] = 0.f;
         if (x < W && y < H) {
-            if (kf != FVV_KEY_EMPTY) {
-                const float zf = u2f((uint32_t)(kf >> 32));
+            if (STACK && f2u(zf[q]) != FVV_NO_DEPTH) {
                 uint32_t col;
-                if (blend_pixel<STACK>(vd, 0, x, y, zf, col, ch)) {
-                    pslot[q] = f2u(zf);
+                if (blend_pixel<true>(vd, 0, x, y, zf[q], col, ch)) {
+                    pslot[q] = f2u(zf[q]);
                     prgb[q] = col;
                 }
             }
@@ -881,10 +1046,10 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
                                                  zb[2 * WN + 2]};
                     const unsigned long long kb = filter_key(cb, nbb, vd.tau);
                     if ((pslot[q] & FVV_HOLE) && kb != FVV_KEY_EMPTY) {
-                        const float zf = u2f((uint32_t)(kb >> 32));
+                        const float zb0 = u2f((uint32_t)(kb >> 32));
                         uint32_t col;
-                        if (blend_pixel<false>(vd, vd.K, x, y, zf, col)) {
-                            pslot[q] = f2u(zf);
+                        if (blend_pixel<false>(vd, vd.K, x, y, zb0, col)) {
+                            pslot[q] = f2u(zb0);
                             prgb[q] = col;
                         }
                     }
@@ -895,7 +1060,6 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
                 }
             }
             if (vd.dbg_z) vd.dbg_z[o] = zk[(ly + 1) * WN + lx0 + q + 1];
-            if (vd.dbg_zf) vd.dbg_zf[o] = kf;
             if (vd.dbg_rgba) vd.dbg_rgba[o] = prgb[q];
             if (vd.dbg_depth) vd.dbg_depth[o] = (pslot[q] & FVV_HOLE) ? 0.0f : u2f(pslot[q]);
         }
@@ -1044,7 +1208,12 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
     }
 }
 
-// The plain kernel is held to 64 VGPRs (8 waves per SIMD; it uses 52), so
+// Bound by vector issue.  60 views of 1080p from three 720p cameras per launch:
+// 1.92 -> 1.61 ms (2,370 -> 2,000 vector and 1,420 -> 1,010 scalar instructions
+// per wave) with the samples camera by camera, their descriptor in scalar
+// registers and interior ones without edge handling, list entries that carry
+// the block's row and column, and a filter that shares its windows' depth words.
+// The plain kernel is held to 64 VGPRs (8 waves per SIMD), so
 // the waves of eight workgroups share each SIMD; the stack variant keeps
 // its registers.
 __global__ void __launch_bounds__(TNT) __attribute__((amdgpu_waves_per_eu(8, 8)))
