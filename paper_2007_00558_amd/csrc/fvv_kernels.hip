@@ -919,14 +919,34 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
             }
         }
     } else {
-        // more entries than the list holds: test every block's tile range
-        for (int e = wave; e < fvv_nsrc(vd) * vd.blk_stride; e += TNW) {
-            const int k = e / vd.blk_stride, blk = e - k * vd.blk_stride;
-            if (blk >= vd.src[k].nblk) continue;
-            const int4 r = vd.bbox[e];
-            if (!(r.x <= tx && tx <= r.y && r.z <= ty && ty <= r.w)) continue;
-            const int by = block_row(blk, vd.src[k]);
-            splat(take(fvv_list_entry(k, by, blk - by * vd.src[k].nbx)));
+        // More entries than the list holds: test every block's tile range, a
+        // block per lane, SCAN blocks of 64 in flight per wave, and splat the
+        // hits.  (With a block per wave, as the hits are taken, one such tile of
+        // a 43,200-block view, 204 entries for a list of 192, kept a launch of
+        // 60 views 3.3 ms longer; now within the run to run differences.)
+        constexpr int SCAN = 4;
+        for (int k = 0; k < fvv_nsrc(vd); ++k) {
+            const int nblk = vd.src[k].nblk;
+            const int4 *const box = vd.bbox + (int64_t)k * vd.blk_stride;
+            for (int b0 = wave * SCAN * 64; b0 < nblk; b0 += TNW * SCAN * 64) {
+                int4 r[SCAN];
+#pragma unroll
+                for (int c = 0; c < SCAN; ++c) {
+                    const int blk = b0 + c * 64 + lane;
+                    r[c] = make_int4(1, 0, 1, 0);
+                    if (blk < nblk) r[c] = box[blk];
+                }
+#pragma unroll
+                for (int c = 0; c < SCAN; ++c) {
+                    unsigned long long m = __builtin_amdgcn_ballot_w64((r[c].x <= tx) & (tx <= r[c].y) & (r[c].z <= ty) & (ty <= r[c].w));
+                    while (m) {
+                        const int blk = b0 + c * 64 + __builtin_ctzll(m);
+                        m &= m - 1;
+                        const int by = block_row(blk, vd.src[k]);
+                        splat(take(fvv_list_entry(k, by, blk - by * vd.src[k].nbx)));
+                    }
+                }
+            }
         }
     }
     __syncthreads();
