@@ -190,7 +190,10 @@ __device__ __forceinline__ uint32_t live_mm(const fvv_repack_batch &b, const fvv
         const int64_t uvp = c.depth_pitch >> 1;
         const uint8_t *pl = c.depth + (int64_t)c.H * c.depth_pitch + ((y & 1) ? (int64_t)(c.H >> 1) * uvp : 0);
         const uint32_t uv = pl[(int64_t)(y >> 1) * uvp + (x >> 1)];
-        return y12_dequantise(y12_unfold(c.depth[(int64_t)y * c.depth_pitch + x], y12_msb(uv, x & 1)), b.planes);
+        const uint32_t code = y12_unfold(c.depth[(int64_t)y * c.depth_pitch + x], y12_msb(uv, x & 1));
+        bool sure = true;
+        const uint32_t mm = y12_dequantise_est(code, b.planes, sure);
+        return __builtin_expect(sure, 1) ? mm : y12_dequantise(code, b.planes);
     }
     return *(const uint16_t *)(c.depth + (int64_t)y * c.depth_pitch + (int64_t)x * 2);
 }

@@ -20,19 +20,39 @@
 #include <stdint.h>
 
 // The two plane terms of Eq. 2, 1/z_far and 1/z_near - 1/z_far, each one
-// correctly rounded double operation; the host evaluates them once per call
-// (the same IEEE operations give the same bits there).
+// correctly rounded double operation, evaluated on the host once per call
+// (the same IEEE operations give the same bits there), and the terms of the
+// estimates below: code + 0.5 = enc1 / mm + enc0, 1/z = (code - 2) dec1 + inv_zf.
 struct y12_planes {
     double inv_zf, span;
+    double enc1, enc0, enc_eps, dec1;
 };
 __host__ __device__ inline y12_planes y12_make_planes(float z_near, float z_far)
 {
     const double zn = z_near, zf = z_far;
-    return {1.0 / zf, 1.0 / zn - 1.0 / zf};
+    y12_planes p{};
+    p.inv_zf = 1.0 / zf;
+    p.span = 1.0 / zn - 1.0 / zf;
+    p.enc1 = 1000.0 * 4093.0 / p.span;
+    p.enc0 = 2.5 - p.inv_zf * (4093.0 / p.span);
+    // bound on estimate and Eq. 2 sequence being apart, for codes in range: both
+    // are sums of terms up to (4093 / span) / z_near, a few roundings of 2^-53
+    // each; 2^-40 leaves a factor of a thousand
+    p.enc_eps = (4093.0 / p.span) / zn * 0x1p-40 + 1e-9;
+    p.dec1 = p.span / 4093.0;
+    return p;
+}
+
+// 1/x for a positive double within 2^-45: the hardware estimate (2^-23) and a
+// Newton step
+__device__ __forceinline__ double y12_rcp(double x)
+{
+    const double r = __builtin_amdgcn_rcp(x);
+    return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
 }
 
 // Eq. 2: millimetres -> code
-__device__ __forceinline__ uint32_t y12_quantise(uint32_t mm, y12_planes p)
+__device__ __forceinline__ uint32_t y12_quantise(uint32_t mm, const y12_planes &p)
 {
     if (mm == 0xFFFFu) return 0u;
     if (mm == 0) return 1u;
@@ -41,10 +61,24 @@ __device__ __forceinline__ uint32_t y12_quantise(uint32_t mm, y12_planes p)
     const double r = floor(4093.0 * a / p.span + 2.0 + 0.5);
     return (r >= 2.0 && r <= 4095.0) ? (uint32_t)r : 1u;
 }
+// The same, and whether it is certain: the code is the floor of code + 0.5,
+// which an estimate within enc_eps of the sequence above decides unless it lies
+// that close to an integer (some 1e-8 of the values for planes metres apart,
+// every value for planes too close together).  A third of the double
+// instructions, and no branch, so a thread's pixels overlap.
+__device__ __forceinline__ uint32_t y12_quantise_est(uint32_t mm, const y12_planes &p, bool &sure)
+{
+    const double v = __builtin_fma(y12_rcp((double)mm), p.enc1, p.enc0);
+    const int c = (int)v;   // saturating; floor where it matters (v >= 0)
+    const bool none = mm - 1u >= 0xFFFEu;   // 0 or 0xFFFF
+    sure &= none | (fabs(__builtin_amdgcn_fract(v) - 0.5) < 0.5 - p.enc_eps);
+    const uint32_t code = (uint32_t)(c - 2) <= 4093u ? (uint32_t)c : 1u;
+    return none ? (mm == 0) : code;
+}
 
 // inverse of Eq. 2 -> whole millimetres in 1..65535 (0xFFFF for code 0, 0 for
 // code 1)
-__device__ __forceinline__ uint32_t y12_dequantise(uint32_t code, y12_planes p)
+__device__ __forceinline__ uint32_t y12_dequantise(uint32_t code, const y12_planes &p)
 {
     if (code == 0u) return 0xFFFFu;
     if (code == 1u) return 0u;
@@ -52,6 +86,15 @@ __device__ __forceinline__ uint32_t y12_dequantise(uint32_t code, y12_planes p)
     const double inv = t * p.span + p.inv_zf;
     const double mm = floor(1.0 / inv * 1000.0 + 0.5);
     return mm < 1.0 ? 1u : mm > 65535.0 ? 65535u : (uint32_t)mm;
+}
+// The same by estimate, as above: within 1e-8 for results up to 65,535 (1/z is
+// a sum of positive terms, without cancellation).
+__device__ __forceinline__ uint32_t y12_dequantise_est(uint32_t code, const y12_planes &p, bool &sure)
+{
+    const double v = __builtin_fma(y12_rcp(__builtin_fma((double)((int)code - 2), p.dec1, p.inv_zf)), 1000.0, 0.5);
+    const int mm = (int)v;   // saturating; v > 0 for codes from 2 on
+    sure &= (code < 2u) | (mm > 65535) | (fabs(__builtin_amdgcn_fract(v) - 0.5) < 0.5 - 1e-8);
+    return code >= 2u ? (uint32_t)min(max(mm, 1), 65535) : code == 0u ? 0xFFFFu : 0u;
 }
 
 // Eq. 3 and its inverse

@@ -262,3 +262,33 @@ def test_codec_errors(fvv):
         fr = [(f.rgb, np.zeros((96, 95), np.uint8)) for f in w.frames]
         with pytest.raises(fvv.FvvError, match="even"):
             c.upload_mvd(fr)
+
+
+@pytest.mark.parametrize("zn,zf", PLANES + [(1.0, 8.0), (0.001, 65.0), (2.0, 2.0000002), (1.0, 1.0005), (1e-30, 1e30)])
+@pytest.mark.parametrize("W,shift", [(256, 0), (258, 0), (256, 2)])
+def test_every_value_both_ways(fvv, oracle_lib, zn, zf, W, shift):
+    """All 65,536 millimetre values and all 4,096 codes against the oracle, for
+    ordinary planes and for planes where the rounding estimate decides little or
+    nothing (a few float32 steps apart, 60 orders of magnitude apart), through
+    the 16-byte accesses (width and rows that allow them) and the narrow ones
+    (width not a multiple of 8; rows off their boundary)."""
+    import torch
+    H = 256
+    d = np.zeros((H, W), np.uint16)
+    d[:, :256] = np.arange(65536, dtype=np.uint16).reshape(256, 256)
+    buf = torch.zeros((H, W + 8), dtype=torch.int16, device="cuda")
+    dev = buf[:, shift // 2:shift // 2 + W]
+    dev.copy_(torch.from_numpy(d.view(np.int16)))
+    yuv = fvv.depth_encode_y12(dev, zn, zf)
+    torch.cuda.synchronize()
+    assert np.array_equal(yuv.cpu().numpy(), i420(*oracle_lib.encode_depth_y12(d, zn, zf)))
+    # every code: Y bytes 0..255 down a column, U and V bytes 0..255 along a row of blocks
+    Y = np.repeat(np.arange(256, dtype=np.uint8)[:, None], 2 * W, 1)
+    UV = np.resize(np.arange(256, dtype=np.uint8), (128, W))
+    img = np.concatenate([Y.reshape(-1), UV.reshape(-1), UV.reshape(-1)]).reshape(H * 3 // 2, 2 * W)
+    raw = torch.zeros(img.size + 16, dtype=torch.uint8, device="cuda")
+    src = raw[shift:shift + img.size].view(img.shape)
+    src.copy_(torch.from_numpy(img))
+    mm = fvv.depth_decode_y12(src, 2 * W, H, zn, zf)
+    torch.cuda.synchronize()
+    assert np.array_equal(mm.cpu().numpy().view(np.uint16), oracle_lib.decode_depth_y12(Y, UV, UV, zn, zf))
