@@ -13,6 +13,8 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <type_traits>
+#include <utility>
 
 #include "fvv_unet.h"
 
@@ -22,8 +24,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-enum { TAP_CONV3 = 0, TAP_ONE = 1, TAP_FINE4 = 2 };
-enum { EPI_RELU_BF16 = 0, EPI_F32 = 1, EPI_CONVT_BF16 = 2 };
+// EPI_GRAD: a gradient that the next layer's products read -- masked by that
+// layer's ReLU and rounded to bfloat16, with the sums of the float32 masked
+// values per channel (its bias gradient) as a row of partials per block
+enum { EPI_RELU_BF16 = 0, EPI_F32 = 1, EPI_CONVT_BF16 = 2, EPI_GRAD = 3 };
 
 // bfloat16 rounding to nearest even, written out on the bit pattern (the
 // definition the hardware conversion below is checked against)
@@ -65,6 +69,13 @@ struct GemmArgs {
     int k_src;               // channels Bsrc holds at b_off (0 = K); staged channels beyond are zero
     int M;                   // rows (multiple of 16)
     int cout;                // EPI_CONVT_BF16: output channels (M = 4 cout)
+    // EPI_GRAD: out = bfloat16 [P][M] of the rows masked by act [P][M] (> 0);
+    // with split (a concatenation's gradient), of the first split rows,
+    // unmasked, and float32 [P][M - split] of the rest in skip
+    const uint16_t *act;
+    int split;
+    float *skip;
+    float *bpart;            // [rows][M] bias partials
     uint16_t *pool;          // k_conv3w, EPI_RELU_BF16: also the 2x2 max-pooled output [NB][H/2][W/2][32] (or null)
     // k_conv3w<.., 2, .., UPC>: input chunk 0 is the 2x2 transposed
     // convolution (32 output channels, 64 input channels) of up_in
@@ -86,8 +97,8 @@ struct HeadArgs {
     int NB, H, W, valid_h, valid_w;
     const float *target;     // [P][3] training
     float inv_n;             // 1 / (NB * valid_h * W * 3)
-    float *g_a;              // [P][32] fp32 gradient at the head input
-    float *part;             // per workgroup: 3*32 weight + 3 bias partials + 1 loss partial
+    uint16_t *G;             // [P][32] gradient at dec0b's output, masked, bfloat16
+    float *part;             // [blocks][HEAD_PART] partial sums
 };
 
 // The head's 1x1 convolution (32 -> 3) of 32 pixels on one MFMA pair: A =
@@ -132,106 +143,130 @@ __device__ __forceinline__ void head_store(const HeadArgs &h, const float z[3], 
         for (int c = 0; c < 3; ++c) o[c] = (uint8_t)fminf(floorf(s[c] * 255.f + 0.5f), 255.f);
 }
 
-// Source pixel of tap t for column pixel (b, y, x); -1 outside.
-template <int TAP>
-__device__ __forceinline__ int64_t tap_src(int b, int y, int x, int t, int H, int W)
+// Sum over the 16 lanes of a row, in every lane of the row (DPP lane moves).
+__device__ __forceinline__ float row_sum(float v)
 {
-    if (TAP == TAP_CONV3) {
-        const int sy = y + t / 3 - 1, sx = x + t % 3 - 1;
-        if (sy < 0 || sx < 0 || sy >= H || sx >= W) return -1;
-        return ((int64_t)b * H + sy) * W + sx;
-    } else if (TAP == TAP_FINE4) {
-        return ((int64_t)b * 2 * H + 2 * y + (t >> 1)) * (2 * W) + 2 * x + (t & 1);
-    } else {
-        return ((int64_t)b * H + y) * W + x;
-    }
+    auto dpp = [](float x, auto c) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), c.value, 0xF, 0xF, false)); };
+    v += dpp(v, std::integral_constant<int, 0xB1>());    // quad_perm 1,0,3,2
+    v += dpp(v, std::integral_constant<int, 0x4E>());    // quad_perm 2,3,0,1
+    v += dpp(v, std::integral_constant<int, 0x141>());   // row_half_mirror
+    return v + dpp(v, std::integral_constant<int, 0x140>());   // row_mirror
+}
+// ... over lanes 0..31 and 32..63 separately
+__device__ __forceinline__ float half_sum(float v)
+{
+    v = row_sum(v);
+    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
 }
 
-template <int MC, int NP, int TAP, int EPI>
-__global__ void __launch_bounds__(256) k_gemm(const GemmArgs g)
+// The masked gradient of four channels of a pixel: v kept where the activation
+// (bfloat16, not negative after its ReLU) is positive, added to the bias sums,
+// packed.
+__device__ __forceinline__ uint2 grad4(float (&v)[4], uint2 act, bool masked, float *bsum)
 {
+    const uint32_t h[4] = {act.x & 0xFFFFu, act.x >> 16, act.y & 0xFFFFu, act.y >> 16};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        v[r] = masked && h[r] == 0u ? 0.f : v[r];
+        bsum[r] += v[r];
+    }
+    return make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+}
+// A block's bias sums: bs[i * 16 + 4 j + r] of channel 32 i + 8 j + 4 lh + r,
+// summed over the lanes of a half wave, then over the block's waves in order,
+// to out[0 .. 32 MT - 1].
+template <int MT>
+__device__ __forceinline__ void bias_row(float (&bs)[MT * 16], float *lds, float *out)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lh = lane >> 5;
+#pragma unroll
+    for (int e = 0; e < MT * 16; ++e) {
+        const float t = half_sum(bs[e]);
+        if ((lane & 31) == 0) lds[wave * 32 * MT + (e >> 4) * 32 + 8 * ((e >> 2) & 3) + 4 * lh + (e & 3)] = t;
+    }
+    __syncthreads();
+    const int c = threadIdx.x;
+    if (c < 32 * MT) out[c] = lds[c] + lds[32 * MT + c] + lds[64 * MT + c] + lds[96 * MT + c];
+}
+
+// ---------------------------------------------------------------- transposed convolution, data gradient
+// Data gradient of a 2x2 transposed convolution on v_mfma_f32_16x16x32_bf16:
+// coarse pixel p, row m: sum over taps t and channels k of A[m][t][k] G[fine
+// pixel of (p, t)][k], both operands from L1 / L2, written as EPI_GRAD (masked
+// by the activation the transposed convolution read).  A wave takes 64 rows x
+// 16 NP pixels; blocks walk the pixels in steps of the grid, so the bias sums
+// stay in registers.
+template <int NP>
+__global__ void __launch_bounds__(256) k_convT_grad(const GemmArgs g)
+{
+    constexpr int MC = 4;
+    __shared__ float s_b[4 * 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lr = lane & 15, lg = lane >> 4;
     const int HW = g.H * g.W;
     const int P = g.NB * HW;
-    const int taps = TAP == TAP_CONV3 ? 9 : (TAP == TAP_FINE4 ? 4 : 1);
-    int pb[NP], py[NP], px[NP];
-    bool pv[NP];
-    const int pbase = blockIdx.x * (64 * NP) + wave * (16 * NP);
-#pragma unroll
-    for (int n = 0; n < NP; ++n) {
-        const int p = pbase + n * 16 + lr;
-        pv[n] = p < P;
-        const int pp = pv[n] ? p : 0;
-        pb[n] = pp / HW;
-        const int r = pp - pb[n] * HW;
-        py[n] = r / g.W;
-        px[n] = r - py[n] * g.W;
-    }
     const int mbase = blockIdx.y * (16 * MC);
-    f32x4 acc[MC][NP];
+    const bf16x8 zero8 = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+    float bs[MC][4];
+#pragma unroll
+    for (int i = 0; i < MC; ++i) bs[i][0] = bs[i][1] = bs[i][2] = bs[i][3] = 0.f;
+    for (int p0 = blockIdx.x * (64 * NP); p0 < P; p0 += gridDim.x * (64 * NP)) {
+        int fine[NP];   // element offset of the pixel's tap (0, 0)
+        bool pv[NP];
+#pragma unroll
+        for (int n = 0; n < NP; ++n) {
+            const int p = p0 + wave * (16 * NP) + n * 16 + lr;
+            pv[n] = p < P;
+            const int pp = pv[n] ? p : 0, b = pp / HW, r = pp - b * HW, y = r / g.W, x = r - y * g.W;
+            fine[n] = ((b * 2 * g.H + 2 * y) * (2 * g.W) + 2 * x) * g.b_cs + g.b_off;
+        }
+        f32x4 acc[MC][NP];
+#pragma unroll
+        for (int i = 0; i < MC; ++i)
+#pragma unroll
+            for (int n = 0; n < NP; ++n) acc[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int toff = ((t >> 1) * 2 * g.W + (t & 1)) * g.b_cs;
+            for (int c0 = 0; c0 < g.K; c0 += 32) {
+                const int kk = c0 + 8 * lg;
+                bf16x8 bfr[NP], afr[MC];
+#pragma unroll
+                for (int n = 0; n < NP; ++n) bfr[n] = pv[n] ? ld8(g.Bsrc + (uint32_t)(fine[n] + toff + kk)) : zero8;
+#pragma unroll
+                for (int i = 0; i < MC; ++i) afr[i] = ld8(g.A + ((uint32_t)(mbase + i * 16 + lr) * 4 + t) * (uint32_t)g.K + kk);
+#pragma unroll
+                for (int i = 0; i < MC; ++i)
+#pragma unroll
+                    for (int n = 0; n < NP; ++n)
+                        acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[i], bfr[n], acc[i][n], 0, 0, 0);
+            }
+        }
+        // lane holds rows m0..m0+3 of pixel lr
+#pragma unroll
+        for (int n = 0; n < NP; ++n) {
+            const int p = p0 + wave * (16 * NP) + n * 16 + lr;
+            if (!pv[n]) continue;
+#pragma unroll
+            for (int i = 0; i < MC; ++i) {
+                const uint32_t o = (uint32_t)p * (uint32_t)g.M + (uint32_t)(mbase + i * 16 + 4 * lg);
+                float v[4] = {acc[i][n][0], acc[i][n][1], acc[i][n][2], acc[i][n][3]};
+                *(uint2 *)((uint16_t *)g.out + o) = grad4(v, *(const uint2 *)(g.act + o), true, bs[i]);
+            }
+        }
+    }
 #pragma unroll
     for (int i = 0; i < MC; ++i)
 #pragma unroll
-        for (int n = 0; n < NP; ++n) acc[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const bf16x8 zero8 = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
-    for (int t = 0; t < taps; ++t) {
-        int64_t src[NP];
-#pragma unroll
-        for (int n = 0; n < NP; ++n) {
-            const int64_t q = pv[n] ? tap_src<TAP>(pb[n], py[n], px[n], t, g.H, g.W) : -1;
-            src[n] = q < 0 ? -1 : q * g.b_cs + g.b_off;
+        for (int r = 0; r < 4; ++r) {
+            const float t = row_sum(bs[i][r]);
+            if (lr == 0) s_b[wave * 64 + i * 16 + 4 * lg + r] = t;
         }
-        for (int c0 = 0; c0 < g.K; c0 += 32) {
-            const int kk = c0 + 8 * lg;
-            bf16x8 bfr[NP], afr[MC];
-#pragma unroll
-            for (int n = 0; n < NP; ++n) bfr[n] = src[n] >= 0 ? ld8(g.Bsrc + src[n] + kk) : zero8;
-#pragma unroll
-            for (int i = 0; i < MC; ++i) {
-                const int m = mbase + i * 16 + lr;
-                afr[i] = m < g.M ? ld8(g.A + ((int64_t)m * taps + t) * g.K + kk) : zero8;
-            }
-#pragma unroll
-            for (int i = 0; i < MC; ++i)
-#pragma unroll
-                for (int n = 0; n < NP; ++n)
-                    acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[i], bfr[n], acc[i][n], 0, 0, 0);
-        }
-    }
-    // epilogue: lane holds rows m0..m0+3 of column pixel (pb, py, px)
-#pragma unroll
-    for (int i = 0; i < MC; ++i) {
-        const int m0 = mbase + i * 16 + 4 * lg;
-        if (m0 >= g.M) continue;
-#pragma unroll
-        for (int n = 0; n < NP; ++n) {
-            if (!pv[n]) continue;
-            const int64_t pix = ((int64_t)pb[n] * g.H + py[n]) * g.W + px[n];
-            float v0 = acc[i][n][0], v1 = acc[i][n][1], v2 = acc[i][n][2], v3 = acc[i][n][3];
-            if (EPI == EPI_F32) {
-                float *o = (float *)g.out + pix * g.o_cs + g.o_off + m0;
-                *(float4 *)o = make_float4(v0, v1, v2, v3);
-            } else if (EPI == EPI_RELU_BF16) {
-                v0 = fmaxf(v0 + g.bias[m0 + 0], 0.f);
-                v1 = fmaxf(v1 + g.bias[m0 + 1], 0.f);
-                v2 = fmaxf(v2 + g.bias[m0 + 2], 0.f);
-                v3 = fmaxf(v3 + g.bias[m0 + 3], 0.f);
-                uint16_t *o = (uint16_t *)g.out + pix * g.o_cs + g.o_off + m0;
-                *(uint2 *)o = make_uint2(pack_bf16(v0, v1),
-                                         pack_bf16(v2, v3));
-            } else {
-                const int d = m0 / g.cout, co = m0 - d * g.cout;
-                const int64_t fp = ((int64_t)pb[n] * 2 * g.H + 2 * py[n] + (d >> 1)) * (2 * g.W) + 2 * px[n] + (d & 1);
-                v0 += g.bias[co + 0];
-                v1 += g.bias[co + 1];
-                v2 += g.bias[co + 2];
-                v3 += g.bias[co + 3];
-                uint16_t *o = (uint16_t *)g.out + fp * g.o_cs + g.o_off + co;
-                *(uint2 *)o = make_uint2(pack_bf16(v0, v1),
-                                         pack_bf16(v2, v3));
-            }
-        }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const int c = threadIdx.x;
+        g.bpart[(int64_t)blockIdx.x * g.M + mbase + c] = s_b[c] + s_b[64 + c] + s_b[128 + c] + s_b[192 + c];
     }
 }
 
@@ -356,8 +391,22 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     };
     // poff holds the offsets of the item whose chunks are being fetched: the
     // current one's, then (from its last chunk on) the next one's
+    // EPI_GRAD: the grid being a multiple of 8 and mgroups a divisor of 8, a
+    // block's items have one channel group
+    float bs[MT * 16];
+    __shared__ float s_b[EPI == EPI_GRAD ? 4 * 32 * MT : 1];
+    if (EPI == EPI_GRAD)
+#pragma unroll
+        for (int e = 0; e < MT * 16; ++e) bs[e] = 0.f;
+    auto bias_out = [&]() {
+        const int lin = item_of(0);
+        bias_row<MT>(bs, s_b, g.bpart + (int64_t)(lin / mgroups) * g.M + (lin % mgroups) * 32 * MT);
+    };
     int cur = item_of(0);
-    if (cur >= items) return;
+    if (cur >= items) {
+        if (EPI == EPI_GRAD) bias_out();
+        return;
+    }
     int32_t poff[NPF];
     {
         const Item it = decode(cur);
@@ -438,6 +487,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
                     float v2 = acc[i][n][4 * j + 2], v3 = acc[i][n][4 * j + 3];
                     if (EPI == EPI_F32) {
                         *(float4 *)((float *)g.out + pix * g.o_cs + g.o_off + m0) = make_float4(v0, v1, v2, v3);
+                    } else if (EPI == EPI_GRAD) {
+                        if (g.split && m0 >= g.split) {
+                            *(float4 *)(g.skip + pix * (g.M - g.split) + m0 - g.split) = make_float4(v0, v1, v2, v3);
+                        } else {
+                            float v[4] = {v0, v1, v2, v3};
+                            const uint2 a = g.split ? make_uint2(0, 0) : *(const uint2 *)(g.act + pix * g.M + m0);
+                            *(uint2 *)((uint16_t *)g.out + pix * (g.split ? g.split : g.M) + m0) =
+                                grad4(v, a, !g.split, bs + i * 16 + 4 * j);
+                        }
                     } else {
                         v0 = fmaxf(v0 + g.bias[m0 + 0], 0.f);
                         v1 = fmaxf(v1 + g.bias[m0 + 1], 0.f);
@@ -461,7 +519,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
                     }
                 }
         }
-        if (!more) break;
+        if (!more) {
+            if (EPI == EPI_GRAD) bias_out();
+            break;
+        }
         cur = nxt;
         nxt = item_of(++step);
         mbase = (cur % mgroups) * 32 * MT;
@@ -590,8 +651,18 @@ __global__ void __launch_bounds__(256, 2) k_conv3r(const GemmArgs g)
                                              (__attribute__((address_space(3))) void *)(wts + ub * 16), 16, 0, 0);
         }
     };
+    // EPI_GRAD: bias sums, a slot per wave (the registers have no room for sums
+    // carried through the items); the grid being a multiple of 8 and mgroups a
+    // divisor of 8, a block's items have one channel group
+    __shared__ float s_b[EPI == EPI_GRAD ? 4 * 32 * MT : 1];
     int cur = item_of(0);
-    if (cur >= items) return;
+    float *const brow = EPI == EPI_GRAD ? g.bpart + (int64_t)(cur / mgroups) * g.M + (cur % mgroups) * 32 * MT : nullptr;
+    if (EPI == EPI_GRAD)
+        for (int e = tid; e < 4 * 32 * MT; e += 256) s_b[e] = 0.f;   // (a barrier follows before the first epilogue)
+    if (cur >= items) {
+        if (EPI == EPI_GRAD && tid < 32 * MT) brow[tid] = 0.f;
+        return;
+    }
     Item it = decode(cur);
     fetch(it, 0);
     int step = 0, c0 = 0;
@@ -660,10 +731,35 @@ __global__ void __launch_bounds__(256, 2) k_conv3r(const GemmArgs g)
                 if (EPI == EPI_RELU_BF16)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) bj[j] = *(const float4 *)(g.bias + mi + 8 * j + 4 * lh);
+                float bs[16];
+                const bool up = EPI == EPI_GRAD && (!g.split || mi < g.split);
+                if (EPI == EPI_GRAD)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) bs[e] = 0.f;
 #pragma unroll
                 for (int n = 0; n < RW; ++n) {
                     const int py = it.y0 + wave * RW + n;
                     const bool ok = py < g.H && px < g.W;
+                    if (EPI == EPI_GRAD) {
+                        const uint32_t pix = (uint32_t)((it.b * g.H + py) * g.W + px);
+                        if (!ok) continue;
+                        if (!up) {   // the skip half's rows
+                            float *d = g.skip + (pix * (uint32_t)(g.M - g.split) + (uint32_t)(mi - g.split + 4 * lh));
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+                                *(float4 *)(d + 8 * j) =
+                                    make_float4(acc[i][n][4 * j], acc[i][n][4 * j + 1], acc[i][n][4 * j + 2], acc[i][n][4 * j + 3]);
+                            continue;
+                        }
+                        const uint32_t e0 = pix * (uint32_t)(g.split ? g.split : g.M) + (uint32_t)(mi + 4 * lh);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            float v[4] = {acc[i][n][4 * j], acc[i][n][4 * j + 1], acc[i][n][4 * j + 2], acc[i][n][4 * j + 3]};
+                            const uint2 a = g.split ? make_uint2(0, 0) : *(const uint2 *)(g.act + e0 + 8 * j);
+                            *(uint2 *)((uint16_t *)g.out + e0 + 8 * j) = grad4(v, a, !g.split, bs + 4 * j);
+                        }
+                        continue;
+                    }
                     const uint32_t o = (uint32_t)(((it.b * g.H + py) * g.W + px) * g.o_cs + g.o_off + mi);
                     if (EPI == EPI_F32) {
                         if (ok)
@@ -715,6 +811,13 @@ __global__ void __launch_bounds__(256, 2) k_conv3r(const GemmArgs g)
                         }
                     }
                 }
+                if (EPI == EPI_GRAD && up) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) bs[e] = half_sum(bs[e]);
+                    if (lc == 0)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) s_b[wave * 32 * MT + i * 32 + 8 * (e >> 2) + 4 * lh + (e & 3)] += bs[e];
+                }
             }
             if (!more) break;
 #pragma unroll
@@ -727,6 +830,10 @@ __global__ void __launch_bounds__(256, 2) k_conv3r(const GemmArgs g)
         }
         it = nx;
         c0 = nc;
+    }
+    if (EPI == EPI_GRAD) {
+        __syncthreads();
+        if (tid < 32 * MT) brow[tid] = s_b[tid] + s_b[32 * MT + tid] + s_b[64 * MT + tid] + s_b[96 * MT + tid];
     }
 }
 
@@ -882,6 +989,11 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g, const HeadArgs
                 for (int c = UPC ? 1 : 0; c < KC; ++c) *(uint4 *)(patch + (e >> 2) * PXS + c * 64 + (e & 3) * 16) = fp[c][k];
         }
     };
+    float bs[16];
+    __shared__ float s_b[EPI == EPI_GRAD ? 4 * 32 : 1];
+    if (EPI == EPI_GRAD)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) bs[e] = 0.f;
     int cur = tile_of(0);
     if (cur < tiles) {
         fetch(cur);
@@ -976,6 +1088,10 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g, const HeadArgs
                 float v2 = acc[n][4 * j + 2], v3 = acc[n][4 * j + 3];
                 if (EPI == EPI_F32) {
                     *(float4 *)((float *)g.out + pix * g.o_cs + g.o_off + m0) = make_float4(v0, v1, v2, v3);
+                } else if (EPI == EPI_GRAD) {   // 32 rows, never a concatenation
+                    float gv[4] = {v0, v1, v2, v3};
+                    *(uint2 *)((uint16_t *)g.out + pix * 32 + m0) =
+                        grad4(gv, *(const uint2 *)(g.act + pix * 32 + m0), true, bs + 4 * j);
                 } else {
                     v0 = fmaxf(v0 + g.bias[m0 + 0], 0.f);
                     v1 = fmaxf(v1 + g.bias[m0 + 1], 0.f);
@@ -1017,6 +1133,7 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g, const HeadArgs
         }
         cur = nxt;
     }
+    if (EPI == EPI_GRAD) bias_row<1>(bs, s_b, g.bpart + (int64_t)blockIdx.x * 32);
 }
 
 // ---------------------------------------------------------------- 1x1 GEMM, LDS-staged
@@ -1492,13 +1609,35 @@ __global__ void __launch_bounds__(256, 2) k_wgradT(const WgradArgs a)
 // 36 blocks of one long chain (9,216 columns x 1,024 chunks): a 4 x 256x256
 // training step took 3.31 ms that way, 2.23 ms this way, 9 x 960x544 22.0 and
 // 20.6 ms.
+// Further blocks of the launch sum the layer's bias partials (cols / 16 blocks).
 constexpr int WR_COLS = 64, WR_SLICES = 16;
+struct BiasPart {
+    const float *part;       // [rows][stride] partials
+    int rows, stride, cols;  // cols a multiple of 16 (0 = none)
+    float *out;
+};
 __global__ void __launch_bounds__(256) k_wgrad_reduce(const float *__restrict__ part, int chunks, int M, int taps,
-                                                      int K, int cin, float *__restrict__ gw)
+                                                      int K, int cin, float *__restrict__ gw, const BiasPart bp)
 {
     __shared__ __attribute__((aligned(16))) float red[WR_SLICES][WR_COLS];
-    const int c4 = threadIdx.x & 15, sl = threadIdx.x >> 4;
     const int64_t n = (int64_t)M * taps * K;   // K is a multiple of 32
+    const int wblocks = (int)((n + WR_COLS - 1) / WR_COLS);
+    if ((int)blockIdx.x >= wblocks) {
+        // the bias gradient, 16 columns per block: slice s adds rows s, s + 16, ...
+        const int c = threadIdx.x & 15, sl = threadIdx.x >> 4, col = ((int)blockIdx.x - wblocks) * 16 + c;
+        float a = 0.f;
+#pragma unroll 4
+        for (int r = sl; r < bp.rows; r += 16) a += bp.part[(int64_t)r * bp.stride + col];
+        red[sl][c] = a;
+        __syncthreads();
+        if (threadIdx.x >= 16) return;
+        float t = 0.f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) t += red[k][c];
+        bp.out[col] = t;
+        return;
+    }
+    const int c4 = threadIdx.x & 15, sl = threadIdx.x >> 4;
     const int64_t col = (int64_t)blockIdx.x * WR_COLS + 4 * c4;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
     if (col < n)
@@ -1546,113 +1685,211 @@ __global__ void __launch_bounds__(256) k_pool(const uint16_t *in, int i_cs, int 
     *(uint4 *)(out + op * C + gi * 8) = *(const uint4 *)best;
 }
 
-// Pool backward fused with the skip-connection gradient: g_fine[p] =
-// (p is the first maximum of its window ? g_coarse : 0) + skip[p].
-__global__ void __launch_bounds__(256) k_pool_back(const uint16_t *a, int a_cs, int a_off, const float *g_coarse,
-                                                   const float *skip, int s_cs, int s_off, float *g_fine, int NB,
-                                                   int H, int W, int C)
+// Max-pool gradient, the skip connection's gradient, the ReLU mask and the
+// bfloat16 rounding in one pass: fine pixel p's gradient is (p is the first
+// maximum of its window ? g_coarse : 0) + skip[p], masked by its activation (the
+// pool's input), with a row of bias partials per block.  A thread takes a coarse
+// pixel's window and 8 channels; blocks walk the windows in steps of the grid
+// (a multiple of the channel groups), so a thread's channels stay the same.
+// Bound by memory; as two passes with the
+// float32 gradient stored between them, 1.9 + 0.4 ms of a 9 x 960x544 step (three
+// levels); now 0.48 ms, near the time its bytes take.
+constexpr int POOL_BLOCKS = 2048;
+__global__ void __launch_bounds__(256) k_pool_grad(const uint16_t *act, const float *g_coarse, const float *skip,
+                                                   uint16_t *G, float *bpart, int NB, int H, int W, int C)
 {
     const int groups = C / 8;
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int Ho = H / 2, Wo = W / 2;
-    if (e >= (int64_t)NB * Ho * Wo * groups) return;
-    const int gi = (int)(e % groups);
-    const int64_t op = e / groups;
-    const int b = (int)(op / (Ho * Wo)), r = (int)(op % (Ho * Wo)), y = r / Wo, x = r - y * Wo;
-    float best[8];
-    int arg[8];
-    for (int d = 0; d < 4; ++d) {
-        const int64_t ip = ((int64_t)b * H + 2 * y + (d >> 1)) * W + 2 * x + (d & 1);
-        const uint4 v = *(const uint4 *)(a + ip * a_cs + a_off + gi * 8);
-        const uint16_t *h = (const uint16_t *)&v;
+    const int64_t n = (int64_t)NB * Ho * Wo * groups;
+    const int tid = threadIdx.x, gi = tid % groups;
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int64_t e = (int64_t)blockIdx.x * 256 + tid; e < n; e += (int64_t)gridDim.x * 256) {
+        const uint32_t op = (uint32_t)(e / groups);
+        const uint32_t b = op / (uint32_t)(Ho * Wo), r = op % (uint32_t)(Ho * Wo), y = r / (uint32_t)Wo, x = r - y * (uint32_t)Wo;
+        const uint32_t ip = (b * (uint32_t)H + 2 * y) * (uint32_t)W + 2 * x;
+        uint4 av[4];
+        float gc[8], gs[4][8];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const uint32_t o = (ip + (uint32_t)((d >> 1) * W + (d & 1))) * (uint32_t)C + (uint32_t)gi * 8;
+            av[d] = *(const uint4 *)(act + o);
+            *(float4 *)&gs[d][0] = *(const float4 *)(skip + o);
+            *(float4 *)&gs[d][4] = *(const float4 *)(skip + o + 4);
+        }
+        *(float4 *)&gc[0] = *(const float4 *)(g_coarse + op * (uint32_t)C + gi * 8);
+        *(float4 *)&gc[4] = *(const float4 *)(g_coarse + op * (uint32_t)C + gi * 8 + 4);
+        uint32_t w[4][4];
+#pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const float f = bf2f(h[j]);
-            if (d == 0 || f > best[j]) {
-                best[j] = f;
-                arg[j] = d;
+            float f[4], v[4];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t word = (&av[d].x)[j >> 1];
+                f[d] = __uint_as_float(j & 1 ? word & 0xFFFF0000u : word << 16);
+            }
+            int arg = 0;
+            float best = f[0];
+#pragma unroll
+            for (int d = 1; d < 4; ++d)
+                if (f[d] > best) {
+                    best = f[d];
+                    arg = d;
+                }
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                v[d] = (arg == d ? gc[j] : 0.f) + gs[d][j];
+                v[d] = f[d] > 0.f ? v[d] : 0.f;
+                s[j] += v[d];
+                const uint32_t h = pack_bf16(v[d], 0.f) & 0xFFFFu;
+                w[d][j >> 1] = j & 1 ? w[d][j >> 1] | h << 16 : h;
             }
         }
-    }
-    for (int d = 0; d < 4; ++d) {
-        const int64_t ip = ((int64_t)b * H + 2 * y + (d >> 1)) * W + 2 * x + (d & 1);
-        for (int j = 0; j < 8; ++j) {
-            const int c = gi * 8 + j;
-            const float gv = arg[j] == d ? g_coarse[op * C + c] : 0.f;
-            g_fine[ip * C + c] = gv + skip[ip * s_cs + s_off + c];
-        }
-    }
-}
-
-// Gradient at a layer output -> bf16 matrix-core operand (masked by the ReLU
-// when relu != 0) and per-workgroup bias partial sums of the fp32 masked
-// gradient.  Workgroup: 64 pixels; thread: 8 channels.
-__global__ void __launch_bounds__(256) k_mask_round(const float *g, int g_cs, int g_off, const uint16_t *act, int a_cs,
-                                                    int a_off, int relu, uint16_t *G, int C, int P, float *bpart)
-{
-    const int groups = C / 8;
-    const int tid = threadIdx.x;
-    const int gi = tid % groups;
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const int p0 = blockIdx.x * 64;
-    for (int e = tid; e < 64 * groups; e += 256) {
-        const int p = p0 + e / groups;
-        if (p >= P) break;
-        const float4 ga = *(const float4 *)(g + (int64_t)p * g_cs + g_off + gi * 8);
-        const float4 gb = *(const float4 *)(g + (int64_t)p * g_cs + g_off + gi * 8 + 4);
-        float v[8] = {ga.x, ga.y, ga.z, ga.w, gb.x, gb.y, gb.z, gb.w};
-        if (relu) {
-            const uint4 av = *(const uint4 *)(act + (int64_t)p * a_cs + a_off + gi * 8);
-            const uint16_t *h = (const uint16_t *)&av;
-            for (int j = 0; j < 8; ++j)
-                if (!(bf2f(h[j]) > 0.f)) v[j] = 0.f;
-        }
-        uint16_t o[8];
-        for (int j = 0; j < 8; ++j) {
-            s[j] += v[j];
-            o[j] = f2bf(v[j]);
-        }
-        *(uint4 *)(G + (int64_t)p * C + gi * 8) = *(const uint4 *)o;
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            *(uint4 *)(G + (ip + (uint32_t)((d >> 1) * W + (d & 1))) * (uint32_t)C + (uint32_t)gi * 8) =
+                make_uint4(w[d][0], w[d][1], w[d][2], w[d][3]);
     }
     __shared__ float red[256 * 8];
+#pragma unroll
     for (int j = 0; j < 8; ++j) red[tid * 8 + j] = s[j];
     __syncthreads();
-    if (tid < groups) {
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int u = tid; u < 256; u += groups)
-            for (int j = 0; j < 8; ++j) acc[j] += red[u * 8 + j];
-        for (int j = 0; j < 8; ++j) bpart[(int64_t)blockIdx.x * C + tid * 8 + j] = acc[j];
+    if (tid < C) {
+        float acc = 0.f;
+        for (int u = tid >> 3; u < 256; u += groups) acc += red[u * 8 + (tid & 7)];
+        bpart[(int64_t)blockIdx.x * C + tid] = acc;
     }
 }
 
-// Column sums of a rows x n matrix of partials: one workgroup per column,
-// thread t adds rows t, t+256, ... in order, then a fixed tree combines the
-// 256 sums -- the same result on every run.
-__global__ void __launch_bounds__(256) k_reduce_rows(const float *part, int rows, int n, float *out)
+// Head of a training step: z = 1x1 convolution of dec0b's output a (32 -> 3) on
+// the matrix cores as in k_head, sigmoid, loss, d loss / d z; the gradient at
+// dec0b's output masked by its ReLU and rounded (EPI_GRAD's form), and per block
+// the partial sums of the head's weight (96) and bias (3) gradients, the loss
+// and dec0b's bias gradient (32).  A lane takes a pixel per step and carries its
+// 132 sums in registers through the launch; summing them per 256 pixels through
+// LDS, 24 rounds of four threads adding 256 values, and storing the float32
+// gradient for another pass took 1.05 + 0.3 ms on 9 x 960x544; now 0.40 ms.
+constexpr int HEAD_PART = 132;
+__global__ void __launch_bounds__(256, 2) k_head_grad(const HeadArgs h)
+{
+    __shared__ float4 s_w[32];                // channel: its three weights
+    __shared__ float s_p[4][HEAD_PART];
+    const int P = h.NB * h.H * h.W, HW = h.H * h.W;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lc = lane & 31, lh = lane >> 5;
+    if (tid < 32) s_w[tid] = make_float4(bf2f(h.w[tid]), bf2f(h.w[32 + tid]), bf2f(h.w[64 + tid]), 0.f);
+    __syncthreads();
+    const float b0 = h.bias[0], b1 = h.bias[1], b2 = h.bias[2];
+    float wg[3][32], bg[32], zg[3] = {0.f, 0.f, 0.f}, loss = 0.f;
+#pragma unroll
+    for (int ci = 0; ci < 32; ++ci) wg[0][ci] = wg[1][ci] = wg[2][ci] = bg[ci] = 0.f;
+    const bf16x8 zero8 = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+    for (int base = blockIdx.x * 256 + wave * 64; base < P; base += gridDim.x * 256) {
+        // the wave's 64 pixels as two 32-pixel columns, the second column's
+        // results moved to lanes 32..63
+        f32x16 d[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int q = base + 32 * t + lc;
+            const bf16x8 x0 = q < P ? ld8(h.a + (uint32_t)q * 32 + 8 * lh) : zero8;
+            const bf16x8 x1 = q < P ? ld8(h.a + (uint32_t)q * 32 + 16 + 8 * lh) : zero8;
+            d[t] = head_mfma(h.w, x0, x1);
+        }
+        float z[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[1][c]), __float_as_uint(d[1][c]), false, false);
+            z[c] = (lh ? __uint_as_float(sw[0]) : d[0][c]) + (c == 0 ? b0 : c == 1 ? b1 : b2);
+        }
+        const int p = base + lane;
+        if (p >= P) continue;
+        const int r = p % HW, y = r / h.W;
+        float gzr[3] = {0.f, 0.f, 0.f};
+        if (y < h.valid_h)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const float sg = 1.0f / (1.0f + expf(-z[c]));
+                const float df = sg - h.target[(int64_t)p * 3 + c];
+                loss += fabsf(df);
+                const float sign = df > 0.f ? 1.f : (df < 0.f ? -1.f : 0.f);
+                const float gz = sign * h.inv_n * sg * (1.f - sg);
+                zg[c] += gz;
+                gzr[c] = bf2f(f2bf(gz));
+            }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint4 v = *(const uint4 *)(h.a + (uint32_t)p * 32 + q * 8);
+            const uint32_t word[4] = {v.x, v.y, v.z, v.w};
+            uint32_t o[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                float ga[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int ci = q * 8 + 2 * k + e;
+                    const float a = __uint_as_float(e ? word[k] & 0xFFFF0000u : word[k] << 16);
+                    const float4 w = s_w[ci];
+                    float t = gzr[0] * w.x;
+                    t += gzr[1] * w.y;
+                    t += gzr[2] * w.z;
+                    ga[e] = a > 0.f ? t : 0.f;
+                    bg[ci] += ga[e];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) wg[c][ci] = fmaf(gzr[c], a, wg[c][ci]);
+                }
+                o[k] = pack_bf16(ga[0], ga[1]);
+            }
+            *(uint4 *)(h.G + (uint32_t)p * 32 + q * 8) = make_uint4(o[0], o[1], o[2], o[3]);
+        }
+    }
+    auto put = [&](int at, float v) {
+        v = half_sum(v);
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+        if (lane == 0) s_p[wave][at] = v;
+    };
+#pragma unroll
+    for (int ci = 0; ci < 32; ++ci) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) put(c * 32 + ci, wg[c][ci]);
+        put(100 + ci, bg[ci]);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) put(96 + c, zg[c]);
+    put(99, loss);
+    __syncthreads();
+    if (tid < HEAD_PART) h.part[(int64_t)blockIdx.x * HEAD_PART + tid] = s_p[0][tid] + s_p[1][tid] + s_p[2][tid] + s_p[3][tid];
+}
+
+// The sums of k_head_grad's partial rows, one workgroup per column, in a fixed
+// order: weight and bias gradients of the head, the loss, dec0b's bias gradient.
+__global__ void __launch_bounds__(256) k_head_reduce(const float *part, int rows, float *gw, float *gb, float *loss, float *gb0)
 {
     __shared__ float red[256];
     const int col = blockIdx.x;
     float acc = 0.f;
-    for (int r = threadIdx.x; r < rows; r += 256) acc += part[(int64_t)r * n + col];
+    for (int r = threadIdx.x; r < rows; r += 256) acc += part[(int64_t)r * HEAD_PART + col];
     red[threadIdx.x] = acc;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[col] = red[0];
+    if (threadIdx.x != 0) return;
+    if (col < 96)
+        gw[col] = red[0];
+    else if (col < 99)
+        gb[col - 96] = red[0];
+    else if (col == 99)
+        loss[0] = red[0];
+    else
+        gb0[col - 100] = red[0];
 }
 
-// Head: 1x1 conv 32->3 + bias, sigmoid.  mode 0: inference (s and/or RGB8
-// of finite pixels); mode 1: training (loss partials, d loss / d z, the
-// gradient at the head input and the head's weight/bias partials).
-
-__global__ void __launch_bounds__(256) k_head(const HeadArgs h, int mode)
+// Head of a forward pass: 1x1 conv 32->3 + bias, sigmoid (s and/or RGB8 of
+// finite pixels).
+__global__ void __launch_bounds__(256) k_head(const HeadArgs h)
 {
-    __shared__ float red[256 * 4];
-    __shared__ float wred[32 * 4];
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int P = h.NB * h.H * h.W;
-    const bool in = p < P;
     // z on the matrix cores: the wave's 64 pixels as two 32-pixel columns
     // (head_mfma), pixel 32 t + lc of the wave in lane lc of column t; the
     // second column's results move to lanes 32..63 (v_permlane32_swap)
@@ -1667,75 +1904,16 @@ __global__ void __launch_bounds__(256) k_head(const HeadArgs h, int mode)
         const bf16x8 b1 = q < P ? ld8(h.a + q * 32 + 16 + 8 * lh) : zero8;
         d[t] = head_mfma(h.w, b0, b1);
     }
-    float z[3] = {0.f, 0.f, 0.f};
+    float z[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[1][c]), __float_as_uint(d[1][c]), false,
                                                          false);
-        const float zc = lh ? __uint_as_float(sw[0]) : d[0][c];
-        if (in) z[c] = zc + h.bias[c];
+        z[c] = (lh ? __uint_as_float(sw[0]) : d[0][c]) + h.bias[c];
     }
-    float a[32];
-    if (in && mode != 0)
-        for (int q = 0; q < 4; ++q) {
-            const uint4 v = *(const uint4 *)(h.a + p * 32 + q * 8);
-            const uint16_t *hv = (const uint16_t *)&v;
-            for (int j = 0; j < 8; ++j) a[q * 8 + j] = bf2f(hv[j]);
-        }
-    const int b = in ? (int)(p / (h.H * h.W)) : 0;
-    const int r = in ? (int)(p % (h.H * h.W)) : 0;
-    const int y = r / h.W, x = r - y * h.W;
-    if (mode == 0) {
-        if (in) head_store(h, z, p, b, y, x);
-        return;
-    }
-    float s[3];
-    for (int c = 0; c < 3; ++c) s[c] = 1.0f / (1.0f + expf(-z[c]));
-    // training
-    float gz[3] = {0.f, 0.f, 0.f}, loss = 0.f;
-    if (in && y < h.valid_h) {
-        for (int c = 0; c < 3; ++c) {
-            const float d = s[c] - h.target[p * 3 + c];
-            loss += fabsf(d);
-            const float sg = d > 0.f ? 1.f : (d < 0.f ? -1.f : 0.f);
-            gz[c] = sg * h.inv_n * s[c] * (1.f - s[c]);
-        }
-    }
-    float gzr[3];
-    for (int c = 0; c < 3; ++c) gzr[c] = bf2f(f2bf(gz[c]));
-    if (in)
-        for (int ci = 0; ci < 32; ++ci) {
-            float acc = 0.f;
-            for (int c = 0; c < 3; ++c) acc += gzr[c] * bf2f(h.w[c * 32 + ci]);
-            h.g_a[p * 32 + ci] = acc;
-        }
-    // per-workgroup partials: weights (3 x 32), bias (3), loss (1), fixed order
-    const int tid = threadIdx.x;
-    float *outp = h.part + (int64_t)blockIdx.x * (96 + 4);
-    for (int c = 0; c < 3; ++c) {
-        for (int q = 0; q < 8; ++q) {   // 32 input channels in 8 rounds of 4
-            for (int j = 0; j < 4; ++j) red[tid * 4 + j] = in ? gzr[c] * a[q * 4 + j] : 0.f;
-            __syncthreads();
-            if (tid < 4) {
-                float acc = 0.f;
-                for (int u = 0; u < 256; ++u) acc += red[u * 4 + tid];
-                wred[(q * 4 + tid)] = acc;
-            }
-            __syncthreads();
-        }
-        if (tid < 32) outp[c * 32 + tid] = wred[tid];
-        __syncthreads();
-    }
-    red[tid * 4 + 0] = gz[0];
-    red[tid * 4 + 1] = gz[1];
-    red[tid * 4 + 2] = gz[2];
-    red[tid * 4 + 3] = loss;
-    __syncthreads();
-    if (tid < 4) {
-        float acc = 0.f;
-        for (int u = 0; u < 256; ++u) acc += red[u * 4 + tid];
-        outp[96 + tid] = acc;
-    }
+    if (p >= P) return;
+    const int b = (int)(p / (h.H * h.W)), r = (int)(p % (h.H * h.W)), y = r / h.W, x = r - y * h.W;
+    head_store(h, z, p, b, y, x);
 }
 
 // Adam on the fp32 master parameters of one layer, and the bf16 copies in
@@ -1881,7 +2059,7 @@ int wg_chunks(int64_t stages, int tiles)
 size_t partial_floats(size_t P0)
 {
     const Layers &T = layers();
-    size_t m = ((P0 + 63) / 64) * 256;   // bias partials (<= 256 channels per 64-pixel group)
+    size_t m = 0;
     for (int i = 0; i < kNL; ++i) {
         const unet_layer &l = T.L[i];
         if (l.kind == 2) continue;
@@ -1921,10 +2099,11 @@ struct unet_act {
     uint16_t *e0a = nullptr, *cat0 = nullptr, *p1 = nullptr, *e1a = nullptr, *cat1 = nullptr, *p2 = nullptr,
              *e2a = nullptr, *cat2 = nullptr, *p3 = nullptr, *ma = nullptr, *mb = nullptr, *d2a = nullptr,
              *d2b = nullptr, *d1a = nullptr, *d1b = nullptr, *d0a = nullptr, *d0b = nullptr;
-    float *g0 = nullptr, *g1 = nullptr;                  // [P0][32] each
-    float *gs0 = nullptr, *gs1 = nullptr, *gs2 = nullptr;   // [P0][64], [P1][128], [P2][256]
-    uint16_t *G = nullptr;                                // [P0][32]
+    float *g0 = nullptr;                                  // gradient at a pool's output: [P1][32] and smaller
+    float *gs0 = nullptr, *gs1 = nullptr, *gs2 = nullptr;   // skip halves' gradients [P0][32], [P1][64], [P2][128]
+    uint16_t *G = nullptr, *G2 = nullptr;                 // [P0][32] each: the layer's and the next one's
     float *part = nullptr;
+    float *bpart = nullptr;                               // bias partials (kBiasPart floats)
     float *head_part = nullptr;
     float *loss_dev = nullptr;
     void *blocks[40] = {};
@@ -1945,6 +2124,12 @@ struct Plan {
         return o;
     }
 };
+
+// Blocks of the head's training kernel, and bias partials: the widest row
+// matrix is the pool gradient's (POOL_BLOCKS rows of 128 channels); the
+// convolutions have at most 4,096 resident blocks of 64 channels.
+constexpr int kHeadBlocks = 512;
+constexpr size_t kBiasPart = (size_t)POOL_BLOCKS * 128;
 
 // One allocation per set; the plan gives every buffer its offset.
 template <typename F>
@@ -1969,15 +2154,16 @@ void act_plan(size_t P0, bool train, F &&put)
     put(15, P0 * 32 * 2);    // d0a
     put(16, P0 * 32 * 2);    // d0b
     if (!train) return;
-    put(17, P0 * 32 * 4);    // g0
-    put(18, P0 * 32 * 4);    // g1
-    put(19, P0 * 64 * 4);    // gs0
-    put(20, P1 * 128 * 4);   // gs1
-    put(21, P2 * 256 * 4);   // gs2
+    put(17, P1 * 32 * 4);    // g0
+    put(18, P0 * 32 * 2);    // G2
+    put(19, P0 * 32 * 4);    // gs0
+    put(20, P1 * 64 * 4);    // gs1
+    put(21, P2 * 128 * 4);   // gs2
     put(22, P0 * 32 * 2);    // G
     put(23, partial_floats(P0) * 4);
-    put(24, ((P0 + 255) / 256) * 100 * 4);
+    put(24, (size_t)kHeadBlocks * HEAD_PART * 4);
     put(25, 256);            // loss
+    put(26, kBiasPart * 4);
 }
 
 }  // namespace
@@ -2044,7 +2230,7 @@ hipError_t unet_act_reserve(unet_act *a, size_t pixels, bool train)
     for (int i = 0; i < 17; ++i) *bf[i] = (uint16_t *)(base + off[i]);
     if (train) {
         a->g0 = (float *)(base + off[17]);
-        a->g1 = (float *)(base + off[18]);
+        a->G2 = (uint16_t *)(base + off[18]);
         a->gs0 = (float *)(base + off[19]);
         a->gs1 = (float *)(base + off[20]);
         a->gs2 = (float *)(base + off[21]);
@@ -2052,6 +2238,7 @@ hipError_t unet_act_reserve(unet_act *a, size_t pixels, bool train)
         a->part = (float *)(base + off[23]);
         a->head_part = (float *)(base + off[24]);
         a->loss_dev = (float *)(base + off[25]);
+        a->bpart = (float *)(base + off[26]);
     }
     return hipSuccess;
 }
@@ -2072,35 +2259,28 @@ int resident_blocks(F kernel, size_t lds)
     return std::max(1, per) * std::max(1, cus);
 }
 
-template <int MC, int NP, int TAP, int EPI>
-hipError_t gemm(const GemmArgs &g, hipStream_t s)
-{
-    const int P = g.NB * g.H * g.W;
-    dim3 grid((P + 64 * NP - 1) / (64 * NP), (g.M + 16 * MC - 1) / (16 * MC));
-    hipLaunchKernelGGL((k_gemm<MC, NP, TAP, EPI>), grid, dim3(256), 0, s, g);
-    return hipGetLastError();
-}
-
 template <int MT, int TH, int EPI, bool POOL = false>
-hipError_t conv3_launch(const GemmArgs &g, hipStream_t s)
+hipError_t conv3_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr)
 {
     constexpr int lds = c3_lds_bytes<MT, TH>();
     static_assert(lds <= 65536, "staged patch and weights must fit 64 KB");
     const int64_t items = (int64_t)((g.W + 15) / 16) * ((g.H + TH - 1) / TH) * g.NB * ((g.M + 32 * MT - 1) / (32 * MT));
     static const int rb = std::max(8, resident_blocks(k_conv3<MT, TH, EPI, POOL>, lds) / 8 * 8);
     const int grid = (int)std::min<int64_t>(rb, (items + 7) / 8 * 8);
+    if (rows) *rows = grid / ((g.M + 32 * MT - 1) / (32 * MT));
     hipLaunchKernelGGL((k_conv3<MT, TH, EPI, POOL>), dim3(grid), dim3(256), lds, s, g);
     return hipGetLastError();
 }
 
 template <int MT, int RW, int EPI, bool POOL = false>
-hipError_t conv3r_launch(const GemmArgs &g, hipStream_t s)
+hipError_t conv3r_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr)
 {
     constexpr int lds = c3r_lds_bytes<MT, RW>();
     static_assert(2 * lds <= 160 * 1024, "two blocks share a CU's LDS");
     const int64_t items = (int64_t)((g.W + 31) / 32) * ((g.H + 4 * RW - 1) / (4 * RW)) * g.NB * (g.M / (32 * MT));
     static const int rb = std::max(8, resident_blocks(k_conv3r<MT, RW, EPI, POOL>, lds) / 8 * 8);
     const int grid = (int)std::min<int64_t>(rb, (items + 7) / 8 * 8);
+    if (rows) *rows = grid / (g.M / (32 * MT));
     hipLaunchKernelGGL((k_conv3r<MT, RW, EPI, POOL>), dim3(grid), dim3(256), lds, s, g);
     return hipGetLastError();
 }
@@ -2111,11 +2291,12 @@ hipError_t conv3r_launch(const GemmArgs &g, hipStream_t s)
 // of grids from 64 K pixels in 32-column patches (k_conv3r), smaller grids in
 // 8 x 16 patches of 32 output channels
 template <int TH, int KC, int EPI, bool POOL, bool UPC = false, bool HEAD = false, bool K16 = false>
-hipError_t conv3w_launch(const GemmArgs &g, hipStream_t s, const HeadArgs &h = HeadArgs{})
+hipError_t conv3w_launch(const GemmArgs &g, hipStream_t s, const HeadArgs &h = HeadArgs{}, int *rows = nullptr)
 {
     constexpr int lds = c3w_lds_bytes<TH, KC>();
     static_assert(lds <= 65536, "staged patches and weights must fit 64 KB");
     static const int grid = std::max(8, resident_blocks(k_conv3w<TH, KC, EPI, POOL, UPC, HEAD, K16>, lds) / 8 * 8);
+    if (rows) *rows = grid;
     hipLaunchKernelGGL((k_conv3w<TH, KC, EPI, POOL, UPC, HEAD, K16>), dim3(grid), dim3(256), lds, s, g, h);
     return hipGetLastError();
 }
@@ -2123,10 +2304,11 @@ hipError_t conv3w_launch(const GemmArgs &g, hipStream_t s, const HeadArgs &h = H
 // *pooled (if given) tells whether the launch also wrote the 2x2 max-pool
 // of the output to g.pool; *headed (if given) whether it also ran the head
 // (only the weights-resident kernel with one input chunk runs it), and then
-// head_only leaves the output itself unstored.
+// head_only leaves the output itself unstored; *rows (EPI_GRAD) the number of
+// rows of bias partials written.
 template <int EPI>
 hipError_t conv3(GemmArgs g, hipStream_t s, bool *pooled = nullptr, const HeadArgs *head = nullptr,
-                 bool *headed = nullptr, bool head_only = false)
+                 bool *headed = nullptr, bool head_only = false, int *rows = nullptr)
 {
     if (g.K % 32 != 0) return hipErrorInvalidValue;
     if (pooled) *pooled = false;
@@ -2148,10 +2330,12 @@ hipError_t conv3(GemmArgs g, hipStream_t s, bool *pooled = nullptr, const HeadAr
         }
         // an input of 16 channels or fewer (the stack): the zero half of the
         // chunk is neither staged nor multiplied
-        if (g.k_src > 0 && g.k_src <= 16) return conv3w_launch<16, 1, EPI, false, false, false, true>(g, s);
-        return conv3w_launch<16, 1, EPI, false>(g, s);
+        if constexpr (EPI == EPI_RELU_BF16)
+            if (g.k_src > 0 && g.k_src <= 16) return conv3w_launch<16, 1, EPI, false, false, false, true>(g, s);
+        return conv3w_launch<16, 1, EPI, false>(g, s, HeadArgs{}, rows);
     }
-    if (g.M == 32 && g.K == 64 && tiles8 >= 2048) return conv3w_launch<8, 2, EPI, false>(g, s);
+    if constexpr (EPI != EPI_GRAD)
+        if (g.M == 32 && g.K == 64 && tiles8 >= 2048) return conv3w_launch<8, 2, EPI, false>(g, s);
     // 64 output channels x 16 rows x 32 columns per block from 64 K pixels on
     // (2.1 M to 130 K pixels on the 16 x 960x544 network: 113 - 288 us per
     // launch against 195 - 397 for blocks of 16 x 16 pixels), else 32 channels
@@ -2163,7 +2347,7 @@ hipError_t conv3(GemmArgs g, hipStream_t s, bool *pooled = nullptr, const HeadAr
             return big ? conv3r_launch<2, 4, EPI, true>(g, s) : conv3_launch<1, 8, EPI, true>(g, s);
         }
     }
-    return big ? conv3r_launch<2, 4, EPI>(g, s) : conv3_launch<1, 8, EPI>(g, s);
+    return big ? conv3r_launch<2, 4, EPI>(g, s, rows) : conv3_launch<1, 8, EPI>(g, s, rows);
 }
 
 // 3x3 conv + bias + ReLU into (out, o_cs, o_off); with pool_out, *pooled
@@ -2333,21 +2517,6 @@ hipError_t forward_all(unet_state *n, unet_act *a, const uint16_t *stack, int NB
     return hipSuccess;
 }
 
-// gradient g (fp32, C channels at g_off of a g_cs-channel buffer) of layer
-// li's output -> bf16 operand a->G [P][C] (ReLU-masked by the stored output
-// when relu) and the layer's bias gradient
-hipError_t mask_round(unet_state *n, unet_act *a, const float *g, int g_cs, int g_off, const uint16_t *act,
-                      int a_cs, int a_off, bool relu, int C, int P, int li, hipStream_t s)
-{
-    const int wgs = (P + 63) / 64;
-    hipLaunchKernelGGL(k_mask_round, dim3(wgs), dim3(256), 0, s, g, g_cs, g_off, act, a_cs, a_off, relu ? 1 : 0, a->G,
-                       C, P, a->part);
-    NCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_reduce_rows, dim3(C), dim3(256), 0, s, (const float *)a->part, wgs, C,
-                       n->g + layers().L[li].b_off);
-    return hipGetLastError();
-}
-
 template <int WM, int WK, int WP, int ROWS>
 void wgrad3_launch(const WgradArgs &w, int chunks, hipStream_t s)
 {
@@ -2368,9 +2537,10 @@ void wgradT_launch(const WgradArgs &w, int chunks, hipStream_t s)
 
 // weight gradient of layer li from a->G (its masked output gradient) and
 // its input X; (NB, H, W) is the contraction grid (the coarse grid for convT);
-// split as in conv_fwd
-hipError_t wgrad(unet_state *n, unet_act *a, int li, const uint16_t *X, int x_cs, int NB, int H, int W, hipStream_t s,
-                 int split = 0)
+// split as in conv_fwd; bias: the partials of its bias gradient, if still to be
+// summed (their out is set here)
+hipError_t wgrad(unet_state *n, unet_act *a, int li, const BiasPart &bias, const uint16_t *X, int x_cs, int NB, int H,
+                 int W, hipStream_t s, int split = 0)
 {
     const unet_layer &l = layers().L[li];
     WgradArgs w{};
@@ -2405,53 +2575,86 @@ hipError_t wgrad(unet_state *n, unet_act *a, int li, const uint16_t *X, int x_cs
     }
     NCHK(hipGetLastError());
     const int nel = l.cout * l.taps * l.cin_pad;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((nel + WR_COLS - 1) / WR_COLS), dim3(256), 0, s, (const float *)a->part,
-                       chunks, l.cout, l.taps, l.cin_pad, l.cin, n->g + l.w_off);
+    BiasPart bp = bias;
+    bp.out = n->g + l.b_off;
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((nel + WR_COLS - 1) / WR_COLS + bp.cols / 16), dim3(256), 0, s,
+                       (const float *)a->part, chunks, l.cout, l.taps, l.cin_pad, l.cin, n->g + l.w_off, bp);
     return hipGetLastError();
 }
 
-// data gradient of a 3x3 conv from a->G: fp32 [P][cin]
-hipError_t conv_dgrad(unet_state *n, unet_act *a, int li, float *out, int NB, int H, int W, hipStream_t s)
+// The data gradient of layer li from a->G.  With f32, float32 [P][cin] there
+// (the gradient at a pool's output); else the next layer's gradient operand in
+// a->G2, then swapped with a->G, masked by act (the activation the layer read)
+// or, with split, the first split channels unmasked and the rest as float32 in
+// skip.  Returns the bias partials of that next layer in bias.
+hipError_t conv_dgrad(unet_state *n, unet_act *a, int li, int NB, int H, int W, hipStream_t s, BiasPart &bias,
+                      const uint16_t *act, int split = 0, float *skip = nullptr, float *f32 = nullptr)
 {
     const unet_layer &l = layers().L[li];
     GemmArgs g{};
     g.A = n->wd + l.wd_off;
     g.Bsrc = a->G;
     g.b_cs = l.cout;
-    g.out = out;
-    g.o_cs = l.cin;
     g.NB = NB;
     g.H = H;
     g.W = W;
     g.K = l.cout;
     g.M = l.cin;
-    return conv3<EPI_F32>(g, s);
+    bias = BiasPart{};
+    if (f32) {
+        g.out = f32;
+        g.o_cs = l.cin;
+        return conv3<EPI_F32>(g, s);
+    }
+    g.out = a->G2;
+    g.act = act;
+    g.split = split;
+    g.skip = skip;
+    g.bpart = a->bpart;
+    int rows = 0;
+    NCHK(conv3<EPI_GRAD>(g, s, nullptr, nullptr, nullptr, false, &rows));
+    bias = BiasPart{a->bpart, rows, l.cin, split ? split : l.cin, nullptr};
+    std::swap(a->G, a->G2);
+    return (size_t)rows * l.cin <= kBiasPart ? hipSuccess : hipErrorInvalidValue;
 }
 
-// data gradient of a 2x2 transposed conv: a->G on the fine grid -> fp32 [P_coarse][cin]
-hipError_t convT_dgrad(unet_state *n, unet_act *a, int li, float *out, int NB, int Hc, int Wc, hipStream_t s)
+// ... of a 2x2 transposed convolution: a->G on the fine grid -> [P_coarse][cin],
+// masked by act
+hipError_t convT_dgrad(unet_state *n, unet_act *a, int li, int NB, int Hc, int Wc, hipStream_t s, BiasPart &bias,
+                       const uint16_t *act)
 {
     const unet_layer &l = layers().L[li];
     GemmArgs g{};
     g.A = n->wd + l.wd_off;
     g.Bsrc = a->G;
     g.b_cs = l.cout;
-    g.out = out;
-    g.o_cs = l.cin;
+    g.out = a->G2;
+    g.act = act;
+    g.bpart = a->bpart;
     g.NB = NB;
     g.H = Hc;
     g.W = Wc;
     g.K = l.cout;
     g.M = l.cin;
-    return gemm<4, 1, TAP_FINE4, EPI_F32>(g, s);
+    const int P = NB * Hc * Wc, mg = g.M / 64;
+    static const int rb = std::max(8, resident_blocks(k_convT_grad<2>, 0));
+    const int rows = std::max(1, std::min((P + 127) / 128, rb / mg));
+    hipLaunchKernelGGL(k_convT_grad<2>, dim3(rows, mg), dim3(256), 0, s, g);
+    NCHK(hipGetLastError());
+    bias = BiasPart{a->bpart, rows, l.cin, l.cin, nullptr};
+    std::swap(a->G, a->G2);
+    return (size_t)rows * l.cin <= kBiasPart ? hipSuccess : hipErrorInvalidValue;
 }
 
-hipError_t pool_back(const uint16_t *act, int a_cs, int a_off, const float *g_coarse, const float *skip, int s_cs,
-                     int s_off, float *g_fine, int NB, int H, int W, int C, hipStream_t s)
+// the gradient operand (a->G) of the encoder layer before a pool, from the
+// pool's output gradient a->g0 and the skip half's
+hipError_t pool_grad(unet_act *a, const uint16_t *act, const float *skip, int NB, int H, int W, int C, hipStream_t s,
+                     BiasPart &bias)
 {
     const int64_t n = (int64_t)NB * (H / 2) * (W / 2) * (C / 8);
-    hipLaunchKernelGGL(k_pool_back, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, act, a_cs, a_off, g_coarse,
-                       skip, s_cs, s_off, g_fine, NB, H, W, C);
+    const int rows = (int)std::min<int64_t>(POOL_BLOCKS, (n + 255) / 256);
+    hipLaunchKernelGGL(k_pool_grad, dim3(rows), dim3(256), 0, s, act, (const float *)a->g0, skip, a->G, a->bpart, NB, H, W, C);
+    bias = BiasPart{a->bpart, rows, C, C, nullptr};
     return hipGetLastError();
 }
 
@@ -2574,7 +2777,7 @@ hipError_t unet_forward(unet_state *n, unet_act *a, const uint16_t *stack, int N
     NCHK(forward_all(n, a, stack, NB, H, W, s, !keep, &h, &done));
     if (done) return hipSuccess;
     const int P = NB * H * W;
-    hipLaunchKernelGGL(k_head, dim3((P + 255) / 256), dim3(256), 0, s, h, 0);
+    hipLaunchKernelGGL(k_head, dim3((P + 255) / 256), dim3(256), 0, s, h);
     return hipGetLastError();
 }
 
@@ -2602,7 +2805,7 @@ hipError_t unet_forward_batch(unet_state *n, unet_act *a, const uint16_t *stack,
     NCHK(forward_all(n, a, stack, NB, H, W, s, !keep, &h, &done));
     if (done) return hipSuccess;
     const int P = NB * H * W;
-    hipLaunchKernelGGL(k_head, dim3((P + 255) / 256), dim3(256), 0, s, h, 0);
+    hipLaunchKernelGGL(k_head, dim3((P + 255) / 256), dim3(256), 0, s, h);
     return hipGetLastError();
 }
 
@@ -2618,7 +2821,7 @@ hipError_t unet_train(unet_state *n, unet_act *a, const uint16_t *stack, const f
         return hipErrorInvalidValue;
     }
     NCHK(forward_all(n, a, stack, NB, H, W, s));
-    const int P0 = NB * H * W, P1 = P0 / 4, P2 = P1 / 4, P3 = P2 / 4;
+    const int P0 = NB * H * W;
     const int H1 = H / 2, W1 = W / 2, H2 = H / 4, W2 = W / 4, H3 = H / 8, W3 = W / 8;
     const Layers &T = layers();
     const uint16_t *const sk0 = skip_plane(a->cat0, 0, NB, H, W), *const sk1 = skip_plane(a->cat1, 1, NB, H, W),
@@ -2635,76 +2838,58 @@ hipError_t unet_train(unet_state *n, unet_act *a, const uint16_t *stack, const f
     h.valid_w = W;
     h.target = target;
     h.inv_n = (float)(1.0 / ((double)NB * valid_h * W * 3));
-    h.g_a = a->g0;
+    h.G = a->G;
     h.part = a->head_part;
-    const int hwg = (P0 + 255) / 256;
-    hipLaunchKernelGGL(k_head, dim3(hwg), dim3(256), 0, s, h, 1);
+    const int hwg = std::min(kHeadBlocks, (P0 + 255) / 256);
+    hipLaunchKernelGGL(k_head_grad, dim3(hwg), dim3(256), 0, s, h);
     NCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_reduce_rows, dim3(100), dim3(256), 0, s, (const float *)a->head_part, hwg, 100, a->part);
+    hipLaunchKernelGGL(k_head_reduce, dim3(HEAD_PART), dim3(256), 0, s, (const float *)a->head_part, hwg,
+                       n->g + T.L[L_HEAD].w_off, n->g + T.L[L_HEAD].b_off, a->loss_dev, n->g + T.L[L_D0B].b_off);
     NCHK(hipGetLastError());
-    NCHK(hipMemcpyAsync(n->g + T.L[L_HEAD].w_off, a->part, 96 * 4, hipMemcpyDeviceToDevice, s));
-    NCHK(hipMemcpyAsync(n->g + T.L[L_HEAD].b_off, a->part + 96, 3 * 4, hipMemcpyDeviceToDevice, s));
-    NCHK(hipMemcpyAsync(a->loss_dev, a->part + 99, 4, hipMemcpyDeviceToDevice, s));
+    BiasPart bp{};
     // decoder, level 0
-    NCHK(mask_round(n, a, a->g0, 32, 0, a->d0b, 32, 0, true, 32, P0, L_D0B, s));
-    NCHK(wgrad(n, a, L_D0B, a->d0a, 32, NB, H, W, s));
-    NCHK(conv_dgrad(n, a, L_D0B, a->g1, NB, H, W, s));
-    NCHK(mask_round(n, a, a->g1, 32, 0, a->d0a, 32, 0, true, 32, P0, L_D0A, s));
-    NCHK(wgrad(n, a, L_D0A, a->cat0, 32, NB, H, W, s, 32));
-    NCHK(conv_dgrad(n, a, L_D0A, a->gs0, NB, H, W, s));              // [g_up0 | g_skip0]
-    NCHK(mask_round(n, a, a->gs0, 64, 0, nullptr, 0, 0, false, 32, P0, L_UP0, s));
-    NCHK(wgrad(n, a, L_UP0, a->d1b, 64, NB, H1, W1, s));
-    NCHK(convT_dgrad(n, a, L_UP0, a->g0, NB, H1, W1, s));            // g(d1b) [P1][64]
+    NCHK(wgrad(n, a, L_D0B, bp, a->d0a, 32, NB, H, W, s));
+    NCHK(conv_dgrad(n, a, L_D0B, NB, H, W, s, bp, a->d0a));
+    NCHK(wgrad(n, a, L_D0A, bp, a->cat0, 32, NB, H, W, s, 32));
+    NCHK(conv_dgrad(n, a, L_D0A, NB, H, W, s, bp, nullptr, 32, a->gs0));   // [G of up0 | g_skip0]
+    NCHK(wgrad(n, a, L_UP0, bp, a->d1b, 64, NB, H1, W1, s));
+    NCHK(convT_dgrad(n, a, L_UP0, NB, H1, W1, s, bp, a->d1b));
     // level 1
-    NCHK(mask_round(n, a, a->g0, 64, 0, a->d1b, 64, 0, true, 64, P1, L_D1B, s));
-    NCHK(wgrad(n, a, L_D1B, a->d1a, 64, NB, H1, W1, s));
-    NCHK(conv_dgrad(n, a, L_D1B, a->g1, NB, H1, W1, s));
-    NCHK(mask_round(n, a, a->g1, 64, 0, a->d1a, 64, 0, true, 64, P1, L_D1A, s));
-    NCHK(wgrad(n, a, L_D1A, a->cat1, 64, NB, H1, W1, s, 64));
-    NCHK(conv_dgrad(n, a, L_D1A, a->gs1, NB, H1, W1, s));            // [g_up1 | g_skip1]
-    NCHK(mask_round(n, a, a->gs1, 128, 0, nullptr, 0, 0, false, 64, P1, L_UP1, s));
-    NCHK(wgrad(n, a, L_UP1, a->d2b, 128, NB, H2, W2, s));
-    NCHK(convT_dgrad(n, a, L_UP1, a->g0, NB, H2, W2, s));            // g(d2b) [P2][128]
+    NCHK(wgrad(n, a, L_D1B, bp, a->d1a, 64, NB, H1, W1, s));
+    NCHK(conv_dgrad(n, a, L_D1B, NB, H1, W1, s, bp, a->d1a));
+    NCHK(wgrad(n, a, L_D1A, bp, a->cat1, 64, NB, H1, W1, s, 64));
+    NCHK(conv_dgrad(n, a, L_D1A, NB, H1, W1, s, bp, nullptr, 64, a->gs1));
+    NCHK(wgrad(n, a, L_UP1, bp, a->d2b, 128, NB, H2, W2, s));
+    NCHK(convT_dgrad(n, a, L_UP1, NB, H2, W2, s, bp, a->d2b));
     // level 2
-    NCHK(mask_round(n, a, a->g0, 128, 0, a->d2b, 128, 0, true, 128, P2, L_D2B, s));
-    NCHK(wgrad(n, a, L_D2B, a->d2a, 128, NB, H2, W2, s));
-    NCHK(conv_dgrad(n, a, L_D2B, a->g1, NB, H2, W2, s));
-    NCHK(mask_round(n, a, a->g1, 128, 0, a->d2a, 128, 0, true, 128, P2, L_D2A, s));
-    NCHK(wgrad(n, a, L_D2A, a->cat2, 128, NB, H2, W2, s, 128));
-    NCHK(conv_dgrad(n, a, L_D2A, a->gs2, NB, H2, W2, s));            // [g_up2 | g_skip2]
-    NCHK(mask_round(n, a, a->gs2, 256, 0, nullptr, 0, 0, false, 128, P2, L_UP2, s));
-    NCHK(wgrad(n, a, L_UP2, a->mb, 256, NB, H3, W3, s));
-    NCHK(convT_dgrad(n, a, L_UP2, a->g0, NB, H3, W3, s));            // g(mb) [P3][256]
+    NCHK(wgrad(n, a, L_D2B, bp, a->d2a, 128, NB, H2, W2, s));
+    NCHK(conv_dgrad(n, a, L_D2B, NB, H2, W2, s, bp, a->d2a));
+    NCHK(wgrad(n, a, L_D2A, bp, a->cat2, 128, NB, H2, W2, s, 128));
+    NCHK(conv_dgrad(n, a, L_D2A, NB, H2, W2, s, bp, nullptr, 128, a->gs2));
+    NCHK(wgrad(n, a, L_UP2, bp, a->mb, 256, NB, H3, W3, s));
+    NCHK(convT_dgrad(n, a, L_UP2, NB, H3, W3, s, bp, a->mb));
     // bottleneck
-    NCHK(mask_round(n, a, a->g0, 256, 0, a->mb, 256, 0, true, 256, P3, L_MB, s));
-    NCHK(wgrad(n, a, L_MB, a->ma, 256, NB, H3, W3, s));
-    NCHK(conv_dgrad(n, a, L_MB, a->g1, NB, H3, W3, s));
-    NCHK(mask_round(n, a, a->g1, 256, 0, a->ma, 256, 0, true, 256, P3, L_MA, s));
-    NCHK(wgrad(n, a, L_MA, a->p3, 128, NB, H3, W3, s));
-    NCHK(conv_dgrad(n, a, L_MA, a->g0, NB, H3, W3, s));              // g(p3) [P3][128]
-    // encoder, level 2: g(enc2b) = pool routing of g(p3) + skip
-    NCHK(pool_back(sk2, 128, 0, a->g0, a->gs2, 256, 128, a->g1, NB, H2, W2, 128, s));
-    NCHK(mask_round(n, a, a->g1, 128, 0, sk2, 128, 0, true, 128, P2, L_E2B, s));
-    NCHK(wgrad(n, a, L_E2B, a->e2a, 128, NB, H2, W2, s));
-    NCHK(conv_dgrad(n, a, L_E2B, a->g0, NB, H2, W2, s));
-    NCHK(mask_round(n, a, a->g0, 128, 0, a->e2a, 128, 0, true, 128, P2, L_E2A, s));
-    NCHK(wgrad(n, a, L_E2A, a->p2, 64, NB, H2, W2, s));
-    NCHK(conv_dgrad(n, a, L_E2A, a->g1, NB, H2, W2, s));             // g(p2) [P2][64]
+    NCHK(wgrad(n, a, L_MB, bp, a->ma, 256, NB, H3, W3, s));
+    NCHK(conv_dgrad(n, a, L_MB, NB, H3, W3, s, bp, a->ma));
+    NCHK(wgrad(n, a, L_MA, bp, a->p3, 128, NB, H3, W3, s));
+    NCHK(conv_dgrad(n, a, L_MA, NB, H3, W3, s, bp, nullptr, 0, nullptr, a->g0));   // g(p3) [P3][128]
+    // encoder, level 2
+    NCHK(pool_grad(a, sk2, a->gs2, NB, H2, W2, 128, s, bp));
+    NCHK(wgrad(n, a, L_E2B, bp, a->e2a, 128, NB, H2, W2, s));
+    NCHK(conv_dgrad(n, a, L_E2B, NB, H2, W2, s, bp, a->e2a));
+    NCHK(wgrad(n, a, L_E2A, bp, a->p2, 64, NB, H2, W2, s));
+    NCHK(conv_dgrad(n, a, L_E2A, NB, H2, W2, s, bp, nullptr, 0, nullptr, a->g0));   // g(p2) [P2][64]
     // level 1
-    NCHK(pool_back(sk1, 64, 0, a->g1, a->gs1, 128, 64, a->g0, NB, H1, W1, 64, s));
-    NCHK(mask_round(n, a, a->g0, 64, 0, sk1, 64, 0, true, 64, P1, L_E1B, s));
-    NCHK(wgrad(n, a, L_E1B, a->e1a, 64, NB, H1, W1, s));
-    NCHK(conv_dgrad(n, a, L_E1B, a->g1, NB, H1, W1, s));
-    NCHK(mask_round(n, a, a->g1, 64, 0, a->e1a, 64, 0, true, 64, P1, L_E1A, s));
-    NCHK(wgrad(n, a, L_E1A, a->p1, 32, NB, H1, W1, s));
-    NCHK(conv_dgrad(n, a, L_E1A, a->g0, NB, H1, W1, s));             // g(p1) [P1][32]
+    NCHK(pool_grad(a, sk1, a->gs1, NB, H1, W1, 64, s, bp));
+    NCHK(wgrad(n, a, L_E1B, bp, a->e1a, 64, NB, H1, W1, s));
+    NCHK(conv_dgrad(n, a, L_E1B, NB, H1, W1, s, bp, a->e1a));
+    NCHK(wgrad(n, a, L_E1A, bp, a->p1, 32, NB, H1, W1, s));
+    NCHK(conv_dgrad(n, a, L_E1A, NB, H1, W1, s, bp, nullptr, 0, nullptr, a->g0));   // g(p1) [P1][32]
     // level 0
-    NCHK(pool_back(sk0, 32, 0, a->g0, a->gs0, 64, 32, a->g1, NB, H, W, 32, s));
-    NCHK(mask_round(n, a, a->g1, 32, 0, sk0, 32, 0, true, 32, P0, L_E0B, s));
-    NCHK(wgrad(n, a, L_E0B, a->e0a, 32, NB, H, W, s));
-    NCHK(conv_dgrad(n, a, L_E0B, a->g0, NB, H, W, s));
-    NCHK(mask_round(n, a, a->g0, 32, 0, a->e0a, 32, 0, true, 32, P0, L_E0A, s));
-    NCHK(wgrad(n, a, L_E0A, stack, UNET_IN, NB, H, W, s));
+    NCHK(pool_grad(a, sk0, a->gs0, NB, H, W, 32, s, bp));
+    NCHK(wgrad(n, a, L_E0B, bp, a->e0a, 32, NB, H, W, s));
+    NCHK(conv_dgrad(n, a, L_E0B, NB, H, W, s, bp, a->e0a));
+    NCHK(wgrad(n, a, L_E0A, bp, stack, UNET_IN, NB, H, W, s));
     if (apply) {
         n->step += 1;
         NCHK(prep_weights(n, lr, 1, s));
