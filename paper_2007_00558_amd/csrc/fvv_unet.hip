@@ -1764,23 +1764,30 @@ __global__ void __launch_bounds__(256) k_pool_grad(const uint16_t *act, const fl
 // the matrix cores as in k_head, sigmoid, loss, d loss / d z; the gradient at
 // dec0b's output masked by its ReLU and rounded (EPI_GRAD's form), and per block
 // the partial sums of the head's weight (96) and bias (3) gradients, the loss
-// and dec0b's bias gradient (32).  A lane takes a pixel per step and carries its
-// 132 sums in registers through the launch; summing them per 256 pixels through
-// LDS, 24 rounds of four threads adding 256 values, and storing the float32
-// gradient for another pass took 1.05 + 0.3 ms on 9 x 960x544; now 0.40 ms.
+// and dec0b's bias gradient (32).  A lane takes a pixel per step and carries the
+// sums through the launch; the weight gradient, a contraction of the rounded
+// d loss / d z with the activations over pixels, runs on the matrix cores as
+// well (the wave's 64 pixels through LDS, read back by transpose reads).
+// Summing per 256 pixels through LDS, 24 rounds of four threads adding 256
+// values, and storing the float32 gradient for another pass took 1.05 + 0.3 ms
+// on 9 x 960x544; now 0.25 ms.
 constexpr int HEAD_PART = 132;
-__global__ void __launch_bounds__(256, 2) k_head_grad(const HeadArgs h)
+__global__ void __launch_bounds__(256, 4) k_head_grad(const HeadArgs h)
 {
     __shared__ float4 s_w[32];                // channel: its three weights
+    __shared__ __attribute__((aligned(16))) uint16_t s_a[4][64 * 32], s_g[4][3 * 64];
     __shared__ float s_p[4][HEAD_PART];
     const int P = h.NB * h.H * h.W, HW = h.H * h.W;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lc = lane & 31, lh = lane >> 5;
     if (tid < 32) s_w[tid] = make_float4(bf2f(h.w[tid]), bf2f(h.w[32 + tid]), bf2f(h.w[64 + tid]), 0.f);
     __syncthreads();
     const float b0 = h.bias[0], b1 = h.bias[1], b2 = h.bias[2];
-    float wg[3][32], bg[32], zg[3] = {0.f, 0.f, 0.f}, loss = 0.f;
+    float bg[32], zg[3] = {0.f, 0.f, 0.f}, loss = 0.f;
 #pragma unroll
-    for (int ci = 0; ci < 32; ++ci) wg[0][ci] = wg[1][ci] = wg[2][ci] = bg[ci] = 0.f;
+    for (int ci = 0; ci < 32; ++ci) bg[ci] = 0.f;
+    f32x16 wg;   // rows 0..2: the weight gradient
+#pragma unroll
+    for (int r = 0; r < 16; ++r) wg[r] = 0.f;
     const bf16x8 zero8 = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
     for (int base = blockIdx.x * 256 + wave * 64; base < P; base += gridDim.x * 256) {
         // the wave's 64 pixels as two 32-pixel columns, the second column's
@@ -1800,10 +1807,10 @@ __global__ void __launch_bounds__(256, 2) k_head_grad(const HeadArgs h)
             z[c] = (lh ? __uint_as_float(sw[0]) : d[0][c]) + (c == 0 ? b0 : c == 1 ? b1 : b2);
         }
         const int p = base + lane;
-        if (p >= P) continue;
+        const bool in = p < P;
         const int r = p % HW, y = r / h.W;
         float gzr[3] = {0.f, 0.f, 0.f};
-        if (y < h.valid_h)
+        if (in && y < h.valid_h)
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const float sg = 1.0f / (1.0f + expf(-z[c]));
@@ -1815,8 +1822,11 @@ __global__ void __launch_bounds__(256, 2) k_head_grad(const HeadArgs h)
                 gzr[c] = bf2f(f2bf(gz));
             }
 #pragma unroll
+        for (int c = 0; c < 3; ++c) s_g[wave][c * 64 + lane] = (uint16_t)(__float_as_uint(gzr[c]) >> 16);
+#pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const uint4 v = *(const uint4 *)(h.a + (uint32_t)p * 32 + q * 8);
+            const uint4 v = in ? *(const uint4 *)(h.a + (uint32_t)p * 32 + q * 8) : make_uint4(0, 0, 0, 0);
+            *(uint4 *)(s_a[wave] + lane * 32 + q * 8) = v;
             const uint32_t word[4] = {v.x, v.y, v.z, v.w};
             uint32_t o[4];
 #pragma unroll
@@ -1832,13 +1842,19 @@ __global__ void __launch_bounds__(256, 2) k_head_grad(const HeadArgs h)
                     t += gzr[2] * w.z;
                     ga[e] = a > 0.f ? t : 0.f;
                     bg[ci] += ga[e];
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) wg[c][ci] = fmaf(gzr[c], a, wg[c][ci]);
                 }
                 o[k] = pack_bf16(ga[0], ga[1]);
             }
-            *(uint4 *)(h.G + (uint32_t)p * 32 + q * 8) = make_uint4(o[0], o[1], o[2], o[3]);
+            if (in) *(uint4 *)(h.G + (uint32_t)p * 32 + q * 8) = make_uint4(o[0], o[1], o[2], o[3]);
         }
+        // (a wave's LDS accesses are in order: its own pixels only)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bf16x8 ga = lc < 3 ? ld8(s_g[wave] + lc * 64 + 16 * k + 8 * lh) : zero8;
+            wg = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, tr_frag(s_a[wave] + 16 * k * 32 + tr_lane()), wg, 0, 0, 0);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     }
     auto put = [&](int at, float v) {
         v = half_sum(v);
@@ -1846,12 +1862,12 @@ __global__ void __launch_bounds__(256, 2) k_head_grad(const HeadArgs h)
         v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
         if (lane == 0) s_p[wave][at] = v;
     };
+    // wg[r] of lane (lc, lh = 0): row r (< 3), channel lc
+    if (lh == 0)
 #pragma unroll
-    for (int ci = 0; ci < 32; ++ci) {
+        for (int c = 0; c < 3; ++c) s_p[wave][c * 32 + lc] = wg[c];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) put(c * 32 + ci, wg[c][ci]);
-        put(100 + ci, bg[ci]);
-    }
+    for (int ci = 0; ci < 32; ++ci) put(100 + ci, bg[ci]);
 #pragma unroll
     for (int c = 0; c < 3; ++c) put(96 + c, zg[c]);
     put(99, loss);
@@ -2128,7 +2144,7 @@ struct Plan {
 // Blocks of the head's training kernel, and bias partials: the widest row
 // matrix is the pool gradient's (POOL_BLOCKS rows of 128 channels); the
 // convolutions have at most 4,096 resident blocks of 64 channels.
-constexpr int kHeadBlocks = 512;
+constexpr int kHeadBlocks = 1024;
 constexpr size_t kBiasPart = (size_t)POOL_BLOCKS * 128;
 
 // One allocation per set; the plan gives every buffer its offset.
