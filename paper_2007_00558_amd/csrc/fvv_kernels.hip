@@ -45,10 +45,10 @@ template <typename V> __device__ __forceinline__ gmem<V> *gptr(const V *p) { ret
 
 constexpr int T = FVV_TILE;
 constexpr int WN = FVV_TILE + 2;   // tile window edge with a 1-pixel halo
-constexpr int TNT = T * T / 4;     // threads of a tile workgroup: four pixels each
-constexpr int TNW = TNT / 64;      // its waves
-constexpr int TPR = T / 4;         // threads per tile row
-static_assert(T % 4 == 0 && TNT % 64 == 0 && TNT >= 2 * T && TNT <= 1024, "tile workgroup shape");
+// threads of a tile workgroup with PPT pixels each
+constexpr int tile_threads(int ppt) { return T * T / ppt; }
+constexpr int TNT = tile_threads(4);
+static_assert(T % 4 == 0 && TNT % 64 == 0 && TNT >= 4 * T && tile_threads(1) <= 1024, "tile workgroup shapes");
 
 __device__ __forceinline__ uint32_t f2u(float f) { return __float_as_uint(f); }
 __device__ __forceinline__ float u2f(uint32_t u) { return __uint_as_float(u); }
@@ -695,21 +695,22 @@ __device__ __forceinline__ bool blend_pixel(const fvv_view_desc &vd, int k0, int
     return true;
 }
 
-// Four pixels (x .. x + 3, y) at depths zf (NaN = none) in the first K slots,
+// N pixels (x .. x + N - 1, y) at depths zf (NaN = none) in the first K slots,
 // camera by camera: a camera's matrices and row terms are read and computed
-// once for the four.  slot / rgba of a pixel with a mixed colour.
-__device__ __forceinline__ void blend_four(const fvv_view_desc &vd, int x, int y, const float (&zf)[4],
-                                           uint32_t (&slot)[4], uint32_t (&rgba)[4])
+// once for all.  slot / rgba of a pixel with a mixed colour.
+template <int N>
+__device__ __forceinline__ void blend_row(const fvv_view_desc &vd, int x, int y, const float (&zf)[N],
+                                          uint32_t (&slot)[N], uint32_t (&rgba)[N])
 {
-    float acc[4][3], wsum[4];
+    float acc[N][3], wsum[N];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q][0] = acc[q][1] = acc[q][2] = wsum[q] = 0.f;
+    for (int q = 0; q < N; ++q) acc[q][0] = acc[q][1] = acc[q][2] = wsum[q] = 0.f;
     const float fx = (float)x, fy = (float)y;
     for (int k = 0; k < vd.K; ++k) {
         const Cam s = load_cam<true>(vd.src[k], vd.tau);
         const float by[3] = {__fmul_rn(s.B[1], fy), __fmul_rn(s.B[4], fy), __fmul_rn(s.B[7], fy)};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < N; ++q) {
             float c[3], r;
             const float csum = sample(s, by, fx + (float)q, zf[q], c, r);
             if (csum > 0.f) {
@@ -721,7 +722,7 @@ __device__ __forceinline__ void blend_four(const fvv_view_desc &vd, int x, int y
         }
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < N; ++q)
         if (wsum[q] > 0.f) {
             slot[q] = f2u(zf[q]);
             rgba[q] = mixed(acc[q], wsum[q]);
@@ -774,9 +775,11 @@ __device__ __forceinline__ void offer(Cand &b, float z, int dist, int idx)
 // ---------------------------------------------------------------- fused tile
 // STACK: views may carry a learned-path stack (a separate instantiation, so
 // the plain kernel keeps its register budget and occupancy).
-template <bool STACK, bool LAYERED>
+template <bool STACK, bool LAYERED, int PPT>
 __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ views, int mtx, int mty, int n_views)
 {
+    constexpr int TNT = tile_threads(PPT);   // threads, waves, and threads per tile row
+    constexpr int TNW = TNT / 64, TPR = T / PPT;
     // XCD-aware order: workgroups are dealt to the 8 XCDs round-robin, so
     // dispatch index b runs on XCD b % 8.  Each XCD takes a contiguous
     // eighth of the (view, tile) sequence in raster order; neighbouring
@@ -960,14 +963,14 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
     // sorting network a wave would otherwise run whenever one of its lanes
     // needs it.  Those pixels are listed and the list is spread over every
     // thread of the tile.
-    const int ly = t / TPR, lx0 = (t % TPR) * 4;
+    const int ly = t / TPR, lx0 = (t % TPR) * PPT;
     const int y = Y0 + ly;
     // the depths of the filtered points (an empty key's depth word is a NaN;
     // pixels off the image have none)
-    float zf[4];
+    float zf[PPT];
     if (LAYERED) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < PPT; ++q) {
             const int x = X0 + lx0 + q;
             unsigned long long kf = FVV_KEY_EMPTY;
             if (x < W && y < H) {
@@ -984,17 +987,17 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
         // and the four pixels' 3 x 3 windows share theirs: 18 words, whose
         // column sums of empty marks (sign bits: an empty key's word is all
         // ones, a valid depth's sign is clear) serve three pixels each.
-        uint32_t h[3][6];
+        uint32_t h[3][PPT + 2];
 #pragma unroll
         for (int r = 0; r < 3; ++r)
 #pragma unroll
-            for (int c = 0; c < 6; ++c) h[r][c] = (uint32_t)(zk[(ly + r) * WN + lx0 + c] >> 32);
-        uint32_t col[6];
+            for (int c = 0; c < PPT + 2; ++c) h[r][c] = (uint32_t)(zk[(ly + r) * WN + lx0 + c] >> 32);
+        uint32_t col[PPT + 2];
 #pragma unroll
-        for (int c = 0; c < 6; ++c) col[c] = (h[0][c] >> 31) + (h[1][c] >> 31) + (h[2][c] >> 31);
-        bool need[4];
+        for (int c = 0; c < PPT + 2; ++c) col[c] = (h[0][c] >> 31) + (h[1][c] >> 31) + (h[2][c] >> 31);
+        bool need[PPT];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < PPT; ++q) {
             const uint32_t cz = h[1][q + 1];
             const uint32_t empty = col[q] + col[q + 1] + col[q + 2] - (cz >> 31);
             const float z0 = u2f(cz);
@@ -1026,7 +1029,7 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
         }
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < PPT; ++q) {
             const int pix = ly * T + lx0 + q;
             if (need[q]) zf[q] = u2f((uint32_t)(s_kf[pix] >> 32));
             if (vd.dbg_zf && X0 + lx0 + q < W && y < H)
@@ -1036,15 +1039,15 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
     }
 
     // ---- S3: backward fetch and blend
-    uint32_t pslot[4], prgb[4];
+    uint32_t pslot[PPT], prgb[PPT];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < PPT; ++q) {
         pslot[q] = FVV_HOLE;
         prgb[q] = 0;
     }
-    if (!STACK) blend_four(vd, X0 + lx0, y, zf, pslot, prgb);
+    if (!STACK) blend_row<PPT>(vd, X0 + lx0, y, zf, pslot, prgb);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < PPT; ++q) {
         const int x = X0 + lx0 + q;
         float ch[STACK ? 16 : 1];   // the learned-path stack channels of the pixel
 #pragma unroll
@@ -1090,7 +1093,7 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
     }
     bool any_hole = false;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < PPT; ++q) {
         s_slot[ly * T + lx0 + q] = pslot[q];
         s_rgb[ly * T + lx0 + q] = prgb[q];
         any_hole |= (pslot[q] & FVV_HOLE) && lx0 + q < tw && ly < th;
@@ -1136,9 +1139,9 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
         }
         __syncthreads();
     }
-    uint32_t osl[4], ocol[4];
+    uint32_t osl[PPT], ocol[PPT];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < PPT; ++q) {
         const int lx = lx0 + q;
         osl[q] = FVV_HOLE;
         ocol[q] = 0;
@@ -1178,15 +1181,20 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
         const int x = X0 + lx0;
         const int64_t so = (int64_t)y * W + x;
         uint8_t *po = vd.out + (int64_t)y * vd.out_pitch + (int64_t)x * 3;
-        if (lx0 + 3 < tw && (so & 3) == 0 && ((uintptr_t)po & 3) == 0) {
-            *(uint4 *)(vd.slot + so) = make_uint4(osl[0], osl[1], osl[2], osl[3]);
-            uint32_t *pw = (uint32_t *)po;
-            pw[0] = (ocol[0] & 0xFFFFFFu) | (ocol[1] << 24);
-            pw[1] = ((ocol[1] >> 8) & 0xFFFFu) | (ocol[2] << 16);
-            pw[2] = ((ocol[2] >> 16) & 0xFFu) | ((ocol[3] & 0xFFFFFFu) << 8);
-        } else {
+        bool wide = false;
+        if constexpr (PPT == 4) {
+            wide = lx0 + 3 < tw && (so & 3) == 0 && ((uintptr_t)po & 3) == 0;
+            if (wide) {
+                *(uint4 *)(vd.slot + so) = make_uint4(osl[0], osl[1], osl[2], osl[3]);
+                uint32_t *pw = (uint32_t *)po;
+                pw[0] = (ocol[0] & 0xFFFFFFu) | (ocol[1] << 24);
+                pw[1] = ((ocol[1] >> 8) & 0xFFFFu) | (ocol[2] << 16);
+                pw[2] = ((ocol[2] >> 16) & 0xFFu) | ((ocol[3] & 0xFFFFFFu) << 8);
+            }
+        }
+        if (!wide) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < PPT; ++q) {
                 if (lx0 + q >= tw) continue;
                 vd.slot[so + q] = osl[q];
                 put_rgb(vd.out, vd.out_pitch, x + q, y, ocol[q]);
@@ -1242,13 +1250,13 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
 __global__ void __launch_bounds__(TNT) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_tile_plain(const fvv_view_desc *__restrict__ views, int mtx, int mty, int n_views)
 {
-    tile_body<false, false>(views, mtx, mty, n_views);
+    tile_body<false, false, 4>(views, mtx, mty, n_views);
 }
 
 __global__ void __launch_bounds__(TNT) k_tile_stack(const fvv_view_desc *__restrict__ views, int mtx, int mty,
                                                     int n_views)
 {
-    tile_body<true, false>(views, mtx, mty, n_views);
+    tile_body<true, false, 4>(views, mtx, mty, n_views);
 }
 
 // Layered synthesis (Section VI): foreground and background layers splatted
@@ -1260,13 +1268,56 @@ __global__ void __launch_bounds__(TNT) k_tile_stack(const fvv_view_desc *__restr
 // CU through LDS, so registers are not capped.
 __global__ void __launch_bounds__(TNT) k_tile_layered(const fvv_view_desc *__restrict__ views, int mtx, int mty, int n_views)
 {
-    tile_body<false, true>(views, mtx, mty, n_views);
+    tile_body<false, true, 4>(views, mtx, mty, n_views);
 }
 
 __global__ void __launch_bounds__(TNT) k_tile_stack_layered(const fvv_view_desc *__restrict__ views, int mtx,
                                                             int mty, int n_views)
 {
-    tile_body<true, true>(views, mtx, mty, n_views);
+    tile_body<true, true, 4>(views, mtx, mty, n_views);
+}
+
+// The same with one or two pixels per thread, for launches of few tiles.
+template <bool STACK, bool LAYERED, int PPT>
+__global__ void __launch_bounds__(tile_threads(PPT)) k_tile_few(const fvv_view_desc *__restrict__ views, int mtx,
+                                                                int mty, int n_views)
+{
+    tile_body<STACK, LAYERED, PPT>(views, mtx, mty, n_views);
+}
+
+// Pixels per thread of a launch: the fewest at which every tile still runs at
+// once.  A CU holds 32 waves: eight workgroups of 256 threads (four pixels
+// each), four of 512 or two of 1024.  A tile is one long chain (list entry,
+// splat record, LDS key, filter, taps, fill), so a launch of fewer tiles than
+// that leaves the SIMDs waiting on a few waves, and more threads per tile
+// shorten the chain; a launch of more only pays for the entries, barriers and
+// row terms that more waves repeat.  Kernel at 4 / 2 / 1 pixels per thread, us:
+// 60 tiles 21 / 16 / 14; 240 47 / 29 / 23; 510 33 / 25 / 23; 920 35 / 31 / 36;
+// 1,450 41 / 43 / 49; 2,040 43 / 49 / 64; 24,480 483 / 568 / 722.  Layered:
+// 240 57 / 35 / 25; 510 41 / 28 / 31; 920 40 / 33 / 43; 2,040 55 / 55 / 83;
+// 24,480 552 / 605 / 1,015.
+constexpr int kTileCus = 256;
+constexpr int tile_ppt(int64_t tiles) { return tiles <= 2 * kTileCus ? 1 : tiles <= 4 * kTileCus ? 2 : 4; }
+
+template <bool STACK, bool LAYERED>
+void launch_tile_few_as(const fvv_batch_dims &b, const fvv_view_desc *d_views, dim3 grid, int ppt, hipStream_t s)
+{
+    if (ppt == 1)
+        hipLaunchKernelGGL((k_tile_few<STACK, LAYERED, 1>), grid, dim3(tile_threads(1)), 0, s, d_views, b.max_tiles_x,
+                           b.max_tiles_y, b.n_views);
+    else
+        hipLaunchKernelGGL((k_tile_few<STACK, LAYERED, 2>), grid, dim3(tile_threads(2)), 0, s, d_views, b.max_tiles_x,
+                           b.max_tiles_y, b.n_views);
+}
+
+void launch_tile_few(const fvv_batch_dims &b, const fvv_view_desc *d_views, dim3 grid, int ppt, hipStream_t s)
+{
+    if (b.any_layered)
+        b.any_stack ? launch_tile_few_as<true, true>(b, d_views, grid, ppt, s)
+                    : launch_tile_few_as<false, true>(b, d_views, grid, ppt, s);
+    else
+        b.any_stack ? launch_tile_few_as<true, false>(b, d_views, grid, ppt, s)
+                    : launch_tile_few_as<false, false>(b, d_views, grid, ppt, s);
 }
 
 // ---------------------------------------------------------------- open holes
@@ -1417,7 +1468,10 @@ hipError_t launch_stages(fvv_view_desc *d_views, const fvv_batch_dims &b, hipStr
         // 1-D dispatch of every (view, tile), rounded up to whole XCD rounds
         const int total = b.max_tiles_x * b.max_tiles_y * b.n_views;
         const dim3 grid((total + FVV_XCDS - 1) / FVV_XCDS * FVV_XCDS);
-        if (b.any_layered && b.any_stack)
+        const int ppt = tile_ppt((int64_t)b.max_tiles_x * b.max_tiles_y * b.n_views);
+        if (ppt < 4)
+            launch_tile_few(b, d_views, grid, ppt, s);
+        else if (b.any_layered && b.any_stack)
             hipLaunchKernelGGL(k_tile_stack_layered, grid, dim3(TNT), 0, s, d_views, b.max_tiles_x, b.max_tiles_y,
                                b.n_views);
         else if (b.any_layered)
