@@ -23,6 +23,9 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // EPI_GRAD: a gradient that the next layer's products read -- masked by that
 // layer's ReLU and rounded to bfloat16, with the sums of the float32 masked
@@ -76,8 +79,8 @@ struct GemmArgs {
     int split;
     float *skip;
     float *bpart;            // [rows][M] bias partials
-    uint16_t *pool;          // k_conv3w, EPI_RELU_BF16: also the 2x2 max-pooled output [NB][H/2][W/2][32] (or null)
-    // k_conv3w<.., 2, .., UPC>: input chunk 0 is the 2x2 transposed
+    uint16_t *pool;          // EPI_RELU_BF16: also the 2x2 max-pooled output [NB][H/2][W/2][M] (or null)
+    // k_conv3w<.., UPC>: input chunk 0 is the 2x2 transposed
     // convolution (32 output channels, 64 input channels) of up_in
     // [NB][H/2][W/2][64] with weights up_w [4 x 32][64] and bias up_b,
     // computed per patch instead of read from Bsrc
@@ -107,17 +110,26 @@ struct HeadArgs {
 // 8 lh + 7 (b0) and 16 + 8 lh .. 23 + 8 lh (b1) of pixel lc.  Lane lc (< 32)
 // receives z_0..z_2 of pixel lc in d[0..2]; the result of a pixel depends
 // only on its own inputs.
-__device__ __forceinline__ f32x16 head_mfma(const uint16_t *w, bf16x8 b0, bf16x8 b1)
+__device__ __forceinline__ void head_frags(const uint16_t *w, bf16x8 &a0, bf16x8 &a1)
 {
     const int lane = threadIdx.x & 63, lc = lane & 31, lh = lane >> 5;
     const bf16x8 zero8 = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
-    const bf16x8 a0 = lc < 3 ? ld8(w + lc * 32 + 8 * lh) : zero8;
-    const bf16x8 a1 = lc < 3 ? ld8(w + lc * 32 + 16 + 8 * lh) : zero8;
+    a0 = lc < 3 ? ld8(w + lc * 32 + 8 * lh) : zero8;
+    a1 = lc < 3 ? ld8(w + lc * 32 + 16 + 8 * lh) : zero8;
+}
+__device__ __forceinline__ f32x16 head_mfma(bf16x8 a0, bf16x8 a1, bf16x8 b0, bf16x8 b1)
+{
     f32x16 d;
 #pragma unroll
     for (int r = 0; r < 16; ++r) d[r] = 0.f;
     d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, d, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, d, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16 head_mfma(const uint16_t *w, bf16x8 b0, bf16x8 b1)
+{
+    bf16x8 a0, a1;
+    head_frags(w, a0, a1);
+    return head_mfma(a0, a1, b0, b1);
 }
 
 // Sigmoid outputs of the head for pixel p (image b, row y, column x): the
@@ -131,12 +143,14 @@ __device__ __forceinline__ void head_store(const HeadArgs &h, const float z[3], 
 #pragma unroll
         for (int c = 0; c < 3; ++c) h.s_out[p * 3 + c] = s[c];
     const bool fin = isfinite(s[0]) && isfinite(s[1]) && isfinite(s[2]);
-    uint8_t *o = nullptr;
+    // global memory and a table that no kernel in flight writes, said so: a
+    // flat store would order every later wait for a load behind all of them
+    __attribute__((address_space(1))) uint8_t *o = nullptr;
     if (h.outs) {
-        const unet_out d = h.outs[b];
-        if (y < d.h && x < d.w) o = d.rgb + (int64_t)y * d.pitch + (int64_t)x * 3;
+        const auto &d = ((const __attribute__((address_space(4))) unet_out *)h.outs)[b];
+        if (y < d.h && x < d.w) o = (__attribute__((address_space(1))) uint8_t *)d.rgb + (int64_t)y * d.pitch + (int64_t)x * 3;
     } else if (h.rgb && y < h.valid_h && x < h.valid_w) {
-        o = h.rgb + b * h.img_stride + (int64_t)y * h.pitch + (int64_t)x * 3;
+        o = (__attribute__((address_space(1))) uint8_t *)h.rgb + b * h.img_stride + (int64_t)y * h.pitch + (int64_t)x * 3;
     }
     if (o && fin)
 #pragma unroll
@@ -838,36 +852,28 @@ __global__ void __launch_bounds__(256, 2) k_conv3r(const GemmArgs g)
 }
 
 // ---------------------------------------------------------------- 3x3 convolution, weights resident
-// The 32-output-channel layers with one or two input chunks (the full-
-// resolution level; 16-row patches with one chunk, 8-row ones with two, or
-// with the head): the same implicit GEMM as k_conv3<1, TH>, but a block
-// stages the whole weight slice (KC chunks x 32 rows x 9 taps x 32 channels)
-// in LDS once and then walks over patches (TH x 16 pixels), so the weights
-// are not fetched again for every patch; the next patch (all KC chunks) is
-// fetched into registers while the current one's MFMAs and stores run.
+// The 32-output-channel layers with two input chunks (the full-resolution
+// level): the same implicit GEMM as k_conv3<1, 8>, but a block stages the whole
+// weight slice (two chunks x 32 rows x 9 taps x 32 channels) in LDS once and
+// then walks over patches (8 x 16 pixels), so the weights are not fetched again
+// for every patch; the next patch (both chunks) is fetched into registers while
+// the current one's MFMAs and stores run.
 // Blocks take patches in steps of the grid; block b's patches in one step
 // are contiguous with those of the blocks on its XCD (b mod 8), so patches
 // whose halos overlap are read through the same L2.
-// A staged pixel holds its KC chunks side by side (KC x 64 bytes + 16 bytes
-// of padding: 80 or 144 bytes, both keep the 16-byte fragment reads of 8
-// consecutive lanes in distinct banks).
-template <int KC>
-constexpr int c3w_pxs() { return KC * 64 + 16; }
-template <int TH, int KC>
-constexpr int c3w_lds_bytes() { return (TH + 2) * 18 * c3w_pxs<KC>() + KC * 32 * C3_RS; }
+// A staged pixel holds its two chunks side by side (128 bytes + 16 bytes of
+// padding, which keeps the 16-byte fragment reads of 8 consecutive lanes in
+// distinct banks).
+constexpr int C3W_PXS = 2 * 64 + 16;
+constexpr int C3W_LDS = 10 * 18 * C3W_PXS + 2 * 32 * C3_RS;
 
-
-template <int TH, int KC, int EPI, bool POOL, bool UPC = false, bool HEAD = false, bool K16 = false>
-__global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g, const HeadArgs hd)
+template <int EPI, bool UPC = false>
+__global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g)
 {
-    static_assert(!HEAD || EPI == EPI_RELU_BF16, "the head follows a ReLU output");
-    static_assert(TH % 8 == 0, "each wave takes TH/4 rows, two per 32-pixel tile");
-    static_assert(!UPC || (KC == 2 && TH == 8), "the transposed convolution feeds chunk 0 of 8-row patches");
-    static_assert(!K16 || KC == 1, "K16: one chunk whose channels 16..31 are zero (not staged, not multiplied)");
-    constexpr int NT = TH / 8;
+    constexpr int TH = 8, KC = 2;
     constexpr int PW = 18;
     constexpr int PH = TH + 2;
-    constexpr int PXS = c3w_pxs<KC>();
+    constexpr int PXS = C3W_PXS;
     extern __shared__ __attribute__((aligned(16))) uint8_t c3w_smem[];
     uint8_t *patch = c3w_smem;                    // PH x PW pixels, KC chunks each
     uint8_t *wts = c3w_smem + PH * PW * PXS;      // KC weight slices
@@ -984,16 +990,11 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g, const HeadArgs
 #pragma unroll
         for (int k = 0; k < NPF; ++k) {
             const int e = tid + k * 256;
-            if (e < PH * PW * 4 && !(K16 && (e & 3) >= 2))
+            if (e < PH * PW * 4)
 #pragma unroll
                 for (int c = UPC ? 1 : 0; c < KC; ++c) *(uint4 *)(patch + (e >> 2) * PXS + c * 64 + (e & 3) * 16) = fp[c][k];
         }
     };
-    float bs[16];
-    __shared__ float s_b[EPI == EPI_GRAD ? 4 * 32 : 1];
-    if (EPI == EPI_GRAD)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) bs[e] = 0.f;
     int cur = tile_of(0);
     if (cur < tiles) {
         fetch(cur);
@@ -1006,133 +1007,325 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g, const HeadArgs
         __syncthreads();
         const int nxt = tile_of(k + 1);
         if (nxt < tiles) fetch(nxt);
-        f32x16 acc[NT];
+        f32x16 acc;
 #pragma unroll
-        for (int n = 0; n < NT; ++n)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[n][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
         for (int c = 0; c < KC; ++c)
 #pragma unroll
             for (int tap = 0; tap < 9; ++tap) {
                 const int dy = tap / 3, dx = tap - dy * 3;
 #pragma unroll
-                for (int kk = 0; kk < (K16 ? 1 : 2); ++kk) {
+                for (int kk = 0; kk < 2; ++kk) {
                     const int koff = (kk * 16 + 8 * lh) * 2;
                     const bf16x8 af = __builtin_bit_cast(bf16x8, *(const uint4 *)(wts + (c * 32 + lc) * C3_RS + tap * 64 + koff));
-#pragma unroll
-                    for (int n = 0; n < NT; ++n) {
-                        const int pr = wave * (TH / 4) + 2 * n + (lc >> 4) + dy;
-                        const int pc = (lc & 15) + dx;
-                        const bf16x8 bfr = __builtin_bit_cast(bf16x8, *(const uint4 *)(patch + (pr * PW + pc) * PXS + c * 64 + koff));
-                        acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bfr, acc[n], 0, 0, 0);
-                    }
+                    const int pr = wave * 2 + (lc >> 4) + dy, pc = (lc & 15) + dx;
+                    const bf16x8 bfr = __builtin_bit_cast(bf16x8, *(const uint4 *)(patch + (pr * PW + pc) * PXS + c * 64 + koff));
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bfr, acc, 0, 0, 0);
                 }
             }
         if constexpr (UPC)
             if (nxt < tiles) up_mfma();
-        // epilogue: lane holds, for pixel lc of each 32-pixel tile, channels
-        // 8 j + 4 lh + {0..3} (j = 0..3)
+        // epilogue: lane holds, for its pixel, channels 8 j + 4 lh + {0..3}
         int t = cur;
         const int txi = t % tiles_x;
         t /= tiles_x;
         const int tyi = t % tiles_y;
         const int b = t / tiles_y;
-        if constexpr (HEAD) {
-            // the output as in the loop below (stored unless g.out is null:
-            // only the head reads it), then the head on the matrix cores: the
-            // packed bfloat16 halves of lanes l and l + 32 swapped
-            // (v_permlane32_swap) into the B fragments of head_mfma
-#pragma unroll
-            for (int n = 0; n < NT; ++n) {
-                const int py = tyi * TH + wave * (TH / 4) + 2 * n + (lc >> 4), px = txi * 16 + (lc & 15);
-                const bool ok = py < g.H && px < g.W;
-                const int64_t pix = ((int64_t)b * g.H + py) * g.W + px;
-                uint32_t w[4][2];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int m0 = 8 * j + 4 * lh;
-                    w[j][0] = pack_bf16(fmaxf(acc[n][4 * j + 0] + g.bias[m0 + 0], 0.f),
-                                        fmaxf(acc[n][4 * j + 1] + g.bias[m0 + 1], 0.f));
-                    w[j][1] = pack_bf16(fmaxf(acc[n][4 * j + 2] + g.bias[m0 + 2], 0.f),
-                                        fmaxf(acc[n][4 * j + 3] + g.bias[m0 + 3], 0.f));
-                    if (ok && g.out)
-                        *(uint2 *)((uint16_t *)g.out + pix * g.o_cs + g.o_off + m0) = make_uint2(w[j][0], w[j][1]);
-                }
-                uint4 o[2];
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const auto s0 = __builtin_amdgcn_permlane32_swap(w[2 * q][0], w[2 * q + 1][0], false, false);
-                    const auto s1 = __builtin_amdgcn_permlane32_swap(w[2 * q][1], w[2 * q + 1][1], false, false);
-                    o[q] = make_uint4(s0[0], s1[0], s0[1], s1[1]);
-                }
-                const f32x16 dz = head_mfma(hd.w, __builtin_bit_cast(bf16x8, o[0]), __builtin_bit_cast(bf16x8, o[1]));
-                if (ok && !lh) {
-                    const float z[3] = {dz[0] + hd.bias[0], dz[1] + hd.bias[1], dz[2] + hd.bias[2]};
-                    head_store(hd, z, pix, b, py, px);
-                }
-            }
-            cur = nxt;
-            continue;
-        }
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            const int py = tyi * TH + wave * (TH / 4) + 2 * n + (lc >> 4), px = txi * 16 + (lc & 15);
-            if (py >= g.H || px >= g.W) continue;
+        const int py = tyi * TH + wave * 2 + (lc >> 4), px = txi * 16 + (lc & 15);
+        if (py < g.H && px < g.W) {
             const int64_t pix = ((int64_t)b * g.H + py) * g.W + px;
-            float v[16];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int m0 = 8 * j + 4 * lh;
-                float v0 = acc[n][4 * j + 0], v1 = acc[n][4 * j + 1];
-                float v2 = acc[n][4 * j + 2], v3 = acc[n][4 * j + 3];
-                if (EPI == EPI_F32) {
+                const float v0 = acc[4 * j + 0], v1 = acc[4 * j + 1], v2 = acc[4 * j + 2], v3 = acc[4 * j + 3];
+                if (EPI == EPI_F32)
                     *(float4 *)((float *)g.out + pix * g.o_cs + g.o_off + m0) = make_float4(v0, v1, v2, v3);
-                } else if (EPI == EPI_GRAD) {   // 32 rows, never a concatenation
-                    float gv[4] = {v0, v1, v2, v3};
-                    *(uint2 *)((uint16_t *)g.out + pix * 32 + m0) =
-                        grad4(gv, *(const uint2 *)(g.act + pix * 32 + m0), true, bs + 4 * j);
-                } else {
-                    v0 = fmaxf(v0 + g.bias[m0 + 0], 0.f);
-                    v1 = fmaxf(v1 + g.bias[m0 + 1], 0.f);
-                    v2 = fmaxf(v2 + g.bias[m0 + 2], 0.f);
-                    v3 = fmaxf(v3 + g.bias[m0 + 3], 0.f);
+                else
                     *(uint2 *)((uint16_t *)g.out + pix * g.o_cs + g.o_off + m0) =
-                        make_uint2(pack_bf16(v0, v1),
-                                   pack_bf16(v2, v3));
-                    v[4 * j + 0] = v0;
-                    v[4 * j + 1] = v1;
-                    v[4 * j + 2] = v2;
-                    v[4 * j + 3] = v3;
-                }
-            }
-            if (EPI == EPI_RELU_BF16 && POOL) {
-                // 2x2 max-pool: the window of pooled pixel (py/2, px/2) is
-                // lanes lc, lc^1 (columns) and lc^16 (rows) of this wave
-                // (patch origins, rows and widths are even).  The max of the
-                // float32 values rounds to the max of their bfloat16 values.
-#pragma unroll
-                for (int r = 0; r < 16; ++r) v[r] = pool_max4(v[r]);
-                // the four lanes of a window share its 32 channels' maxima;
-                // lane (column bit a, row bit c) writes group j = 2 c + a
-                const int jsel = 2 * ((lc >> 4) & 1) + (lc & 1);
-                float q0 = v[0], q1 = v[1], q2 = v[2], q3 = v[3];
-#pragma unroll
-                for (int j = 1; j < 4; ++j)
-                    if (jsel == j) {
-                        q0 = v[4 * j + 0];
-                        q1 = v[4 * j + 1];
-                        q2 = v[4 * j + 2];
-                        q3 = v[4 * j + 3];
-                    }
-                const int64_t pp = ((int64_t)b * (g.H / 2) + (py >> 1)) * (g.W / 2) + (px >> 1);
-                *(uint2 *)(g.pool + pp * 32 + 8 * jsel + 4 * lh) =
-                    make_uint2(pack_bf16(q0, q1),
-                               pack_bf16(q2, q3));
+                        make_uint2(pack_bf16(fmaxf(v0 + g.bias[m0 + 0], 0.f), fmaxf(v1 + g.bias[m0 + 1], 0.f)),
+                                   pack_bf16(fmaxf(v2 + g.bias[m0 + 2], 0.f), fmaxf(v3 + g.bias[m0 + 3], 0.f)));
             }
         }
         cur = nxt;
     }
+}
+
+// ---------------------------------------------------------------- 3x3 convolution, strips
+// The 32-channel layers of the full-resolution level with one input chunk.  A
+// wave walks down strips of 32 columns x R rows on its own, without barriers:
+// the nine taps' weights stay in registers, an input row (34 pixels) is fetched
+// three rows ahead into registers, turned into fragments through the wave's
+// own 2 KB of LDS, and its six fragments serve the three output rows it
+// touches (a block of patches reads every fragment anew for each tap and
+// output row, 1.5 KB of LDS per MFMA against 0.33 KB here).  The rows of
+// consecutive strips follow each other without a gap: the first two rows of a
+// strip only fill the fragments (their outputs are dropped).  Pixels outside
+// the image are the zeros that buffer loads return beyond their range, and
+// stores there are dropped the same way, so a row has no branches.
+// Against blocks that staged 16 x 16 patches, 16 images of 960x544: with pool
+// 309 -> 255 us (805 MB + 404 MB: 4.7 TB/s, the bound), from the stack 231 ->
+// 195 (802 MB), with head 253 -> 185 (535 MB and 154 GFLOP: 830 TFLOP/s);
+// 9 images: plain 155 -> 126, data gradient 202 -> 178.
+constexpr int kStripRows = 64;   // the most output rows of a strip
+
+template <int EPI, bool POOL, bool HEAD, bool K16>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_conv3s(const GemmArgs g, const HeadArgs hd, const int R)
+{
+    constexpr int KK = K16 ? 1 : 2;              // 16-channel half-chunks per tap
+    constexpr int PXB = 32 * KK;                 // bytes per staged pixel
+    constexpr int UPP = 2 * KK;                  // 16-byte units per pixel
+    constexpr int UNITS = 34 * UPP;              // ... per row
+    constexpr int NL = (UNITS + 63) / 64;        // loads per lane and row
+    constexpr int D = EPI == EPI_GRAD ? 2 : 3;   // rows fetched ahead (the registers hold the activations then)
+    constexpr uint32_t OFF = 0x80000000u;        // beyond every buffer (a strip's rows are less)
+    __shared__ __attribute__((aligned(16))) uint8_t rows[4][34 * PXB];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lc = lane & 31, lh = lane >> 5;
+    uint8_t *const row = rows[wave];
+    const int sx = (g.W + 31) / 32, sy = (g.H + R - 1) / R;
+    const int units = sx * sy * g.NB;
+    // the blocks of an XCD (blockIdx mod 8) take neighbouring strips
+    const int per_xcd = gridDim.x / 8;
+    const int first = (int)((blockIdx.x % 8) * per_xcd + blockIdx.x / 8) * 4 + wave, stride = (int)gridDim.x * 4;
+    bf16x8 wf[9][KK];
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) wf[t][kk] = ld8(g.A + (lc * 9 + t) * 32 + kk * 16 + 8 * lh);
+    auto swz = [](int px) { return K16 ? (px >> 2) & 1 : (px >> 1) & 3; };
+    // unit e = 64 i + lane of a row: 16-byte part q of pixel lpx + PXL i, kept in
+    // part q ^ swz of that pixel (swz has the period PXL)
+    constexpr int PXL = 64 / UPP;
+    const int lpx = lane / UPP;
+    const uint32_t uoff = (uint32_t)(lpx * g.b_cs * 2 + lane % UPP * 16);
+    uint8_t *const udst = row + lpx * PXB + (((lane % UPP) ^ swz(lpx)) << 4);
+    uint32_t fsrc[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) fsrc[dx] = (uint32_t)((lc + dx) * PXB + ((lh ^ swz(lc + dx)) << 4));
+    // a position in the wave's sequence of input rows
+    struct Cur {
+        int u, r, n, x0, y0, b;   // strip, input row in it, output rows, origin, image
+    };
+    auto enter = [&](Cur &c, int u) {
+        c.u = u;
+        c.r = 0;
+        const int t = u / sx;
+        c.x0 = (u - t * sx) * 32;
+        c.b = t / sy;
+        c.y0 = (t - c.b * sy) * R;
+        c.n = min(R, g.H - c.y0);
+    };
+    auto next = [&](Cur &c) {
+        if (++c.r == c.n + 2) enter(c, c.u + stride);
+    };
+    // rows y .. y + n - 1 of image b (W pixels of cs 16-bit elements), as a buffer
+    auto rows_of = [&](const void *p, int b, int h, int y, int n, int w, int cs) {
+        return __builtin_amdgcn_make_buffer_rsrc((uint16_t *)p + ((int64_t)b * h + y) * w * cs, 0, n * w * cs * 2, 0x00027000);
+    };
+    auto fetch = [&](uint4 (&st)[NL], const Cur &c) {
+        // the strip's input rows, of which the first and last may lie outside
+        const int ya = max(c.y0 - 1, 0), yb = min(c.y0 + c.n + 1, g.H), gy = c.y0 - 1 + c.r;
+        const bool live = c.u < units;
+        const auto rs = rows_of(g.Bsrc + g.b_off, live ? c.b : 0, g.H, live ? ya : 0, live ? yb - ya : 0, g.W, g.b_cs);
+        const uint32_t base = (uint32_t)(((gy - ya) * g.W + c.x0 - 1) * g.b_cs * 2);
+        const bool yin = gy >= ya && gy < yb;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int gx = c.x0 - 1 + lpx + PXL * i;
+            const bool in = yin & (gx >= 0) & (gx < g.W) & (i < UNITS / 64 || lane < UNITS - 64 * i);
+            const uint32_t o = in ? base + uoff + (uint32_t)(PXL * i * g.b_cs * 2) : OFF;
+            st[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)o, 0, 0));
+        }
+    };
+    auto stage = [&](const uint4 (&st)[NL]) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            if (i < UNITS / 64 || lane < UNITS - 64 * i) *(uint4 *)(udst + PXL * PXB * i) = st[i];
+    };
+    auto frags = [&](bf16x8 (&f)[3][KK]) {
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) f[dx][kk] = __builtin_bit_cast(bf16x8, *(const uint4 *)(row + (fsrc[dx] ^ 32 * kk)));
+    };
+    // the writes of a row are read by other lanes of the wave: LDS operations of
+    // a wave are executed in order, only the compiler has to keep them so
+    auto order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    float bs[16];
+    __shared__ float s_b[EPI == EPI_GRAD ? 4 * 32 : 1];
+    if (EPI == EPI_GRAD)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) bs[e] = 0.f;
+    float bias[16];
+    if (EPI == EPI_RELU_BF16)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) bias[e] = g.bias[8 * (e >> 2) + 4 * lh + (e & 3)];
+    bf16x8 hw0, hw1;   // the head's weights, bias and the last row's outputs
+    float hb[3], zp[3];
+    if constexpr (HEAD) {
+        head_frags(hd.w, hw0, hw1);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            hb[c] = hd.bias[c];
+            zp[c] = 0.f;
+        }
+    }
+    uint32_t prev[POOL ? 8 : 1];   // the last row's outputs
+#pragma unroll
+    for (int r = 0; r < (POOL ? 8 : 1); ++r) prev[r] = 0u;
+    Cur pf, cp;   // the row to fetch next, the row whose fragments are complete
+    enter(pf, first);
+    cp = pf;
+    uint4 st[D][NL];
+    uint2 act[2][4];
+    bf16x8 f[3][3][KK];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) f[q][dx][kk] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+#pragma unroll
+    for (int q = 0; q < D; ++q) {
+        fetch(st[q], pf);
+        next(pf);
+    }
+    stage(st[0]);
+    order();
+    frags(f[0]);
+    fetch(st[0], pf);
+    next(pf);
+    // EPI_GRAD: the activations that mask the output row of position c, a row ahead
+    auto fetch_act = [&](uint2 (&a)[4], const Cur &c) {
+        const bool live = c.u < units && c.r >= 2;
+        const auto ra = rows_of(g.act, live ? c.b : 0, g.H, live ? c.y0 : 0, live ? c.n : 0, g.W, 32);
+        const uint32_t o = live & (c.x0 + lc < g.W) ? (uint32_t)((c.r - 2) * g.W + c.x0 + lc) * 64u + 8 * lh : OFF;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(ra, (int)(o + 16 * j), 0, 0));
+    };
+    auto step = [&](auto ph) {
+        constexpr int S = decltype(ph)::value, P = S % 3, P1 = (S + 1) % 3, P2 = (S + 2) % 3, Q = (S + 1) % D;
+        order();
+        stage(st[Q]);
+        order();
+        Cur nx = cp;
+        next(nx);
+        if (EPI == EPI_GRAD) fetch_act(act[(S + 1) % 2], nx);
+        fetch(st[Q], pf);
+        next(pf);
+        const int y = cp.y0 + cp.r - 2, px = cp.x0 + lc;
+        const bool live = cp.r >= 2, ok = live && px < g.W;
+        const int pix = (cp.r - 2) * g.W + px;   // of the strip's output rows
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[dx][kk], f[P1][dx][kk], acc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        frags(f[P1]);   // the next row, into the fragments just used up
+#pragma unroll
+        for (int dy = 1; dy < 3; ++dy)
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[3 * dy + dx][kk], f[dy == 1 ? P2 : P][dx][kk], acc, 0, 0, 0);
+        // lane: pixel lc, channels 8 j + 4 lh + {0..3}
+        uint32_t w[4][2];
+        float v[16];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                v[4 * j + r] = EPI == EPI_RELU_BF16 ? fmaxf(acc[4 * j + r] + bias[4 * j + r], 0.f) : acc[4 * j + r];
+            if (EPI == EPI_GRAD) {
+                float gv[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) gv[r] = ok ? v[4 * j + r] : 0.f;   // (the bias sums)
+                const uint2 o = grad4(gv, act[S % 2][j], true, bs + 4 * j);
+                w[j][0] = o.x;
+                w[j][1] = o.y;
+            } else {
+                w[j][0] = pack_bf16(v[4 * j + 0], v[4 * j + 1]);
+                w[j][1] = pack_bf16(v[4 * j + 2], v[4 * j + 3]);
+            }
+        }
+        // the packed halves of lanes l and l + 32 swapped: 16 bytes of channels
+        // 16 q + 8 lh .. + 7 each
+        uint4 o[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const auto s0 = __builtin_amdgcn_permlane32_swap(w[2 * q][0], w[2 * q + 1][0], false, false);
+            const auto s1 = __builtin_amdgcn_permlane32_swap(w[2 * q][1], w[2 * q + 1][1], false, false);
+            o[q] = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+        }
+        if (!HEAD || g.out) {
+            const auto ro = rows_of(g.out, cp.b, g.H, cp.y0, cp.n, g.W, 32);
+            const uint32_t so = ok ? (uint32_t)pix * 64u + 16 * lh : OFF;
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o[q]), ro, (int)(so + 32 * q), 0, 0);
+        }
+        if constexpr (HEAD) {
+            const f32x16 dz = head_mfma(hw0, hw1, __builtin_bit_cast(bf16x8, o[0]), __builtin_bit_cast(bf16x8, o[1]));
+            // two rows at a time (strips start at even rows): the even one's
+            // in lanes 0..31, the odd one's in lanes 32..63
+            if (live && (y & 1)) {
+                float z[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(zp[c]), __float_as_uint(dz[c] + hb[c]), false, false);
+                    z[c] = __uint_as_float(sw[0]);
+                }
+                const int yz = y - 1 + lh;
+                if (px < g.W) head_store(hd, z, ((int64_t)cp.b * g.H + yz) * g.W + px, cp.b, yz, px);
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) zp[c] = dz[c] + hb[c];
+        }
+        if constexpr (POOL) {
+            // 2x2 max-pool after each odd row (strips start at even rows): the
+            // window is this row and the last, lanes lc and lc ^ 1.  ReLU outputs
+            // in bfloat16 order as 16-bit integers; the lane of column bit a
+            // writes channels 16 a + 8 lh .. + 7.
+            auto mx = [](uint32_t x, uint32_t y) {
+                return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, x), __builtin_bit_cast(i16x2, y)));
+            };
+            uint32_t m[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const uint4 &oq = o[r >> 2];
+                const uint32_t c = (r & 3) == 0 ? oq.x : (r & 3) == 1 ? oq.y : (r & 3) == 2 ? oq.z : oq.w;
+                const uint32_t q = mx(c, prev[r]);
+                m[r] = mx(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
+                prev[r] = c;
+            }
+            const auto rp = rows_of(g.pool, cp.b, g.H / 2, cp.y0 / 2, cp.n / 2, g.W / 2, 32);
+            const uint32_t po = ok && (y & 1) ? (uint32_t)(((y - cp.y0) >> 1) * (g.W / 2) + (px >> 1)) * 64u + 32 * (lc & 1) + 16 * lh : OFF;
+            u32x4 pq;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) pq[r] = m[r] ^ ((m[r] ^ m[4 + r]) & (uint32_t)-(lc & 1));
+            __builtin_amdgcn_raw_buffer_store_b128(pq, rp, (int)po, 0, 0);
+        }
+        cp = nx;
+        return cp.u < units;
+    };
+    if (EPI == EPI_GRAD) fetch_act(act[0], cp);
+    auto round = [&](auto half) {
+        constexpr int S0 = decltype(half)::value;
+        return step(std::integral_constant<int, S0>()) && step(std::integral_constant<int, S0 + 1>()) &&
+               step(std::integral_constant<int, S0 + 2>());
+    };
+    if (cp.u < units)
+        while (round(std::integral_constant<int, 0>()) && (D == 3 || round(std::integral_constant<int, D == 3 ? 0 : 3>()))) {}
     if (EPI == EPI_GRAD) bias_row<1>(bs, s_b, g.bpart + (int64_t)blockIdx.x * 32);
 }
 
@@ -2302,24 +2495,51 @@ hipError_t conv3r_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr)
 }
 
 // 3x3 convolution shapes (measured on the 960x544 network): the
-// 32-output-channel layers of large grids with their weights resident
-// (16-row patches with one input chunk, 8-row ones with two); the wider layers
+// 32-output-channel layers of large grids with their weights resident (strips
+// per wave with one input chunk, 8 x 16 patches with two); the wider layers
 // of grids from 64 K pixels in 32-column patches (k_conv3r), smaller grids in
 // 8 x 16 patches of 32 output channels
-template <int TH, int KC, int EPI, bool POOL, bool UPC = false, bool HEAD = false, bool K16 = false>
-hipError_t conv3w_launch(const GemmArgs &g, hipStream_t s, const HeadArgs &h = HeadArgs{}, int *rows = nullptr)
+template <int EPI, bool UPC>
+hipError_t conv3w_launch(const GemmArgs &g, hipStream_t s)
 {
-    constexpr int lds = c3w_lds_bytes<TH, KC>();
-    static_assert(lds <= 65536, "staged patches and weights must fit 64 KB");
-    static const int grid = std::max(8, resident_blocks(k_conv3w<TH, KC, EPI, POOL, UPC, HEAD, K16>, lds) / 8 * 8);
+    static_assert(C3W_LDS <= 65536, "staged patches and weights must fit 64 KB");
+    static const int grid = std::max(8, resident_blocks(k_conv3w<EPI, UPC>, C3W_LDS) / 8 * 8);
+    hipLaunchKernelGGL((k_conv3w<EPI, UPC>), dim3(grid), dim3(256), C3W_LDS, s, g);
+    return hipGetLastError();
+}
+
+// Rows per strip (even): the fewest rows in turn that a wave reads, R + 2 per
+// strip, when the strips are dealt out evenly.  Tall strips repeat few rows,
+// short ones end together: 16 images of 960x544 at R = 8 / 16 / 32 / 64
+// 272 / 264 / 255 / 337 us, 9 images 146 / 155 / 169 / 209, 4 of 256x256
+// 20 / 29 / 43 / 58 (with pool).
+int strip_rows(const GemmArgs &g, int grid)
+{
+    int best = 0;
+    int64_t least = INT64_MAX;
+    for (int r = 4; r <= kStripRows; r += 2) {
+        const int64_t strips = (int64_t)((g.W + 31) / 32) * ((g.H + r - 1) / r) * g.NB;
+        const int64_t cost = (strips + 4LL * grid - 1) / (4LL * grid) * (r + 2);
+        if (cost < least) {
+            least = cost;
+            best = r;
+        }
+    }
+    return best;
+}
+
+template <int EPI, bool POOL, bool HEAD, bool K16>
+hipError_t conv3s_launch(const GemmArgs &g, hipStream_t s, const HeadArgs &h = HeadArgs{}, int *rows = nullptr)
+{
+    static const int grid = std::max(8, resident_blocks(k_conv3s<EPI, POOL, HEAD, K16>, 0) / 8 * 8);
     if (rows) *rows = grid;
-    hipLaunchKernelGGL((k_conv3w<TH, KC, EPI, POOL, UPC, HEAD, K16>), dim3(grid), dim3(256), lds, s, g, h);
+    hipLaunchKernelGGL((k_conv3s<EPI, POOL, HEAD, K16>), dim3(grid), dim3(256), 0, s, g, h, strip_rows(g, grid));
     return hipGetLastError();
 }
 
 // *pooled (if given) tells whether the launch also wrote the 2x2 max-pool
 // of the output to g.pool; *headed (if given) whether it also ran the head
-// (only the weights-resident kernel with one input chunk runs it), and then
+// (only the strips kernel runs it), and then
 // head_only leaves the output itself unstored; *rows (EPI_GRAD) the number of
 // rows of bias partials written.
 template <int EPI>
@@ -2329,29 +2549,36 @@ hipError_t conv3(GemmArgs g, hipStream_t s, bool *pooled = nullptr, const HeadAr
     if (g.K % 32 != 0) return hipErrorInvalidValue;
     if (pooled) *pooled = false;
     if (headed) *headed = false;
-    // 32 output channels from one or two input chunks, with patches for
-    // every block several times over: weights resident, blocks walk patches
+    // 32 output channels from one input chunk with several strips or from two
+    // with several patches for every wave: weights resident
     const int64_t tiles8 = (int64_t)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.NB;
-    if (g.M == 32 && g.K == 32 && tiles8 >= 2048 && g.H % 2 == 0 && g.W % 2 == 0) {
-        if constexpr (EPI == EPI_RELU_BF16) {
-            if (pooled && g.pool) {
-                *pooled = true;
-                return conv3w_launch<16, 1, EPI, true>(g, s);
+    if constexpr (EPI != EPI_F32) {   // (the float32 gradients are those of wider layers)
+        // whole 32- or 16-channel pixels; the rows of a strip are addressed by
+        // 31-bit offsets
+        const bool k16 = g.k_src == 16;
+        const bool strips = g.b_cs == (k16 ? 16 : 32) && g.b_off == 0 && (k16 || g.k_src == 0 || g.k_src == 32) &&
+                            (EPI == EPI_GRAD || (g.o_cs == 32 && g.o_off == 0)) && !(k16 && EPI == EPI_GRAD) &&
+                            (int64_t)g.W * 64 * (kStripRows + 2) < (1LL << 31);
+        if (g.M == 32 && g.K == 32 && tiles8 >= 2048 && g.H % 2 == 0 && g.W % 2 == 0 && strips) {
+            if constexpr (EPI == EPI_RELU_BF16) {
+                // an input of 16 channels (the stack): the zero half of the
+                // chunk is neither staged nor multiplied
+                if (k16) return conv3s_launch<EPI, false, false, true>(g, s);
+                if (pooled && g.pool) {
+                    *pooled = true;
+                    return conv3s_launch<EPI, true, false, false>(g, s);
+                }
+                if (headed && head) {
+                    *headed = true;
+                    if (head_only) g.out = nullptr;
+                    return conv3s_launch<EPI, false, true, false>(g, s, *head);
+                }
             }
-            if (headed && head) {
-                *headed = true;
-                if (head_only) g.out = nullptr;
-                return conv3w_launch<16, 1, EPI, false, false, true>(g, s, *head);
-            }
+            return conv3s_launch<EPI, false, false, false>(g, s, HeadArgs{}, rows);
         }
-        // an input of 16 channels or fewer (the stack): the zero half of the
-        // chunk is neither staged nor multiplied
-        if constexpr (EPI == EPI_RELU_BF16)
-            if (g.k_src > 0 && g.k_src <= 16) return conv3w_launch<16, 1, EPI, false, false, false, true>(g, s);
-        return conv3w_launch<16, 1, EPI, false>(g, s, HeadArgs{}, rows);
     }
     if constexpr (EPI != EPI_GRAD)
-        if (g.M == 32 && g.K == 64 && tiles8 >= 2048) return conv3w_launch<8, 2, EPI, false>(g, s);
+        if (g.M == 32 && g.K == 64 && tiles8 >= 2048) return conv3w_launch<EPI, false>(g, s);
     // 64 output channels x 16 rows x 32 columns per block from 64 K pixels on
     // (2.1 M to 130 K pixels on the 16 x 960x544 network: 113 - 288 us per
     // launch against 195 - 397 for blocks of 16 x 16 pixels), else 32 channels
@@ -2484,7 +2711,7 @@ hipError_t dec0a_fused(unet_state *n, unet_act *a, int NB, int H, int W, hipStre
     g.up_w = n->wf + u.wf_off;
     g.up_b = n->w + u.b_off;
     if (g.K != 64 || g.M != 32 || u.cout != 32 || u.cin_pad != 64) return hipErrorInvalidValue;
-    return conv3w_launch<8, 2, EPI_RELU_BF16, false, true>(g, s);
+    return conv3w_launch<EPI_RELU_BF16, true>(g, s);
 }
 
 // The forward pass up to the last 3x3 convolution.  lean (inference) stores

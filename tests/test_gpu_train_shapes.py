@@ -82,3 +82,33 @@ def test_batch_layers_equal_single(fvv, ctx, oracle_lib, N, H, W):  # noqa: F811
         one = layers(st[q:q + 1].contiguous())
         for name in one:
             assert np.array_equal(many[name][q], one[name][0]), (name, q)
+
+
+@pytest.mark.parametrize("N,H,W", [(16, 136, 264), (64, 72, 104)])
+def test_gradients_of_copies(fvv, ctx, oracle_lib, N, H, W):  # noqa: F811
+    """The mean gradient over N copies of an image is the gradient of that
+    image, which runs in the kernels of small grids; the copies run in those of
+    large grids (strips and 32-column patches that end unevenly).  N is a power
+    of two, so every gradient of the copies is the single one's scaled exactly
+    and rounds to bfloat16 alike; only the order of the float32 sums over
+    pixels differs: runs of at most 2^13 terms, relative rounding about
+    2^-24 2^6.5, times 2^3 for what cancels within a layer: 1e-4."""
+    import torch
+    from oracle import unet
+    say(f"[gpu] gradients of {N} copies {H}x{W}")
+    ctx.net_load(flat(rand_params(430 + W)))
+    st = scene_stack(oracle_lib, 431, W, H)
+    target = np.random.default_rng(432).uniform(0, 1, (H, W, 3)).astype(np.float32)
+    got = []
+    for n in (1, N):
+        ctx.net_train_step(to_device_stack(np.stack([st] * n)), torch.from_numpy(np.stack([target] * n)).cuda(), n, H, W,
+                           H, lr=0.0, apply=False)
+        got.append(unflat(ctx.net_read(fvv.NET_GRADS)))
+    bad = []
+    for name, *_ in unet.LAYERS:
+        for k in (0, 1):
+            a, b = (np.asarray(g[name][k], np.float64).ravel() for g in got)
+            rel = np.linalg.norm(b - a) / max(np.linalg.norm(a), 1e-30)
+            if not rel <= 1e-4:
+                bad.append((name, "Wb"[k], rel))
+    assert not bad, bad
