@@ -316,9 +316,26 @@ __device__ __forceinline__ float pool_max4(float v)
     return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
 }
 
-template <int MT, int TH, int EPI, bool POOL = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_conv3(const GemmArgs g)
+// Four accumulators' quadruples of one pixel (channels 8 j + 4 lh + 0..3) as
+// packed bfloat16 w[j][2] -> the lane's 16 channels' worth of stores: lanes
+// l and l + 32 exchange halves, so each holds 8 consecutive channels,
+// 16 q + 8 lh .. + 7 (q = 0, 1), for one 16-byte store each.
+__device__ __forceinline__ void swap_halves(const uint32_t (&w)[4][2], uint4 (&o)[2])
 {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const auto s0 = __builtin_amdgcn_permlane32_swap(w[2 * q][0], w[2 * q + 1][0], false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(w[2 * q][1], w[2 * q + 1][1], false, false);
+        o[q] = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+    }
+}
+
+// HEAD (32 output channels): the head runs on the output as in k_conv3s.
+template <int MT, int TH, int EPI, bool POOL = false, bool HEAD = false>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_conv3(const GemmArgs g, const HeadArgs hd)
+{
+    static_assert(!HEAD || (MT == 1 && !POOL && EPI == EPI_RELU_BF16), "the head reads 32 channels of one block");
     static_assert(TH % 8 == 0, "each wave takes TH/4 rows, two per 32-pixel tile");
     constexpr int NT = TH / 8;         // 32-pixel tiles per wave (TH/4 rows of 16)
     constexpr int PW = 18;             // staged patch width
@@ -421,6 +438,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
         if (EPI == EPI_GRAD) bias_out();
         return;
     }
+    bf16x8 hw0, hw1;   // the head's weights and bias
+    float hb[3];
+    if constexpr (HEAD) {
+        head_frags(hd.w, hw0, hw1);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) hb[c] = hd.bias[c];
+    }
     int32_t poff[NPF];
     {
         const Item it = decode(cur);
@@ -489,8 +513,32 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
             const int py = it.y0 + wave * (TH / 4) + 2 * n + (lc >> 4), px = it.x0 + (lc & 15);
-            if (py >= g.H || px >= g.W) continue;
             const int64_t pix = ((int64_t)it.b * g.H + py) * g.W + px;
+            if constexpr (HEAD) {
+                const bool ok = py < g.H && px < g.W;
+                uint32_t w[4][2];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int m0 = 8 * j + 4 * lh;
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        w[j][q] = pack_bf16(fmaxf(acc[0][n][4 * j + 2 * q] + g.bias[m0 + 2 * q], 0.f),
+                                            fmaxf(acc[0][n][4 * j + 2 * q + 1] + g.bias[m0 + 2 * q + 1], 0.f));
+                }
+                uint4 o[2];
+                swap_halves(w, o);
+                if (ok && g.out)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        *(uint4 *)((uint16_t *)g.out + pix * g.o_cs + g.o_off + 16 * q + 8 * lh) = o[q];
+                const f32x16 dz = head_mfma(hw0, hw1, __builtin_bit_cast(bf16x8, o[0]), __builtin_bit_cast(bf16x8, o[1]));
+                if (ok && !lh) {
+                    const float z[3] = {dz[0] + hb[0], dz[1] + hb[1], dz[2] + hb[2]};
+                    head_store(hd, z, pix, it.b, py, px);
+                }
+                continue;
+            }
+            if (py >= g.H || px >= g.W) continue;
 #pragma unroll
             for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -573,20 +621,6 @@ __device__ __forceinline__ int c3r_swz(int r) { return (((r >> 1) ^ (r >> 3)) & 
 
 template <int MT, int RW>
 constexpr int c3r_lds_bytes() { return (4 * RW + 2) * C3R_PW * 64 + 32 * MT * 576; }
-
-// Four accumulators' quadruples of one pixel (channels 8 j + 4 lh + 0..3) as
-// packed bfloat16 w[j][2] -> the lane's 16 channels' worth of stores: lanes
-// l and l + 32 exchange halves, so each holds 8 consecutive channels,
-// 16 q + 8 lh .. + 7 (q = 0, 1), for one 16-byte store each.
-__device__ __forceinline__ void swap_halves(const uint32_t (&w)[4][2], uint4 (&o)[2])
-{
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const auto s0 = __builtin_amdgcn_permlane32_swap(w[2 * q][0], w[2 * q + 1][0], false, false);
-        const auto s1 = __builtin_amdgcn_permlane32_swap(w[2 * q][1], w[2 * q + 1][1], false, false);
-        o[q] = make_uint4(s0[0], s1[0], s0[1], s1[1]);
-    }
-}
 
 template <int MT, int RW, int EPI, bool POOL>
 __global__ void __launch_bounds__(256, 2) k_conv3r(const GemmArgs g)
@@ -1258,15 +1292,8 @@ k_conv3s(const GemmArgs g, const HeadArgs hd, const int R)
                 w[j][1] = pack_bf16(v[4 * j + 2], v[4 * j + 3]);
             }
         }
-        // the packed halves of lanes l and l + 32 swapped: 16 bytes of channels
-        // 16 q + 8 lh .. + 7 each
         uint4 o[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const auto s0 = __builtin_amdgcn_permlane32_swap(w[2 * q][0], w[2 * q + 1][0], false, false);
-            const auto s1 = __builtin_amdgcn_permlane32_swap(w[2 * q][1], w[2 * q + 1][1], false, false);
-            o[q] = make_uint4(s0[0], s1[0], s0[1], s1[1]);
-        }
+        swap_halves(w, o);
         if (!HEAD || g.out) {
             const auto ro = rows_of(g.out, cp.b, g.H, cp.y0, cp.n, g.W, 32);
             const uint32_t so = ok ? (uint32_t)pix * 64u + 16 * lh : OFF;
@@ -1855,29 +1882,6 @@ __global__ void __launch_bounds__(256) k_wgrad_reduce(const float *__restrict__ 
     if (ci < cin) gw[mt * cin + ci] = s;
 }
 
-// ---------------------------------------------------------------- elementwise layers
-// 2x2 max-pool, bf16 NHWC; thread per (output pixel, 8 channels).
-__global__ void __launch_bounds__(256) k_pool(const uint16_t *in, int i_cs, int i_off, uint16_t *out, int NB, int H,
-                                              int W, int C)
-{
-    const int groups = C / 8;
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int Ho = H / 2, Wo = W / 2;
-    if (e >= (int64_t)NB * Ho * Wo * groups) return;
-    const int gi = (int)(e % groups);
-    const int64_t op = e / groups;
-    const int b = (int)(op / (Ho * Wo)), r = (int)(op % (Ho * Wo)), y = r / Wo, x = r - y * Wo;
-    uint16_t best[8];
-    for (int d = 0; d < 4; ++d) {
-        const int64_t ip = ((int64_t)b * H + 2 * y + (d >> 1)) * W + 2 * x + (d & 1);
-        const uint4 v = *(const uint4 *)(in + ip * i_cs + i_off + gi * 8);
-        const uint16_t *h = (const uint16_t *)&v;
-        for (int j = 0; j < 8; ++j)
-            if (d == 0 || bf2f(h[j]) > bf2f(best[j])) best[j] = h[j];
-    }
-    *(uint4 *)(out + op * C + gi * 8) = *(const uint4 *)best;
-}
-
 // Max-pool gradient, the skip connection's gradient, the ReLU mask and the
 // bfloat16 rounding in one pass: fine pixel p's gradient is (p is the first
 // maximum of its window ? g_coarse : 0) + skip[p], masked by its activation (the
@@ -1954,7 +1958,7 @@ __global__ void __launch_bounds__(256) k_pool_grad(const uint16_t *act, const fl
 }
 
 // Head of a training step: z = 1x1 convolution of dec0b's output a (32 -> 3) on
-// the matrix cores as in k_head, sigmoid, loss, d loss / d z; the gradient at
+// the matrix cores (head_mfma), sigmoid, loss, d loss / d z; the gradient at
 // dec0b's output masked by its ReLU and rounded (EPI_GRAD's form), and per block
 // the partial sums of the head's weight (96) and bias (3) gradients, the loss
 // and dec0b's bias gradient (32).  A lane takes a pixel per step and carries the
@@ -2091,38 +2095,6 @@ __global__ void __launch_bounds__(256) k_head_reduce(const float *part, int rows
         loss[0] = red[0];
     else
         gb0[col - 100] = red[0];
-}
-
-// Head of a forward pass: 1x1 conv 32->3 + bias, sigmoid (s and/or RGB8 of
-// finite pixels).
-__global__ void __launch_bounds__(256) k_head(const HeadArgs h)
-{
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int P = h.NB * h.H * h.W;
-    // z on the matrix cores: the wave's 64 pixels as two 32-pixel columns
-    // (head_mfma), pixel 32 t + lc of the wave in lane lc of column t; the
-    // second column's results move to lanes 32..63 (v_permlane32_swap)
-    const int lane = threadIdx.x & 63, lc = lane & 31, lh = lane >> 5;
-    const int64_t wbase = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63);
-    f32x16 d[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const int64_t q = wbase + 32 * t + lc;
-        const bf16x8 zero8 = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
-        const bf16x8 b0 = q < P ? ld8(h.a + q * 32 + 8 * lh) : zero8;
-        const bf16x8 b1 = q < P ? ld8(h.a + q * 32 + 16 + 8 * lh) : zero8;
-        d[t] = head_mfma(h.w, b0, b1);
-    }
-    float z[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[1][c]), __float_as_uint(d[1][c]), false,
-                                                         false);
-        z[c] = (lh ? __uint_as_float(sw[0]) : d[0][c]) + h.bias[c];
-    }
-    if (p >= P) return;
-    const int b = (int)(p / (h.H * h.W)), r = (int)(p % (h.H * h.W)), y = r / h.W, x = r - y * h.W;
-    head_store(h, z, p, b, y, x);
 }
 
 // Adam on the fp32 master parameters of one layer, and the bf16 copies in
@@ -2468,16 +2440,16 @@ int resident_blocks(F kernel, size_t lds)
     return std::max(1, per) * std::max(1, cus);
 }
 
-template <int MT, int TH, int EPI, bool POOL = false>
-hipError_t conv3_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr)
+template <int MT, int TH, int EPI, bool POOL = false, bool HEAD = false>
+hipError_t conv3_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr, const HeadArgs &h = HeadArgs{})
 {
     constexpr int lds = c3_lds_bytes<MT, TH>();
     static_assert(lds <= 65536, "staged patch and weights must fit 64 KB");
     const int64_t items = (int64_t)((g.W + 15) / 16) * ((g.H + TH - 1) / TH) * g.NB * ((g.M + 32 * MT - 1) / (32 * MT));
-    static const int rb = std::max(8, resident_blocks(k_conv3<MT, TH, EPI, POOL>, lds) / 8 * 8);
+    static const int rb = std::max(8, resident_blocks(k_conv3<MT, TH, EPI, POOL, HEAD>, lds) / 8 * 8);
     const int grid = (int)std::min<int64_t>(rb, (items + 7) / 8 * 8);
     if (rows) *rows = grid / ((g.M + 32 * MT - 1) / (32 * MT));
-    hipLaunchKernelGGL((k_conv3<MT, TH, EPI, POOL>), dim3(grid), dim3(256), lds, s, g);
+    hipLaunchKernelGGL((k_conv3<MT, TH, EPI, POOL, HEAD>), dim3(grid), dim3(256), lds, s, g, h);
     return hipGetLastError();
 }
 
@@ -2537,18 +2509,15 @@ hipError_t conv3s_launch(const GemmArgs &g, hipStream_t s, const HeadArgs &h = H
     return hipGetLastError();
 }
 
-// *pooled (if given) tells whether the launch also wrote the 2x2 max-pool
-// of the output to g.pool; *headed (if given) whether it also ran the head
-// (only the strips kernel runs it), and then
-// head_only leaves the output itself unstored; *rows (EPI_GRAD) the number of
-// rows of bias partials written.
+// With g.pool (even H and W) the launch also writes the 2x2 max-pool of the
+// output there; with head (32 output channels from 32) it also runs the head on
+// the output, which is stored unless g.out is null; *rows (EPI_GRAD) the number
+// of rows of bias partials written.
 template <int EPI>
-hipError_t conv3(GemmArgs g, hipStream_t s, bool *pooled = nullptr, const HeadArgs *head = nullptr,
-                 bool *headed = nullptr, bool head_only = false, int *rows = nullptr)
+hipError_t conv3(const GemmArgs &g, hipStream_t s, const HeadArgs *head = nullptr, int *rows = nullptr)
 {
-    if (g.K % 32 != 0) return hipErrorInvalidValue;
-    if (pooled) *pooled = false;
-    if (headed) *headed = false;
+    if (g.K % 32 != 0 || (g.pool && (g.H % 2 != 0 || g.W % 2 != 0)) || (head && (g.M != 32 || g.K != 32)))
+        return hipErrorInvalidValue;
     // 32 output channels from one input chunk with several strips or from two
     // with several patches for every wave: weights resident
     const int64_t tiles8 = (int64_t)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.NB;
@@ -2559,20 +2528,13 @@ hipError_t conv3(GemmArgs g, hipStream_t s, bool *pooled = nullptr, const HeadAr
         const bool strips = g.b_cs == (k16 ? 16 : 32) && g.b_off == 0 && (k16 || g.k_src == 0 || g.k_src == 32) &&
                             (EPI == EPI_GRAD || (g.o_cs == 32 && g.o_off == 0)) && !(k16 && EPI == EPI_GRAD) &&
                             (int64_t)g.W * 64 * (kStripRows + 2) < (1LL << 31);
-        if (g.M == 32 && g.K == 32 && tiles8 >= 2048 && g.H % 2 == 0 && g.W % 2 == 0 && strips) {
+        if (g.M == 32 && g.K == 32 && tiles8 >= 2048 && g.H % 2 == 0 && g.W % 2 == 0 && strips && !(k16 && (g.pool || head))) {
             if constexpr (EPI == EPI_RELU_BF16) {
                 // an input of 16 channels (the stack): the zero half of the
                 // chunk is neither staged nor multiplied
                 if (k16) return conv3s_launch<EPI, false, false, true>(g, s);
-                if (pooled && g.pool) {
-                    *pooled = true;
-                    return conv3s_launch<EPI, true, false, false>(g, s);
-                }
-                if (headed && head) {
-                    *headed = true;
-                    if (head_only) g.out = nullptr;
-                    return conv3s_launch<EPI, false, true, false>(g, s, *head);
-                }
+                if (g.pool) return conv3s_launch<EPI, true, false, false>(g, s);
+                if (head) return conv3s_launch<EPI, false, true, false>(g, s, *head);
             }
             return conv3s_launch<EPI, false, false, false>(g, s, HeadArgs{}, rows);
         }
@@ -2585,22 +2547,19 @@ hipError_t conv3(GemmArgs g, hipStream_t s, bool *pooled = nullptr, const HeadAr
     // x 8 rows x 16 columns (more blocks where there are few pixels)
     const bool big = g.M % 64 == 0 && (int64_t)g.NB * g.H * g.W >= 65536;
     if constexpr (EPI == EPI_RELU_BF16) {
-        if (pooled && g.pool && g.H % 2 == 0 && g.W % 2 == 0) {
-            *pooled = true;
-            return big ? conv3r_launch<2, 4, EPI, true>(g, s) : conv3_launch<1, 8, EPI, true>(g, s);
-        }
+        if (g.pool) return big ? conv3r_launch<2, 4, EPI, true>(g, s) : conv3_launch<1, 8, EPI, true>(g, s);
+        if (head) return conv3_launch<1, 8, EPI, false, true>(g, s, nullptr, *head);
     }
     return big ? conv3r_launch<2, 4, EPI>(g, s, rows) : conv3_launch<1, 8, EPI>(g, s, rows);
 }
 
-// 3x3 conv + bias + ReLU into (out, o_cs, o_off); with pool_out, *pooled
-// tells whether the 2x2 max-pool of the output was written there as well,
-// with head, *headed whether the head ran on the output as well (and
-// head_only then leaves out unwritten).  split: the input is a concatenation
-// of two planes of that many channels each (i_cs = split)
+// 3x3 conv + bias + ReLU into (out, o_cs, o_off); with pool_out, also the 2x2
+// max-pool of the output there; with head, also the head on the output (out
+// may then be null).  split: the input is a concatenation of two planes of that
+// many channels each (i_cs = split)
 hipError_t conv_fwd(unet_state *n, int li, const uint16_t *in, int i_cs, int i_off, uint16_t *out, int o_cs, int o_off,
-                    int NB, int H, int W, hipStream_t s, uint16_t *pool_out = nullptr, bool *pooled = nullptr,
-                    const HeadArgs *head = nullptr, bool *headed = nullptr, bool head_only = false, int split = 0)
+                    int NB, int H, int W, hipStream_t s, uint16_t *pool_out = nullptr, const HeadArgs *head = nullptr,
+                    int split = 0)
 {
     const unet_layer &l = layers().L[li];
     GemmArgs g{};
@@ -2621,7 +2580,7 @@ hipError_t conv_fwd(unet_state *n, int li, const uint16_t *in, int i_cs, int i_o
     g.b_skip = split ? (uint32_t)((size_t)NB * H * W - 1) * (uint32_t)split : 0u;
     g.M = l.cout;
     g.pool = pool_out;
-    return conv3<EPI_RELU_BF16>(g, s, pooled, head, headed, head_only);
+    return conv3<EPI_RELU_BF16>(g, s, head);
 }
 
 hipError_t convT_fwd(unet_state *n, int li, const uint16_t *in, int i_cs, int NB, int H, int W, uint16_t *out,
@@ -2665,13 +2624,6 @@ hipError_t convT_fwd(unet_state *n, int li, const uint16_t *in, int i_cs, int NB
     return hipGetLastError();
 }
 
-hipError_t pool(const uint16_t *in, int i_cs, int i_off, uint16_t *out, int NB, int H, int W, int C, hipStream_t s)
-{
-    const int64_t n = (int64_t)NB * (H / 2) * (W / 2) * (C / 8);
-    hipLaunchKernelGGL(k_pool, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, in, i_cs, i_off, out, NB, H, W, C);
-    return hipGetLastError();
-}
-
 // A concatenation at resolution level lv (32 << lv channels per half) holds
 // the up half's plane, then the skip half's, each NHWC: a half is written and
 // read in whole cache lines (interleaved per pixel, the 32-channel halves were
@@ -2681,8 +2633,9 @@ uint16_t *skip_plane(uint16_t *cat, int lv, int NB, int H, int W)
     return cat + (((size_t)NB * H * W) >> (2 * lv)) * (size_t)(32 << lv);
 }
 
-// Whether the finest transposed convolution can run inside the next
-// convolution (weights-resident kernel with two input chunks).
+// Whether the full-resolution level has a large grid: the finest transposed
+// convolution can run inside the next convolution (weights-resident kernel with
+// two input chunks).
 bool up0_fusable(int NB, int H, int W)
 {
     return (int64_t)((W + 15) / 16) * ((H + 7) / 8) * NB >= 2048;
@@ -2716,10 +2669,10 @@ hipError_t dec0a_fused(unet_state *n, unet_act *a, int NB, int H, int W, hipStre
 
 // The forward pass up to the last 3x3 convolution.  lean (inference) stores
 // only what a later launch reads: the finest transposed convolution may run
-// inside dec0a, and dec0b's output, when the head runs in its epilogue, is
-// not stored.  With head, *head_done tells whether the head ran there.
+// inside dec0a, and dec0b's output, which the head reads in its epilogue (head
+// given), is not stored by a large grid.
 hipError_t forward_all(unet_state *n, unet_act *a, const uint16_t *stack, int NB, int H, int W, hipStream_t s,
-                       bool lean = false, const HeadArgs *head = nullptr, bool *head_done = nullptr)
+                       bool lean = false, const HeadArgs *head = nullptr)
 {
     a->NB = NB;
     a->H = H;
@@ -2729,34 +2682,28 @@ hipError_t forward_all(unet_state *n, unet_act *a, const uint16_t *stack, int NB
     uint16_t *const sk0 = skip_plane(a->cat0, 0, NB, H, W), *const sk1 = skip_plane(a->cat1, 1, NB, H, W),
                    *const sk2 = skip_plane(a->cat2, 2, NB, H, W);
     NCHK(conv_fwd(n, L_E0A, stack, UNET_IN, 0, a->e0a, 32, 0, NB, H, W, s));
-    bool pooled = false;
-    NCHK(conv_fwd(n, L_E0B, a->e0a, 32, 0, sk0, 32, 0, NB, H, W, s, a->p1, &pooled));
-    if (!pooled) NCHK(pool(sk0, 32, 0, a->p1, NB, H, W, 32, s));
+    NCHK(conv_fwd(n, L_E0B, a->e0a, 32, 0, sk0, 32, 0, NB, H, W, s, a->p1));
     NCHK(conv_fwd(n, L_E1A, a->p1, 32, 0, a->e1a, 64, 0, NB, H1, W1, s));
-    NCHK(conv_fwd(n, L_E1B, a->e1a, 64, 0, sk1, 64, 0, NB, H1, W1, s, a->p2, &pooled));
-    if (!pooled) NCHK(pool(sk1, 64, 0, a->p2, NB, H1, W1, 64, s));
+    NCHK(conv_fwd(n, L_E1B, a->e1a, 64, 0, sk1, 64, 0, NB, H1, W1, s, a->p2));
     NCHK(conv_fwd(n, L_E2A, a->p2, 64, 0, a->e2a, 128, 0, NB, H2, W2, s));
-    NCHK(conv_fwd(n, L_E2B, a->e2a, 128, 0, sk2, 128, 0, NB, H2, W2, s, a->p3, &pooled));
-    if (!pooled) NCHK(pool(sk2, 128, 0, a->p3, NB, H2, W2, 128, s));
+    NCHK(conv_fwd(n, L_E2B, a->e2a, 128, 0, sk2, 128, 0, NB, H2, W2, s, a->p3));
     NCHK(conv_fwd(n, L_MA, a->p3, 128, 0, a->ma, 256, 0, NB, H3, W3, s));
     NCHK(conv_fwd(n, L_MB, a->ma, 256, 0, a->mb, 256, 0, NB, H3, W3, s));
     NCHK(convT_fwd(n, L_UP2, a->mb, 256, NB, H3, W3, a->cat2, 128, s));
-    NCHK(conv_fwd(n, L_D2A, a->cat2, 128, 0, a->d2a, 128, 0, NB, H2, W2, s, nullptr, nullptr, nullptr, nullptr, false, 128));
+    NCHK(conv_fwd(n, L_D2A, a->cat2, 128, 0, a->d2a, 128, 0, NB, H2, W2, s, nullptr, nullptr, 128));
     NCHK(conv_fwd(n, L_D2B, a->d2a, 128, 0, a->d2b, 128, 0, NB, H2, W2, s));
     NCHK(convT_fwd(n, L_UP1, a->d2b, 128, NB, H2, W2, a->cat1, 64, s));
-    NCHK(conv_fwd(n, L_D1A, a->cat1, 64, 0, a->d1a, 64, 0, NB, H1, W1, s, nullptr, nullptr, nullptr, nullptr, false, 64));
+    NCHK(conv_fwd(n, L_D1A, a->cat1, 64, 0, a->d1a, 64, 0, NB, H1, W1, s, nullptr, nullptr, 64));
     NCHK(conv_fwd(n, L_D1B, a->d1a, 64, 0, a->d1b, 64, 0, NB, H1, W1, s));
     a->up0_stored = !(lean && up0_fusable(NB, H, W));
     if (a->up0_stored) {
         NCHK(convT_fwd(n, L_UP0, a->d1b, 64, NB, H1, W1, a->cat0, 32, s));
-        NCHK(conv_fwd(n, L_D0A, a->cat0, 32, 0, a->d0a, 32, 0, NB, H, W, s, nullptr, nullptr, nullptr, nullptr, false, 32));
+        NCHK(conv_fwd(n, L_D0A, a->cat0, 32, 0, a->d0a, 32, 0, NB, H, W, s, nullptr, nullptr, 32));
     } else {
         NCHK(dec0a_fused(n, a, NB, H, W, s));
     }
-    bool headed = false;
-    NCHK(conv_fwd(n, L_D0B, a->d0a, 32, 0, a->d0b, 32, 0, NB, H, W, s, nullptr, nullptr, head, &headed, lean));
-    a->d0b_stored = !(lean && headed);
-    if (head_done) *head_done = headed;
+    a->d0b_stored = !(lean && head && up0_fusable(NB, H, W));   // (a small grid's store costs nothing)
+    NCHK(conv_fwd(n, L_D0B, a->d0a, 32, 0, a->d0b_stored ? a->d0b : nullptr, 32, 0, NB, H, W, s, nullptr, head));
     return hipSuccess;
 }
 
@@ -2855,7 +2802,7 @@ hipError_t conv_dgrad(unet_state *n, unet_act *a, int li, int NB, int H, int W, 
     g.skip = skip;
     g.bpart = a->bpart;
     int rows = 0;
-    NCHK(conv3<EPI_GRAD>(g, s, nullptr, nullptr, nullptr, false, &rows));
+    NCHK(conv3<EPI_GRAD>(g, s, nullptr, &rows));
     bias = BiasPart{a->bpart, rows, l.cin, split ? split : l.cin, nullptr};
     std::swap(a->G, a->G2);
     return (size_t)rows * l.cin <= kBiasPart ? hipSuccess : hipErrorInvalidValue;
@@ -3016,12 +2963,7 @@ hipError_t unet_forward(unet_state *n, unet_act *a, const uint16_t *stack, int N
     h.W = W;
     h.valid_h = valid_h;
     h.valid_w = valid_w;
-    bool done = false;
-    NCHK(forward_all(n, a, stack, NB, H, W, s, !keep, &h, &done));
-    if (done) return hipSuccess;
-    const int P = NB * H * W;
-    hipLaunchKernelGGL(k_head, dim3((P + 255) / 256), dim3(256), 0, s, h);
-    return hipGetLastError();
+    return forward_all(n, a, stack, NB, H, W, s, !keep, &h);
 }
 
 hipError_t unet_forward_batch(unet_state *n, unet_act *a, const uint16_t *stack, int NB, int H, int W,
@@ -3044,12 +2986,7 @@ hipError_t unet_forward_batch(unet_state *n, unet_act *a, const uint16_t *stack,
     h.NB = NB;
     h.H = H;
     h.W = W;
-    bool done = false;
-    NCHK(forward_all(n, a, stack, NB, H, W, s, !keep, &h, &done));
-    if (done) return hipSuccess;
-    const int P = NB * H * W;
-    hipLaunchKernelGGL(k_head, dim3((P + 255) / 256), dim3(256), 0, s, h);
-    return hipGetLastError();
+    return forward_all(n, a, stack, NB, H, W, s, !keep, &h);
 }
 
 hipError_t unet_train(unet_state *n, unet_act *a, const uint16_t *stack, const float *target, int NB, int H,
