@@ -80,10 +80,10 @@ struct GemmArgs {
     float *skip;
     float *bpart;            // [rows][M] bias partials
     uint16_t *pool;          // EPI_RELU_BF16: also the 2x2 max-pooled output [NB][H/2][W/2][M] (or null)
-    // k_conv3w<.., UPC>: input chunk 0 is the 2x2 transposed
+    // k_conv3t<true>: input chunk 0 is the 2x2 transposed
     // convolution (32 output channels, 64 input channels) of up_in
     // [NB][H/2][W/2][64] with weights up_w [4 x 32][64] and bias up_b,
-    // computed per patch instead of read from Bsrc
+    // computed row by row instead of read from Bsrc
     const uint16_t *up_in;
     const uint16_t *up_w;
     const float *up_b;
@@ -886,8 +886,8 @@ __global__ void __launch_bounds__(256, 2) k_conv3r(const GemmArgs g)
 }
 
 // ---------------------------------------------------------------- 3x3 convolution, weights resident
-// The 32-output-channel layers with two input chunks (the full-resolution
-// level): the same implicit GEMM as k_conv3<1, 8>, but a block stages the whole
+// The float32 gradient at the first pool (32 channels from 64, the half-
+// resolution level): the same implicit GEMM as k_conv3<1, 8>, but a block stages the whole
 // weight slice (two chunks x 32 rows x 9 taps x 32 channels) in LDS once and
 // then walks over patches (8 x 16 pixels), so the weights are not fetched again
 // for every patch; the next patch (both chunks) is fetched into registers while
@@ -901,7 +901,6 @@ __global__ void __launch_bounds__(256, 2) k_conv3r(const GemmArgs g)
 constexpr int C3W_PXS = 2 * 64 + 16;
 constexpr int C3W_LDS = 10 * 18 * C3W_PXS + 2 * 32 * C3_RS;
 
-template <int EPI, bool UPC = false>
 __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g)
 {
     constexpr int TH = 8, KC = 2;
@@ -924,79 +923,6 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g)
     // patch index of this block in step k (the grid is a multiple of 8)
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8, per_xcd = gridDim.x / 8;
     auto tile_of = [&](int k) { return k * gridDim.x + xcd * per_xcd + slot; };
-    // Transposed convolution feeding chunk 0 (UPC): the patch's fine rows
-    // y0 - 1 .. y0 + 8 and columns x0 - 1 .. x0 + 16 come from the coarse
-    // rows y0/2 - 1 .. y0/2 + 4 and columns x0/2 - 1 .. x0/2 + 8, 60 coarse
-    // pixels in two 32-column tiles.  Wave w computes tap w (rows 32 w ..
-    // 32 w + 31 of the weights, kept in registers) for all of them, in the
-    // k-step order of the LDS-staged GEMM, so every value is the bytes that
-    // GEMM would have stored; a fine pixel outside the image is 0 (the
-    // convolution's zero padding).
-    bf16x8 up_a[4], up_b[2][4];
-    float up_bias[16];
-    if constexpr (UPC) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) up_a[k] = ld8(g.up_w + (int64_t)(wave * 32 + lc) * 64 + 16 * k + 8 * lh);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) up_bias[4 * j + r] = g.up_b[8 * j + 4 * lh + r];
-    }
-    auto fetch_up = [&](int tl) {
-        int t = tl;
-        const int txi = t % tiles_x;
-        t /= tiles_x;
-        const int tyi = t % tiles_y;
-        const int b = t / tiles_y;
-        const int Hc = g.H / 2, Wc = g.W / 2;
-#pragma unroll
-        for (int n = 0; n < 2; ++n) {
-            const int sl = 32 * n + lc, cr = sl / 10, cc = sl - cr * 10;
-            const int cy = tyi * 4 - 1 + cr, cx = txi * 8 - 1 + cc;
-            const bool in = sl < 60 && cy >= 0 && cy < Hc && cx >= 0 && cx < Wc;
-            const uint16_t *row = g.up_in + ((int64_t)(b * Hc + (in ? cy : 0)) * Wc + (in ? cx : 0)) * 64 + 8 * lh;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                up_b[n][k] = in ? ld8(row + 16 * k) : __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
-        }
-    };
-    // the MFMAs run after the previous patch's (their inputs have landed by
-    // then); their results wait in registers until the patch is staged
-    f32x16 up_u[2];
-    auto up_mfma = [&]() {
-#pragma unroll
-        for (int n = 0; n < 2; ++n) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) up_u[n][r] = 0.f;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) up_u[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(up_a[k], up_b[n][k], up_u[n], 0, 0, 0);
-        }
-    };
-    auto up_store = [&](int tl) {
-        int t = tl;
-        const int txi = t % tiles_x;
-        t /= tiles_x;
-        const int tyi = t % tiles_y;
-        const int dy = wave >> 1, dx = wave & 1;
-#pragma unroll
-        for (int n = 0; n < 2; ++n) {
-            const int sl = 32 * n + lc, cr = sl / 10, cc = sl - cr * 10;
-            const int pr = 2 * cr + dy - 1, pc = 2 * cc + dx - 1;       // patch row / column of this fine pixel
-            const int fy = tyi * TH - 1 + pr, fx = txi * 16 - 1 + pc;
-            if (sl < 60 && pr >= 0 && pr < PH && pc >= 0 && pc < PW) {
-                const bool in = fy >= 0 && fy < g.H && fx >= 0 && fx < g.W;
-                uint8_t *dst = patch + (pr * PW + pc) * PXS + 8 * lh;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    uint2 w2 = make_uint2(0, 0);
-                    if (in)
-                        w2 = make_uint2(pack_bf16(up_u[n][4 * j + 0] + up_bias[4 * j + 0], up_u[n][4 * j + 1] + up_bias[4 * j + 1]),
-                                        pack_bf16(up_u[n][4 * j + 2] + up_bias[4 * j + 2], up_u[n][4 * j + 3] + up_bias[4 * j + 3]));
-                    *(uint2 *)(dst + 16 * j) = w2;
-                }
-            }
-        }
-    };
     constexpr int NPF = (PH * PW * 4 + 255) / 256;
     uint4 fp[KC][NPF];
     auto fetch = [&](int tl) {
@@ -1013,12 +939,11 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g)
             const bool in = e < PH * PW * 4 && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W;
             const int32_t off = ((b * g.H + gy) * g.W + gx) * g.b_cs + g.b_off + (tid & 3) * 8;
 #pragma unroll
-            for (int c = UPC ? 1 : 0; c < KC; ++c) {
+            for (int c = 0; c < KC; ++c) {
                 fp[c][k] = make_uint4(0, 0, 0, 0);
                 if (in && c * 32 + (tid & 3) * 8 < k_src) fp[c][k] = *(const uint4 *)(g.Bsrc + ((uint32_t)(off + c * 32) + (c * 32 >= g.b_split ? g.b_skip : 0u)));
             }
         }
-        if constexpr (UPC) fetch_up(tl);
     };
     auto stash = [&]() {
 #pragma unroll
@@ -1026,18 +951,14 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g)
             const int e = tid + k * 256;
             if (e < PH * PW * 4)
 #pragma unroll
-                for (int c = UPC ? 1 : 0; c < KC; ++c) *(uint4 *)(patch + (e >> 2) * PXS + c * 64 + (e & 3) * 16) = fp[c][k];
+                for (int c = 0; c < KC; ++c) *(uint4 *)(patch + (e >> 2) * PXS + c * 64 + (e & 3) * 16) = fp[c][k];
         }
     };
     int cur = tile_of(0);
-    if (cur < tiles) {
-        fetch(cur);
-        if constexpr (UPC) up_mfma();
-    }
+    if (cur < tiles) fetch(cur);
     for (int k = 0; cur < tiles; ++k) {
         __syncthreads();   // every wave is done with the previous patch (and the weights are staged)
         stash();
-        if constexpr (UPC) up_store(cur);
         __syncthreads();
         const int nxt = tile_of(k + 1);
         if (nxt < tiles) fetch(nxt);
@@ -1058,8 +979,6 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g)
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bfr, acc, 0, 0, 0);
                 }
             }
-        if constexpr (UPC)
-            if (nxt < tiles) up_mfma();
         // epilogue: lane holds, for its pixel, channels 8 j + 4 lh + {0..3}
         int t = cur;
         const int txi = t % tiles_x;
@@ -1072,13 +991,8 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int m0 = 8 * j + 4 * lh;
-                const float v0 = acc[4 * j + 0], v1 = acc[4 * j + 1], v2 = acc[4 * j + 2], v3 = acc[4 * j + 3];
-                if (EPI == EPI_F32)
-                    *(float4 *)((float *)g.out + pix * g.o_cs + g.o_off + m0) = make_float4(v0, v1, v2, v3);
-                else
-                    *(uint2 *)((uint16_t *)g.out + pix * g.o_cs + g.o_off + m0) =
-                        make_uint2(pack_bf16(fmaxf(v0 + g.bias[m0 + 0], 0.f), fmaxf(v1 + g.bias[m0 + 1], 0.f)),
-                                   pack_bf16(fmaxf(v2 + g.bias[m0 + 2], 0.f), fmaxf(v3 + g.bias[m0 + 3], 0.f)));
+                *(float4 *)((float *)g.out + pix * g.o_cs + g.o_off + m0) =
+                    make_float4(acc[4 * j + 0], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
             }
         }
         cur = nxt;
@@ -1354,6 +1268,239 @@ k_conv3s(const GemmArgs g, const HeadArgs hd, const int R)
     if (cp.u < units)
         while (round(std::integral_constant<int, 0>()) && (D == 3 || round(std::integral_constant<int, D == 3 ? 0 : 3>()))) {}
     if (EPI == EPI_GRAD) bias_row<1>(bs, s_b, g.bpart + (int64_t)blockIdx.x * 32);
+}
+
+// ---------------------------------------------------------------- 3x3 convolution, strips, two input chunks
+// dec0a: 32 output channels from two planes of 32, in the strips of k_conv3s.
+// The weights of both chunks (36 KB) sit in LDS, read once per MFMA by each
+// wave; the fragments of the last three rows of both planes stay in registers.
+// UPC: the first plane is the 2x2 transposed convolution (64 -> 32 channels)
+// of a coarse image, computed here instead of stored and read: the coarse
+// row of two input rows, 18 pixels, is one 32-pixel MFMA column per tap, in the
+// k-step order of the LDS-staged GEMM, so every value is the bytes that GEMM
+// would have stored.  Bound by the matrix cores and LDS together (44 MFMAs and
+// 56 KB of fragments per row of 32 pixels, 1,410 and 450 cycles): 16 images of
+// 960x544, 376 GFLOP with the transposed convolution, 604 -> 434 us (867
+// TFLOP/s) against blocks of 8 x 16 pixels between barriers (72 KB of fragments
+// and 1.4 input pixels staged per output pixel); 9 images from two stored
+// planes 285 -> 213.
+constexpr int c3t_rows(bool upc) { return upc ? 3 : 2; }   // LDS rows of a wave: chunk 0 (two if computed), chunk 1
+constexpr int C3T_WTS = 18 * 32 * 64, C3T_UP = 4 * 32 * 128;
+constexpr int c3t_lds_bytes(bool upc) { return C3T_WTS + (upc ? C3T_UP : 0) + 64 * 4 + 4 * c3t_rows(upc) * 34 * 64; }
+
+template <bool UPC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_conv3t(const GemmArgs g, const int R)
+{
+    constexpr uint32_t OFF = 0x80000000u;        // beyond every buffer (a strip's rows are less)
+    constexpr int ROW = 34 * 64;
+    extern __shared__ __attribute__((aligned(16))) uint8_t c3t_smem[];
+    uint8_t *const wts = c3t_smem, *const upw = wts + C3T_WTS;
+    float *const s_bias = (float *)(upw + (UPC ? C3T_UP : 0)), *const s_upb = s_bias + 32;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lc = lane & 31, lh = lane >> 5;
+    uint8_t *const row0 = (uint8_t *)(s_bias + 64) + wave * c3t_rows(UPC) * ROW, *const row1 = row0 + (UPC ? 2 : 1) * ROW;
+    auto swz = [](int px) { return (px >> 1) & 3; };
+    // weights: [chunk][32][9][32] to [chunk][tap][32 rows][4 quarters, swizzled]
+    for (int e = tid; e < 2 * 32 * 36; e += 256) {
+        const int c = e / (32 * 36), r = e / 36 % 32, tap = e % 36 >> 2, q = e & 3;
+        *(uint4 *)(wts + ((c * 9 + tap) * 32 + r) * 64 + ((q ^ swz(r)) << 4)) = *(const uint4 *)(g.A + (int64_t)e * 8);
+    }
+    if (UPC)   // [tap][32][64], 8 quarters a row
+        for (int e = tid; e < 4 * 32 * 8; e += 256)
+            *(uint4 *)(upw + (e >> 3) * 128 + (((e & 7) ^ (e >> 3 & 7)) << 4)) = *(const uint4 *)(g.up_w + (int64_t)e * 8);
+    if (tid < 32) {
+        s_bias[tid] = g.bias[tid];
+        if (UPC) s_upb[tid] = g.up_b[tid];
+    }
+    const int sx = (g.W + 31) / 32, sy = (g.H + R - 1) / R;
+    const int units = sx * sy * g.NB;
+    const int per_xcd = gridDim.x / 8;
+    const int first = (int)((blockIdx.x % 8) * per_xcd + blockIdx.x / 8) * 4 + wave, stride = (int)gridDim.x * 4;
+    // unit e = 64 i + lane of a staged row, as in k_conv3s
+    const int lpx = lane / 4;
+    const uint32_t uoff = (uint32_t)(lpx * 64 + lane % 4 * 16);
+    const int udst = lpx * 64 + (((lane % 4) ^ swz(lpx)) << 4);
+    uint32_t fsrc[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) fsrc[dx] = (uint32_t)((lc + dx) * 64 + ((lh ^ swz(lc + dx)) << 4));
+    const uint32_t asrc = (uint32_t)(lc * 64 + ((lh ^ swz(lc)) << 4));
+    struct Cur {
+        int u, r, n, x0, y0, b;   // strip, input row in it, output rows, origin, image
+    };
+    auto enter = [&](Cur &c, int u) {
+        c.u = u;
+        c.r = 0;
+        const int t = u / sx;
+        c.x0 = (u - t * sx) * 32;
+        c.b = t / sy;
+        c.y0 = (t - c.b * sy) * R;
+        c.n = min(R, g.H - c.y0);
+    };
+    auto next = [&](Cur &c) {
+        if (++c.r == c.n + 2) enter(c, c.u + stride);
+    };
+    auto rows_of = [&](const void *p, int b, int h, int y, int n, int w, int cs) {
+        return __builtin_amdgcn_make_buffer_rsrc((uint16_t *)p + ((int64_t)b * h + y) * w * cs, 0, n * w * cs * 2, 0x00027000);
+    };
+    // input row c.r of plane p into registers
+    auto fetch = [&](uint4 (&st)[3], const uint16_t *p, const Cur &c) __attribute__((always_inline)) {
+        const int ya = max(c.y0 - 1, 0), yb = min(c.y0 + c.n + 1, g.H), gy = c.y0 - 1 + c.r;
+        const bool live = c.u < units;
+        const auto rs = rows_of(p, live ? c.b : 0, g.H, live ? ya : 0, live ? yb - ya : 0, g.W, 32);
+        const uint32_t base = (uint32_t)(((gy - ya) * g.W + c.x0 - 1) * 64);
+        const bool yin = gy >= ya && gy < yb;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int gx = c.x0 - 1 + lpx + 16 * i;
+            const bool in = yin & (gx >= 0) & (gx < g.W) & (i < 2 || lane < 8);
+            st[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(in ? base + uoff + 1024 * i : OFF), 0, 0));
+        }
+    };
+    auto stage = [&](const uint4 (&st)[3], uint8_t *row) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (i < 2 || lane < 8) *(uint4 *)(row + udst + 1024 * i) = st[i];
+    };
+    // UPC: input rows come in pairs of a coarse row, which starts with row 0 of
+    // a strip (its second) and then with the odd ones
+    auto opens = [](const Cur &c) { return c.r == 0 || (c.r & 1); };
+    auto fetch_up = [&](bf16x8 (&b)[4], const Cur &c) __attribute__((always_inline)) {
+        const int Hc = g.H / 2, Wc = g.W / 2, cy = c.y0 / 2 + ((c.r + 1) >> 1) - 1, cx = c.x0 / 2 - 1 + lc;
+        const bool live = c.u < units && opens(c) && cy >= 0 && cy < Hc;
+        const auto rs = rows_of(g.up_in, live ? c.b : 0, Hc, live ? cy : 0, live ? 1 : 0, Wc, 64);
+        const uint32_t o = (lc < 18) & (cx >= 0) & (cx < Wc) ? (uint32_t)(cx * 128 + 16 * lh) : OFF;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) b[k] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(o + 32 * k), 0, 0));
+    };
+    // the two input rows of a coarse row (c.r the first needed one) into row0
+    auto up_rows = [&](const bf16x8 (&b)[4], const Cur &c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int tap = 0; tap < 4; ++tap) {
+            const int dy = tap >> 1, dx = tap & 1;
+            f32x16 u;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) u[r] = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const bf16x8 a = __builtin_bit_cast(bf16x8, *(const uint4 *)(upw + (tap * 32 + lc) * 128 + (((2 * k + lh) ^ (lc & 7)) << 4)));
+                u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[k], u, 0, 0, 0);
+            }
+            const int pc = 2 * lc + dx - 1;   // row pixel of this fine pixel
+            const int fy = 2 * (c.y0 / 2 + ((c.r + 1) >> 1) - 1) + dy, fx = c.x0 - 1 + pc;
+            const bool in = fy >= 0 && fy < g.H && fx >= 0 && fx < g.W;
+            if (pc >= 0 && pc < 34)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float4 ub = *(const float4 *)(s_upb + 8 * j + 4 * lh);
+                    uint2 w2 = make_uint2(pack_bf16(u[4 * j + 0] + ub.x, u[4 * j + 1] + ub.y),
+                                          pack_bf16(u[4 * j + 2] + ub.z, u[4 * j + 3] + ub.w));
+                    if (!in) w2 = make_uint2(0, 0);   // the convolution's zero padding
+                    *(uint2 *)(row0 + dy * ROW + pc * 64 + ((j ^ swz(pc)) << 4) + 8 * lh) = w2;
+                }
+        }
+    };
+    auto order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto frags = [&](bf16x8 (&f)[3][2], const uint8_t *row) __attribute__((always_inline)) {
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) f[dx][kk] = __builtin_bit_cast(bf16x8, *(const uint4 *)(row + (fsrc[dx] ^ 32 * kk)));
+    };
+    const uint16_t *const plane1 = g.Bsrc + 32 + g.b_skip;   // the second plane
+    uint4 st0[3], st1[3];
+    bf16x8 ub[4];
+    auto fetch_row = [&](const Cur &c) __attribute__((always_inline)) {
+        if constexpr (UPC) fetch_up(ub, c);
+        else fetch(st0, g.Bsrc, c);
+        fetch(st1, plane1, c);
+    };
+    // the fetched row c into LDS (UPC: chunk 0's is there already if it is the
+    // second of its pair)
+    auto stage_row = [&](const Cur &c) __attribute__((always_inline)) {
+        if constexpr (UPC) {
+            if (opens(c)) up_rows(ub, c);
+        } else {
+            stage(st0, row0);
+        }
+        stage(st1, row1);
+    };
+    auto row0_of = [&](const Cur &c) { return UPC && !(c.r & 1) ? row0 + ROW : row0; };
+    __syncthreads();   // the weights are staged
+    Cur cp, nx, pf;    // the row whose fragments are complete, the next, the one after
+    enter(cp, first);
+    bf16x8 f0[3][3][2], f1[3][3][2];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) f0[q][dx][kk] = f1[q][dx][kk] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+    fetch_row(cp);
+    nx = cp;
+    next(nx);
+    pf = nx;
+    next(pf);
+    stage_row(cp);
+    fetch_row(nx);
+    order();
+    frags(f0[0], row0_of(cp));
+    frags(f1[0], row1);
+    auto step = [&](auto ph) __attribute__((always_inline)) {
+        constexpr int P = decltype(ph)::value, P1 = (P + 1) % 3, P2 = (P + 2) % 3;
+        order();
+        stage_row(nx);
+        order();
+        fetch_row(pf);
+        const int px = cp.x0 + lc;
+        const bool ok = cp.r >= 2 && px < g.W;
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        // 36 MFMAs, weight fragments read L steps ahead; the next row's fragments
+        // into those that the first taps row has used up
+        constexpr int L = 4;
+        bf16x8 w[36];
+        auto wfrag = [&](int q) __attribute__((always_inline)) { w[q] = __builtin_bit_cast(bf16x8, *(const uint4 *)(wts + (q >> 1) * 2048 + (asrc ^ 32 * (q & 1)))); };
+#pragma unroll
+        for (int q = 0; q < L; ++q) wfrag(q);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 36; ++q) {
+            const int c = q / 18, t = q % 18 >> 1, dy = t / 3, dx = t % 3, kk = q & 1;
+            if (q + L < 36) wfrag(q + L);
+            if (q == 6) frags(f0[P1], row0_of(nx));
+            if (q == 24) frags(f1[P1], row1);
+            const int fr = dy == 0 ? P1 : dy == 1 ? P2 : P;
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[q], c ? f1[fr][dx][kk] : f0[fr][dx][kk], acc, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        uint32_t pk[4][2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float4 bi = *(const float4 *)(s_bias + 8 * j + 4 * lh);
+            pk[j][0] = pack_bf16(fmaxf(acc[4 * j + 0] + bi.x, 0.f), fmaxf(acc[4 * j + 1] + bi.y, 0.f));
+            pk[j][1] = pack_bf16(fmaxf(acc[4 * j + 2] + bi.z, 0.f), fmaxf(acc[4 * j + 3] + bi.w, 0.f));
+        }
+        uint4 o[2];
+        swap_halves(pk, o);
+        const auto ro = rows_of(g.out, cp.b, g.H, cp.y0, cp.n, g.W, 32);
+        const uint32_t so = ok ? (uint32_t)((cp.r - 2) * g.W + px) * 64u + 16 * lh : OFF;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o[q]), ro, (int)(so + 32 * q), 0, 0);
+        cp = nx;
+        nx = pf;
+        next(pf);
+        return cp.u < units;
+    };
+    if (cp.u < units)
+        while (step(std::integral_constant<int, 0>()) && step(std::integral_constant<int, 1>()) &&
+               step(std::integral_constant<int, 2>())) {}
 }
 
 // ---------------------------------------------------------------- 1x1 GEMM, LDS-staged
@@ -2468,17 +2615,19 @@ hipError_t conv3r_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr)
 
 // 3x3 convolution shapes (measured on the 960x544 network): the
 // 32-output-channel layers of large grids with their weights resident (strips
-// per wave with one input chunk, 8 x 16 patches with two); the wider layers
+// per wave); the wider layers
 // of grids from 64 K pixels in 32-column patches (k_conv3r), smaller grids in
 // 8 x 16 patches of 32 output channels
-template <int EPI, bool UPC>
 hipError_t conv3w_launch(const GemmArgs &g, hipStream_t s)
 {
     static_assert(C3W_LDS <= 65536, "staged patches and weights must fit 64 KB");
-    static const int grid = std::max(8, resident_blocks(k_conv3w<EPI, UPC>, C3W_LDS) / 8 * 8);
-    hipLaunchKernelGGL((k_conv3w<EPI, UPC>), dim3(grid), dim3(256), C3W_LDS, s, g);
+    static const int grid = std::max(8, resident_blocks(k_conv3w, C3W_LDS) / 8 * 8);
+    hipLaunchKernelGGL(k_conv3w, dim3(grid), dim3(256), C3W_LDS, s, g);
     return hipGetLastError();
 }
+
+// The rows of a strip are addressed by 31-bit offsets.
+bool strips_fit(int W) { return (int64_t)W * 64 * (kStripRows + 2) < (1LL << 31); }
 
 // Rows per strip (even): the fewest rows in turn that a wave reads, R + 2 per
 // strip, when the strips are dealt out evenly.  Tall strips repeat few rows,
@@ -2509,6 +2658,16 @@ hipError_t conv3s_launch(const GemmArgs &g, hipStream_t s, const HeadArgs &h = H
     return hipGetLastError();
 }
 
+template <bool UPC>
+hipError_t conv3t_launch(const GemmArgs &g, hipStream_t s)
+{
+    constexpr int lds = c3t_lds_bytes(UPC);
+    static_assert(2 * lds <= 160 * 1024, "two blocks share a CU's LDS");
+    static const int grid = std::max(8, resident_blocks(k_conv3t<UPC>, lds) / 8 * 8);
+    hipLaunchKernelGGL((k_conv3t<UPC>), dim3(grid), dim3(256), lds, s, g, strip_rows(g, grid));
+    return hipGetLastError();
+}
+
 // With g.pool (even H and W) the launch also writes the 2x2 max-pool of the
 // output there; with head (32 output channels from 32) it also runs the head on
 // the output, which is stored unless g.out is null; *rows (EPI_GRAD) the number
@@ -2518,16 +2677,14 @@ hipError_t conv3(const GemmArgs &g, hipStream_t s, const HeadArgs *head = nullpt
 {
     if (g.K % 32 != 0 || (g.pool && (g.H % 2 != 0 || g.W % 2 != 0)) || (head && (g.M != 32 || g.K != 32)))
         return hipErrorInvalidValue;
-    // 32 output channels from one input chunk with several strips or from two
-    // with several patches for every wave: weights resident
+    // 32 output channels and strips for every wave: weights resident
     const int64_t tiles8 = (int64_t)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.NB;
     if constexpr (EPI != EPI_F32) {   // (the float32 gradients are those of wider layers)
-        // whole 32- or 16-channel pixels; the rows of a strip are addressed by
-        // 31-bit offsets
+        // whole 32- or 16-channel pixels
         const bool k16 = g.k_src == 16;
         const bool strips = g.b_cs == (k16 ? 16 : 32) && g.b_off == 0 && (k16 || g.k_src == 0 || g.k_src == 32) &&
                             (EPI == EPI_GRAD || (g.o_cs == 32 && g.o_off == 0)) && !(k16 && EPI == EPI_GRAD) &&
-                            (int64_t)g.W * 64 * (kStripRows + 2) < (1LL << 31);
+                            strips_fit(g.W);
         if (g.M == 32 && g.K == 32 && tiles8 >= 2048 && g.H % 2 == 0 && g.W % 2 == 0 && strips && !(k16 && (g.pool || head))) {
             if constexpr (EPI == EPI_RELU_BF16) {
                 // an input of 16 channels (the stack): the zero half of the
@@ -2539,8 +2696,13 @@ hipError_t conv3(const GemmArgs &g, hipStream_t s, const HeadArgs *head = nullpt
             return conv3s_launch<EPI, false, false, false>(g, s, HeadArgs{}, rows);
         }
     }
-    if constexpr (EPI != EPI_GRAD)
-        if (g.M == 32 && g.K == 64 && tiles8 >= 2048) return conv3w_launch<EPI, false>(g, s);
+    // from two chunks: a concatenation's planes, or the gradient at the first pool
+    if constexpr (EPI == EPI_RELU_BF16)
+        if (g.M == 32 && g.K == 64 && tiles8 >= 2048 && g.b_cs == 32 && g.b_off == 0 && g.b_split == 32 && g.o_cs == 32 &&
+            g.o_off == 0 && g.H % 2 == 0 && g.W % 2 == 0 && strips_fit(g.W))
+            return conv3t_launch<false>(g, s);
+    if constexpr (EPI == EPI_F32)
+        if (g.M == 32 && g.K == 64 && tiles8 >= 2048) return conv3w_launch(g, s);
     // 64 output channels x 16 rows x 32 columns per block from 64 K pixels on
     // (2.1 M to 130 K pixels on the 16 x 960x544 network: 113 - 288 us per
     // launch against 195 - 397 for blocks of 16 x 16 pixels), else 32 channels
@@ -2634,11 +2796,10 @@ uint16_t *skip_plane(uint16_t *cat, int lv, int NB, int H, int W)
 }
 
 // Whether the full-resolution level has a large grid: the finest transposed
-// convolution can run inside the next convolution (weights-resident kernel with
-// two input chunks).
+// convolution can run inside the next convolution (k_conv3t).
 bool up0_fusable(int NB, int H, int W)
 {
-    return (int64_t)((W + 15) / 16) * ((H + 7) / 8) * NB >= 2048;
+    return (int64_t)((W + 15) / 16) * ((H + 7) / 8) * NB >= 2048 && strips_fit(W);
 }
 
 // dec0a with its input chunk 0 (the finest transposed convolution of d1b)
@@ -2664,7 +2825,7 @@ hipError_t dec0a_fused(unet_state *n, unet_act *a, int NB, int H, int W, hipStre
     g.up_w = n->wf + u.wf_off;
     g.up_b = n->w + u.b_off;
     if (g.K != 64 || g.M != 32 || u.cout != 32 || u.cin_pad != 64) return hipErrorInvalidValue;
-    return conv3w_launch<EPI_RELU_BF16, true>(g, s);
+    return conv3t_launch<true>(g, s);
 }
 
 // The forward pass up to the last 3x3 convolution.  lean (inference) stores

@@ -112,3 +112,25 @@ def test_gradients_of_copies(fvv, ctx, oracle_lib, N, H, W):  # noqa: F811
             if not rel <= 1e-4:
                 bad.append((name, "Wb"[k], rel))
     assert not bad, bad
+
+
+@pytest.mark.parametrize("N,H,W", [(17, 64, 264), (5, 232, 264), (40, 72, 104), (72, 8, 480)])
+def test_batch_output_equals_single(fvv, ctx, oracle_lib, N, H, W):  # noqa: F811
+    """The same without debug taps: the batch computes the finest transposed
+    convolution inside the next one and stores neither it nor the head's input;
+    its strips end unevenly in rows and columns.  Bytes of the single image."""
+    import torch
+    ctx.net_load(flat(rand_params(520 + W)))
+    st = to_device_stack(np.stack([scene_stack(oracle_lib, 530 + q, W, H) for q in range(2)]))
+    st = st[torch.arange(N, device="cuda") % 2].contiguous()
+    say(f"[gpu] outputs of {N} images {H}x{W}")
+
+    def run(stack):
+        out = torch.full((stack.shape[0], H, W, 3), 7.0, dtype=torch.float32, device="cuda")
+        ctx.net_forward(stack, stack.shape[0], H, W, out)
+        torch.cuda.synchronize()
+        return out.cpu().numpy()
+
+    many, one = run(st), [run(st[q:q + 1].contiguous())[0] for q in range(2)]
+    for q in range(N):
+        assert np.array_equal(many[q], one[q % 2]), q
