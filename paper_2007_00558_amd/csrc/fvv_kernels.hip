@@ -804,9 +804,12 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
     constexpr int NZ = LAYERED ? 2 * WN * WN : WN * WN;
     __shared__ unsigned long long zk[NZ];
     // the tile's filtered keys during the filter, then its slots and colours
-    __shared__ unsigned long long s_buf[T * T];
+    // (the slots' rows padded by a word, the fill's flags by four bytes, so that
+    // the lines of a scan along rows lie in different banks)
+    constexpr int SP = T + 1, IP = T + 4;
+    __shared__ unsigned long long s_buf[T * (T + SP) / 2];
     uint32_t *const s_slot = (uint32_t *)s_buf;
-    uint32_t *const s_rgb = s_slot + T * T;
+    uint32_t *const s_rgb = s_slot + T * SP;
     unsigned long long *const s_kf = s_buf;
     // pixels whose filtered key is a median (the two-window variant filters
     // in place: its LDS budget has no room for the list)
@@ -1094,7 +1097,7 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
     bool any_hole = false;
 #pragma unroll
     for (int q = 0; q < PPT; ++q) {
-        s_slot[ly * T + lx0 + q] = pslot[q];
+        s_slot[ly * SP + lx0 + q] = pslot[q];
         s_rgb[ly * T + lx0 + q] = prgb[q];
         any_hole |= (pslot[q] & FVV_HOLE) && lx0 + q < tw && ly < th;
     }
@@ -1110,31 +1113,22 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
     // none): one scan per row and column, in the z-buffer's LDS, which is
     // dead by now; only tiles with holes
     int8_t *s_in = (int8_t *)zk;
-    static_assert(4 * T * T <= WN * WN * 8, "the scan arrays fit the key window");
+    static_assert(4 * T * IP <= WN * WN * 8, "the scan arrays fit the key window");
     if (fill && s_hole) {
         if (t < 4 * T) {
+            // every pixel of the tile (those beyond the image are holes)
             const int d = t / T, q = t - d * T;
-            int last = -1;
-            if (d == 0 && q < th) {
-                for (int lx = 0; lx < tw; ++lx) {
-                    s_in[q * T + lx] = (int8_t)last;
-                    if (!(s_slot[q * T + lx] & FVV_HOLE)) last = lx;
-                }
-            } else if (d == 1 && q < th) {
-                for (int lx = tw - 1; lx >= 0; --lx) {
-                    s_in[T * T + q * T + lx] = (int8_t)last;
-                    if (!(s_slot[q * T + lx] & FVV_HOLE)) last = lx;
-                }
-            } else if (d == 2 && q < tw) {
-                for (int ly2 = 0; ly2 < th; ++ly2) {
-                    s_in[2 * T * T + ly2 * T + q] = (int8_t)last;
-                    if (!(s_slot[ly2 * T + q] & FVV_HOLE)) last = ly2;
-                }
-            } else if (d == 3 && q < tw) {
-                for (int ly2 = th - 1; ly2 >= 0; --ly2) {
-                    s_in[3 * T * T + ly2 * T + q] = (int8_t)last;
-                    if (!(s_slot[ly2 * T + q] & FVV_HOLE)) last = ly2;
-                }
+            const bool col = d >= 2, back = !(d & 1);
+            int last = -1, l = back ? 0 : T - 1;
+            int e = col ? l * SP + q : q * SP + l, o = d * (T * IP) + (col ? l * IP + q : q * IP + l);
+            const int ls = back ? 1 : -1, es = col ? ls * SP : ls, os = col ? ls * IP : ls;
+#pragma unroll 4
+            for (int k = 0; k < T; ++k) {
+                s_in[o] = (int8_t)last;
+                last = s_slot[e] & FVV_HOLE ? last : l;
+                l += ls;
+                e += es;
+                o += os;
             }
         }
         __syncthreads();
@@ -1152,17 +1146,17 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
             sl = FVV_HOLE;
             if (fill) {
                 Cand b{0.f, 0, -1};
-                const int e = ly * T + lx;
-                const int xl = s_in[e], xr = s_in[T * T + e], yu = s_in[2 * T * T + e], yd = s_in[3 * T * T + e];
+                const int e = ly * IP + lx;
+                const int xl = s_in[e], xr = s_in[T * IP + e], yu = s_in[2 * T * IP + e], yd = s_in[3 * T * IP + e];
                 // open: some direction has no covered pixel inside the tile
                 // and the tile does not end at the image edge there
                 const bool open = (xl < 0 && X0 > 0) || (xr < 0 && X0 + tw < W) || (yu < 0 && Y0 > 0) ||
                                   (yd < 0 && Y0 + th < H);
                 if (!open) {
-                    if (xl >= 0) offer(b, u2f(s_slot[ly * T + xl]), lx - xl, ly * T + xl);
-                    if (xr >= 0) offer(b, u2f(s_slot[ly * T + xr]), xr - lx, ly * T + xr);
-                    if (yu >= 0) offer(b, u2f(s_slot[yu * T + lx]), ly - yu, yu * T + lx);
-                    if (yd >= 0) offer(b, u2f(s_slot[yd * T + lx]), yd - ly, yd * T + lx);
+                    if (xl >= 0) offer(b, u2f(s_slot[ly * SP + xl]), lx - xl, ly * T + xl);
+                    if (xr >= 0) offer(b, u2f(s_slot[ly * SP + xr]), xr - lx, ly * T + xr);
+                    if (yu >= 0) offer(b, u2f(s_slot[yu * SP + lx]), ly - yu, yu * T + lx);
+                    if (yd >= 0) offer(b, u2f(s_slot[yd * SP + lx]), yd - ly, yd * T + lx);
                 }
                 if (open) {
                     sl = FVV_HOLE_OPEN;
@@ -1212,7 +1206,7 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
             last = X0 + tw - 1;
         } else if (t < th)
             for (int c = 0; c < tw; ++c)
-                if (!(s_slot[t * T + c] & FVV_HOLE)) {
+                if (!(s_slot[t * SP + c] & FVV_HOLE)) {
                     if (first < 0) first = X0 + c;
                     last = X0 + c;
                 }
@@ -1225,7 +1219,7 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
             last = Y0 + th - 1;
         } else if (c < tw)
             for (int r = 0; r < th; ++r)
-                if (!(s_slot[r * T + c] & FVV_HOLE)) {
+                if (!(s_slot[r * SP + c] & FVV_HOLE)) {
                     if (first < 0) first = Y0 + r;
                     last = Y0 + r;
                 }
@@ -1243,7 +1237,8 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
 // 1.92 -> 1.61 ms (2,370 -> 2,000 vector and 1,420 -> 1,010 scalar instructions
 // per wave) with the samples camera by camera, their descriptor in scalar
 // registers and interior ones without edge handling, list entries that carry
-// the block's row and column, and a filter that shares its windows' depth words.
+// the block's row and column, and a filter that shares its windows' depth words;
+// -> 1.55 ms with the hole scans' rows in different LDS banks.
 // The plain kernel is held to 64 VGPRs (8 waves per SIMD), so
 // the waves of eight workgroups share each SIMD; the stack variant keeps
 // its registers.
@@ -1324,6 +1319,11 @@ void launch_tile_few(const fvv_batch_dims &b, const fvv_view_desc *d_views, dim3
 // Holes whose nearest covered neighbour in some direction lies outside their
 // tile: scan the tile, then walk the per-tile summaries of the row or column.
 // A fixed grid walks the batch's list of tiles with open holes.
+// Bound by LDS and its latency.  60 views of 1080p 235 -> 168 us, one view of
+// 640x360 13.3 -> 10.5: the scans along rows read addresses a multiple of 32
+// words apart, one bank for all lanes, until their rows were padded (213 ->
+// 168); the slots now arrive in registers while the walks run (235 -> 218), and
+// one loop serves the two directions of a wave (218 -> 213).
 // threads per open tile: one per row and direction of the walks and scans
 // (4 x 32), every thread busy in those serial phases; twice the tiles in
 // flight of a 256-thread block
@@ -1336,13 +1336,16 @@ __global__ void __launch_bounds__(FILL_NT) k_fill_open(const fvv_view_desc *__re
     // row and direction: s_ox[d][q] = the nearest covered image coordinate
     // outside the tile (x for left / right of row q, y for up / down of
     // column q; -1 = none) and s_oz[d][q] its depth bits.
-    __shared__ uint32_t s_slot[T * T];
+    // rows padded by a word (flags by four bytes), so that the lines of a scan
+    // along rows lie in different banks
+    constexpr int SP = T + 1, IP = T + 4;
+    __shared__ uint32_t s_slot[T * SP];
     __shared__ int s_ox[4][T];
     __shared__ uint32_t s_oz[4][T];
     // nearest covered pixel inside the tile in each direction (tile-local
     // column for left / right, row for up / down; -1 = none), one scan per
     // row or column instead of one per hole
-    __shared__ int8_t s_in[4][T * T];
+    __shared__ int8_t s_in[4][T * IP];
     const int n_open = *views[0].open_count;
     for (int item = blockIdx.x; item < n_open; item += gridDim.x) {
         const int2 vt = views[0].open_list[item];
@@ -1352,84 +1355,71 @@ __global__ void __launch_bounds__(FILL_NT) k_fill_open(const fvv_view_desc *__re
         const int W = vd.W;
         const int X0 = tx * T, Y0 = ty * T;
         const int tw = min(T, W - X0), th = min(T, vd.H - Y0);
-        const uint32_t *slot = vd.slot;
+        const auto *const slot = gptr((const uint32_t *)vd.slot);
+        const auto *const rowsum = gptr((const int *)vd.rowsum), *const colsum = gptr((const int *)vd.colsum);
         __syncthreads();   // the previous item's readers are done
-        for (int e = threadIdx.x; e < T * T; e += blockDim.x) {
-            const int ly = e / T, lx = e - ly * T;
-            s_slot[e] = (lx < tw && ly < th) ? slot[(int64_t)(Y0 + ly) * W + X0 + lx] : FVV_HOLE;
+        uint32_t sl[T * T / FILL_NT];   // in flight during the walks
+#pragma unroll
+        for (int k = 0; k < T * T / FILL_NT; ++k) {
+            const int e = threadIdx.x + k * FILL_NT, ly = e / T, lx = e - ly * T;
+            sl[k] = FVV_HOLE;
+            if (lx < tw && ly < th) sl[k] = slot[(uint32_t)((Y0 + ly) * W + X0 + lx)];
         }
-        if (threadIdx.x < 4 * T) {
+        {
+            // a thread's walk: line q, direction d, the nearest tile first (one
+            // loop for the directions of a wave)
             const int d = threadIdx.x / T, q = threadIdx.x - d * T;
+            const bool col = d >= 2, back = !(d & 1);
+            const int at = col ? ty : tx, n = q < (col ? tw : th) ? (back ? at : (col ? vd.nty : vd.ntx) - 1 - at) : 0;
+            const auto *const sum = (col ? colsum : rowsum) + 2 * (tile * T + q) + back;
+            const int step = (back ? -2 : 2) * (col ? vd.ntx : 1) * T;
             int pos = -1;
-            if (d < 2 && q < th) {
-                const int y = Y0 + q;
-                if (d == 0) {
-                    for (int t2 = tx - 1; t2 >= 0 && pos < 0; --t2) pos = vd.rowsum[(int64_t)(ty * vd.ntx + t2) * T + q].y;
-                } else {
-                    for (int t2 = tx + 1; t2 < vd.ntx && pos < 0; ++t2)
-                        pos = vd.rowsum[(int64_t)(ty * vd.ntx + t2) * T + q].x;
-                }
-                s_oz[d][q] = pos >= 0 ? slot[(int64_t)y * W + pos] : 0u;
-            } else if (d >= 2 && q < tw) {
-                const int x = X0 + q;
-                if (d == 2) {
-                    for (int t2 = ty - 1; t2 >= 0 && pos < 0; --t2) pos = vd.colsum[(int64_t)(t2 * vd.ntx + tx) * T + q].y;
-                } else {
-                    for (int t2 = ty + 1; t2 < vd.nty && pos < 0; ++t2)
-                        pos = vd.colsum[(int64_t)(t2 * vd.ntx + tx) * T + q].x;
-                }
-                s_oz[d][q] = pos >= 0 ? slot[(int64_t)pos * W + x] : 0u;
-            }
+            for (int k = 1; k <= n && pos < 0; ++k) pos = sum[k * step];
+            s_oz[d][q] = pos >= 0 ? slot[(uint32_t)(col ? pos * W + X0 + q : (Y0 + q) * W + pos)] : 0u;
             s_ox[d][q] = pos;
         }
+#pragma unroll
+        for (int k = 0; k < T * T / FILL_NT; ++k) s_slot[(threadIdx.x / T + k * (FILL_NT / T)) * SP + threadIdx.x % T] = sl[k];
         __syncthreads();
-        if (threadIdx.x < 4 * T) {
+        {
+            // every pixel of the tile (those beyond the image are holes), eight
+            // reads in flight
             const int d = threadIdx.x / T, q = threadIdx.x - d * T;
-            int last = -1;
-            if (d == 0 && q < th) {
-                for (int lx = 0; lx < tw; ++lx) {
-                    s_in[0][q * T + lx] = (int8_t)last;
-                    if (!(s_slot[q * T + lx] & FVV_HOLE)) last = lx;
-                }
-            } else if (d == 1 && q < th) {
-                for (int lx = tw - 1; lx >= 0; --lx) {
-                    s_in[1][q * T + lx] = (int8_t)last;
-                    if (!(s_slot[q * T + lx] & FVV_HOLE)) last = lx;
-                }
-            } else if (d == 2 && q < tw) {
-                for (int ly = 0; ly < th; ++ly) {
-                    s_in[2][ly * T + q] = (int8_t)last;
-                    if (!(s_slot[ly * T + q] & FVV_HOLE)) last = ly;
-                }
-            } else if (d == 3 && q < tw) {
-                for (int ly = th - 1; ly >= 0; --ly) {
-                    s_in[3][ly * T + q] = (int8_t)last;
-                    if (!(s_slot[ly * T + q] & FVV_HOLE)) last = ly;
-                }
+            const bool col = d >= 2, back = !(d & 1);
+            int last = -1, l = back ? 0 : T - 1;
+            int e = col ? l * SP + q : q * SP + l, o = col ? l * IP + q : q * IP + l;
+            const int ls = back ? 1 : -1, es = col ? ls * SP : ls, os = col ? ls * IP : ls;
+#pragma unroll 8
+            for (int k = 0; k < T; ++k) {
+                s_in[d][o] = (int8_t)last;
+                last = s_slot[e] & FVV_HOLE ? last : l;
+                l += ls;
+                e += es;
+                o += os;
             }
         }
         __syncthreads();
         for (int e = threadIdx.x; e < T * T; e += blockDim.x) {
             const int ly = e / T, lx = e - ly * T;
-            if (lx >= tw || ly >= th || s_slot[e] != FVV_HOLE_OPEN) continue;
+            if (lx >= tw || ly >= th || s_slot[ly * SP + lx] != FVV_HOLE_OPEN) continue;
             const int x = X0 + lx, y = Y0 + ly;
             // candidates carry image indices y*W + x; depths from the slots
             Cand c{0.f, 0, -1};
             // left
-            const int l = s_in[0][e];
-            if (l >= 0) offer(c, u2f(s_slot[ly * T + l]), lx - l, y * W + X0 + l);
+            const int l = s_in[0][ly * IP + lx];
+            if (l >= 0) offer(c, u2f(s_slot[ly * SP + l]), lx - l, y * W + X0 + l);
             else if (s_ox[0][ly] >= 0) offer(c, u2f(s_oz[0][ly]), x - s_ox[0][ly], y * W + s_ox[0][ly]);
             // right
-            const int r = s_in[1][e];
-            if (r >= 0) offer(c, u2f(s_slot[ly * T + r]), r - lx, y * W + X0 + r);
+            const int r = s_in[1][ly * IP + lx];
+            if (r >= 0) offer(c, u2f(s_slot[ly * SP + r]), r - lx, y * W + X0 + r);
             else if (s_ox[1][ly] >= 0) offer(c, u2f(s_oz[1][ly]), s_ox[1][ly] - x, y * W + s_ox[1][ly]);
             // up
-            const int u = s_in[2][e];
-            if (u >= 0) offer(c, u2f(s_slot[u * T + lx]), ly - u, (Y0 + u) * W + x);
+            const int u = s_in[2][ly * IP + lx];
+            if (u >= 0) offer(c, u2f(s_slot[u * SP + lx]), ly - u, (Y0 + u) * W + x);
             else if (s_ox[2][lx] >= 0) offer(c, u2f(s_oz[2][lx]), y - s_ox[2][lx], s_ox[2][lx] * W + x);
             // down
-            const int d = s_in[3][e];
-            if (d >= 0) offer(c, u2f(s_slot[d * T + lx]), d - ly, (Y0 + d) * W + x);
+            const int d = s_in[3][ly * IP + lx];
+            if (d >= 0) offer(c, u2f(s_slot[d * SP + lx]), d - ly, (Y0 + d) * W + x);
             else if (s_ox[3][lx] >= 0) offer(c, u2f(s_oz[3][lx]), s_ox[3][lx] - y, s_ox[3][lx] * W + x);
             uint32_t col = 0;
             if (c.idx >= 0) {
