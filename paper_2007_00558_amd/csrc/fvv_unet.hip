@@ -1281,7 +1281,7 @@ k_conv3s(const GemmArgs g, const HeadArgs hd, const int R)
 // k-step order of the LDS-staged GEMM, so every value is the bytes that GEMM
 // would have stored.  Bound by the matrix cores and LDS together (44 MFMAs and
 // 56 KB of fragments per row of 32 pixels, 1,410 and 450 cycles): 16 images of
-// 960x544, 376 GFLOP with the transposed convolution, 604 -> 434 us (867
+// 960x544, 342 GFLOP with the transposed convolution, 604 -> 434 us (789
 // TFLOP/s) against blocks of 8 x 16 pixels between barriers (72 KB of fragments
 // and 1.4 input pixels staged per output pixel); 9 images from two stored
 // planes 285 -> 213.
