@@ -18,6 +18,7 @@
 #include <utility>
 
 #include "fvv_unet.h"
+#include "fvv_unet_sizes.h"
 
 namespace {
 
@@ -2471,9 +2472,9 @@ struct Plan {
     }
 };
 
-// Blocks of the head's training kernel, and bias partials: the widest row
-// matrix is the pool gradient's (POOL_BLOCKS rows of 128 channels); the
-// convolutions have at most 4,096 resident blocks of 64 channels.
+// Blocks of the head's training kernel, and floats of the bias partials: the
+// pool gradient's rows (POOL_BLOCKS of up to 128 channels); every launch that
+// writes rows of partials takes no more blocks than have rows in it.
 constexpr int kHeadBlocks = 1024;
 constexpr size_t kBiasPart = (size_t)POOL_BLOCKS * 128;
 
@@ -2610,10 +2611,12 @@ hipError_t conv3_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr, c
 {
     constexpr int lds = c3_lds_bytes<MT, TH>();
     static_assert(lds <= 65536, "staged patch and weights must fit 64 KB");
-    const int64_t items = (int64_t)((g.W + 15) / 16) * ((g.H + TH - 1) / TH) * g.NB * ((g.M + 32 * MT - 1) / (32 * MT));
+    const int mgroups = (g.M + 32 * MT - 1) / (32 * MT);
+    const int64_t items = (int64_t)((g.W + 15) / 16) * ((g.H + TH - 1) / TH) * g.NB * mgroups;
     static const int rb = std::max(8, resident_blocks(k_conv3<MT, TH, EPI, POOL, HEAD>, lds) / 8 * 8);
-    const int grid = (int)std::min<int64_t>(rb, (items + 7) / 8 * 8);
-    if (rows) *rows = grid / ((g.M + 32 * MT - 1) / (32 * MT));
+    int grid = (int)std::min<int64_t>(rb, (items + 7) / 8 * 8);
+    if (EPI == EPI_GRAD) grid = unet_bias_grid(grid, mgroups, g.M, kBiasPart);
+    if (rows) *rows = grid / mgroups;
     hipLaunchKernelGGL((k_conv3<MT, TH, EPI, POOL, HEAD>), dim3(grid), dim3(256), lds, s, g, h);
     return hipGetLastError();
 }
@@ -2623,10 +2626,12 @@ hipError_t conv3r_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr)
 {
     constexpr int lds = c3r_lds_bytes<MT, RW>();
     static_assert(2 * lds <= 160 * 1024, "two blocks share a CU's LDS");
-    const int64_t items = (int64_t)((g.W + 31) / 32) * ((g.H + 4 * RW - 1) / (4 * RW)) * g.NB * (g.M / (32 * MT));
+    const int mgroups = g.M / (32 * MT);
+    const int64_t items = (int64_t)((g.W + 31) / 32) * ((g.H + 4 * RW - 1) / (4 * RW)) * g.NB * mgroups;
     static const int rb = std::max(8, resident_blocks(k_conv3r<MT, RW, EPI, POOL>, lds) / 8 * 8);
-    const int grid = (int)std::min<int64_t>(rb, (items + 7) / 8 * 8);
-    if (rows) *rows = grid / (g.M / (32 * MT));
+    int grid = (int)std::min<int64_t>(rb, (items + 7) / 8 * 8);
+    if (EPI == EPI_GRAD) grid = unet_bias_grid(grid, mgroups, g.M, kBiasPart);
+    if (rows) *rows = grid / mgroups;
     hipLaunchKernelGGL((k_conv3r<MT, RW, EPI, POOL>), dim3(grid), dim3(256), lds, s, g);
     return hipGetLastError();
 }
@@ -2670,7 +2675,8 @@ int strip_rows(const GemmArgs &g, int grid)
 template <int EPI, bool POOL, bool HEAD, bool K16>
 hipError_t conv3s_launch(const GemmArgs &g, hipStream_t s, const HeadArgs &h = HeadArgs{}, int *rows = nullptr)
 {
-    static const int grid = std::max(8, resident_blocks(k_conv3s<EPI, POOL, HEAD, K16>, 0) / 8 * 8);
+    static const int rb = std::max(8, resident_blocks(k_conv3s<EPI, POOL, HEAD, K16>, 0) / 8 * 8);
+    const int grid = EPI == EPI_GRAD ? unet_bias_grid(rb, 1, g.M, kBiasPart) : rb;
     if (rows) *rows = grid;
     hipLaunchKernelGGL((k_conv3s<EPI, POOL, HEAD, K16>), dim3(grid), dim3(256), 0, s, g, h, strip_rows(g, grid));
     return hipGetLastError();
@@ -2984,7 +2990,7 @@ hipError_t conv_dgrad(unet_state *n, unet_act *a, int li, int NB, int H, int W, 
     NCHK(conv3<EPI_GRAD>(g, s, nullptr, &rows));
     bias = BiasPart{a->bpart, rows, l.cin, split ? split : l.cin, nullptr};
     std::swap(a->G, a->G2);
-    return (size_t)rows * l.cin <= kBiasPart ? hipSuccess : hipErrorInvalidValue;
+    return hipSuccess;
 }
 
 // ... of a 2x2 transposed convolution: a->G on the fine grid -> [P_coarse][cin],
@@ -3007,12 +3013,12 @@ hipError_t convT_dgrad(unet_state *n, unet_act *a, int li, int NB, int Hc, int W
     g.M = l.cin;
     const int P = NB * Hc * Wc, mg = g.M / 64;
     static const int rb = std::max(8, resident_blocks(k_convT_grad<2>, 0));
-    const int rows = std::max(1, std::min((P + 127) / 128, rb / mg));
+    const int rows = std::max(1, std::min({(P + 127) / 128, rb / mg, (int)(kBiasPart / l.cin)}));
     hipLaunchKernelGGL(k_convT_grad<2>, dim3(rows, mg), dim3(256), 0, s, g);
     NCHK(hipGetLastError());
     bias = BiasPart{a->bpart, rows, l.cin, l.cin, nullptr};
     std::swap(a->G, a->G2);
-    return (size_t)rows * l.cin <= kBiasPart ? hipSuccess : hipErrorInvalidValue;
+    return hipSuccess;
 }
 
 // the gradient operand (a->G) of the encoder layer before a pool, from the
@@ -3021,7 +3027,7 @@ hipError_t pool_grad(unet_act *a, const uint16_t *act, const float *skip, int NB
                      BiasPart &bias)
 {
     const int64_t n = (int64_t)NB * (H / 2) * (W / 2) * (C / 8);
-    const int rows = (int)std::min<int64_t>(POOL_BLOCKS, (n + 255) / 256);
+    const int rows = (int)std::min<int64_t>({POOL_BLOCKS, (n + 255) / 256, (int64_t)(kBiasPart / C)});
     hipLaunchKernelGGL(k_pool_grad, dim3(rows), dim3(256), 0, s, act, (const float *)a->g0, skip, a->G, a->bpart, NB, H, W, C);
     bias = BiasPart{a->bpart, rows, C, C, nullptr};
     return hipGetLastError();
