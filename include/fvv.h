@@ -467,7 +467,9 @@ int32_t fvv_server_stats(fvv_ctx *ctx, uint64_t *out6);
  *   layer then fails with FVV_E_ARG.  The network's results are the same
  *   bytes either way.
  * fvv_net_device_bytes: device memory held by the network and its
- *   activation sets (part of the context's budget). */
+ *   activation sets (part of the context's budget).  Where a training set does
+ *   not fit the budget or the device, a smaller one is taken whose weight
+ *   gradients sum fewer partials (the same sums in another float32 order). */
 enum { FVV_NET_PARAMS = 0, FVV_NET_GRADS = 1 };
 uint64_t fvv_net_param_count(void);
 int32_t fvv_net_layer_info(int32_t layer, int32_t *out4);

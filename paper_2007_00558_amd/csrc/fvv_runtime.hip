@@ -681,23 +681,28 @@ int32_t find_slot(fvv_ctx *c, uint64_t version, int &si)
 }
 
 // Grow an activation set to hold `px` network pixels (and the training
-// buffers if train), within the context's memory budget.
+// buffers if train), within the context's memory budget; a training set that
+// does not fit is taken lean.
 int32_t reserve_act(fvv_ctx *c, unet_act *a, size_t px, bool train)
 {
     const bool tr = train || unet_act_trainable(a);
     const size_t cap = std::max(px, unet_act_cap(a));
     if (cap == unet_act_cap(a) && tr == unet_act_trainable(a)) return FVV_OK;
-    const size_t before = unet_act_bytes(a), after = unet_act_need(cap, tr);
-    if (c->budget && c->allocated - before + after > c->budget)
-        return fail(c, FVV_E_NOMEM, "device memory budget exceeded by the network activations (%zu bytes)", after);
-    const hipError_t e = unet_act_reserve(a, cap, tr);
-    c->allocated = c->allocated - before + unet_act_bytes(a);
-    c->net_bytes = c->net_bytes - before + unet_act_bytes(a);
-    if (e != hipSuccess) {
+    int32_t rc = FVV_OK;
+    for (int lean = 0; lean <= (tr ? 1 : 0); ++lean) {
+        const size_t before = unet_act_bytes(a), after = unet_act_need(cap, tr, lean != 0);
+        if (c->budget && c->allocated - before + after > c->budget) {
+            rc = fail(c, FVV_E_NOMEM, "device memory budget exceeded by the network activations (%zu bytes)", after);
+            continue;
+        }
+        const hipError_t e = unet_act_reserve(a, cap, tr, lean != 0);
+        c->allocated = c->allocated - before + unet_act_bytes(a);
+        c->net_bytes = c->net_bytes - before + unet_act_bytes(a);
+        if (e == hipSuccess) return FVV_OK;
         (void)hipGetLastError();
-        return fail(c, FVV_E_NOMEM, "network activations (%zu bytes): %s", after, hipGetErrorString(e));
+        rc = fail(c, FVV_E_NOMEM, "network activations (%zu bytes): %s", after, hipGetErrorString(e));
     }
-    return FVV_OK;
+    return rc;
 }
 
 int32_t net_status(fvv_ctx *c, hipError_t e, const std::string &err, const char *what)

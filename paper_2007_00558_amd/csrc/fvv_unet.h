@@ -37,7 +37,9 @@ size_t unet_param_floats();
 int unet_layer_count();
 const unet_layer *unet_layer_info(int i);
 size_t unet_weight_bytes();                            // device bytes of a loaded network
-size_t unet_act_need(size_t pixels, bool train);       // device bytes of an activation set
+// device bytes of an activation set; lean: a training set with fewer partials of
+// the weight gradients (the sums in another order, fewer blocks at a time)
+size_t unet_act_need(size_t pixels, bool train, bool lean);
 size_t unet_act_bytes(const unet_act *a);              // bytes it holds now
 size_t unet_act_cap(const unet_act *a);                // pixels it holds now
 bool unet_act_trainable(const unet_act *a);            // holds the training buffers
@@ -50,7 +52,7 @@ hipError_t unet_get_params(unet_state *n, float *host, hipStream_t s);
 hipError_t unet_get_grads(unet_state *n, float *host, hipStream_t s);
 // Make the activation set hold B*H*W pixels (grows only; synchronises the
 // device when it reallocates).
-hipError_t unet_act_reserve(unet_act *a, size_t pixels, bool train);
+hipError_t unet_act_reserve(unet_act *a, size_t pixels, bool train, bool lean);
 // Forward over a stack [B][H][W][16] bf16 (H, W multiples of 8).  Writes
 // s = sigmoid output fp32 [B][H][W][3] to s_out if non-null and, if rgb is
 // non-null, RGB8 of the first valid_h rows and valid_w columns of image b at

@@ -2450,7 +2450,8 @@ struct unet_act {
     float *gs0 = nullptr, *gs1 = nullptr, *gs2 = nullptr;   // skip halves' gradients [P0][32], [P1][64], [P2][128]
     uint16_t *G = nullptr, *G2 = nullptr;                 // [P0][32] each: the layer's and the next one's
     float *part = nullptr;
-    float *bpart = nullptr;                               // bias partials (kBiasPart floats)
+    float *bpart = nullptr;                               // bias partials (unet_bias_floats)
+    bool lean = false;                                    // part holds unet_lean_partials only
     float *head_part = nullptr;
     float *loss_dev = nullptr;
     void *blocks[40] = {};
@@ -2472,15 +2473,17 @@ struct Plan {
     }
 };
 
-// Blocks of the head's training kernel, and floats of the bias partials: the
-// pool gradient's rows (POOL_BLOCKS of up to 128 channels); every launch that
-// writes rows of partials takes no more blocks than have rows in it.
-constexpr int kHeadBlocks = 1024;
-constexpr size_t kBiasPart = (size_t)POOL_BLOCKS * 128;
+// Bias partials that a launch may write, and the rows it wrote: a launch takes
+// no more blocks than have rows.
+struct BiasRows {
+    size_t floats;
+    int rows;
+};
 
-// One allocation per set; the plan gives every buffer its offset.
+// One allocation per set; the plan gives every buffer its offset.  lean: the
+// weight gradients' partials within unet_lean_partials.
 template <typename F>
-void act_plan(size_t P0, bool train, F &&put)
+void act_plan(size_t P0, bool train, bool lean, F &&put)
 {
     const size_t P1 = P0 / 4, P2 = P1 / 4, P3 = P2 / 4;
     put(0, P0 * 32 * 2);     // e0a
@@ -2507,10 +2510,10 @@ void act_plan(size_t P0, bool train, F &&put)
     put(20, P1 * 64 * 4);    // gs1
     put(21, P2 * 128 * 4);   // gs2
     put(22, P0 * 32 * 2);    // G
-    put(23, partial_floats(P0) * 4);
-    put(24, (size_t)kHeadBlocks * HEAD_PART * 4);
+    put(23, (lean ? std::min(partial_floats(P0), unet_lean_partials(P0)) : partial_floats(P0)) * 4);
+    put(24, (size_t)unet_head_blocks(P0) * HEAD_PART * 4);
     put(25, 256);            // loss
-    put(26, kBiasPart * 4);
+    put(26, unet_bias_floats(P0) * 4);
 }
 
 }  // namespace
@@ -2542,10 +2545,10 @@ size_t unet_weight_bytes()
     const Layers &T = layers();
     return T.n_params * 4 * 4 + (T.n_wf + T.n_wd) * 2;
 }
-size_t unet_act_need(size_t pixels, bool train)
+size_t unet_act_need(size_t pixels, bool train, bool lean)
 {
     size_t total = 0;
-    act_plan(pixels, train, [&](int, size_t b) { total += (b + 255) & ~(size_t)255; });
+    act_plan(pixels, train, lean, [&](int, size_t b) { total += (b + 255) & ~(size_t)255; });
     return total;
 }
 size_t unet_act_bytes(const unet_act *a) { return a ? a->bytes : 0; }
@@ -2553,7 +2556,7 @@ size_t unet_act_cap(const unet_act *a) { return a ? a->cap : 0; }
 bool unet_act_trainable(const unet_act *a) { return a && a->train; }
 bool unet_loaded(const unet_state *n) { return n && n->loaded; }
 
-hipError_t unet_act_reserve(unet_act *a, size_t pixels, bool train)
+hipError_t unet_act_reserve(unet_act *a, size_t pixels, bool train, bool lean)
 {
     if (a->cap >= pixels && (a->train || !train)) return hipSuccess;
     const size_t cap = std::max(pixels, a->cap);
@@ -2562,7 +2565,7 @@ hipError_t unet_act_reserve(unet_act *a, size_t pixels, bool train)
     if (a->blocks[0]) (void)hipFree(a->blocks[0]);
     *a = unet_act();
     size_t off[32] = {}, total = 0;
-    act_plan(cap, train, [&](int i, size_t b) {
+    act_plan(cap, train, lean, [&](int i, size_t b) {
         off[i] = total;
         total += (b + 255) & ~(size_t)255;
     });
@@ -2572,6 +2575,7 @@ hipError_t unet_act_reserve(unet_act *a, size_t pixels, bool train)
     a->bytes = total;
     a->cap = cap;
     a->train = train;
+    a->lean = lean;
     uint16_t **bf[17] = {&a->e0a, &a->cat0, &a->p1, &a->e1a, &a->cat1, &a->p2, &a->e2a, &a->cat2, &a->p3,
                          &a->ma,  &a->mb,   &a->d2a, &a->d2b, &a->d1a, &a->d1b, &a->d0a, &a->d0b};
     for (int i = 0; i < 17; ++i) *bf[i] = (uint16_t *)(base + off[i]);
@@ -2607,7 +2611,7 @@ int resident_blocks(F kernel, size_t lds)
 }
 
 template <int MT, int TH, int EPI, bool POOL = false, bool HEAD = false>
-hipError_t conv3_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr, const HeadArgs &h = HeadArgs{})
+hipError_t conv3_launch(const GemmArgs &g, hipStream_t s, BiasRows *bias = nullptr, const HeadArgs &h = HeadArgs{})
 {
     constexpr int lds = c3_lds_bytes<MT, TH>();
     static_assert(lds <= 65536, "staged patch and weights must fit 64 KB");
@@ -2615,14 +2619,16 @@ hipError_t conv3_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr, c
     const int64_t items = (int64_t)((g.W + 15) / 16) * ((g.H + TH - 1) / TH) * g.NB * mgroups;
     static const int rb = std::max(8, resident_blocks(k_conv3<MT, TH, EPI, POOL, HEAD>, lds) / 8 * 8);
     int grid = (int)std::min<int64_t>(rb, (items + 7) / 8 * 8);
-    if (EPI == EPI_GRAD) grid = unet_bias_grid(grid, mgroups, g.M, kBiasPart);
-    if (rows) *rows = grid / mgroups;
+    if (bias) {
+        grid = unet_bias_grid(grid, mgroups, g.M, bias->floats);
+        bias->rows = grid / mgroups;
+    }
     hipLaunchKernelGGL((k_conv3<MT, TH, EPI, POOL, HEAD>), dim3(grid), dim3(256), lds, s, g, h);
     return hipGetLastError();
 }
 
 template <int MT, int RW, int EPI, bool POOL = false>
-hipError_t conv3r_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr)
+hipError_t conv3r_launch(const GemmArgs &g, hipStream_t s, BiasRows *bias = nullptr)
 {
     constexpr int lds = c3r_lds_bytes<MT, RW>();
     static_assert(2 * lds <= 160 * 1024, "two blocks share a CU's LDS");
@@ -2630,8 +2636,10 @@ hipError_t conv3r_launch(const GemmArgs &g, hipStream_t s, int *rows = nullptr)
     const int64_t items = (int64_t)((g.W + 31) / 32) * ((g.H + 4 * RW - 1) / (4 * RW)) * g.NB * mgroups;
     static const int rb = std::max(8, resident_blocks(k_conv3r<MT, RW, EPI, POOL>, lds) / 8 * 8);
     int grid = (int)std::min<int64_t>(rb, (items + 7) / 8 * 8);
-    if (EPI == EPI_GRAD) grid = unet_bias_grid(grid, mgroups, g.M, kBiasPart);
-    if (rows) *rows = grid / mgroups;
+    if (bias) {
+        grid = unet_bias_grid(grid, mgroups, g.M, bias->floats);
+        bias->rows = grid / mgroups;
+    }
     hipLaunchKernelGGL((k_conv3r<MT, RW, EPI, POOL>), dim3(grid), dim3(256), lds, s, g);
     return hipGetLastError();
 }
@@ -2673,11 +2681,11 @@ int strip_rows(const GemmArgs &g, int grid)
 }
 
 template <int EPI, bool POOL, bool HEAD, bool K16>
-hipError_t conv3s_launch(const GemmArgs &g, hipStream_t s, const HeadArgs &h = HeadArgs{}, int *rows = nullptr)
+hipError_t conv3s_launch(const GemmArgs &g, hipStream_t s, const HeadArgs &h = HeadArgs{}, BiasRows *bias = nullptr)
 {
     static const int rb = std::max(8, resident_blocks(k_conv3s<EPI, POOL, HEAD, K16>, 0) / 8 * 8);
-    const int grid = EPI == EPI_GRAD ? unet_bias_grid(rb, 1, g.M, kBiasPart) : rb;
-    if (rows) *rows = grid;
+    const int grid = bias ? unet_bias_grid(rb, 1, g.M, bias->floats) : rb;
+    if (bias) bias->rows = grid;
     hipLaunchKernelGGL((k_conv3s<EPI, POOL, HEAD, K16>), dim3(grid), dim3(256), 0, s, g, h, strip_rows(g, grid));
     return hipGetLastError();
 }
@@ -2694,11 +2702,12 @@ hipError_t conv3t_launch(const GemmArgs &g, hipStream_t s)
 
 // With g.pool (even H and W) the launch also writes the 2x2 max-pool of the
 // output there; with head (32 output channels from 32) it also runs the head on
-// the output, which is stored unless g.out is null; *rows (EPI_GRAD) the number
-// of rows of bias partials written.
+// the output, which is stored unless g.out is null; bias (EPI_GRAD): the bias
+// partials.
 template <int EPI>
-hipError_t conv3(const GemmArgs &g, hipStream_t s, const HeadArgs *head = nullptr, int *rows = nullptr)
+hipError_t conv3(const GemmArgs &g, hipStream_t s, const HeadArgs *head = nullptr, BiasRows *bias = nullptr)
 {
+    if ((EPI == EPI_GRAD) != (bias != nullptr)) return hipErrorInvalidValue;
     if (g.K % 32 != 0 || (g.pool && (g.H % 2 != 0 || g.W % 2 != 0)) || (head && (g.M != 32 || g.K != 32)))
         return hipErrorInvalidValue;
     // 32 output channels and strips for every wave: weights resident
@@ -2717,7 +2726,7 @@ hipError_t conv3(const GemmArgs &g, hipStream_t s, const HeadArgs *head = nullpt
                 if (g.pool) return conv3s_launch<EPI, true, false, false>(g, s);
                 if (head) return conv3s_launch<EPI, false, true, false>(g, s, *head);
             }
-            return conv3s_launch<EPI, false, false, false>(g, s, HeadArgs{}, rows);
+            return conv3s_launch<EPI, false, false, false>(g, s, HeadArgs{}, bias);
         }
     }
     // from two chunks: a concatenation's planes, or the gradient at the first pool
@@ -2736,7 +2745,7 @@ hipError_t conv3(const GemmArgs &g, hipStream_t s, const HeadArgs *head = nullpt
         if (g.pool) return big ? conv3r_launch<2, 4, EPI, true>(g, s) : conv3_launch<1, 8, EPI, true>(g, s);
         if (head) return conv3_launch<1, 8, EPI, false, true>(g, s, nullptr, *head);
     }
-    return big ? conv3r_launch<2, 4, EPI>(g, s, rows) : conv3_launch<1, 8, EPI>(g, s, rows);
+    return big ? conv3r_launch<2, 4, EPI>(g, s, bias) : conv3_launch<1, 8, EPI>(g, s, bias);
 }
 
 // 3x3 conv + bias + ReLU into (out, o_cs, o_off); with pool_out, also the 2x2
@@ -2892,6 +2901,9 @@ hipError_t forward_all(unet_state *n, unet_act *a, const uint16_t *stack, int NB
     return hipSuccess;
 }
 
+// full-resolution pixels of the set's last forward
+size_t act_px(const unet_act *a) { return (size_t)a->NB * a->H * a->W; }
+
 template <int WM, int WK, int WP, int ROWS>
 void wgrad3_launch(const WgradArgs &w, int chunks, hipStream_t s)
 {
@@ -2933,7 +2945,9 @@ hipError_t wgrad(unet_state *n, unet_act *a, int li, const BiasPart &bias, const
     w.K = l.cin_pad;
     w.x_src = l.cin;
     const WgShape h = wg_shape(l);
-    const int chunks = wg_chunks((int64_t)NB * ((H + h.rows - 1) / h.rows) * ((W + 15) / 16), wg_tiles(l));
+    const size_t nw = (size_t)l.cout * l.taps * l.cin_pad;
+    int chunks = wg_chunks((int64_t)NB * ((H + h.rows - 1) / h.rows) * ((W + 15) / 16), wg_tiles(l));
+    if (a->lean) chunks = std::min(chunks, (int)(unet_lean_partials(act_px(a)) / nw));
     if (l.kind == 1) {
         if (h.wm == 1)
             wgradT_launch<1, 1, 4, 8>(w, chunks, s);
@@ -2949,10 +2963,9 @@ hipError_t wgrad(unet_state *n, unet_act *a, int li, const BiasPart &bias, const
         wgrad3_launch<2, 2, 1, 8>(w, chunks, s);
     }
     NCHK(hipGetLastError());
-    const int nel = l.cout * l.taps * l.cin_pad;
     BiasPart bp = bias;
     bp.out = n->g + l.b_off;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((nel + WR_COLS - 1) / WR_COLS + bp.cols / 16), dim3(256), 0, s,
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((nw + WR_COLS - 1) / WR_COLS) + bp.cols / 16), dim3(256), 0, s,
                        (const float *)a->part, chunks, l.cout, l.taps, l.cin_pad, l.cin, n->g + l.w_off, bp);
     return hipGetLastError();
 }
@@ -2986,9 +2999,9 @@ hipError_t conv_dgrad(unet_state *n, unet_act *a, int li, int NB, int H, int W, 
     g.split = split;
     g.skip = skip;
     g.bpart = a->bpart;
-    int rows = 0;
-    NCHK(conv3<EPI_GRAD>(g, s, nullptr, &rows));
-    bias = BiasPart{a->bpart, rows, l.cin, split ? split : l.cin, nullptr};
+    BiasRows br{unet_bias_floats(act_px(a)), 0};
+    NCHK(conv3<EPI_GRAD>(g, s, nullptr, &br));
+    bias = BiasPart{a->bpart, br.rows, l.cin, split ? split : l.cin, nullptr};
     std::swap(a->G, a->G2);
     return hipSuccess;
 }
@@ -3013,7 +3026,7 @@ hipError_t convT_dgrad(unet_state *n, unet_act *a, int li, int NB, int Hc, int W
     g.M = l.cin;
     const int P = NB * Hc * Wc, mg = g.M / 64;
     static const int rb = std::max(8, resident_blocks(k_convT_grad<2>, 0));
-    const int rows = std::max(1, std::min({(P + 127) / 128, rb / mg, (int)(kBiasPart / l.cin)}));
+    const int rows = std::max(1, std::min({(P + 127) / 128, rb / mg, (int)(unet_bias_floats(act_px(a)) / l.cin)}));
     hipLaunchKernelGGL(k_convT_grad<2>, dim3(rows, mg), dim3(256), 0, s, g);
     NCHK(hipGetLastError());
     bias = BiasPart{a->bpart, rows, l.cin, l.cin, nullptr};
@@ -3027,7 +3040,7 @@ hipError_t pool_grad(unet_act *a, const uint16_t *act, const float *skip, int NB
                      BiasPart &bias)
 {
     const int64_t n = (int64_t)NB * (H / 2) * (W / 2) * (C / 8);
-    const int rows = (int)std::min<int64_t>({POOL_BLOCKS, (n + 255) / 256, (int64_t)(kBiasPart / C)});
+    const int rows = (int)std::min<int64_t>({POOL_BLOCKS, (n + 255) / 256, (int64_t)(unet_bias_floats(act_px(a)) / C)});
     hipLaunchKernelGGL(k_pool_grad, dim3(rows), dim3(256), 0, s, act, (const float *)a->g0, skip, a->G, a->bpart, NB, H, W, C);
     bias = BiasPart{a->bpart, rows, C, C, nullptr};
     return hipGetLastError();
@@ -3205,7 +3218,7 @@ hipError_t unet_train(unet_state *n, unet_act *a, const uint16_t *stack, const f
     h.inv_n = (float)(1.0 / ((double)NB * valid_h * W * 3));
     h.G = a->G;
     h.part = a->head_part;
-    const int hwg = std::min(kHeadBlocks, (P0 + 255) / 256);
+    const int hwg = unet_head_blocks((size_t)P0);
     hipLaunchKernelGGL(k_head_grad, dim3(hwg), dim3(256), 0, s, h);
     NCHK(hipGetLastError());
     hipLaunchKernelGGL(k_head_reduce, dim3(HEAD_PART), dim3(256), 0, s, (const float *)a->head_part, hwg,

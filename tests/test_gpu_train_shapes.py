@@ -134,3 +134,40 @@ def test_batch_output_equals_single(fvv, ctx, oracle_lib, N, H, W):  # noqa: F81
     many, one = run(st), [run(st[q:q + 1].contiguous())[0] for q in range(2)]
     for q in range(N):
         assert np.array_equal(many[q], one[q % 2]), q
+
+
+@pytest.mark.parametrize("N,H,W,need", [(1, 8, 8, 2447872), (1, 64, 64, 7985664), (64, 8, 8, 7985664),
+                                        (1, 128, 128, 27223296), (1, 256, 256, 108892416), (16, 64, 64, 108892416)])
+def test_training_within_a_memory_budget(fvv, N, H, W, need):  # noqa: F811
+    """A training step fits a context whose budget holds the weights and `need`
+    bytes for the activation set (short of what the gradients' partial sums take
+    where memory is free), and its gradients are those of a context without a
+    budget up to the order of float32 sums: the norm of a sum of n terms in
+    another order differs by less than sqrt(n) 2^-24 of the norm of the terms'
+    magnitudes; 1e-5 of the gradient's norm allows for 64 K terms that cancel to
+    a 40th."""
+    import torch
+    say(f"[gpu] training in a budget {N}x{H}x{W}")
+    P = flat(rand_params(600 + H))
+    g = torch.Generator(device="cuda").manual_seed(N + H)
+    st = torch.rand((N, H, W, 16), generator=g, device="cuda").to(torch.bfloat16)
+    st[..., 15] = 0
+    target = torch.rand((N, H, W, 3), generator=g, device="cuda")
+
+    def step(budget):
+        c = fvv.Context(0, mem_budget=budget)
+        c.net_load(P)
+        weights = c.net_device_bytes()
+        loss = c.net_train_step(st, target, N, H, W, H, lr=0.0, apply=False)
+        grads, held = c.net_read(fvv.NET_GRADS), c.net_device_bytes()
+        c.close()
+        return loss, grads, weights, held
+
+    loss, grads, weights, _ = step(0)
+    loss_b, grads_b, _, held = step(weights + need)
+    assert held <= weights + need and loss_b == loss
+    a, b = unflat(grads), unflat(grads_b)
+    for name in a:
+        for k in (0, 1):
+            d = np.linalg.norm(a[name][k].astype(np.float64) - b[name][k].astype(np.float64))
+            assert d <= 1e-5 * np.linalg.norm(a[name][k].astype(np.float64)), (name, k)
