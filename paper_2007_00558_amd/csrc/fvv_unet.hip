@@ -60,6 +60,17 @@ __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint
 
 __device__ __forceinline__ bf16x8 ld8(const uint16_t *p) { return __builtin_bit_cast(bf16x8, *(const uint4 *)p); }
 
+// Between the LDS accesses of a wave's lanes and those of its other lanes to the
+// same bytes (a hand-over, or the overwriting of what was read), without a
+// barrier: a wave's LDS operations are executed in order, only the compiler has
+// to keep them so.
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 struct GemmArgs {
     const uint16_t *A;       // [M][taps][K] bf16
     const uint16_t *Bsrc;    // NHWC bf16 activations
@@ -1100,13 +1111,6 @@ k_conv3s(const GemmArgs g, const HeadArgs hd, const int R)
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) f[dx][kk] = __builtin_bit_cast(bf16x8, *(const uint4 *)(row + (fsrc[dx] ^ 32 * kk)));
     };
-    // the writes of a row are read by other lanes of the wave: LDS operations of
-    // a wave are executed in order, only the compiler has to keep them so
-    auto order = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
     float bs[16];
     __shared__ float s_b[EPI == EPI_GRAD ? 4 * 32 : 1];
     if (EPI == EPI_GRAD)
@@ -1147,7 +1151,7 @@ k_conv3s(const GemmArgs g, const HeadArgs hd, const int R)
         next(pf);
     }
     stage(st[0]);
-    order();
+    wave_order();
     frags(f[0]);
     fetch(st[0], pf);
     next(pf);
@@ -1161,9 +1165,9 @@ k_conv3s(const GemmArgs g, const HeadArgs hd, const int R)
     };
     auto step = [&](auto ph) {
         constexpr int S = decltype(ph)::value, P = S % 3, P1 = (S + 1) % 3, P2 = (S + 2) % 3, Q = (S + 1) % D;
-        order();
+        wave_order();
         stage(st[Q]);
-        order();
+        wave_order();
         Cur nx = cp;
         next(nx);
         if (EPI == EPI_GRAD) fetch_act(act[(S + 1) % 2], nx);
@@ -1402,11 +1406,6 @@ k_conv3t(const GemmArgs g, const int R)
                 }
         }
     };
-    auto order = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
     auto frags = [&](bf16x8 (&f)[3][2], const uint8_t *row) __attribute__((always_inline)) {
 #pragma unroll
         for (int dx = 0; dx < 3; ++dx)
@@ -1449,14 +1448,14 @@ k_conv3t(const GemmArgs g, const int R)
     next(pf);
     stage_row(cp);
     fetch_row(nx);
-    order();
+    wave_order();
     frags(f0[0], row0_of(cp));
     frags(f1[0], row1);
     auto step = [&](auto ph) __attribute__((always_inline)) {
         constexpr int P = decltype(ph)::value, P1 = (P + 1) % 3, P2 = (P + 2) % 3;
-        order();
+        wave_order();
         stage_row(nx);
-        order();
+        wave_order();
         fetch_row(pf);
         const int px = cp.x0 + lc;
         const bool ok = cp.r >= 2 && px < g.W;
@@ -2210,14 +2209,13 @@ __global__ void __launch_bounds__(256, 4) k_head_grad(const HeadArgs h)
             }
             if (in) *(uint4 *)(h.G + (uint32_t)p * 32 + q * 8) = make_uint4(o[0], o[1], o[2], o[3]);
         }
-        // (a wave's LDS accesses are in order: its own pixels only)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        wave_order();   // the lanes' pixels, read by the whole wave
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const bf16x8 ga = lc < 3 ? ld8(s_g[wave] + lc * 64 + 16 * k + 8 * lh) : zero8;
             wg = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, tr_frag(s_a[wave] + 16 * k * 32 + tr_lane()), wg, 0, 0, 0);
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        wave_order();   // before the next step's pixels
     }
     auto put = [&](int at, float v) {
         v = half_sum(v);
