@@ -51,6 +51,16 @@ __device__ __forceinline__ double y12_rcp(double x)
     return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
 }
 
+// v without its fraction, as an int; beyond int's range the nearest end, 0 for a
+// NaN (the instruction's own results: the language leaves such a conversion
+// undefined, and depths far outside close planes get there)
+__device__ __forceinline__ int y12_int(double v)
+{
+    int i;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(v));
+    return i;
+}
+
 // Eq. 2: millimetres -> code
 __device__ __forceinline__ uint32_t y12_quantise(uint32_t mm, const y12_planes &p)
 {
@@ -69,10 +79,10 @@ __device__ __forceinline__ uint32_t y12_quantise(uint32_t mm, const y12_planes &
 __device__ __forceinline__ uint32_t y12_quantise_est(uint32_t mm, const y12_planes &p, bool &sure)
 {
     const double v = __builtin_fma(y12_rcp((double)mm), p.enc1, p.enc0);
-    const int c = (int)v;   // saturating; floor where it matters (v >= 0)
+    const uint32_t c = (uint32_t)y12_int(v);   // the floor where it matters (v >= 0)
     const bool none = mm - 1u >= 0xFFFEu;   // 0 or 0xFFFF
     sure &= none | (fabs(__builtin_amdgcn_fract(v) - 0.5) < 0.5 - p.enc_eps);
-    const uint32_t code = (uint32_t)(c - 2) <= 4093u ? (uint32_t)c : 1u;
+    const uint32_t code = c - 2u <= 4093u ? c : 1u;
     return none ? (mm == 0) : code;
 }
 
@@ -92,7 +102,7 @@ __device__ __forceinline__ uint32_t y12_dequantise(uint32_t code, const y12_plan
 __device__ __forceinline__ uint32_t y12_dequantise_est(uint32_t code, const y12_planes &p, bool &sure)
 {
     const double v = __builtin_fma(y12_rcp(__builtin_fma((double)((int)code - 2), p.dec1, p.inv_zf)), 1000.0, 0.5);
-    const int mm = (int)v;   // saturating; v > 0 for codes from 2 on
+    const int mm = y12_int(v);   // v > 0 for codes from 2 on
     sure &= (code < 2u) | (mm > 65535) | (fabs(__builtin_amdgcn_fract(v) - 0.5) < 0.5 - 1e-8);
     return code >= 2u ? (uint32_t)min(max(mm, 1), 65535) : code == 0u ? 0xFFFFu : 0u;
 }
