@@ -116,6 +116,7 @@ __global__ void __launch_bounds__(256) k_y12_decode(const fvv_y12_batch b)
     uint32_t code[2][2 * NB];
     alignas(16) typename Run<NB>::mm d[2];
     bool sure = true;
+    uint32_t any = 0u;
 #pragma unroll
     for (int row = 0; row < 2; ++row) {
         alignas(16) typename Run<NB>::y y;
@@ -125,8 +126,20 @@ __global__ void __launch_bounds__(256) k_y12_decode(const fvv_y12_batch b)
 #pragma unroll
         for (int i = 0; i < 2 * NB; ++i) {
             code[row][i] = y12_unfold(y[i], y12_msb(uv[i >> 1], i & 1));
-            d[row][i] = (uint16_t)y12_dequantise_est(code[row][i], b.planes, sure);
+            any |= code[row][i];
         }
+    }
+    // (uniform) waves of background and missing depth only have nothing to
+    // estimate: 9 x 1920x1080 without depth 26.6 -> 18.2 us, with depth
+    // everywhere 26.6 and 26.8
+    if (__builtin_amdgcn_ballot_w64(any > 1u)) {
+#pragma unroll
+        for (int i = 0; i < 4 * NB; ++i)
+            d[i / (2 * NB)][i % (2 * NB)] =
+                (uint16_t)y12_dequantise_est(code[i / (2 * NB)][i % (2 * NB)], b.planes, sure);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4 * NB; ++i) d[i / (2 * NB)][i % (2 * NB)] = code[i / (2 * NB)][i % (2 * NB)] ? 0u : 0xFFFFu;
     }
     if (!sure)
 #pragma unroll

@@ -292,3 +292,27 @@ def test_every_value_both_ways(fvv, oracle_lib, zn, zf, W, shift):
     mm = fvv.depth_decode_y12(src, 2 * W, H, zn, zf)
     torch.cuda.synchronize()
     assert np.array_equal(mm.cpu().numpy().view(np.uint16), oracle_lib.decode_depth_y12(Y, UV, UV, zn, zf))
+
+
+@pytest.mark.parametrize("W,H,n", [(256, 64, 1), (2048, 2048, 1), (64, 64, 3)])
+def test_decode_where_waves_have_no_depth(fvv, oracle_lib, W, H, n):
+    """Images of background (code 0) and missing depth (code 1), alone, mixed and
+    with one depth code in the first, a middle or the last place: waves without
+    any depth take a path of their own."""
+    import torch
+    zn, zf = 1.0, 8.0
+    rng = np.random.default_rng(9)
+    for kind in ("zeros", "ones", "mixed", "first", "middle", "last"):
+        d = rng.choice(np.array([0, 0xFFFF], np.uint16), (H, W))
+        if kind in ("zeros", "ones"):
+            d[:] = 0xFFFF if kind == "zeros" else 0
+        elif kind != "mixed":
+            d.reshape(-1)[{"first": 0, "middle": H * W // 2 + W // 3, "last": -1}[kind]] = 2345
+        Y, U, V = oracle_lib.encode_depth_y12(d, zn, zf)
+        src = [torch.from_numpy(i420(Y, U, V)).cuda() for _ in range(n)]
+        out = [torch.full((H, W), 77, dtype=torch.int16, device="cuda") for _ in range(n)]
+        fvv.depth_decode_y12_batch(src, W, H, zn, zf, out)
+        torch.cuda.synchronize()
+        want = oracle_lib.decode_depth_y12(Y, U, V, zn, zf)
+        for o in out:
+            assert np.array_equal(o.cpu().numpy().view(np.uint16), want), kind
