@@ -100,6 +100,16 @@ __device__ __forceinline__ float rcp_rn(float b)
     return __fmaf_rn(__fmaf_rn(-b, y0, 1.0f), y0, y0);
 }
 
+// v without its fraction as an int, whatever v is (beyond int's range the nearest
+// end, 0 for a NaN): the instruction itself, for values that are only tested
+// afterwards (a cast of such a value is undefined)
+__device__ __forceinline__ uint32_t cvt_i32(float v)
+{
+    int i;
+    asm("v_cvt_i32_f32 %0, %1" : "=v"(i) : "v"(v));
+    return (uint32_t)i;
+}
+
 // Row of source block blk (< 2^24; nbx <= 8192): with m = ceil(2^40 / nbx),
 // blk m / 2^40 exceeds blk / nbx by less than blk / 2^40 < 2^-16 <= 1 / nbx,
 // too little to reach the next integer, so its floor is the quotient: a
@@ -348,8 +358,7 @@ __global__ void __launch_bounds__(256) k_bin(const fvv_view_desc *__restrict__ v
             // an infinite u or v gives an empty range; only a NaN has to be
             // asked for (the clips pass over it)
             const bool ok = q2 > FVV_ZCLIP && !__builtin_isunordered(u, v) && x0f <= x1f && y0f <= y1f;
-            const uint32_t ix0 = (uint32_t)(int)x0f, ix1 = (uint32_t)(int)x1f;
-            const uint32_t iy0 = (uint32_t)(int)y0f, iy1 = (uint32_t)(int)y1f;
+            const uint32_t ix0 = cvt_i32(x0f), ix1 = cvt_i32(x1f), iy0 = cvt_i32(y0f), iy1 = cvt_i32(y1f);
             x0[q] = ok ? ix0 : 0x7FFFu;
             y0[q] = ok ? iy0 : 0x7FFFu;
             x1[q] = ok ? ix1 : 0u;

@@ -67,3 +67,14 @@ def test_non_square_pixels_ragged_sources(fvv, ctx, oracle_lib, cw, ch, ratio, l
     else:
         out, taps = gpu_run(fvv, ctx, w, v, max_fp=16.0)
         compare(oracle_lib, w, v, out, taps, max_fp=16.0)
+
+
+@pytest.mark.parametrize("fx", [1e7, 1e11, 1e20, 3e38])
+def test_points_far_outside(fvv, ctx, oracle_lib, fx):  # noqa: F811
+    """Focal lengths at which almost every point projects beyond the range of an
+    int, of a float32 or to a NaN: none of them may leave a footprint."""
+    w = sg.config_small(65, n_cams=3, w=96, h=64, out_w=150, out_h=90, n_virtual=2)
+    for v in (replace(w.virtual[1], fx=fx, fy=fx), replace(w.virtual[1], fx=fx)):
+        say(f"[gpu] virtual focal lengths {v.fx} {v.fy}")
+        out, taps = gpu_run(fvv, ctx, w, v)
+        compare(oracle_lib, w, v, out, taps)
