@@ -90,10 +90,10 @@ __device__ __forceinline__ float div_by(float a, float b, float y)
 // by one Newton step in fused multiply-adds, y0 + y0 (1 - b y0), is the
 // correctly rounded reciprocal for every significand of b and every such y0 but
 // one: b all ones and y0 the even neighbour below 1/b, where the step ends in a
-// tie.  The hardware's y0 for that significand is the odd neighbour above (its
-// result depends on the significand alone), so the step is exact for all;
-// fvv_check_reciprocal compares it with the correctly rounded division over
-// every significand of a range of binades on the device.
+// tie.  The hardware's y0 for that significand is the odd neighbour above, so the
+// step is exact for all: on the device fvv_check_reciprocal finds no difference
+// from the correctly rounded division for any significand of any binade from
+// 2^-100 to 2^125.
 __device__ __forceinline__ float rcp_rn(float b)
 {
     const float y0 = __builtin_amdgcn_rcpf(b);

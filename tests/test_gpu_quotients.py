@@ -1,6 +1,5 @@
-"""The kernels' reciprocal of a projected depth (hardware estimate, one
-Newton step, the all-ones-significand correction) and the quotients derived
-from it, against correctly rounded division on the device: every
+"""The kernels' reciprocal of a projected depth (hardware estimate and one
+Newton step) and the quotients derived from it, against correctly rounded division on the device: every
 significand of the binades 2^-7 .. 2^20 (projected depths from the 0.01 m
 clip plane to a million metres), two dividends per divisor."""
 import sys

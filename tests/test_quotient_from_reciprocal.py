@@ -8,9 +8,11 @@ rest on the GPU tests alone.
 
 The reciprocal itself comes from the hardware estimate (documented within
 one ulp of 1/p2) and one Newton step y0 + y0 (1 - p2 y0) in fused
-multiply-adds, with the low bit set where the significand of p2 is all ones.
-The second test runs that step from every float within one ulp of 1/p2, for
-every significand of three binades, and requires RN(1/p2) every time."""
+multiply-adds.  The second test runs a step that needs no more of the estimate
+than that bound, with the low bit set where the significand of p2 is all ones,
+from every float within one ulp of 1/p2, for every significand of three
+binades, and requires RN(1/p2) every time.  The kernels leave that bit alone;
+test_reciprocal_step.py has their step and the one start it must not have."""
 import os
 import subprocess
 
