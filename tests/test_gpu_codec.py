@@ -316,3 +316,71 @@ def test_decode_where_waves_have_no_depth(fvv, oracle_lib, W, H, n):
         want = oracle_lib.decode_depth_y12(Y, U, V, zn, zf)
         for o in out:
             assert np.array_equal(o.cpu().numpy().view(np.uint16), want), kind
+
+
+# 4 Mi pixels and more per launch take runs of two blocks (8 bytes of depth, 4 of
+# Y, 2 of U and V) where width, bases and pitches allow them: the first of each
+# list does, the others are refused for the width, a base and a pitch of the
+# depth, a base and a pitch of the image
+@pytest.mark.parametrize("zn,zf", [(0.5, 10.0), (2.0, 2.0000002), (1.0, 1.0005), (1e-30, 1e30)])
+@pytest.mark.parametrize("W,d_off,d_pad,y_off,y_pad", [(2048, 0, 0, 0, 0), (2052, 0, 0, 0, 0), (2050, 0, 0, 0, 0),
+                                                       (2048, 2, 8, 0, 0), (2048, 0, 2, 0, 0), (2048, 0, 0, 2, 0),
+                                                       (2048, 0, 0, 0, 2), (2048, 8, 16, 4, 8)])
+def test_large_batches(fvv, oracle_lib, zn, zf, W, d_off, d_pad, y_off, y_pad):
+    """Two images, every millimetre value and then every code in each, rows of
+    several lengths and starts (in bytes): the oracle's bytes both ways."""
+    import ctypes as C
+    import torch
+    H, n = 1026, 2
+    assert n * W * H >= 4 << 20
+    L, s = fvv.lib(), fvv._stream_handle(None)
+    d = np.resize(np.arange(65536, dtype=np.uint16), (n, H, W))
+    d[1] = d[0][::-1, ::-1]
+    dp, yp = W * 2 + d_pad, W + y_pad
+    say = lambda t: print(f"[gpu] {t} {n}x{W}x{H} {zn} {zf} {d_off} {d_pad} {y_off} {y_pad}", flush=True)  # noqa: E731
+    # images start on 256-byte boundaries plus their offset
+    mm = torch.zeros(n * (d_off + H * dp + 512), dtype=torch.uint8, device="cuda")
+    yuv = torch.zeros(n * (y_off + H * yp * 2 + 512), dtype=torch.uint8, device="cuda")
+    d_at = [k * ((d_off + H * dp + 511) // 256 * 256) + d_off for k in range(n)]
+    y_at = [k * ((y_off + H * yp * 2 + 255) // 256 * 256) + y_off for k in range(n)]
+    host = np.zeros(mm.numel(), np.uint8)
+    for k in range(n):
+        rows = host[d_at[k]:d_at[k] + H * dp].reshape(H, dp)
+        rows[:, :W * 2] = d[k].view(np.uint8).reshape(H, W * 2)
+    mm.copy_(torch.from_numpy(host))
+    d_ptr = (C.c_void_p * n)(*[mm.data_ptr() + a for a in d_at])
+    y_ptr = (C.c_void_p * n)(*[yuv.data_ptr() + a for a in y_at])
+    d_pitch, y_pitch = np.full(n, dp, np.int64), np.full(n, yp, np.int64)
+    say("encode")
+    assert L.fvv_depth_encode_y12_batch(n, C.cast(d_ptr, C.c_void_p), d_pitch.ctypes.data, W, H, zn, zf,
+                                        C.cast(y_ptr, C.c_void_p), y_pitch.ctypes.data, s) == 0
+    torch.cuda.synchronize()
+
+    def planes(buf, at):
+        Y = buf[at:at + H * yp].reshape(H, yp)[:, :W]
+        u = buf[at + H * yp:at + H * yp + H // 2 * (yp // 2)].reshape(H // 2, yp // 2)[:, :W // 2]
+        v = buf[at + H * yp + H // 2 * (yp // 2):at + H * yp + H * (yp // 2)].reshape(H // 2, yp // 2)[:, :W // 2]
+        return Y, u, v
+
+    got = yuv.cpu().numpy()
+    for k in range(n):
+        for a, b in zip(planes(got, y_at[k]), oracle_lib.encode_depth_y12(d[k], zn, zf)):
+            assert np.array_equal(a, b)
+    # every code: Y bytes 0..255 down a column, U and V bytes along a row of blocks
+    Y = np.repeat(np.resize(np.arange(256, dtype=np.uint8), H)[:, None], W, 1)
+    UV = np.resize(np.arange(256, dtype=np.uint8), (H // 2, W // 2))
+    host = np.zeros(yuv.numel(), np.uint8)
+    for k in range(n):
+        for a, b in zip(planes(host, y_at[k]), (Y, UV, UV)):
+            a[:] = b
+    yuv.copy_(torch.from_numpy(host))
+    mm.fill_(7)
+    say("decode")
+    assert L.fvv_depth_decode_y12_batch(n, C.cast(y_ptr, C.c_void_p), y_pitch.ctypes.data, W, H, zn, zf,
+                                        C.cast(d_ptr, C.c_void_p), d_pitch.ctypes.data, s) == 0
+    torch.cuda.synchronize()
+    got, want = mm.cpu().numpy(), oracle_lib.decode_depth_y12(Y, UV, UV, zn, zf)
+    for k in range(n):
+        rows = got[d_at[k]:d_at[k] + H * dp].reshape(H, dp)
+        assert np.array_equal(np.ascontiguousarray(rows[:, :W * 2]).view(np.uint16), want)
+        assert (rows[:, W * 2:] == 7).all()
