@@ -1057,7 +1057,16 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
         pslot[q] = FVV_HOLE;
         prgb[q] = 0;
     }
-    if (!STACK) blend_row<PPT>(vd, X0 + lx0, y, zf, pslot, prgb);
+    if (!STACK) {
+        // a wave without a filtered point has nothing to sample (uniform): a
+        // 4096x2304 view of one 33x33 camera, no fill, 110 -> 104 us; 12 layered
+        // 1080p views without foreground 632 -> 588; 60 full 1080p views with
+        // upload 2,191 either way
+        bool any = false;
+#pragma unroll
+        for (int q = 0; q < PPT; ++q) any |= f2u(zf[q]) != FVV_NO_DEPTH;
+        if (__builtin_amdgcn_ballot_w64(any)) blend_row<PPT>(vd, X0 + lx0, y, zf, pslot, prgb);
+    }
 #pragma unroll
     for (int q = 0; q < PPT; ++q) {
         const int x = X0 + lx0 + q;
