@@ -2730,16 +2730,19 @@ hipError_t conv3(const GemmArgs &g, hipStream_t s, const HeadArgs *head = nullpt
     // from two chunks: a concatenation's planes, or the gradient at the first pool
     if constexpr (EPI == EPI_RELU_BF16)
         if (g.M == 32 && g.K == 64 && tiles8 >= 2048 && g.b_cs == 32 && g.b_off == 0 && g.b_split == 32 && g.o_cs == 32 &&
-            g.o_off == 0 && g.H % 2 == 0 && g.W % 2 == 0 && strips_fit(g.W))
+            g.o_off == 0 && g.H % 2 == 0 && g.W % 2 == 0 && g.W > 8 && strips_fit(g.W))
             return conv3t_launch<false>(g, s);
     if constexpr (EPI == EPI_F32)
         if (g.M == 32 && g.K == 64 && tiles8 >= 2048) return conv3w_launch(g, s);
     // 64 output channels x 16 rows x 32 columns per block from 64 K pixels on
     // (2.1 M to 130 K pixels on the 16 x 960x544 network: 113 - 288 us per
-    // launch against 195 - 397 for blocks of 16 x 16 pixels), else 32 channels
-    // x 8 rows x 16 columns (more blocks where there are few pixels)
+    // launch against 195 - 397 for blocks of 16 x 16 pixels), x 16 columns where
+    // rows are no longer than that (the layers of 16 images of 8192x16, 4 to 8
+    // columns: 71 - 276 us per launch against 71 - 408), else 32 channels x 8
+    // rows x 16 columns (more blocks where there are few pixels)
     const bool big = g.M % 64 == 0 && (int64_t)g.NB * g.H * g.W >= 65536;
     if constexpr (EPI == EPI_RELU_BF16) {
+        if (big && g.W <= 16) return g.pool ? conv3_launch<2, 16, EPI, true>(g, s) : conv3_launch<2, 16, EPI>(g, s);
         if (g.pool) return big ? conv3r_launch<2, 4, EPI, true>(g, s) : conv3_launch<1, 8, EPI, true>(g, s);
         if (head) return conv3_launch<1, 8, EPI, false, true>(g, s, nullptr, *head);
     }
@@ -2826,12 +2829,16 @@ uint16_t *skip_plane(uint16_t *cat, int lv, int NB, int H, int W)
     return cat + (((size_t)NB * H * W) >> (2 * lv)) * (size_t)(32 << lv);
 }
 
-// Whether the full-resolution level has a large grid: the finest transposed
-// convolution can run inside the next convolution (k_conv3t).
-bool up0_fusable(int NB, int H, int W)
+// Whether the full-resolution level has a large grid: the head runs in the last
+// convolution without its output stored, ...
+bool large_grid(int NB, int H, int W)
 {
     return (int64_t)((W + 15) / 16) * ((H + 7) / 8) * NB >= 2048 && strips_fit(W);
 }
+// ... and the finest transposed convolution can run inside the next convolution
+// (k_conv3t; not in rows of 8, where three quarters of its columns are empty: 16
+// images of 8192x8 193 us, separately 159; of 8192x16 203 and 210).
+bool up0_fusable(int NB, int H, int W) { return large_grid(NB, H, W) && W > 8; }
 
 // dec0a with its input chunk 0 (the finest transposed convolution of d1b)
 // computed per patch: cat0's first plane is neither written nor read
@@ -2894,7 +2901,7 @@ hipError_t forward_all(unet_state *n, unet_act *a, const uint16_t *stack, int NB
     } else {
         NCHK(dec0a_fused(n, a, NB, H, W, s));
     }
-    a->d0b_stored = !(lean && head && up0_fusable(NB, H, W));   // (a small grid's store costs nothing)
+    a->d0b_stored = !(lean && head && large_grid(NB, H, W));   // (a small grid's store costs nothing)
     NCHK(conv_fwd(n, L_D0B, a->d0a, 32, 0, a->d0b_stored ? a->d0b : nullptr, 32, 0, NB, H, W, s, nullptr, head));
     return hipSuccess;
 }

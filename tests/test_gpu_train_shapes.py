@@ -171,3 +171,15 @@ def test_training_within_a_memory_budget(fvv, N, H, W, need):  # noqa: F811
         for k in (0, 1):
             d = np.linalg.norm(a[name][k].astype(np.float64) - b[name][k].astype(np.float64))
             assert d <= 1e-5 * np.linalg.norm(a[name][k].astype(np.float64)), (name, k)
+
+
+@pytest.mark.parametrize("N,H,W", [(16, 520, 32), (64, 264, 16), (64, 520, 8)])
+def test_narrow_batches(fvv, ctx, oracle_lib, N, H, W):  # noqa: F811
+    """Batches of images no wider than 16 pixels at the levels with 64 K pixels
+    and more, which take patches of 16 columns (16, 8 and 4 columns, rows
+    that end patches unevenly), and no wider than 8 at the finest, where the
+    finest transposed convolution stays a launch of its own: layers and outputs
+    have the bytes of the single image."""
+    say(f"[gpu] narrow batch {N}x{H}x{W}")
+    test_batch_layers_equal_single(fvv, ctx, oracle_lib, N, H, W)
+    test_batch_output_equals_single(fvv, ctx, oracle_lib, N, H, W)
