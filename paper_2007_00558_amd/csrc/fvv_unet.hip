@@ -32,7 +32,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // EPI_GRAD: a gradient that the next layer's products read -- masked by that
 // layer's ReLU and rounded to bfloat16, with the sums of the float32 masked
 // values per channel (its bias gradient) as a row of partials per block
-enum { EPI_RELU_BF16 = 0, EPI_F32 = 1, EPI_CONVT_BF16 = 2, EPI_GRAD = 3 };
+enum { EPI_RELU_BF16 = 0, EPI_F32 = 1, EPI_GRAD = 2 };
 
 // bfloat16 rounding to nearest even, written out on the bit pattern (the
 // definition the hardware conversion below is checked against)
@@ -77,14 +77,14 @@ struct GemmArgs {
     int b_cs, b_off;         // channel stride / offset of Bsrc
     int b_split;             // channels from b_split on lie b_skip elements further on (a concatenation's
     uint32_t b_skip;         // second plane); b_skip 0 = one plane
-    const float *bias;       // per output channel (EPI_RELU_BF16, EPI_CONVT_BF16)
+    const float *bias;       // per output channel (EPI_RELU_BF16, transposed convolutions)
     void *out;
     int o_cs, o_off;
     int NB, H, W;            // column pixels: NB images of H x W
     int K;                   // channels per tap (multiple of 32)
     int k_src;               // channels Bsrc holds at b_off (0 = K); staged channels beyond are zero
     int M;                   // rows (multiple of 16)
-    int cout;                // EPI_CONVT_BF16: output channels (M = 4 cout)
+    int cout;                // transposed convolutions: output channels (M = 4 cout)
     // EPI_GRAD: out = bfloat16 [P][M] of the rows masked by act [P][M] (> 0);
     // with split (a concatenation's gradient), of the first split rows,
     // unmasked, and float32 [P][M - split] of the rest in skip
@@ -103,7 +103,7 @@ struct GemmArgs {
 };
 
 struct HeadArgs {
-    const uint16_t *a;       // [P][32] bf16
+    const uint16_t *a;       // [P][32] bf16 (training; else the head runs in the last convolution)
     const uint16_t *w;       // [3][32] bf16
     const float *bias;       // [3]
     float *s_out;            // [P][3] or null
@@ -926,7 +926,6 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int tiles_x = (g.W + 15) / 16, tiles_y = (g.H + TH - 1) / TH;
     const int tiles = tiles_x * tiles_y * g.NB;
-    const int k_src = g.k_src ? g.k_src : g.K;
     const int lc = lane & 31, lh = lane >> 5;
     // the weight slices, once: chunk-major [K/32][32][9][32]
     for (int e = tid; e < KC * 32 * 36; e += 256) {
@@ -954,7 +953,7 @@ __global__ void __launch_bounds__(256) k_conv3w(const GemmArgs g)
 #pragma unroll
             for (int c = 0; c < KC; ++c) {
                 fp[c][k] = make_uint4(0, 0, 0, 0);
-                if (in && c * 32 + (tid & 3) * 8 < k_src) fp[c][k] = *(const uint4 *)(g.Bsrc + ((uint32_t)(off + c * 32) + (c * 32 >= g.b_split ? g.b_skip : 0u)));
+                if (in) fp[c][k] = *(const uint4 *)(g.Bsrc + (uint32_t)(off + c * 32));
             }
         }
     };
@@ -1510,7 +1509,7 @@ k_conv3t(const GemmArgs g, const int R)
 // TM rows x TN pixels per block (128 x 128, or 64 x 64 on small grids),
 // 32-channel chunks of A and B staged in LDS, four waves of TM/2 x TN/2 on
 // v_mfma_f32_32x32x16_bf16.
-template <int EPI, int TM, int TN>
+template <int TM, int TN>
 __global__ void __launch_bounds__(256) k_gemm1(const GemmArgs g)
 {
     constexpr int MI = TM / 64, NI = TN / 64;   // 32x32 tiles per wave in each direction
@@ -1593,19 +1592,13 @@ __global__ void __launch_bounds__(256) k_gemm1(const GemmArgs g)
                 if (m0 >= g.M) continue;
                 float v0 = acc[i][n][4 * j + 0], v1 = acc[i][n][4 * j + 1];
                 float v2 = acc[i][n][4 * j + 2], v3 = acc[i][n][4 * j + 3];
-                if (EPI == EPI_CONVT_BF16) {
-                    const int d = m0 / g.cout, co = m0 - d * g.cout;
-                    const int64_t fp = ((int64_t)b * 2 * g.H + 2 * y + (d >> 1)) * (2 * g.W) + 2 * x + (d & 1);
-                    v0 += g.bias[co + 0];
-                    v1 += g.bias[co + 1];
-                    v2 += g.bias[co + 2];
-                    v3 += g.bias[co + 3];
-                    *(uint2 *)((uint16_t *)g.out + fp * g.o_cs + g.o_off + co) =
-                        make_uint2(pack_bf16(v0, v1),
-                                   pack_bf16(v2, v3));
-                } else {
-                    *(float4 *)((float *)g.out + (int64_t)p * g.o_cs + g.o_off + m0) = make_float4(v0, v1, v2, v3);
-                }
+                const int d = m0 / g.cout, co = m0 - d * g.cout;
+                const int64_t fp = ((int64_t)b * 2 * g.H + 2 * y + (d >> 1)) * (2 * g.W) + 2 * x + (d & 1);
+                v0 += g.bias[co + 0];
+                v1 += g.bias[co + 1];
+                v2 += g.bias[co + 2];
+                v3 += g.bias[co + 3];
+                *(uint2 *)((uint16_t *)g.out + fp * g.o_cs + g.o_off + co) = make_uint2(pack_bf16(v0, v1), pack_bf16(v2, v3));
             }
     }
 }
@@ -2458,19 +2451,6 @@ struct unet_act {
 
 namespace {
 
-struct Plan {
-    size_t off[40];
-    int n = 0;
-    size_t total = 0;
-    size_t add(size_t bytes)
-    {
-        off[n++] = total;
-        const size_t o = total;
-        total += (bytes + 255) & ~(size_t)255;
-        return o;
-    }
-};
-
 // Bias partials that a launch may write, and the rows it wrote: a launch takes
 // no more blocks than have rows.
 struct BiasRows {
@@ -2733,7 +2713,7 @@ hipError_t conv3(const GemmArgs &g, hipStream_t s, const HeadArgs *head = nullpt
             g.o_off == 0 && g.H % 2 == 0 && g.W % 2 == 0 && g.W > 8 && strips_fit(g.W))
             return conv3t_launch<false>(g, s);
     if constexpr (EPI == EPI_F32)
-        if (g.M == 32 && g.K == 64 && tiles8 >= 2048) return conv3w_launch(g, s);
+        if (g.M == 32 && g.K == 64 && tiles8 >= 2048 && g.k_src == 0 && g.b_skip == 0) return conv3w_launch(g, s);
     // 64 output channels x 16 rows x 32 columns per block from 64 K pixels on
     // (2.1 M to 130 K pixels on the 16 x 960x544 network: 113 - 288 us per
     // launch against 195 - 397 for blocks of 16 x 16 pixels), x 16 columns where
@@ -2812,10 +2792,10 @@ hipError_t convT_fwd(unet_state *n, int li, const uint16_t *in, int i_cs, int NB
     const int64_t big = (int64_t)((P + 127) / 128) * ((g.M + 127) / 128);
     if (big >= 1024) {
         dim3 grid((P + 127) / 128, (g.M + 127) / 128);
-        hipLaunchKernelGGL((k_gemm1<EPI_CONVT_BF16, 128, 128>), grid, dim3(256), 0, s, g);
+        hipLaunchKernelGGL((k_gemm1<128, 128>), grid, dim3(256), 0, s, g);
     } else {
         dim3 grid((P + 63) / 64, (g.M + 63) / 64);
-        hipLaunchKernelGGL((k_gemm1<EPI_CONVT_BF16, 64, 64>), grid, dim3(256), 0, s, g);
+        hipLaunchKernelGGL((k_gemm1<64, 64>), grid, dim3(256), 0, s, g);
     }
     return hipGetLastError();
 }
@@ -3154,7 +3134,6 @@ hipError_t unet_forward(unet_state *n, unet_act *a, const uint16_t *stack, int N
     }
     const unet_layer &hl = layers().L[L_HEAD];
     HeadArgs h{};
-    h.a = a->d0b;
     h.w = n->wf + hl.wf_off;
     h.bias = n->w + hl.b_off;
     h.s_out = s_out;
@@ -3182,7 +3161,6 @@ hipError_t unet_forward_batch(unet_state *n, unet_act *a, const uint16_t *stack,
     }
     const unet_layer &hl = layers().L[L_HEAD];
     HeadArgs h{};
-    h.a = a->d0b;
     h.w = n->wf + hl.wf_off;
     h.bias = n->w + hl.b_off;
     h.outs = outs;
