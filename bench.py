@@ -135,12 +135,15 @@ def count_atomics(fvv, torch, ctx, rig, virts, k: int = 3) -> dict:
       tile: LDS atomicMin per output-tile window (the tile plus a 1-pixel
         halo) that a point's footprint covers: sum over points of
         sum over covered pixels of the number of windows holding the pixel;
-      bin: one list append (global atomic add) per (8x8 source block, output
-        tile whose window the block's footprints touch)."""
+      bin: list entries, one per (8x8 source block, output tile whose window
+        the block's footprints touch), and the global atomic adds that reserve
+        their space: one per tile and 4x4 square of blocks, or one per entry in
+        squares with a range wider than 8x2 tiles or more than 16 tiles a side."""
     dev = torch.device("cuda:0")
     planes = {}
     lds = 0
     glob = 0
+    entries = 0
     for v in virts:
         W, H = v.width, v.height
         ntx, nty = (W + 31) // 32, (H + 31) // 32
@@ -192,8 +195,24 @@ def count_atomics(fvv, torch, ctx, rig, virts, k: int = 3) -> dict:
             tx1 = torch.clamp((bx1 + 1) // 32, max=ntx - 1)
             ty0 = torch.clamp((by0 + 31) // 32 - 1, min=0)
             ty1 = torch.clamp((by1 + 1) // 32, max=nty - 1)
-            glob += int(torch.where(has, (tx1 - tx0 + 1) * (ty1 - ty0 + 1), 0).sum())
-    return {"tile_lds": lds, "bin_global": glob}
+            n = torch.where(has, (tx1 - tx0 + 1) * (ty1 - ty0 + 1), 0)
+            entries += int(n.sum())
+            # the squares of blocks: (squares, 16 blocks)
+            hg, wg = (hb + 3) // 4, (wb + 3) // 4
+            sq = lambda t, fill: torch.nn.functional.pad(t, (0, wg * 4 - wb, 0, hg * 4 - hb), value=fill) \
+                .reshape(hg, 4, wg, 4).permute(0, 2, 1, 3).reshape(hg * wg, 16)
+            on, n = sq(has.long(), 0) > 0, sq(n, 0)
+            sx0, sx1, sy0, sy1 = (sq(t, 0) for t in (tx0, tx1, ty0, ty1))
+            ux0, uy0 = (torch.where(on, t, big).amin(1) for t in (sx0, sy0))
+            ux1, uy1 = (torch.where(on, t, -1).amax(1) for t in (sx1, sy1))
+            shared = (~on | ((sx1 - sx0 < 8) & (sy1 - sy0 < 2))).all(1) & (ux1 - ux0 < 16) & (uy1 - uy0 < 16) & on.any(1)
+            gx = (ux0[:, None] + torch.arange(16, device=dev))[:, None, :]
+            gy = (uy0[:, None] + torch.arange(16, device=dev))[:, None, :]
+            inx = (sx0[:, :, None] <= gx) & (gx <= sx1[:, :, None]) & on[:, :, None]
+            iny = (sy0[:, :, None] <= gy) & (gy <= sy1[:, :, None])
+            tiles = (inx[:, :, None, :] & iny[:, :, :, None]).any(1).sum((1, 2))
+            glob += int(torch.where(shared, tiles, n.sum(1)).sum())
+    return {"tile_lds": lds, "bin_entries": entries, "bin_global": glob}
 
 
 def cpu_model() -> str:
@@ -823,10 +842,11 @@ def main():
         one = count_atomics(fvv, torch, ctx, w.rig, [v])
         atomics = {"peaks": {k: round(v, 1) for k, v in peaks.items()},
                    "bin_count_check": {"view": vq, "tap_entries": int(tiles[:, 0].sum()),
-                                       "counted": one["bin_global"]},
+                                       "counted": one["bin_entries"]},
                    "tile_lds_atomic_min_per_launch": cnt["tile_lds"],
                    "tile_lds_atomic_min_per_s": round(lds_rate, 1),
                    "tile_frac_of_lds_window_peak": round(lds_rate / peaks["lds_atomic_min_window_per_s"], 4),
+                   "bin_entries_per_launch": cnt["bin_entries"],
                    "bin_global_atomics_per_launch": cnt["bin_global"],
                    "bin_global_atomics_per_s": round(glob_rate, 1),
                    "bin_frac_of_global_distinct_peak": round(glob_rate / peaks["global_atomic_min_distinct_per_s"], 4),
