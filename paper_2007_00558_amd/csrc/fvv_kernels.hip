@@ -820,8 +820,8 @@ __device__ __forceinline__ void tile_body(const fvv_view_desc *__restrict__ view
     uint32_t *const s_slot = (uint32_t *)s_buf;
     uint32_t *const s_rgb = s_slot + T * SP;
     unsigned long long *const s_kf = s_buf;
-    // pixels whose filtered key is a median (the two-window variant filters
-    // in place: its LDS budget has no room for the list)
+    // pixels whose filtered key is a median (the two-window variant has no list:
+    // it sorts where a pixel needs it)
     __shared__ uint16_t s_med[LAYERED ? 2 : T * T];
     __shared__ int s_open, s_hole, s_nmed;
     const int t = threadIdx.x;
@@ -1277,8 +1277,8 @@ __global__ void __launch_bounds__(TNT) k_tile_stack(const fvv_view_desc *__restr
 // slots, the foreground stacked over the background.  Plain views of a batch
 // that also holds layered views run here too (their second window stays
 // empty), and a batch that also holds learned views takes the variant that
-// writes their stacks.  The two windows bound occupancy to 5 workgroups per
-// CU through LDS, so registers are not capped.
+// writes their stacks.  The two windows (26.8 KB) bound occupancy to six
+// workgroups per CU through LDS, so registers are not capped.
 __global__ void __launch_bounds__(TNT) k_tile_layered(const fvv_view_desc *__restrict__ views, int mtx, int mty, int n_views)
 {
     tile_body<false, true, 4>(views, mtx, mty, n_views);
@@ -1298,13 +1298,17 @@ __global__ void __launch_bounds__(tile_threads(PPT)) k_tile_few(const fvv_view_d
     tile_body<STACK, LAYERED, PPT>(views, mtx, mty, n_views);
 }
 
-// Pixels per thread of a launch: the fewest at which every tile still runs at
-// once.  A CU holds 32 waves: eight workgroups of 256 threads (four pixels
-// each), four of 512 or two of 1024.  A tile is one long chain (list entry,
-// splat record, LDS key, filter, taps, fill), so a launch of fewer tiles than
-// that leaves the SIMDs waiting on a few waves, and more threads per tile
-// shorten the chain; a launch of more only pays for the entries, barriers and
-// row terms that more waves repeat.  Kernel at 4 / 2 / 1 pixels per thread, us:
+// Pixels per thread of a launch: one up to two tiles per CU, two up to four.  A
+// tile is one long chain (list entry, splat record, LDS key, filter, taps,
+// fill), so a launch of few tiles leaves the SIMDs waiting on a few waves, and
+// more threads per tile shorten the chain; a launch of more only pays for the
+// entries, barriers and row terms that more waves repeat.  The lines are where
+// the plain kernel's tiles still run all at once (a CU holds 32 waves: eight
+// workgroups of 256 threads, four of 512 or two of 1024); the other variants
+// share them, though the layered one would take two pixels a little earlier and
+// the one with stacks and layers holds one workgroup of 1024 at a time (66
+// registers; 480 tiles of a mixed batch 38 us, of four pixels 71 in the kernel
+// before).  Kernel at 4 / 2 / 1 pixels per thread, us:
 // 60 tiles 21 / 16 / 14; 240 47 / 29 / 23; 510 33 / 25 / 23; 920 35 / 31 / 36;
 // 1,450 41 / 43 / 49; 2,040 43 / 49 / 64; 24,480 483 / 568 / 722.  Layered:
 // 240 57 / 35 / 25; 510 41 / 28 / 31; 920 40 / 33 / 43; 2,040 55 / 55 / 83;

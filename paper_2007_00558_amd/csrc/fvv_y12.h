@@ -35,9 +35,11 @@ __host__ __device__ inline y12_planes y12_make_planes(float z_near, float z_far)
     p.span = 1.0 / zn - 1.0 / zf;
     p.enc1 = 1000.0 * 4093.0 / p.span;
     p.enc0 = 2.5 - p.inv_zf * (4093.0 / p.span);
-    // bound on estimate and Eq. 2 sequence being apart, for codes in range: both
-    // are sums of terms up to (4093 / span) / z_near, a few roundings of 2^-53
-    // each; 2^-40 leaves a factor of a thousand
+    // bound on estimate and Eq. 2 sequence being apart, for codes in range: with
+    // S = (4093 / span) / z_near (more than 4093, and than the codes' other term)
+    // enc1 / mm is at most 2 S, its reciprocal within 2^-45, so the estimate is
+    // within 2^-44 S, and the roundings of both sums are 2^-53 S each: 2^-40
+    // leaves a factor of sixteen
     p.enc_eps = (4093.0 / p.span) / zn * 0x1p-40 + 1e-9;
     p.dec1 = p.span / 4093.0;
     return p;
