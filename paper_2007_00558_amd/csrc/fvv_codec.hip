@@ -61,7 +61,7 @@ __device__ __forceinline__ bool y12_block(const fvv_y12_batch &b, int &r, int &c
     return true;
 }
 
-template <int NB>
+template <int NB, bool EST>
 __global__ void __launch_bounds__(256) k_y12_encode(const fvv_y12_batch b)
 {
     int r, c;
@@ -73,18 +73,14 @@ __global__ void __launch_bounds__(256) k_y12_encode(const fvv_y12_batch b)
     uint8_t *UV = Y + (int64_t)b.H * ypitch;
     alignas(16) typename Run<NB>::mm d[2];
     uint32_t p[2][2 * NB];
+    bool sure = EST;
 #pragma unroll
-    for (int row = 0; row < 2; ++row)
+    for (int row = 0; row < 2; ++row) {
         load_run<(NB > 1)>((const uint16_t *)(dep + (int64_t)(2 * r + row) * dpitch) + 2 * c, d[row]);
-    // (uniform) planes so close together that the estimates leave a value of
-    // most waves to the divisions, at twice the bound each of a wave's 256 NB:
-    // below 2^-11, nearer than some 8 millionths of their distance.  Planes a
-    // float32 step apart, 9 x 1280x720: 27.4 us with the estimates, 23.9 without
-    bool sure = b.planes.enc_eps < 0x1p-11;
-    if (sure)
+        if (EST)
 #pragma unroll
-        for (int i = 0; i < 4 * NB; ++i)
-            p[i / (2 * NB)][i % (2 * NB)] = y12_quantise_est(d[i / (2 * NB)][i % (2 * NB)], b.planes, sure);
+            for (int i = 0; i < 2 * NB; ++i) p[row][i] = y12_quantise_est(d[row][i], b.planes, sure);
+    }
     if (!sure)
 #pragma unroll
         for (int i = 0; i < 4 * NB; ++i) p[i / (2 * NB)][i % (2 * NB)] = y12_quantise(d[i / (2 * NB)][i % (2 * NB)], b.planes);
@@ -171,8 +167,14 @@ void launch(const fvv_y12_batch &b, bool encode, hipStream_t s)
 {
     const int64_t threads = (int64_t)(b.W / (2 * NB)) * (b.H / 2);
     const dim3 grid((unsigned)((threads + 255) / 256), b.n);
-    if (encode)
-        hipLaunchKernelGGL(k_y12_encode<NB>, grid, dim3(256), 0, s, b);
+    // without estimates between planes so close together that they leave a value
+    // of most waves to the divisions, at twice the bound each of a wave's 256 NB:
+    // from 2^-11 on, nearer than some 8 millionths of their distance.  Planes a
+    // float32 step apart, 9 x 1280x720: 27.5 us with the estimates, 24.7 without
+    if (encode && b.planes.enc_eps < 0x1p-11)
+        hipLaunchKernelGGL((k_y12_encode<NB, true>), grid, dim3(256), 0, s, b);
+    else if (encode)
+        hipLaunchKernelGGL((k_y12_encode<NB, false>), grid, dim3(256), 0, s, b);
     else
         hipLaunchKernelGGL(k_y12_decode<NB>, grid, dim3(256), 0, s, b);
 }
